@@ -19,9 +19,10 @@ namespace ekv {
 constexpr int kScoreThreads = 256;
 constexpr int kSolveThreads = 1024;
 constexpr int kSolveWaves = kSolveThreads / 64;
-constexpr int kListCap = 4096;          // candidate entries held in LDS (u, pos, row): 48 KB
+constexpr int kListCap = 4096;          // candidate entries the general path holds in LDS
+constexpr int kSegCap = 768;            // candidate entries a wavefront of the solve holds in LDS (and in registers)
 constexpr int kSpillCap = 65536;        // entries of a row's overflow list in the workspace (longer lists: the row is streamed)
-constexpr int kPreR = kPreGroups / kSolveThreads;    // group maxima a thread of the solve holds at most
+constexpr int kWaveGroups = 1024;       // up to this many group maxima are bounded by one wavefront, more by all of them
 constexpr int kRoundLoads = 16;         // loads per lane and compaction round
 constexpr int kRoundTokens = kSolveThreads * kRoundLoads;
 
@@ -503,16 +504,39 @@ __global__ __launch_bounds__(kFilterThreads) void filter_compact_kernel(const Fi
 // pass 2: threshold, probabilities, weighted value sum
 // ------------------------------------------------------------------------------------------
 struct SolveShared {
-  float list_u[kListCap];         // z - zmax of the candidates that can be in the support
-  int32_t list_pos[kListCap];     // their position in the candidate order
-  uint32_t list_row[kListCap];    // their V row: (phys*Hkv + hkv)*P + tok
+  // Candidates, z - zmax and position in the candidate order: wavefront w's segment is [w * kSegCap, (w + 1) * kSegCap).
+  // The general path uses the first kListCap entries as one list.
+  float list_u[kSolveWaves * kSegCap];
+  int32_t list_pos[kSolveWaves * kSegCap];
+  union {
+    uint32_t list_row[kListCap];  // their V row: (phys*Hkv + hkv)*P + tok
+    uint16_t glist[kPreGroups];   // the groups that can hold a candidate, ascending
+  };
   float obuf[kSolveWaves][kD];
   float red[2][kSolveWaves][3];
   int wcount[2][kSolveWaves];
+  int pre[kSolveWaves + 1];       // exclusive prefix of the segments' lengths
   float red1[kSolveWaves];
   int hist[64];                   // candidates per 1/64 slice of [thr, zmax] (threshold tightening)
   int flags[64];
+  float zmax, bound;              // row maximum, certified lower bound of tau relative to it
+  int n_pass;
 };
+static_assert(kListCap <= kSolveWaves * kSegCap, "the general path's list lies in the segments");
+static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
+
+// Sum of one value per wavefront kept in LDS at a stride: one read per lane and a DPP row sum, the same in every
+// wavefront (a loop over the wavefronts reads LDS sixteen times in a row).
+__device__ __forceinline__ float sum_waves(const float* v, int stride) {
+  const int l = threadIdx.x & 15;
+  return row16_sum(l < kSolveWaves ? v[l * stride] : 0.f);
+}
+__device__ __forceinline__ int sum_waves_i(const int* v, int stride) {
+  const int l = threadIdx.x & 15;
+  int x = l < kSolveWaves ? v[l * stride] : 0;
+  x += dpp_move_i<0xB1>(x); x += dpp_move_i<0x4E>(x); x += dpp_move_i<0x141>(x); x += dpp_move_i<0x140>(x);
+  return __builtin_amdgcn_readfirstlane(x);
+}
 
 // Candidate source: the compacted list (in LDS, or the row's overflow list in the workspace), or the score row itself.
 struct ListSrc {
@@ -546,11 +570,9 @@ __device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta,
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; sh.red[parity][w][2] = __int_as_float(c); }
   __syncthreads();
-  float Fs = 0.f, Ds = 0.f; int Cs = 0;
-  for (int i = 0; i < kSolveWaves; ++i) {
-    Fs += sh.red[parity][i][0]; Ds += sh.red[parity][i][1]; Cs += __float_as_int(sh.red[parity][i][2]);
-  }
-  F = Fs; D = beta * Ds; cnt = Cs;
+  F = sum_waves(&sh.red[parity][0][0], 3);
+  D = beta * sum_waves(&sh.red[parity][0][1], 3);
+  cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
 }
 
 // Root of sum (u - tau)_+^beta = 1 for u <= 0 with max u = 0: tau in [lo_init, 0), where lo_init >= -1
@@ -624,17 +646,25 @@ __device__ __forceinline__ float solve_tau(const Src& src, float lo_init, float 
 // to the other wavefronts through LDS.  Called by the whole workgroup.
 constexpr int kWaveList = 256;
 // entries of one wavefront in registers (u[k] of lane l is list entry l + 64 k, -inf past the end)
-__device__ __forceinline__ float solve_tau_regs(const float (&u)[kWaveList / 64], float lo_init, float seed, float beta,
-                                                int ibeta, int& supp, int& evals) {
-  return solve_tau_core([&](float t, float& F, float& D, int& cnt) {
-    float f = 0.f, d = 0.f; int c = 0;
+template <int KW>
+__device__ __forceinline__ float solve_tau_regs(const float (&u)[KW], float lo_init, float seed, float beta, int ibeta,
+                                                int& supp, int& evals) {
+  return with_beta(ibeta, [&](auto ib) {
+    constexpr int IB = decltype(ib)::value;
+    return solve_tau_core([&](float t, float& F, float& D, int& cnt) {
+      float f = 0.f, d = 0.f;
+      cnt = 0;
 #pragma unroll
-    for (int k = 0; k < kWaveList / 64; ++k) {
-      const float x = u[k] - t;
-      if (x > 0.f) { f += pow_beta(x, beta, ibeta); d += pow_beta_m1(x, beta, ibeta); ++c; }
-    }
-    F = wave_sum(f); D = beta * wave_sum(d); cnt = wave_sum_i(c);
-  }, lo_init, seed, ibeta, supp, evals);
+      for (int k = 0; k < KW; ++k) {
+        const float x = fmaxf(u[k] - t, 0.f);
+        const bool in = x > 0.f;
+        f += IB == 0 && !in ? 0.f : pow_beta(x, beta, IB);
+        d += in ? pow_beta_m1(x, beta, IB) : 0.f;
+        cnt += __popcll(__ballot(in));
+      }
+      F = wave_sum(f); D = beta * wave_sum(d);
+    }, lo_init, seed, IB, supp, evals);
+  });
 }
 __device__ __forceinline__ float solve_tau_wave(const float* list_u, int n, float lo_init, float seed, float beta,
                                                 int ibeta, SolveShared& sh, int& supp, int& evals) {
@@ -732,12 +762,409 @@ __device__ __forceinline__ void gather_support(const T* __restrict__ v_pool, con
   }
 }
 
+// Ranges of a row's candidates, as a wavefront that finishes the row needs them.
+struct RowRef { int b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks; };
+
+// A certified lower bound of tau (relative to the row maximum) from group maxima relative to it: every group holds at
+// least its maximum, so the mass of the maxima alone is a lower bound of the mass, and any point where it is >= 1 lies
+// left of tau.  F^(1/beta) is a norm of (u - t)_+, hence convex in t: Newton's steps on it from a point where F >= 1
+// stay left of the root.  They aim at a mass of 1.0001, which covers the rounding of the sums.  `sums(f, d)` adds f and
+// d up over all threads that hold maxima.
+template <int R, typename Sums>
+__device__ __forceinline__ float group_bound(const float (&u)[R], float t0, float beta, int ibeta, Sums&& sums) {
+  return with_beta(ibeta, [&](auto ib) {
+    constexpr int IB = decltype(ib)::value;
+    const float target = 1.0f + 1e-4f / beta;
+    float t = t0;
+    for (int it = 0; it < 8; ++it) {
+      float f = 0.f, d = 0.f;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const float x = fmaxf(u[k] - t, 0.f);
+        const bool in = x > 0.f;
+        f += IB == 0 && !in ? 0.f : pow_beta(x, beta, IB);
+        d += IB == 1 || IB == 0 ? (in ? pow_beta_m1(x, beta, IB) : 0.f) : pow_beta_m1(x, beta, IB);
+      }
+      sums(f, d);
+      const float r = IB == 1 ? f : IB == 2 ? __builtin_amdgcn_sqrtf(f) : __builtin_exp2f(__builtin_log2f(f) / beta);
+      if (!(r > target)) break;
+      t += (r - target) * f * __builtin_amdgcn_rcpf(r * d);
+      if (r < 1.02f) break;                                   // within two per cent of the norm: close enough
+    }
+    return t;
+  });
+}
+
+// The end of a row whose candidates are few: threshold, support and weighted value sum by ONE wavefront, KW entries per
+// lane, taken from the segments (sh.pre: the prefix of their lengths).  V rows are looked up while the threshold is solved.
+template <typename T, bool DENSE, int KW>
+__device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef& R, int n_list, float lo_u, float zmax,
+                                                float seed_u, SolveShared& sh) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const T* v_pool = (const T*)A.v_pool;
+  float* lu = sh.list_u; int32_t* lp = sh.list_pos; uint32_t* lr = sh.list_row;
+  float u[KW]; int pos[KW]; uint32_t row[KW];
+  int at[KW];
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const int e = lane + 64 * k;
+    int seg = 0;                                                      // last segment that starts at or before e
+#pragma unroll
+    for (int d = kSolveWaves / 2; d >= 1; d >>= 1) seg += sh.pre[seg + d] <= e ? d : 0;
+    at[k] = seg * kSegCap + min(e - sh.pre[seg], kSegCap - 1);
+  }
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const int e = lane + 64 * k;
+    u[k] = e < n_list ? lu[at[k]] : -INFINITY;
+    pos[k] = e < n_list ? lp[at[k]] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < KW; ++k) row[k] = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, pos[k]);     // clamped, unconditional
+  int supp = 0, evals = 0;
+  const float tau_u = solve_tau_regs<KW>(u, lo_u, seed_u, A.beta, A.ibeta, supp, evals);
+  // ordered compaction of the support: (p, row, position) of entry e = lane + 64 k, k-major = candidate order
+  int n_sup = 0;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    const float x = u[k] - tau_u;
+    const bool in = x > 0.f;
+    const uint64_t mk = __ballot(in);
+    if (in) {
+      const int o = n_sup + __popcll(mk & lt);
+      lu[o] = pow_beta(x, A.beta, A.ibeta);
+      lr[o] = row[k];
+      lp[o] = pos[k];
+    }
+    n_sup += __popcll(mk);
+  }
+  __builtin_amdgcn_wave_barrier();
+  // weighted value sum: 4 row slots x 16 lanes, batches of 8 independent 16-byte loads per lane
+  const int rs = lane >> 4, c = lane & 15;
+  float acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+  for (int e0 = 0; e0 < n_sup; e0 += 32) {
+    Raw8<T> vr[8]; float pw[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int e = e0 + 4 * j + rs;
+      const int ec = min(e, n_sup - 1);                              // clamped: loads stay unconditional
+      pw[j] = e < n_sup ? lu[ec] : 0.f;
+      load_raw8(v_pool + (size_t)lr[ec] * kD + 8 * c, vr[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      float vv[8];
+      widen8(vr[j], vv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = fmaf(pw[j], vv[i], acc[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    acc[i] += __shfl_xor(acc[i], 16);
+    acc[i] += __shfl_xor(acc[i], 32);
+  }
+  float* out = A.out + (size_t)R.bh * kD;
+  if (lane < 16) {
+    *reinterpret_cast<float4*>(out + 8 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    *reinterpret_cast<float4*>(out + 8 * c + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  }
+  if (A.ex.support_tokens != nullptr) {
+    int32_t* dst = A.ex.support_tokens + (size_t)R.bh * A.ex.support_cap;
+    for (int e = lane; e < n_sup && e < A.ex.support_cap; e += 64) dst[e] = token_of<DENSE>(A, R.lrow, lp[e]);
+  }
+  if (lane == 0) {
+    A.tau_out[R.bh] = tau_u + zmax; A.supp_out[R.bh] = supp;
+    if (A.ex.solve_evals != nullptr) A.ex.solve_evals[R.bh] = evals;
+  }
+}
+
+// Outputs of a row without any valid candidate, written by one wavefront.
+template <bool DENSE>
+__device__ __forceinline__ void empty_row_wave(const SolveArgs& A, int bh) {
+  const int lane = threadIdx.x & 63;
+  if (lane < kD / 4) *reinterpret_cast<float4*>(A.out + (size_t)bh * kD + 4 * lane) = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (lane == 0) {
+    A.tau_out[bh] = INFINITY; A.supp_out[bh] = 0;
+    if (A.ex.solve_evals != nullptr) A.ex.solve_evals[bh] = 0;
+    if (A.ex.tau_ref != nullptr && A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = 0.f;
+    if (A.ex.tau_ref != nullptr && A.ex.kept_supp_ref != nullptr) A.ex.kept_supp_ref[bh] = 0;
+    if (DENSE && A.ex.lse != nullptr) A.ex.lse[bh] = -INFINITY;
+  }
+}
+
+// Maxima of a row's groups -> row maximum, bound of tau and the ordered list of the groups above it (sh.zmax, sh.bound,
+// sh.n_pass, sh.glist), by the wavefronts whose turn it is: group (w * 64 * R + 64 k + lane) sits in register k.  With one
+// wavefront (rows of up to kWaveGroups groups: up to 65 536 candidates) nothing in here waits at a barrier.
+template <int R, bool ONE_WAVE>
+__device__ __forceinline__ void bound_groups(const float* pm, int n_chunks, float beta, int ibeta, SolveShared& sh) {
+  const int lane = threadIdx.x & 63, w = ONE_WAVE ? 0 : uniform(threadIdx.x >> 6);
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const int g0 = w * 64 * R + lane, last = max(n_chunks - 1, 0);
+  float m[R];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < R; ++k) m[k] = pm[min(g0 + 64 * k, last)];
+#pragma unroll
+  for (int k = 0; k < R; ++k) { m[k] = g0 + 64 * k < n_chunks ? m[k] : -INFINITY; mx = fmaxf(mx, m[k]); }
+  const float zmax = ONE_WAVE ? wave_max(mx) : block_max(mx, sh.red1);
+  const float eps = 4e-6f * fmaxf(1.f, fabsf(zmax));
+  float t = -1.0f - eps;
+  int n_pass = 0;
+  if (zmax > -INFINITY) {                                             // the same for all threads
+#pragma unroll
+    for (int k = 0; k < R; ++k) m[k] -= zmax;
+    int parity = 0;
+    t = group_bound(m, t, beta, ibeta, [&](float& f, float& d) {
+      f = wave_sum(f); d = wave_sum(d);
+      if (!ONE_WAVE) {
+        if (lane == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; }
+        __syncthreads();
+        f = sum_waves(&sh.red[parity][0][0], 3); d = sum_waves(&sh.red[parity][0][1], 3);
+        parity ^= 1;
+      }
+    });
+    t = fmaxf(t - eps, -1.0f - eps);
+    int off = 0;
+    if (!ONE_WAVE) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) off += __popcll(__ballot(m[k] > t));
+      if (lane == 0) sh.wcount[0][w] = off;
+      __syncthreads();
+      off = 0;
+      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[0][i]; if (i < w) off += ci; n_pass += ci; }
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const bool in = m[k] > t;
+      const uint64_t mk = __ballot(in);
+      if (in) sh.glist[off + __popcll(mk & lt)] = (uint16_t)(g0 + 64 * k);
+      off += __popcll(mk);
+    }
+    if (ONE_WAVE) n_pass = off;
+  }
+  if (threadIdx.x == 0) { sh.zmax = zmax; sh.bound = t; sh.n_pass = n_pass; }
+}
+
+// Scores of the listed groups above thr -> this wavefront's segment (z - zmax, position), in candidate order: it takes
+// n_pass / kSolveWaves consecutive groups, 16 of them (64 scores each) in flight.  Returns how many there are, also
+// when they are more than the segment holds.
+__device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int n_pass, float zmax, float thr, SolveShared& sh) {
+  const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const int per = (n_pass + kSolveWaves - 1) / kSolveWaves;
+  const int j0 = w * per, j1 = min(j0 + per, n_pass);
+  float* su = sh.list_u + w * kSegCap;
+  int32_t* sp = sh.list_pos + w * kSegCap;
+  int cnt = 0;
+  auto batch = [&](auto nc, int j) {
+    constexpr int N = decltype(nc)::value;
+    const int my_g = sh.glist[min(j + (lane & (N - 1)), j1 - 1)];
+    float v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      // past the row's end lies the next row or the group maxima, inside the workspace: masked below
+      v[i] = (zr + (size_t)__builtin_amdgcn_readlane(my_g, i) * R.chunk_tokens)[lane];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int p0 = __builtin_amdgcn_readlane(my_g, i) * R.chunk_tokens;
+      const bool in = j + i < j1 && lane < min(R.chunk_tokens, R.n_cand - p0) && v[i] > thr;
+      const uint64_t mk = __ballot(in);
+      const int o = cnt + __popcll(mk & lt);
+      if (in && o < kSegCap) { su[o] = v[i] - zmax; sp[o] = p0 + lane; }
+      cnt += __popcll(mk);
+    }
+  };
+  if (j1 - j0 > 0 && j1 - j0 <= 4) batch(IntC<4>{}, j0);
+  else for (int j = j0; j < j1; j += 16) batch(IntC<16>{}, j);
+  return cnt;
+}
+
+// Threshold, support and weighted value sum of a row whose candidates lie in the wavefronts' segments (n of them in this
+// one's): every wavefront keeps its entries in registers, an evaluation of the mass costs one barrier, and each then
+// gathers the value rows of its own part of the support.
+template <typename T, bool DENSE>
+__device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRef& R, int n, float lo_u, float zmax,
+                                                 float seed_u, SolveShared& sh) {
+  constexpr int KR = kSegCap / 64;
+  const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const T* v_pool = (const T*)A.v_pool;
+  float* su = sh.list_u + w * kSegCap;
+  int32_t* sp = sh.list_pos + w * kSegCap;
+  float u[KR];
+#pragma unroll
+  for (int k = 0; k < KR; ++k) u[k] = lane + 64 * k < n ? su[lane + 64 * k] : -INFINITY;
+  int supp = 0, evals = 0, parity = 0;
+  const float tau_u = with_beta(A.ibeta, [&](auto ib) {
+    constexpr int IB = decltype(ib)::value;
+    return solve_tau_core([&](float t, float& F, float& D, int& cnt) {
+      float f = 0.f, d = 0.f;
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < KR; ++k) {
+        if (64 * k < n) {                                             // wave-uniform
+          const float x = fmaxf(u[k] - t, 0.f);
+          const bool in = x > 0.f;
+          f += IB == 0 && !in ? 0.f : pow_beta(x, A.beta, IB);
+          d += in ? pow_beta_m1(x, A.beta, IB) : 0.f;
+          c += __popcll(__ballot(in));
+        }
+      }
+      f = wave_sum(f); d = wave_sum(d);
+      if (lane == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; sh.red[parity][w][2] = __int_as_float(c); }
+      __syncthreads();
+      F = sum_waves(&sh.red[parity][0][0], 3);
+      D = A.beta * sum_waves(&sh.red[parity][0][1], 3);
+      cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
+      parity ^= 1;
+    }, lo_u, seed_u, IB, supp, evals);
+  });
+  // the support in place: (weight, position), ascending
+  int n_sup = 0;
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    if (64 * k < n) {
+      const float x = u[k] - tau_u;
+      const bool in = x > 0.f;
+      const uint64_t mk = __ballot(in);
+      const int pos = in ? sp[lane + 64 * k] : 0;
+      __builtin_amdgcn_wave_barrier();
+      if (in) { const int o = n_sup + __popcll(mk & lt); su[o] = pow_beta(x, A.beta, A.ibeta); sp[o] = pos; }
+      n_sup += __popcll(mk);
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
+  // flight per lane; the next 64 are looked up before these are consumed
+  const int rs = lane >> 4, c = lane & 15;
+  float acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+  uint32_t row = n_sup > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, sp[min(lane, n_sup - 1)]) : 0u;
+  for (int e0 = 0; e0 < n_sup; e0 += 64) {
+    const uint32_t row_now = row;
+    row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, sp[min(e0 + 64 + lane, n_sup - 1)]);
+    const float p_now = e0 + lane < n_sup ? su[e0 + lane] : 0.f;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      Raw8<T> vr[8]; float pw[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int src = 32 * half + 4 * j + rs;
+        pw[j] = __shfl(p_now, src);
+        load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float vv[8];
+        widen8(vr[j], vv);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = fmaf(pw[j], vv[i], acc[i]);
+      }
+      if (e0 + 32 >= n_sup) break;                                    // wave-uniform
+    }
+  }
+  if (A.ex.support_tokens != nullptr) {
+    if (lane == 0) sh.wcount[0][w] = n_sup;
+    __syncthreads();
+    int off = 0;
+    for (int i = 0; i < w; ++i) off += sh.wcount[0][i];
+    int32_t* dst = A.ex.support_tokens + (size_t)R.bh * A.ex.support_cap;
+    for (int e = lane; e < n_sup && off + e < A.ex.support_cap; e += 64) dst[off + e] = token_of<DENSE>(A, R.lrow, sp[e]);
+  }
+  reduce_output(acc, sh, A.out + (size_t)R.bh * kD);
+  if (tid == 0) {
+    A.tau_out[R.bh] = tau_u + zmax; A.supp_out[R.bh] = supp;
+    if (A.ex.solve_evals != nullptr) A.ex.solve_evals[R.bh] = evals;
+  }
+}
+
+// Side outputs over ALL candidates of a row (mass and count above a given threshold, log-sum-exp of the whole cache).
+template <bool DENSE>
+__device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_cand, const float* zr, float zmax, SolveShared& sh) {
+  const int tid = threadIdx.x;
+  if (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) {
+    const float tr = A.ex.tau_ref[bh];
+    float f = 0.f; int c = 0;
+    for (int i = tid; i < n_cand; i += kSolveThreads) {
+      const float x = zr[i] - tr;
+      if (x > 0.f) { f += pow_beta(x, A.beta, A.ibeta); ++c; }
+    }
+    f = block_sum(f, sh.red1);
+    c = block_sum_i(c, sh.wcount[0]);
+    if (tid == 0) {
+      if (A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = f;
+      if (A.ex.kept_supp_ref != nullptr) A.ex.kept_supp_ref[bh] = c;
+    }
+  }
+  if (DENSE && A.ex.lse != nullptr) {
+    // log sum_j exp(s_j) with s_j = z_j / a, shifted by the maximum
+    const float inv_a = 1.0f / A.a;
+    float f = 0.f;
+    for (int i = tid; i < n_cand; i += kSolveThreads) f += __expf((zr[i] - zmax) * inv_a);
+    f = block_sum(f, sh.red1);
+    if (tid == 0) A.ex.lse[bh] = zmax * inv_a + __logf(f);
+  }
+}
+
+// A row of at most kPreGroups groups, from the group maxima to the outputs.  Returns false, with nothing written, when a
+// segment is too small for its candidates (attention so flat that more than about 12 000 are left).
+template <typename T, bool DENSE>
+__device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, const float* zr, const float* pm, float seed_z,
+                                          bool block_extras, SolveShared& sh) {
+  const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+  if (R.n_chunks <= kWaveGroups) {
+    if (w == 0) {
+      if (R.n_chunks <= kWaveGroups / 2) bound_groups<kWaveGroups / 128, true>(pm, R.n_chunks, A.beta, A.ibeta, sh);
+      else bound_groups<kWaveGroups / 64, true>(pm, R.n_chunks, A.beta, A.ibeta, sh);
+    }
+  } else {
+    bound_groups<kPreGroups / kSolveThreads, false>(pm, R.n_chunks, A.beta, A.ibeta, sh);
+  }
+  __syncthreads();
+  const float zmax = sh.zmax, bound = sh.bound;
+  if (!(zmax > -INFINITY)) {                                          // no valid candidate at all
+    if (w == 0) empty_row_wave<DENSE>(A, R.bh);
+    return true;
+  }
+  const int n = fetch_candidates(R, zr, uniform(sh.n_pass), zmax, zmax + bound, sh);
+  if (lane == 0) sh.wcount[1][w] = n;
+  __syncthreads();
+  // this thread's wavefront count -> total, segments too long, and the prefix of the first wavefront's gather
+  int cw = lane < kSolveWaves ? sh.wcount[1][lane] : 0;
+  const bool fits = __ballot(cw > kSegCap) == 0;
+  if (!fits) return false;
+  const int total = sum_waves_i(sh.wcount[1], 1);
+  const float lo_u = fminf(bound, -1e-7f), seed_u = seed_z - zmax;
+  if (__builtin_expect(total <= kWaveList, 1)) {
+    if (w == 0) {
+      int inc = cw;
+#pragma unroll
+      for (int d = 1; d < kSolveWaves; d <<= 1) { const int t = __shfl_up(inc, d); if (lane >= d) inc += t; }
+      if (lane < kSolveWaves) sh.pre[lane + 1] = inc;
+      if (lane == 0) sh.pre[0] = 0;
+      __builtin_amdgcn_wave_barrier();
+      if (total <= 64) finish_row_wave<T, DENSE, 1>(A, R, total, lo_u, zmax, seed_u, sh);
+      else finish_row_wave<T, DENSE, kWaveList / 64>(A, R, total, lo_u, zmax, seed_u, sh);
+    }
+  } else {
+    finish_row_block<T, DENSE>(A, R, n, lo_u, zmax, seed_u, sh);
+  }
+  if (block_extras) { __syncthreads(); side_outputs<DENSE>(A, R.bh, R.n_cand, zr, zmax, sh); }
+  return true;
+}
+
 template <typename T, bool DENSE>
 __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const SolveArgs A) {
   __shared__ SolveShared sh;
   const int Hq = A.Hq, Hkv = A.Hkv, P = A.P;
   const int bh = blockIdx.x, b = bh / Hq, hq = bh % Hq, hkv = hq / (Hq / Hkv);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
   const int n = A.seq_lens[b];
@@ -753,28 +1180,23 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
 
   // warm start (optional): requested with the first loads, used once zmax is known
   const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
+  const bool block_extras = (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) ||
+                            (DENSE && A.ex.lse != nullptr);
+  const RowRef R{b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks};
   float zmax, thr_f = 0.f;
-  // Rows of at most kPreGroups groups: thread t holds the maxima of the gpt consecutive groups gpt*t .. gpt*t+gpt-1
-  // (gpt = 1 up to 1024 groups)
-  float mypm[kPreR];
-#pragma unroll
-  for (int k = 0; k < kPreR; ++k) mypm[k] = -INFINITY;
   const bool pre = n_chunks <= kPreGroups;
-  const int gpt = (n_chunks + kSolveThreads - 1) / kSolveThreads;
-  // The filter passes are launched when the list CAPACITY allows longer rows than that; whether this row took them
-  // is decided here, from its actual length (they leave shorter rows alone).
+  if (__builtin_expect(pre, 1)) {
+    if (__builtin_expect(solve_row<T, DENSE>(A, R, zr, pm, seed_z, block_extras, sh), 1)) return;
+  }
+  // Longer rows, and those whose candidates outgrow LDS.
+  // The filter passes are launched when the list CAPACITY allows longer rows than kPreGroups; whether this row took
+  // them is decided here, from its actual length (they leave shorter rows alone).
   const bool filt = A.fcount != nullptr && !pre;
   if (filt) {
     zmax = n_cand > 0 ? A.frow[2 * bh] : -INFINITY;
     thr_f = n_cand > 0 ? A.frow[2 * bh + 1] : 0.f;
   } else if (pre) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < kPreR; ++k) {
-      const int g = gpt * tid + k;
-      if (k < gpt && g < n_chunks) { mypm[k] = pm[g]; mx = fmaxf(mx, mypm[k]); }
-    }
-    zmax = block_max(mx, sh.red1);
+    zmax = sh.zmax; thr_f = sh.zmax + sh.bound;
   } else {
     float mx = -INFINITY;
     for (int i = tid; i < n_chunks; i += kSolveThreads) mx = fmaxf(mx, pm[i]);
@@ -798,32 +1220,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
   // a lower bound of the mass at every slice boundary (an entry of slice j lies at least j-i slices above
   // boundary i), hence a tighter valid threshold: it becomes the starting point of the solve, and, if the
   // candidates did not fit in LDS, the threshold of one more compaction pass.
-  float thr = filt ? thr_f : zmax - 1.0f - 4e-6f * fmaxf(1.f, fabsf(zmax));
-  // Short rows: the group maxima (held by the threads) give a first certified bound of tau -- every group
-  // counted in a bin holds at least its maximum there -- and only the groups whose maximum exceeds it are
-  // read at all: their scores are fetched through an ordered list of group numbers, so that a row of any
-  // length up to kPreGroups groups normally takes one round of loads.
-  if (pre) {
-    const float step = (zmax - thr) * (1.0f / 64.0f), inv_step = 64.0f / (zmax - thr);
-    if (tid < 64) sh.hist[tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPreR; ++k)
-      if (k < gpt && mypm[k] > thr) atomicAdd(&sh.hist[min(63, (int)((mypm[k] - thr) * inv_step))], 1);
-    __syncthreads();
-    thr += (float)certified_level<64>(sh.hist, step, beta, ibeta, sh.flags) * step;
-    if (A.ex.tau_seed != nullptr) {
-      // A seed above that bound becomes the candidate threshold if the group maxima alone already put a
-      // mass of 1 above it (then the full mass there is >= 1, i.e. the seed is a lower bound of tau).
-      const bool try_seed = seed_z > thr && seed_z < zmax;            // false for NaN
-      float f = 0.f;
-#pragma unroll
-      for (int k = 0; k < kPreR; ++k)
-        if (try_seed && mypm[k] > seed_z) f += pow_beta(mypm[k] - seed_z, beta, ibeta);
-      f = block_sum(f, sh.red1);
-      if (try_seed && f >= 1.0001f) thr = seed_z;
-    }
-  }
+  float thr = filt || pre ? thr_f : zmax - 1.0f - 4e-6f * fmaxf(1.f, fabsf(zmax));
   const float seed_u = seed_z - zmax;
   int evals = 0;
   float lo_u = thr - zmax;
@@ -879,53 +1276,9 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     __syncthreads();
   }
   if (pre) {
-    // ordered list of the groups above the bound: thread t owns consecutive groups, so (thread, k) order is group order
-    int* glist = reinterpret_cast<int*>(sh.list_row);        // free until the solve is done
-    int n_pass = 0;
-    for (int refine = 0;; ++refine) {
-    int goff;
-    n_pass = 0;
-    if (gpt == 1) {                                          // one group per thread (rows up to 65 536 tokens): a ballot
-      const bool gp = mypm[0] > thr;
-      const uint64_t gmk = __ballot(gp);
-      if (lane == 0) sh.wcount[parity][w] = __popcll(gmk);
-      __syncthreads();
-      goff = 0;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) goff += ci; n_pass += ci; }
-      if (gp) glist[goff + __popcll(gmk & lt)] = tid;
-    } else {
-      int mine = 0;
-#pragma unroll
-      for (int k = 0; k < kPreR; ++k) mine += mypm[k] > thr ? 1 : 0;
-      int inc = mine;
-#pragma unroll
-      for (int dlt = 1; dlt < 64; dlt <<= 1) { const int t = __shfl_up(inc, dlt); if (lane >= dlt) inc += t; }
-      if (lane == 63) sh.wcount[parity][w] = inc;
-      __syncthreads();
-      goff = inc - mine;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) goff += ci; n_pass += ci; }
-#pragma unroll
-      for (int k = 0; k < kPreR; ++k)
-        if (mypm[k] > thr) glist[goff++] = gpt * tid + k;
-    }
-    parity ^= 1;
-    n_pass = __builtin_amdgcn_readfirstlane(n_pass);
-    __syncthreads();
-    // The usual row is done here: a few dozen groups pass.  A flat row, where most groups still pass, has its group
-    // maxima crowded into the last few of the 64 steps below the maximum; the same certificate on a histogram of
-    // [bound, maximum] resolves them (twice at most: 1/64^3 of the first width), and the list is rebuilt.
-    if (__builtin_expect(n_pass <= kSolveWaves * kRoundLoads || refine == 2, 1)) break;
-    const float step2 = (zmax - thr) * (1.0f / 64.0f), inv_step2 = 64.0f / (zmax - thr);
-    if (tid < 64) sh.hist[tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPreR; ++k)
-      if (k < gpt && mypm[k] > thr) atomicAdd(&sh.hist[min(63, (int)((mypm[k] - thr) * inv_step2))], 1);
-    __syncthreads();
-    const int level2 = certified_level<64>(sh.hist, step2, beta, ibeta, sh.flags);
-    if (level2 == 0) break;
-    thr += (float)level2 * step2;
-    }
+    // the groups above the bound are listed already (sh.glist)
+    const uint16_t* glist = sh.glist;
+    const int n_pass = uniform(sh.n_pass);
     // wavefront w of a round owns `per` consecutive list entries: (round, w, load, lane) is candidate order
     constexpr int kRoundGroups = kSolveWaves * kRoundLoads;
     // second half of a round: mask, count, exchange the counts (one barrier), ordered compaction into the list
@@ -1052,84 +1405,6 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
   }
   __syncthreads();
 
-  // Short lists and no side output over all candidates (the usual call): ONE wavefront finishes the row --
-  // V rows resolved while it solves in registers, support compacted with ballots, values gathered by its four
-  // 16-lane rows -- and the other fifteen leave; nothing below this point needs a barrier then.
-  const bool block_extras = (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) ||
-                            (DENSE && A.ex.lse != nullptr);
-  if (__builtin_expect(in_lds && n_list <= kWaveList && !block_extras, 1)) {
-    if (w != 0) return;
-    constexpr int KW = kWaveList / 64;
-    float u[KW]; int pos[KW]; uint32_t row[KW];
-#pragma unroll
-    for (int k = 0; k < KW; ++k) {
-      const int e = lane + 64 * k;
-      u[k] = e < n_list ? sh.list_u[e] : -INFINITY;
-      pos[k] = e < n_list ? sh.list_pos[e] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < KW; ++k) row[k] = v_row_of<DENSE>(A, b, lrow, hkv, pos[k]);     // clamped, unconditional
-    int supp_w = 0;
-    const float tau_w = solve_tau_regs(u, lo_u, seed_u, beta, ibeta, supp_w, evals);
-    // ordered compaction of the support: (p, row, position) of entry e = lane + 64 k, k-major = candidate order
-    int n_sup = 0;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < KW; ++k) {
-      const float x = u[k] - tau_w;
-      const bool in = x > 0.f;
-      const uint64_t mk = __ballot(in);
-      if (in) {
-        const int o = n_sup + __popcll(mk & lt);
-        sh.list_u[o] = pow_beta(x, beta, ibeta);
-        sh.list_row[o] = row[k];
-        sh.list_pos[o] = pos[k];
-      }
-      n_sup += __popcll(mk);
-    }
-    __builtin_amdgcn_wave_barrier();
-    // weighted value sum: 4 row slots x 16 lanes, batches of 8 independent 16-byte loads per lane
-    const int rs = lane >> 4, c = lane & 15;
-    float acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-    for (int e0 = 0; e0 < n_sup; e0 += 32) {
-      Raw8<T> vr[8]; float pw[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = e0 + 4 * j + rs;
-        const int ec = min(e, n_sup - 1);                              // clamped: loads stay unconditional
-        pw[j] = e < n_sup ? sh.list_u[ec] : 0.f;
-        load_raw8(v_pool + (size_t)sh.list_row[ec] * kD + 8 * c, vr[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float vv[8];
-        widen8(vr[j], vv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(pw[j], vv[i], acc[i]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      acc[i] += __shfl_xor(acc[i], 16);
-      acc[i] += __shfl_xor(acc[i], 32);
-    }
-    if (lane < 16) {
-      *reinterpret_cast<float4*>(out + 8 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-      *reinterpret_cast<float4*>(out + 8 * c + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    }
-    if (A.ex.support_tokens != nullptr) {
-      int32_t* dst = A.ex.support_tokens + (size_t)bh * A.ex.support_cap;
-      for (int e = lane; e < n_sup && e < A.ex.support_cap; e += 64) dst[e] = token_of<DENSE>(A, lrow, sh.list_pos[e]);
-    }
-    if (lane == 0) {
-      A.tau_out[bh] = tau_w + zmax; A.supp_out[bh] = supp_w;
-      if (A.ex.solve_evals != nullptr) A.ex.solve_evals[bh] = evals;
-    }
-    return;
-  }
-
   float tau_u; int supp;
   if (in_lds) {
     // V row of every candidate, fetched now (two dependent loads) and consumed after the solve
@@ -1249,29 +1524,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     if (A.ex.solve_evals != nullptr) A.ex.solve_evals[bh] = evals;
   }
 
-  // ---- optional side outputs over ALL candidates ----------------------------------------
-  if (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) {
-    const float tr = A.ex.tau_ref[bh];
-    float f = 0.f; int c = 0;
-    for (int i = tid; i < n_cand; i += kSolveThreads) {
-      const float x = zr[i] - tr;
-      if (x > 0.f) { f += pow_beta(x, beta, ibeta); ++c; }
-    }
-    f = block_sum(f, sh.red1);
-    c = block_sum_i(c, sh.wcount[0]);
-    if (tid == 0) {
-      if (A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = f;
-      if (A.ex.kept_supp_ref != nullptr) A.ex.kept_supp_ref[bh] = c;
-    }
-  }
-  if (DENSE && A.ex.lse != nullptr) {
-    // log sum_j exp(s_j) with s_j = z_j / a, shifted by the maximum
-    const float inv_a = 1.0f / A.a;
-    float f = 0.f;
-    for (int i = tid; i < n_cand; i += kSolveThreads) f += __expf((zr[i] - zmax) * inv_a);
-    f = block_sum(f, sh.red1);
-    if (tid == 0) A.ex.lse[bh] = zmax * inv_a + __logf(f);
-  }
+  if (block_extras) side_outputs<DENSE>(A, bh, n_cand, zr, zmax, sh);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -274,4 +274,17 @@ __device__ __forceinline__ float pow_beta_m1(float x, float beta, int ibeta) {
   }
 }
 
+// Calls fn with beta as a compile-time exponent (1..4, or 0 for any other), so that a loop over registers carries one
+// product per entry instead of a branch on the exponent.
+template <int N> struct IntC { static constexpr int value = N; };
+template <typename F> __device__ __forceinline__ auto with_beta(int ibeta, F&& fn) {
+  switch (ibeta) {
+    case 1: return fn(IntC<1>{});
+    case 2: return fn(IntC<2>{});
+    case 3: return fn(IntC<3>{});
+    case 4: return fn(IntC<4>{});
+    default: return fn(IntC<0>{});
+  }
+}
+
 }  // namespace ekv
