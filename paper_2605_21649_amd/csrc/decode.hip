@@ -504,10 +504,15 @@ __global__ __launch_bounds__(kFilterThreads) void filter_compact_kernel(const Fi
 // pass 2: threshold, probabilities, weighted value sum
 // ------------------------------------------------------------------------------------------
 struct SolveShared {
-  // Candidates, z - zmax and position in the candidate order: wavefront w's segment is [w * kSegCap, (w + 1) * kSegCap).
-  // The general path uses the first kListCap entries as one list.
-  float list_u[kSolveWaves * kSegCap];
-  int32_t list_pos[kSolveWaves * kSegCap];
+  union {
+    // Candidates, z - zmax (float bits) and position in the candidate order: wavefront w's segment is
+    // [w * kSegCap, (w + 1) * kSegCap).
+    uint2 seg[kSolveWaves * kSegCap];
+    struct {                      // the general path's one list, and the support of a row that one wavefront finishes
+      float list_u[kListCap];
+      int32_t list_pos[kListCap];
+    };
+  };
   union {
     uint32_t list_row[kListCap];  // their V row: (phys*Hkv + hkv)*P + tok
     uint16_t glist[kPreGroups];   // the groups that can hold a candidate, ascending
@@ -522,7 +527,6 @@ struct SolveShared {
   float zmax, bound;              // row maximum, certified lower bound of tau relative to it
   int n_pass;
 };
-static_assert(kListCap <= kSolveWaves * kSegCap, "the general path's list lies in the segments");
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
 
 // Sum of one value per wavefront kept in LDS at a stride: one read per lane and a DPP row sum, the same in every
@@ -762,16 +766,24 @@ __device__ __forceinline__ void gather_support(const T* __restrict__ v_pool, con
   }
 }
 
+// LDS accesses of one wavefront on either side keep their order (the hardware executes them in order; the compiler is told).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Ranges of a row's candidates, as a wavefront that finishes the row needs them.
 struct RowRef { int b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks; };
 
 // A certified lower bound of tau (relative to the row maximum) from group maxima relative to it: every group holds at
 // least its maximum, so the mass of the maxima alone is a lower bound of the mass, and any point where it is >= 1 lies
 // left of tau.  F^(1/beta) is a norm of (u - t)_+, hence convex in t: Newton's steps on it from a point where F >= 1
-// stay left of the root.  They aim at a mass of 1.0001, which covers the rounding of the sums.  `sums(f, d)` adds f and
-// d up over all threads that hold maxima.
+// stay left of the root.  They aim at a mass of 1.0001, which covers the rounding of the sums.  Below beta = 1 (alpha
+// above 2) that fails, but sum x^beta >= (sum x)^beta there, so the point where the plain sum reaches 1 is a bound.
+// `sums(f, d)` adds f and d up over all threads that hold maxima.
 template <int R, typename Sums>
 __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, float beta, int ibeta, Sums&& sums) {
+  if (beta < 1.f) { beta = 1.f; ibeta = 1; }
   return with_beta(ibeta, [&](auto ib) {
     constexpr int IB = decltype(ib)::value;
     const float target = 1.0f + 1e-4f / beta;
@@ -817,9 +829,11 @@ __device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef
 #pragma unroll
   for (int k = 0; k < KW; ++k) {
     const int e = lane + 64 * k;
-    u[k] = e < n_list ? lu[at[k]] : -INFINITY;
-    pos[k] = e < n_list ? lp[at[k]] : 0;
+    const uint2 c = sh.seg[at[k]];
+    u[k] = e < n_list ? __uint_as_float(c.x) : -INFINITY;
+    pos[k] = e < n_list ? (int)c.y : 0;
   }
+  wave_order();                                                       // the support is written over the segments below
 #pragma unroll
   for (int k = 0; k < KW; ++k) row[k] = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, pos[k]);     // clamped, unconditional
   int supp = 0, evals = 0;
@@ -951,36 +965,58 @@ __device__ __forceinline__ void bound_groups(const float* pm, int n_chunks, floa
 }
 
 // Scores of the listed groups above thr -> this wavefront's segment (z - zmax, position), in candidate order: it takes
-// n_pass / kSolveWaves consecutive groups, 16 of them (64 scores each) in flight.  Returns how many there are, also
-// when they are more than the segment holds.
+// n_pass / kSolveWaves consecutive groups.  Sixteen lanes read the (at most 64) scores of a group with one 16-byte load
+// each, so a load takes four groups and the usual row needs one; the lanes' order, and within a lane the four scores',
+// is candidate order.  Returns how many there are, also when they are more than the segment holds.
 __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int n_pass, float zmax, float thr, SolveShared& sh) {
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  const uint64_t lt = (1ull << lane) - 1ull;
   const int per = (n_pass + kSolveWaves - 1) / kSolveWaves;
   const int j0 = w * per, j1 = min(j0 + per, n_pass);
-  float* su = sh.list_u + w * kSegCap;
-  int32_t* sp = sh.list_pos + w * kSegCap;
+  if (j0 >= j1) return 0;                                             // wave-uniform
+  uint2* seg = sh.seg + w * kSegCap;
+  const int sub = lane >> 4, in_group = 4 * (lane & 15);
   int cnt = 0;
-  auto batch = [&](auto nc, int j) {
-    constexpr int N = decltype(nc)::value;
-    const int my_g = sh.glist[min(j + (lane & (N - 1)), j1 - 1)];
-    float v[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      // past the row's end lies the next row or the group maxima, inside the workspace: masked below
-      v[i] = (zr + (size_t)__builtin_amdgcn_readlane(my_g, i) * R.chunk_tokens)[lane];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int p0 = __builtin_amdgcn_readlane(my_g, i) * R.chunk_tokens;
-      const bool in = j + i < j1 && lane < min(R.chunk_tokens, R.n_cand - p0) && v[i] > thr;
-      const uint64_t mk = __ballot(in);
-      const int o = cnt + __popcll(mk & lt);
-      if (in && o < kSegCap) { su[o] = v[i] - zmax; sp[o] = p0 + lane; }
-      cnt += __popcll(mk);
+  // tokens per group and per row are multiples of 4: a lane's four scores are valid together
+  auto request = [&](int j, int& p, float4& v) {
+    const int g = sh.glist[min(j + sub, j1 - 1)];
+    p = g * R.chunk_tokens + min(in_group, R.chunk_tokens - 4);
+    p = min(p, R.n_cand - 4);
+    v = *reinterpret_cast<const float4*>(zr + p);
+    if (j + sub >= j1 || in_group >= R.chunk_tokens || g * R.chunk_tokens + in_group >= R.n_cand) p = -1;
+  };
+  auto compact = [&](int p, const float4& v) {
+    const float t = p >= 0 ? thr : INFINITY;
+    const bool i0 = v.x > t, i1 = v.y > t, i2 = v.z > t, i3 = v.w > t;
+    const uint64_t m0 = __ballot(i0), m1 = __ballot(i1), m2 = __ballot(i2), m3 = __ballot(i3);
+    int o = cnt;
+    o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m0, o));
+    o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, o));
+    o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2, o));
+    o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3, o));
+    cnt += __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
+    if (cnt <= kSegCap) {                                             // wave-uniform
+      if (i0) seg[o] = make_uint2(__float_as_uint(v.x - zmax), (uint32_t)p);
+      o += i0;
+      if (i1) seg[o] = make_uint2(__float_as_uint(v.y - zmax), (uint32_t)p + 1);
+      o += i1;
+      if (i2) seg[o] = make_uint2(__float_as_uint(v.z - zmax), (uint32_t)p + 2);
+      o += i2;
+      if (i3) seg[o] = make_uint2(__float_as_uint(v.w - zmax), (uint32_t)p + 3);
     }
   };
-  if (j1 - j0 > 0 && j1 - j0 <= 4) batch(IntC<4>{}, j0);
-  else for (int j = j0; j < j1; j += 16) batch(IntC<16>{}, j);
+  if (j1 - j0 <= 4) {
+    int p; float4 v;
+    request(j0, p, v);
+    compact(p, v);
+  } else {
+    for (int j = j0; j < j1; j += 32) {                               // eight loads, 32 groups in flight
+      int p[8]; float4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) request(j + 4 * i, p[i], v[i]);     // past j1: its last group again, masked
+#pragma unroll
+      for (int i = 0; i < 8; ++i) compact(p[i], v[i]);
+    }
+  }
   return cnt;
 }
 
@@ -994,11 +1030,10 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
   const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
-  float* su = sh.list_u + w * kSegCap;
-  int32_t* sp = sh.list_pos + w * kSegCap;
+  uint2* seg = sh.seg + w * kSegCap;
   float u[KR];
 #pragma unroll
-  for (int k = 0; k < KR; ++k) u[k] = lane + 64 * k < n ? su[lane + 64 * k] : -INFINITY;
+  for (int k = 0; k < KR; ++k) u[k] = lane + 64 * k < n ? __uint_as_float(seg[lane + 64 * k].x) : -INFINITY;
   int supp = 0, evals = 0, parity = 0;
   const float tau_u = with_beta(A.ibeta, [&](auto ib) {
     constexpr int IB = decltype(ib)::value;
@@ -1032,11 +1067,11 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
       const float x = u[k] - tau_u;
       const bool in = x > 0.f;
       const uint64_t mk = __ballot(in);
-      const int pos = in ? sp[lane + 64 * k] : 0;
-      __builtin_amdgcn_wave_barrier();
-      if (in) { const int o = n_sup + __popcll(mk & lt); su[o] = pow_beta(x, A.beta, A.ibeta); sp[o] = pos; }
+      const uint32_t pos = seg[lane + 64 * k].y;
+      wave_order();
+      if (in) seg[n_sup + __popcll(mk & lt)] = make_uint2(__float_as_uint(pow_beta(x, A.beta, A.ibeta)), pos);
       n_sup += __popcll(mk);
-      __builtin_amdgcn_wave_barrier();
+      wave_order();
     }
   }
   // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
@@ -1045,11 +1080,11 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
   float acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  uint32_t row = n_sup > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, sp[min(lane, n_sup - 1)]) : 0u;
+  uint32_t row = n_sup > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(lane, n_sup - 1)].y) : 0u;
   for (int e0 = 0; e0 < n_sup; e0 += 64) {
     const uint32_t row_now = row;
-    row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, sp[min(e0 + 64 + lane, n_sup - 1)]);
-    const float p_now = e0 + lane < n_sup ? su[e0 + lane] : 0.f;
+    row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, n_sup - 1)].y);
+    const float p_now = e0 + lane < n_sup ? __uint_as_float(seg[e0 + lane].x) : 0.f;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       Raw8<T> vr[8]; float pw[8];
@@ -1075,7 +1110,7 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
     int off = 0;
     for (int i = 0; i < w; ++i) off += sh.wcount[0][i];
     int32_t* dst = A.ex.support_tokens + (size_t)R.bh * A.ex.support_cap;
-    for (int e = lane; e < n_sup && off + e < A.ex.support_cap; e += 64) dst[off + e] = token_of<DENSE>(A, R.lrow, sp[e]);
+    for (int e = lane; e < n_sup && off + e < A.ex.support_cap; e += 64) dst[off + e] = token_of<DENSE>(A, R.lrow, (int)seg[e].y);
   }
   reduce_output(acc, sh, A.out + (size_t)R.bh * kD);
   if (tid == 0) {

@@ -1,0 +1,91 @@
+"""The end of the entmax decode (threshold, support, value sum) at the sizes where its branches meet: one group of
+scores, a wavefront's 512 and 1024 group maxima and one more of each, groups of fewer than 64 tokens, a partial last
+group, and candidate lists of a lane's one entry, its four, the wavefronts' segments and beyond them.
+
+Results against the float64 oracle under the rules of tests/helpers.py (tau 4e-6, output 1e-5 / 2e-3, support exact up
+to tokens within float32 resolution of tau)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import entmaxkv_oracle as orc
+from paper_2605_21649_amd import binding as ekv
+from paper_2605_21649_amd import synth
+from tests.helpers import DeviceState, unit_kv, check_decode_unit
+
+pytestmark = pytest.mark.gpu
+
+# tokens, page, dtype, score scale (times 1/sqrt(128)), alpha
+CASES = [(1, 16, "bf16", 1.0, 1.5), (4, 4, "f32", 1.0, 2.0), (61, 16, "f32", 1.0, 1.5),
+         (512 * 64, 16, "bf16", 1.0, 1.5), (512 * 64 + 1, 16, "bf16", 1.0, 1.25),
+         (1024 * 64 - 15, 32, "bf16", 0.5, 1.5), (1024 * 64 + 1, 64, "bf16", 1.0, 2.0),
+         (513 * 60 - 7, 12, "bf16", 0.5, 4.0 / 3.0), (1025 * 48 - 3, 48, "bf16", 1.0, 1.5),
+         # candidates after the bound: a few hundred, a few thousand (segments), more than the segments hold
+         (20000, 16, "f32", 0.3, 1.5), (40000, 8, "f32", 0.1, 1.25), (30000, 16, "f32", 0.05, 1.5),
+         (40000, 16, "f32", 0.01, 2.0), (70000, 16, "f32", 0.15, 1.7), (3000, 20, "f32", 0.6, 3.0), (70000, 16, "f32", 0.1, 2.5)]
+
+
+@pytest.mark.parametrize("tokens,page,dtype,scale,alpha", CASES)
+def test_solve_at_the_edges_of_its_paths(tokens, page, dtype, scale, alpha):
+    w = synth.Workload("edge", 1, 2, 1, 128, tokens, page, dtype, alpha=alpha, scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(w, 77 + tokens, device="cpu")
+    st = DeviceState(w, inp)
+    toks = torch.full((1, 2, 65536), -1, device="cuda", dtype=torch.int32)
+    ex = ekv.decode_extras(support_tokens=toks)
+    ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL),
+                        extras=ex)
+    dense = [x.clone() for x in (st.out, st.tau, st.supp, toks)]
+    # the same pages as lists: the sparse decode of every page is the dense one, bit for bit
+    st.page_idx.copy_(torch.arange(st.cap, device="cuda", dtype=torch.int32).expand(1, 2, st.cap))
+    st.n_sel.fill_(st.cap)
+    toks.fill_(-1)
+    ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                          st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=ex)
+    torch.cuda.synchronize()
+    for a, b in zip(dense, (st.out, st.tau, st.supp, toks)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    for hq in range(2):
+        q, K, V = unit_kv(inp, w, 0, hq)
+        ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
+        check_decode_unit(w, st.out[0, hq].cpu().numpy(), float(st.tau[0, hq]), int(st.supp[0, hq]),
+                          toks[0, hq].cpu().numpy(), ref, boundary_expected=True)
+
+
+@pytest.mark.parametrize("lens", [(1, 64, 0), (2048, 1, 700)])
+def test_solve_side_outputs_of_short_and_flat_rows(lens):
+    """Mass and count above a reference threshold and the log-sum-exp cover all candidates, whichever path a row took."""
+    for scale in (1.0, 0.05):
+        w = synth.Workload("edge", 3, 2, 1, 128, 2048, 16, "f32", scale=scale / math.sqrt(128.0))
+        inp = synth.make_inputs(w, 5, device="cpu")
+        inp["seq_lens"] = torch.tensor(lens, dtype=torch.int32)
+        st = DeviceState(w, inp)
+        f = dict(device="cuda", dtype=torch.float32)
+        lse, mass, cnt = torch.zeros(3, 2, **f), torch.zeros(3, 2, **f), torch.zeros(3, 2, device="cuda", dtype=torch.int32)
+        refs = {}
+        for b in range(3):
+            for hq in range(2):
+                if lens[b]:
+                    q, K, V = unit_kv(inp, w, b, hq)
+                    refs[b, hq] = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
+        tau_ref = torch.zeros(3, 2, **f)
+        for (b, hq), r in refs.items():
+            tau_ref[b, hq] = r["tau"] - 0.01
+        ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL),
+                            extras=ekv.decode_extras(tau_ref=tau_ref, kept_mass_ref=mass, kept_supp_ref=cnt, lse=lse))
+        torch.cuda.synchronize()
+        for b in range(3):
+            for hq in range(2):
+                if not lens[b]:
+                    assert torch.isposinf(st.tau[b, hq]) and not st.out[b, hq].any() and int(st.supp[b, hq]) == 0
+                    assert torch.isneginf(lse[b, hq]) and float(mass[b, hq]) == 0 and int(cnt[b, hq]) == 0
+                    continue
+                r = refs[b, hq]
+                check_decode_unit(w, st.out[b, hq].cpu().numpy(), float(st.tau[b, hq]), int(st.supp[b, hq]), None, r,
+                                  boundary_expected=True)
+                z, t = (w.alpha - 1.0) * r["s"], float(tau_ref[b, hq])
+                assert abs(float(lse[b, hq]) - (r["s"].max() + np.log(np.exp(r["s"] - r["s"].max()).sum()))) < 1e-5 * 10
+                over = np.clip(z - t, 0, None)
+                assert abs(float(mass[b, hq]) - (over ** 2).sum()) < 1e-4
+                assert abs(int(cnt[b, hq]) - int((over > 0).sum())) <= int((np.abs(z - t) < 2e-6).sum())
