@@ -20,7 +20,7 @@ constexpr int kScoreThreads = 256;
 constexpr int kSolveThreads = 1024;
 constexpr int kSolveWaves = kSolveThreads / 64;
 constexpr int kListCap = 4096;          // candidate entries the general path holds in LDS
-constexpr int kSegCap = 768;            // candidate entries a wavefront of the solve holds in LDS (and in registers)
+constexpr int kSegs = 16;               // candidate lists are cut into this many segments, whatever the workgroup's size
 constexpr int kSpillCap = 65536;        // entries of a row's overflow list in the workspace (longer lists: the row is streamed)
 constexpr int kWaveGroups = 1024;       // up to this many group maxima are bounded by one wavefront, more by all of them
 constexpr int kRoundLoads = 16;         // loads per lane and compaction round
@@ -504,10 +504,10 @@ __global__ __launch_bounds__(kFilterThreads) void filter_compact_kernel(const Fi
 // pass 2: threshold, probabilities, weighted value sum
 // ------------------------------------------------------------------------------------------
 struct SolveShared {
+  static constexpr int kWaves = kSolveWaves, kSegCap = 768;     // entries per segment, held in LDS and in registers
   union {
-    // Candidates, z - zmax (float bits) and position in the candidate order: wavefront w's segment is
-    // [w * kSegCap, (w + 1) * kSegCap).
-    uint2 seg[kSolveWaves * kSegCap];
+    // Candidates, z - zmax (float bits) and position in the candidate order; segment i is [i * kSegCap, (i + 1) * kSegCap).
+    uint2 seg[kSegs * kSegCap];
     struct {                      // the general path's one list, and the support of a row that one wavefront finishes
       float list_u[kListCap];
       int32_t list_pos[kListCap];
@@ -517,10 +517,10 @@ struct SolveShared {
     uint32_t list_row[kListCap];  // their V row: (phys*Hkv + hkv)*P + tok
     uint16_t glist[kPreGroups];   // the groups that can hold a candidate, ascending
   };
-  float obuf[kSolveWaves][kD];
-  float red[2][kSolveWaves][3];
-  int wcount[2][kSolveWaves];
-  int pre[kSolveWaves + 1];       // exclusive prefix of the segments' lengths
+  float obuf[kSegs][kD];
+  float red[2][kSegs][3];
+  int wcount[2][kSegs];
+  int pre[kSegs + 1];             // exclusive prefix of the segments' lengths
   float red1[kSolveWaves];
   int hist[64];                   // candidates per 1/64 slice of [thr, zmax] (threshold tightening)
   int flags[64];
@@ -529,15 +529,12 @@ struct SolveShared {
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
 
-// Sum of one value per wavefront kept in LDS at a stride: one read per lane and a DPP row sum, the same in every
-// wavefront (a loop over the wavefronts reads LDS sixteen times in a row).
-__device__ __forceinline__ float sum_waves(const float* v, int stride) {
-  const int l = threadIdx.x & 15;
-  return row16_sum(l < kSolveWaves ? v[l * stride] : 0.f);
-}
+// Sum of one value per segment (or wavefront) kept in LDS at a stride: one read per lane and a DPP row sum, the same in
+// every wavefront (a loop reads LDS sixteen times in a row).
+static_assert(kSegs == 16 && kSolveWaves == 16, "one DPP row");
+__device__ __forceinline__ float sum_waves(const float* v, int stride) { return row16_sum(v[(threadIdx.x & 15) * stride]); }
 __device__ __forceinline__ int sum_waves_i(const int* v, int stride) {
-  const int l = threadIdx.x & 15;
-  int x = l < kSolveWaves ? v[l * stride] : 0;
+  int x = v[(threadIdx.x & 15) * stride];
   x += dpp_move_i<0xB1>(x); x += dpp_move_i<0x4E>(x); x += dpp_move_i<0x141>(x); x += dpp_move_i<0x140>(x);
   return __builtin_amdgcn_readfirstlane(x);
 }
@@ -719,24 +716,29 @@ __device__ __forceinline__ int token_of(const SolveArgs& A, int bh, int pos) {
   return lp * A.P + tok;
 }
 
-// Final reduction of the per-lane partial outputs (acc[8] = channels 8c..8c+7 of a row slot).
-__device__ __forceinline__ void reduce_output(float (&acc)[8], SolveShared& sh, float* __restrict__ out) {
-  const int tid = threadIdx.x, c = tid & 15, w = tid >> 6;
+// Partial output of one segment: the per-lane sums acc[8] (channels 8c..8c+7 of a row slot) of one wavefront.
+template <typename SH>
+__device__ __forceinline__ void store_partial(float (&acc)[8], SH& sh, int seg) {
+  const int lane = threadIdx.x & 63, c = lane & 15;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     acc[i] += __shfl_xor(acc[i], 16);
     acc[i] += __shfl_xor(acc[i], 32);
   }
-  __syncthreads();
-  if ((tid & 63) < 16) {
+  if (lane < 16) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sh.obuf[w][8 * c + i] = acc[i];
+    for (int i = 0; i < 8; ++i) sh.obuf[seg][8 * c + i] = acc[i];
   }
+}
+// The segments' partial outputs, added in their order.  Starts with a barrier.
+template <typename SH>
+__device__ __forceinline__ void sum_partials(const SH& sh, float* __restrict__ out) {
   __syncthreads();
-  if (tid < kD) {
+  if (threadIdx.x < kD) {
     float s = 0.f;
-    for (int i = 0; i < kSolveWaves; ++i) s += sh.obuf[i][tid];
-    out[tid] = s;
+#pragma unroll
+    for (int i = 0; i < kSegs; ++i) s += sh.obuf[i][threadIdx.x];
+    out[threadIdx.x] = s;
   }
 }
 
@@ -809,9 +811,9 @@ __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, floa
 
 // The end of a row whose candidates are few: threshold, support and weighted value sum by ONE wavefront, KW entries per
 // lane, taken from the segments (sh.pre: the prefix of their lengths).  V rows are looked up while the threshold is solved.
-template <typename T, bool DENSE, int KW>
+template <typename T, bool DENSE, int KW, typename SH>
 __device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef& R, int n_list, float lo_u, float zmax,
-                                                float seed_u, SolveShared& sh) {
+                                                float seed_u, SH& sh) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
@@ -823,8 +825,8 @@ __device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef
     const int e = lane + 64 * k;
     int seg = 0;                                                      // last segment that starts at or before e
 #pragma unroll
-    for (int d = kSolveWaves / 2; d >= 1; d >>= 1) seg += sh.pre[seg + d] <= e ? d : 0;
-    at[k] = seg * kSegCap + min(e - sh.pre[seg], kSegCap - 1);
+    for (int d = kSegs / 2; d >= 1; d >>= 1) seg += sh.pre[seg + d] <= e ? d : 0;
+    at[k] = seg * SH::kSegCap + min(e - sh.pre[seg], SH::kSegCap - 1);
   }
 #pragma unroll
   for (int k = 0; k < KW; ++k) {
@@ -914,15 +916,15 @@ __device__ __forceinline__ void empty_row_wave(const SolveArgs& A, int bh) {
 // Maxima of a row's groups -> row maximum, bound of tau and the ordered list of the groups above it (sh.zmax, sh.bound,
 // sh.n_pass, sh.glist), by the wavefronts whose turn it is: group (w * 64 * R + 64 k + lane) sits in register k.  With one
 // wavefront (rows of up to kWaveGroups groups: up to 65 536 candidates) nothing in here waits at a barrier.
-template <int R, bool ONE_WAVE>
-__device__ __forceinline__ void bound_groups(const float* pm, int n_chunks, float beta, int ibeta, SolveShared& sh) {
+template <int R, bool ONE_WAVE, typename Max, typename SH>
+__device__ __forceinline__ void bound_groups(Max&& group_max, int n_chunks, float beta, int ibeta, SH& sh) {
   const int lane = threadIdx.x & 63, w = ONE_WAVE ? 0 : uniform(threadIdx.x >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const int g0 = w * 64 * R + lane, last = max(n_chunks - 1, 0);
   float m[R];
   float mx = -INFINITY;
 #pragma unroll
-  for (int k = 0; k < R; ++k) m[k] = pm[min(g0 + 64 * k, last)];
+  for (int k = 0; k < R; ++k) m[k] = group_max(min(g0 + 64 * k, last));
 #pragma unroll
   for (int k = 0; k < R; ++k) { m[k] = g0 + 64 * k < n_chunks ? m[k] : -INFINITY; mx = fmaxf(mx, m[k]); }
   const float zmax = ONE_WAVE ? wave_max(mx) : block_max(mx, sh.red1);
@@ -950,7 +952,7 @@ __device__ __forceinline__ void bound_groups(const float* pm, int n_chunks, floa
       if (lane == 0) sh.wcount[0][w] = off;
       __syncthreads();
       off = 0;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[0][i]; if (i < w) off += ci; n_pass += ci; }
+      for (int i = 0; i < SH::kWaves; ++i) { const int ci = sh.wcount[0][i]; if (i < w) off += ci; n_pass += ci; }
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
@@ -964,16 +966,17 @@ __device__ __forceinline__ void bound_groups(const float* pm, int n_chunks, floa
   if (threadIdx.x == 0) { sh.zmax = zmax; sh.bound = t; sh.n_pass = n_pass; }
 }
 
-// Scores of the listed groups above thr -> this wavefront's segment (z - zmax, position), in candidate order: it takes
-// n_pass / kSolveWaves consecutive groups.  Sixteen lanes read the (at most 64) scores of a group with one 16-byte load
+// Scores of the listed groups above thr -> segment s (z - zmax, position), in candidate order: it takes n_pass / kSegs
+// consecutive groups.  Sixteen lanes read the (at most 64) scores of a group with one 16-byte load
 // each, so a load takes four groups and the usual row needs one; the lanes' order, and within a lane the four scores',
 // is candidate order.  Returns how many there are, also when they are more than the segment holds.
-__device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int n_pass, float zmax, float thr, SolveShared& sh) {
-  const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  const int per = (n_pass + kSolveWaves - 1) / kSolveWaves;
-  const int j0 = w * per, j1 = min(j0 + per, n_pass);
+template <typename SH>
+__device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int s, int n_pass, float zmax, float thr, SH& sh) {
+  const int lane = threadIdx.x & 63;
+  const int per = (n_pass + kSegs - 1) / kSegs;
+  const int j0 = s * per, j1 = min(j0 + per, n_pass);
   if (j0 >= j1) return 0;                                             // wave-uniform
-  uint2* seg = sh.seg + w * kSegCap;
+  uint2* seg = sh.seg + s * SH::kSegCap;
   const int sub = lane >> 4, in_group = 4 * (lane & 15);
   int cnt = 0;
   // tokens per group and per row are multiples of 4: a lane's four scores are valid together
@@ -994,7 +997,7 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2, o));
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3, o));
     cnt += __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
-    if (cnt <= kSegCap) {                                             // wave-uniform
+    if (cnt <= SH::kSegCap) {                                             // wave-uniform
       if (i0) seg[o] = make_uint2(__float_as_uint(v.x - zmax), (uint32_t)p);
       o += i0;
       if (i1) seg[o] = make_uint2(__float_as_uint(v.y - zmax), (uint32_t)p + 1);
@@ -1020,38 +1023,47 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
   return cnt;
 }
 
-// Threshold, support and weighted value sum of a row whose candidates lie in the wavefronts' segments (n of them in this
-// one's): every wavefront keeps its entries in registers, an evaluation of the mass costs one barrier, and each then
-// gathers the value rows of its own part of the support.
-template <typename T, bool DENSE>
-__device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRef& R, int n, float lo_u, float zmax,
-                                                 float seed_u, SolveShared& sh) {
-  constexpr int KR = kSegCap / 64;
-  const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
+// Threshold, support and weighted value sum of a row whose candidates lie in the segments (sh.wcount[1]: their lengths).
+// A wavefront keeps the entries of its kSegs / kWaves segments in registers, an evaluation of the mass costs one barrier,
+// and each then gathers the value rows of its own part of the support.  Every sum is taken per segment first, so the
+// result does not depend on the number of wavefronts.
+template <typename T, bool DENSE, typename SH>
+__device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRef& R, float lo_u, float zmax, float seed_u, SH& sh) {
+  constexpr int KR = SH::kSegCap / 64, SPW = kSegs / SH::kWaves;
+  const int tid = threadIdx.x, lane = tid & 63, s0 = uniform(tid >> 6) * SPW;
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
-  uint2* seg = sh.seg + w * kSegCap;
-  float u[KR];
+  uint2* seg0 = sh.seg + s0 * SH::kSegCap;
+  int n[SPW], n_sup[SPW];
+  float u[SPW][KR];
 #pragma unroll
-  for (int k = 0; k < KR; ++k) u[k] = lane + 64 * k < n ? __uint_as_float(seg[lane + 64 * k].x) : -INFINITY;
+  for (int i = 0; i < SPW; ++i) {
+    n[i] = uniform(sh.wcount[1][s0 + i]);
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+      u[i][k] = lane + 64 * k < n[i] ? __uint_as_float(seg0[i * SH::kSegCap + lane + 64 * k].x) : -INFINITY;
+  }
   int supp = 0, evals = 0, parity = 0;
   const float tau_u = with_beta(A.ibeta, [&](auto ib) {
     constexpr int IB = decltype(ib)::value;
     return solve_tau_core([&](float t, float& F, float& D, int& cnt) {
-      float f = 0.f, d = 0.f;
-      int c = 0;
 #pragma unroll
-      for (int k = 0; k < KR; ++k) {
-        if (64 * k < n) {                                             // wave-uniform
-          const float x = fmaxf(u[k] - t, 0.f);
-          const bool in = x > 0.f;
-          f += IB == 0 && !in ? 0.f : pow_beta(x, A.beta, IB);
-          d += in ? pow_beta_m1(x, A.beta, IB) : 0.f;
-          c += __popcll(__ballot(in));
+      for (int i = 0; i < SPW; ++i) {
+        float f = 0.f, d = 0.f;
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+          if (64 * k < n[i]) {                                        // wave-uniform
+            const float x = fmaxf(u[i][k] - t, 0.f);
+            const bool in = x > 0.f;
+            f += IB == 0 && !in ? 0.f : pow_beta(x, A.beta, IB);
+            d += in ? pow_beta_m1(x, A.beta, IB) : 0.f;
+            c += __popcll(__ballot(in));
+          }
         }
+        f = wave_sum(f); d = wave_sum(d);
+        if (lane == 0) { sh.red[parity][s0 + i][0] = f; sh.red[parity][s0 + i][1] = d; sh.red[parity][s0 + i][2] = __int_as_float(c); }
       }
-      f = wave_sum(f); d = wave_sum(d);
-      if (lane == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; sh.red[parity][w][2] = __int_as_float(c); }
       __syncthreads();
       F = sum_waves(&sh.red[parity][0][0], 3);
       D = A.beta * sum_waves(&sh.red[parity][0][1], 3);
@@ -1060,59 +1072,78 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
     }, lo_u, seed_u, IB, supp, evals);
   });
   // the support in place: (weight, position), ascending
-  int n_sup = 0;
 #pragma unroll
-  for (int k = 0; k < KR; ++k) {
-    if (64 * k < n) {
-      const float x = u[k] - tau_u;
-      const bool in = x > 0.f;
-      const uint64_t mk = __ballot(in);
-      const uint32_t pos = seg[lane + 64 * k].y;
-      wave_order();
-      if (in) seg[n_sup + __popcll(mk & lt)] = make_uint2(__float_as_uint(pow_beta(x, A.beta, A.ibeta)), pos);
-      n_sup += __popcll(mk);
-      wave_order();
+  for (int i = 0; i < SPW; ++i) {
+    uint2* seg = seg0 + i * SH::kSegCap;
+    n_sup[i] = 0;
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      if (64 * k < n[i]) {
+        const float x = u[i][k] - tau_u;
+        const bool in = x > 0.f;
+        const uint64_t mk = __ballot(in);
+        const uint32_t pos = seg[lane + 64 * k].y;
+        wave_order();
+        if (in) seg[n_sup[i] + __popcll(mk & lt)] = make_uint2(__float_as_uint(pow_beta(x, A.beta, A.ibeta)), pos);
+        n_sup[i] += __popcll(mk);
+        wave_order();
+      }
     }
   }
   // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
   // flight per lane; the next 64 are looked up before these are consumed
   const int rs = lane >> 4, c = lane & 15;
-  float acc[8];
+#pragma unroll 1
+  for (int i = 0; i < SPW; ++i) {
+    const uint2* seg = seg0 + i * SH::kSegCap;
+    int ns = n_sup[0];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  uint32_t row = n_sup > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(lane, n_sup - 1)].y) : 0u;
-  for (int e0 = 0; e0 < n_sup; e0 += 64) {
-    const uint32_t row_now = row;
-    row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, n_sup - 1)].y);
-    const float p_now = e0 + lane < n_sup ? __uint_as_float(seg[e0 + lane].x) : 0.f;
+    for (int j = 1; j < SPW; ++j) ns = i == j ? n_sup[j] : ns;
+    float acc[8];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      Raw8<T> vr[8]; float pw[8];
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    uint32_t row = ns > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(lane, ns - 1)].y) : 0u;
+    for (int e0 = 0; e0 < ns; e0 += 64) {
+      const uint32_t row_now = row;
+      row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, ns - 1)].y);
+      const float p_now = e0 + lane < ns ? __uint_as_float(seg[e0 + lane].x) : 0.f;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int src = 32 * half + 4 * j + rs;
-        pw[j] = __shfl(p_now, src);
-        load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
+      for (int half = 0; half < 2; ++half) {
+        Raw8<T> vr[8]; float pw[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int src = 32 * half + 4 * j + rs;
+          pw[j] = __shfl(p_now, src);
+          load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          float vv[8];
+          widen8(vr[j], vv);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
+        }
+        if (e0 + 32 >= ns) break;                                     // wave-uniform
       }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float vv[8];
-        widen8(vr[j], vv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(pw[j], vv[i], acc[i]);
-      }
-      if (e0 + 32 >= n_sup) break;                                    // wave-uniform
     }
+    store_partial(acc, sh, s0 + i);
   }
   if (A.ex.support_tokens != nullptr) {
-    if (lane == 0) sh.wcount[0][w] = n_sup;
+#pragma unroll
+    for (int i = 0; i < SPW; ++i)
+      if (lane == 0) sh.wcount[0][s0 + i] = n_sup[i];
     __syncthreads();
     int off = 0;
-    for (int i = 0; i < w; ++i) off += sh.wcount[0][i];
+    for (int i = 0; i < s0; ++i) off += sh.wcount[0][i];
     int32_t* dst = A.ex.support_tokens + (size_t)R.bh * A.ex.support_cap;
-    for (int e = lane; e < n_sup && off + e < A.ex.support_cap; e += 64) dst[off + e] = token_of<DENSE>(A, R.lrow, (int)seg[e].y);
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      for (int e = lane; e < n_sup[i] && off + e < A.ex.support_cap; e += 64)
+        dst[off + e] = token_of<DENSE>(A, R.lrow, (int)seg0[i * SH::kSegCap + e].y);
+      off += n_sup[i];
+    }
   }
-  reduce_output(acc, sh, A.out + (size_t)R.bh * kD);
+  sum_partials(sh, A.out + (size_t)R.bh * kD);
   if (tid == 0) {
     A.tau_out[R.bh] = tau_u + zmax; A.supp_out[R.bh] = supp;
     if (A.ex.solve_evals != nullptr) A.ex.solve_evals[R.bh] = evals;
@@ -1120,13 +1151,13 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
 }
 
 // Side outputs over ALL candidates of a row (mass and count above a given threshold, log-sum-exp of the whole cache).
-template <bool DENSE>
-__device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_cand, const float* zr, float zmax, SolveShared& sh) {
+template <bool DENSE, typename SH>
+__device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_cand, const float* zr, float zmax, SH& sh) {
   const int tid = threadIdx.x;
   if (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) {
     const float tr = A.ex.tau_ref[bh];
     float f = 0.f; int c = 0;
-    for (int i = tid; i < n_cand; i += kSolveThreads) {
+    for (int i = tid; i < n_cand; i += 64 * SH::kWaves) {
       const float x = zr[i] - tr;
       if (x > 0.f) { f += pow_beta(x, A.beta, A.ibeta); ++c; }
     }
@@ -1141,57 +1172,71 @@ __device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_c
     // log sum_j exp(s_j) with s_j = z_j / a, shifted by the maximum
     const float inv_a = 1.0f / A.a;
     float f = 0.f;
-    for (int i = tid; i < n_cand; i += kSolveThreads) f += __expf((zr[i] - zmax) * inv_a);
+    for (int i = tid; i < n_cand; i += 64 * SH::kWaves) f += __expf((zr[i] - zmax) * inv_a);
     f = block_sum(f, sh.red1);
     if (tid == 0) A.ex.lse[bh] = zmax * inv_a + __logf(f);
   }
 }
 
-// A row of at most kPreGroups groups, from the group maxima to the outputs.  Returns false, with nothing written, when a
-// segment is too small for its candidates (attention so flat that more than about 12 000 are left).
-template <typename T, bool DENSE>
-__device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, const float* zr, const float* pm, float seed_z,
-                                          bool block_extras, SolveShared& sh) {
+// A row from the bound of its groups (sh.zmax, sh.bound, sh.n_pass, sh.glist, visible to all) to the outputs.  Returns
+// false, with nothing written, when a segment is too small for its candidates.
+template <typename T, bool DENSE, typename SH>
+__device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowRef& R, const float* zr, float seed_z,
+                                                  bool block_extras, SH& sh) {
+  constexpr int SPW = kSegs / SH::kWaves;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  if (R.n_chunks <= kWaveGroups) {
-    if (w == 0) {
-      if (R.n_chunks <= kWaveGroups / 2) bound_groups<kWaveGroups / 128, true>(pm, R.n_chunks, A.beta, A.ibeta, sh);
-      else bound_groups<kWaveGroups / 64, true>(pm, R.n_chunks, A.beta, A.ibeta, sh);
-    }
-  } else {
-    bound_groups<kPreGroups / kSolveThreads, false>(pm, R.n_chunks, A.beta, A.ibeta, sh);
-  }
-  __syncthreads();
   const float zmax = sh.zmax, bound = sh.bound;
   if (!(zmax > -INFINITY)) {                                          // no valid candidate at all
     if (w == 0) empty_row_wave<DENSE>(A, R.bh);
     return true;
   }
-  const int n = fetch_candidates(R, zr, uniform(sh.n_pass), zmax, zmax + bound, sh);
-  if (lane == 0) sh.wcount[1][w] = n;
+  const int n_pass = uniform(sh.n_pass);
+#pragma unroll
+  for (int i = 0; i < SPW; ++i) {
+    const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
+    if (lane == 0) sh.wcount[1][w * SPW + i] = n;
+  }
   __syncthreads();
-  // this thread's wavefront count -> total, segments too long, and the prefix of the first wavefront's gather
-  int cw = lane < kSolveWaves ? sh.wcount[1][lane] : 0;
-  const bool fits = __ballot(cw > kSegCap) == 0;
-  if (!fits) return false;
+  const int cw = lane < kSegs ? sh.wcount[1][lane] : 0;
+  if (__ballot(cw > SH::kSegCap) != 0) return false;
   const int total = sum_waves_i(sh.wcount[1], 1);
   const float lo_u = fminf(bound, -1e-7f), seed_u = seed_z - zmax;
+  if (__builtin_expect(block_extras, 0)) side_outputs<DENSE>(A, R.bh, R.n_cand, zr, zmax, sh);
   if (__builtin_expect(total <= kWaveList, 1)) {
     if (w == 0) {
-      int inc = cw;
+      int inc = cw;                                                   // prefix of the segments' lengths
 #pragma unroll
-      for (int d = 1; d < kSolveWaves; d <<= 1) { const int t = __shfl_up(inc, d); if (lane >= d) inc += t; }
-      if (lane < kSolveWaves) sh.pre[lane + 1] = inc;
+      for (int d = 1; d < kSegs; d <<= 1) { const int t = __shfl_up(inc, d); if (lane >= d) inc += t; }
+      if (lane < kSegs) sh.pre[lane + 1] = inc;
       if (lane == 0) sh.pre[0] = 0;
-      __builtin_amdgcn_wave_barrier();
+      wave_order();
       if (total <= 64) finish_row_wave<T, DENSE, 1>(A, R, total, lo_u, zmax, seed_u, sh);
       else finish_row_wave<T, DENSE, kWaveList / 64>(A, R, total, lo_u, zmax, seed_u, sh);
     }
   } else {
-    finish_row_block<T, DENSE>(A, R, n, lo_u, zmax, seed_u, sh);
+    finish_row_block<T, DENSE>(A, R, lo_u, zmax, seed_u, sh);
   }
-  if (block_extras) { __syncthreads(); side_outputs<DENSE>(A, R.bh, R.n_cand, zr, zmax, sh); }
   return true;
+}
+
+// A row of at most kPreGroups groups, from the group maxima to the outputs.  False: its candidates outgrow the segments
+// (attention so flat that more than about 12 000 are left).
+template <typename T, bool DENSE>
+__device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, const float* zr, const float* pm, float seed_z,
+                                          bool block_extras, SolveShared& sh) {
+  const int w = uniform(threadIdx.x >> 6);
+  auto group_max = [pm](int g) { return pm[g]; };
+  if (R.n_chunks <= kWaveGroups) {
+    if (w == 0) {
+      if (R.n_chunks <= 128) bound_groups<2, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+      else if (R.n_chunks <= kWaveGroups / 2) bound_groups<kWaveGroups / 128, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+      else bound_groups<kWaveGroups / 64, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+    }
+  } else {
+    bound_groups<kPreGroups / kSolveThreads, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+  }
+  __syncthreads();
+  return solve_bounded_row<T, DENSE>(A, R, zr, seed_z, block_extras, sh);
 }
 
 template <typename T, bool DENSE>
@@ -1485,7 +1530,9 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     gather_support<T>(v_pool, sh, n_sup, acc);
-    reduce_output(acc, sh, out);
+    __syncthreads();
+    store_partial(acc, sh, w);
+    sum_partials(sh, out);
     if (A.ex.support_tokens != nullptr) {
       int32_t* dst = A.ex.support_tokens + (size_t)bh * A.ex.support_cap;
       for (int e = tid; e < n_sup && e < A.ex.support_cap; e += kSolveThreads)
@@ -1551,7 +1598,9 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     } else {
       finish(RowSrc{zr, n_cand, zmax});
     }
-    reduce_output(acc, sh, out);
+    __syncthreads();
+    store_partial(acc, sh, w);
+    sum_partials(sh, out);
   }
   const float tau = tau_u + zmax;
   if (tid == 0) {
@@ -1560,6 +1609,173 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
   }
 
   if (block_extras) side_outputs<DENSE>(A, bh, n_cand, zr, zmax, sh);
+}
+
+// ------------------------------------------------------------------------------------------
+// both passes in one launch: short per-head page lists
+// ------------------------------------------------------------------------------------------
+// A list of at most kRowTokens tokens is decoded by ONE workgroup: it gathers the K pages, keeps the scores and their
+// maxima in LDS and goes on to the threshold and the values there.  Two launches over such lists are hardly more than two
+// launch latencies with a round trip of the scores through memory between them (4096-token float32 step: 7.6 + 12 us;
+// 64 sequences of 8192 tokens, 2048 lists of 11 pages: 26.5 + 14.2 us), and a workgroup that waits for its own rows
+// overlaps the others of its compute unit, which launches cannot.  A list of kRowTokens tokens is 512 KB of bf16 K: about
+// 8 us for one compute unit, the length at which splitting it over more of them begins to pay again.
+// Scores are those of pass 1 bit for bit (the same products in the same order), and so are the results.
+constexpr int kRowTokens = 2048;
+constexpr int kRowUnits = kRowTokens / 4;          // score units: 16-token chunks (matrix cores) or pages (FMA path)
+
+// GROUP: the least number of tokens in a group, 64 where the page size divides 64, else at least 36 (one page of 36).
+template <int NW, int TOKENS, int GROUP>
+struct RowShared {
+  static constexpr int kWaves = NW, kGroups = (TOKENS + GROUP - 1) / GROUP;
+  static constexpr int kSegCap = (kGroups + kSegs - 1) / kSegs * 64;   // a segment holds all tokens of its groups
+  static_assert(kGroups <= 64, "one maximum per lane");
+  union {                                          // the scores are dead once the candidates are listed
+    float z[TOKENS];
+    float obuf[kSegs][kD];
+    struct { float list_u[kWaveList]; int32_t list_pos[kWaveList]; uint32_t list_row[kWaveList]; };
+  };
+  union {                                          // and the maxima before that
+    uint2 seg[kSegs * kSegCap];
+    float umax[kRowUnits];
+  };
+  float red[2][kSegs][3];
+  int wcount[2][kSegs];
+  int pre[kSegs + 1];
+  float red1[NW];
+  uint16_t glist[64];
+  float zmax, bound;
+  int n_pass;
+};
+
+// PT: page size of the matrix-core path (16, 32, 64), 0: FMA path (float32, or any other page size).
+template <typename T, int PT, int NW, int TOKENS>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 && PT ? (TOKENS > 1024 ? 5 : 6) : 4)))
+void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
+  __shared__ RowShared<NW, TOKENS, PT ? 64 : 36> sh;
+  const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+  const int bh = blockIdx.x, b = bh / S.Hq, hkv = (bh - b * S.Hq) / (S.Hq / S.Hkv);
+  const int P = PT ? PT : S.P;
+  const int n = uniform_load(S.seq_lens + b);
+  const int n_slots = clampi(uniform_load(S.n_sel + bh), 0, S.cap);
+  const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
+  const int gp = pmax_pages(P);
+  constexpr int UPP = PT ? PT / 16 : 1;                   // score units per page
+  const int n_units = n_slots * UPP;
+  // lane l: the page of this wavefront's unit l (units w, w + NW, ...); at most kRowUnits of them, 64 per batch
+  for (int u0 = w; u0 < n_units; u0 += 64 * NW) {
+    const int my_unit = min(u0 + NW * lane, n_units - 1);
+    const int l_lp = clampi(S.page_idx[(size_t)bh * S.cap + my_unit / UPP], 0, S.Mmax - 1);
+    const int l_phys = clampi(S.block_table[(size_t)b * S.Mmax + l_lp], 0, S.n_phys - 1);
+    const int mine = min((n_units - u0 + NW - 1) / NW, 64);
+    if constexpr (PT != 0) {
+      const int m = lane & 15, j = lane >> 4, kq = m & 3, gl = m >> 2;      // as in decode_scores_mfma_kernel, G = 1
+      const bf16_t* k_pool = (const bf16_t*)S.k_pool + gl * kD + (kq * 4 + j) * 8;
+      const uint4 bq = *reinterpret_cast<const uint4*>((const bf16_t*)S.q + (size_t)bh * kD + kq * 32 + j * 8);
+      auto request = [&](int i, uint4 (&a)[4]) {                            // past the end: the last unit again
+        const int ic = min(i, mine - 1), t = (u0 + NW * ic) % UPP;
+        const bf16_t* kc = k_pool + (((size_t)__builtin_amdgcn_readlane(l_phys, ic) * S.HkvPool + hkv) * PT + 16 * t) * kD;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[s] = *reinterpret_cast<const uint4*>(kc + s * 4 * kD);
+      };
+      auto consume = [&](int i, const uint4 (&a)[4]) {
+        if (i >= mine) return;                                              // wave-uniform
+        const int unit = u0 + NW * i, t = unit % UPP;
+        const int tok0 = __builtin_amdgcn_readlane(l_lp, i) * PT + 16 * t + j;
+        float zkeep = 0.f, mx = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+          const f32x4_t c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[s]),
+                                                                    __builtin_bit_cast(bf16x8_t, bq), zero, 0, 0, 0);
+          const float v01 = (kq & 1) ? c[1] : c[0], v23 = (kq & 1) ? c[3] : c[2];
+          float v = (kq & 2) ? v23 : v01;
+          v += dpp_move<0xB1>(v);
+          v += dpp_move<0x4E>(v);
+          const float z = tok0 + 4 * s < n ? S.zscale * v : -INFINITY;
+          if (s == kq) zkeep = z;
+          mx = fmaxf(mx, z);
+        }
+        if (gl == 0) sh.z[16 * unit + 4 * kq + j] = zkeep;
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if (lane == 0) sh.umax[unit] = mx;
+      };
+      uint4 a0[4], a1[4];
+      request(0, a0);
+      for (int i = 0; i < mine; i += 2) {
+        request(i + 1, a1);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(i, a0);
+        request(i + 2, a0);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(i + 1, a1);
+      }
+    } else {
+      const int r = lane >> 4, c = lane & 15;                               // as in decode_scores_valu_kernel, G = 1
+      const T* k_pool = (const T*)S.k_pool + 8 * c;
+      float coef[8];
+      load8<T>((const T*)S.q + (size_t)bh * kD + 8 * c, coef);
+      const int steps = P / 4, batches = (steps + 3) / 4, total = mine * batches;   // four steps = 16 tokens per batch
+      auto request = [&](int i, Raw8<T> (&x)[4]) {
+        const int ic = min(i, total - 1), pg = ic / batches, s0 = 4 * (ic - pg * batches);
+        const T* kpage = k_pool + ((size_t)__builtin_amdgcn_readlane(l_phys, pg) * S.HkvPool + hkv) * P * kD;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) load_raw8(kpage + (size_t)(4 * min(s0 + s, steps - 1) + r) * kD, x[s]);
+      };
+      float wmax = -INFINITY;
+      auto consume = [&](int i, const Raw8<T> (&x)[4]) {
+        if (i >= total) return;                                             // wave-uniform
+        const int pg = i / batches, bt = i - pg * batches, unit = u0 + NW * pg;
+        const int tok0 = __builtin_amdgcn_readlane(l_lp, pg) * P;
+        float zkeep = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int st = 4 * bt + s;
+          float xv[8];
+          widen8(x[s], xv);
+          float acc = 0.f;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc = fmaf(coef[q], xv[q], acc);
+          acc = row16_sum(acc);
+          const float z = st < steps && tok0 + 4 * st + r < n ? S.zscale * acc : -INFINITY;
+          if (c == s) zkeep = z;
+          wmax = fmaxf(wmax, z);
+        }
+        if (c < 4 && 4 * bt + c < steps) sh.z[unit * P + 4 * (4 * bt + c) + r] = zkeep;
+        if (bt == batches - 1) {
+          wmax = fmaxf(wmax, __shfl_xor(wmax, 16));
+          wmax = fmaxf(wmax, __shfl_xor(wmax, 32));
+          if (lane == 0) sh.umax[unit] = wmax;
+          wmax = -INFINITY;
+        }
+      };
+      Raw8<T> x0[4], x1[4];
+      request(0, x0);
+      for (int i = 0; i < total; i += 2) {
+        request(i + 1, x1);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(i, x0);
+        request(i + 2, x0);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(i + 1, x1);
+      }
+    }
+  }
+  __syncthreads();
+  const int upg = gp * UPP;                               // units per group of at most 64 tokens
+  const RowRef R{b, bh, bh, hkv, n_slots * P, gp * P, (n_slots + gp - 1) / gp};
+  if (w == 0) {
+    auto group_max = [&](int g) {
+      float mx = -INFINITY;
+      for (int i = 0; i < upg; ++i) mx = fmaxf(mx, sh.umax[min(g * upg + i, max(n_units - 1, 0))]);
+      return mx;
+    };
+    bound_groups<1, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+  }
+  __syncthreads();
+  const bool block_extras = A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr);
+  solve_bounded_row<T, false>(A, R, sh.z, seed_z, block_extras, sh);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1808,6 +2024,26 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 #undef EKV_SCORES
 }
 
+// Short per-head lists, one workgroup each.  Up to two lists per compute unit get sixteen wavefronts (the length of one
+// list is what the call takes); more of them get four, and eight lists share a compute unit.
+template <typename T, int PT>
+static void launch_rows_T(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {
+  const int rows = dm.B * dm.Hq;
+  if (rows <= 2 * device_compute_units())
+    hipLaunchKernelGGL((decode_row_kernel<T, PT, 16, kRowTokens>), dim3(rows), dim3(1024), 0, st, sa, so);
+  else if ((long long)dm.cap * dm.P <= kRowTokens / 2)
+    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokens / 2>), dim3(rows), dim3(256), 0, st, sa, so);
+  else
+    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokens>), dim3(rows), dim3(256), 0, st, sa, so);
+}
+static void launch_rows(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {
+  if (dm.dtype == EKV_F32) launch_rows_T<float, 0>(dm, sa, so, st);
+  else if (dm.P == 16) launch_rows_T<bf16_t, 16>(dm, sa, so, st);
+  else if (dm.P == 32) launch_rows_T<bf16_t, 32>(dm, sa, so, st);
+  else if (dm.P == 64) launch_rows_T<bf16_t, 64>(dm, sa, so, st);
+  else launch_rows_T<bf16_t, 0>(dm, sa, so, st);
+}
+
 size_t decode_ws_carve(const Dims& dm, bool dense, void* base, DecodeWorkspace* ws) {
   const size_t slots = dense ? dm.Mmax : dm.cap;
   const size_t rows = (size_t)dm.B * dm.Hq;
@@ -1889,6 +2125,7 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
       }
     } else {                                    // G == 1: a group list is a per-head list
       sa.U = dm.B * dm.Hq;
+      if ((long long)dm.cap * dm.P <= kRowTokens && !ex.score_pass_only) { launch_rows(dm, sa, so, st); return; }
       launch_scores<1, kPerHead>(dm, sa, ws.unit_pre, st);
     }
     if (ex.score_pass_only) return;
