@@ -576,6 +576,19 @@ __device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta,
   cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
 }
 
+// f += x^beta, d += x^(beta - 1) (0 for x = 0), x >= 0.  The products are spelled out, and what follows of the solve is
+// compiled without contraction, so that every kernel that solves a row takes the same steps to the last bit.
+template <int IB>
+__device__ __forceinline__ void add_mass(float x, float beta, float& f, float& d) {
+  if constexpr (IB == 0) {
+    if (x > 0.f) { f += pow_beta(x, beta, 0); d += pow_beta_m1(x, beta, 0); }
+  } else {
+    const float y = IB == 1 ? (x > 0.f ? 1.f : 0.f) : pow_beta_m1(x, beta, IB);
+    f = fmaf(x, y, f);
+    d += y;
+  }
+}
+
 // Root of sum (u - tau)_+^beta = 1 for u <= 0 with max u = 0: tau in [lo_init, 0), where lo_init >= -1
 // is any point with mass >= 1.
 // Safeguarded iteration inside a bracket [lo,hi], F(lo) >= 1 > F(hi).  From a left point the step is
@@ -588,6 +601,7 @@ __device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta,
 template <typename Eval>
 __device__ __forceinline__ float solve_tau_core(Eval&& eval, float lo_init, float seed, int ibeta, int& supp,
                                                 int& evals) {
+#pragma clang fp contract(off)
   float lo = lo_init, hi = 0.f;
   float tau = (seed > lo && seed < hi) ? seed : lo;
   int pending_cnt = -1;
@@ -658,10 +672,8 @@ __device__ __forceinline__ float solve_tau_regs(const float (&u)[KW], float lo_i
 #pragma unroll
       for (int k = 0; k < KW; ++k) {
         const float x = fmaxf(u[k] - t, 0.f);
-        const bool in = x > 0.f;
-        f += IB == 0 && !in ? 0.f : pow_beta(x, beta, IB);
-        d += in ? pow_beta_m1(x, beta, IB) : 0.f;
-        cnt += __popcll(__ballot(in));
+        add_mass<IB>(x, beta, f, d);
+        cnt += __popcll(__ballot(x > 0.f));
       }
       F = wave_sum(f); D = beta * wave_sum(d);
     }, lo_init, seed, IB, supp, evals);
@@ -785,8 +797,10 @@ struct RowRef { int b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks; };
 // `sums(f, d)` adds f and d up over all threads that hold maxima.
 template <int R, typename Sums>
 __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, float beta, int ibeta, Sums&& sums) {
+#pragma clang fp contract(off)
   if (beta < 1.f) { beta = 1.f; ibeta = 1; }
   return with_beta(ibeta, [&](auto ib) {
+#pragma clang fp contract(off)
     constexpr int IB = decltype(ib)::value;
     const float target = 1.0f + 1e-4f / beta;
     float t = t0;
@@ -794,10 +808,7 @@ __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, floa
       float f = 0.f, d = 0.f;
 #pragma unroll
       for (int k = 0; k < R; ++k) {
-        const float x = fmaxf(u[k] - t, 0.f);
-        const bool in = x > 0.f;
-        f += IB == 0 && !in ? 0.f : pow_beta(x, beta, IB);
-        d += IB == 1 || IB == 0 ? (in ? pow_beta_m1(x, beta, IB) : 0.f) : pow_beta_m1(x, beta, IB);
+        add_mass<IB>(fmaxf(u[k] - t, 0.f), beta, f, d);
       }
       sums(f, d);
       const float r = IB == 1 ? f : IB == 2 ? __builtin_amdgcn_sqrtf(f) : __builtin_exp2f(__builtin_log2f(f) / beta);
@@ -814,6 +825,7 @@ __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, floa
 template <typename T, bool DENSE, int KW, typename SH>
 __device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef& R, int n_list, float lo_u, float zmax,
                                                 float seed_u, SH& sh) {
+#pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
@@ -918,6 +930,7 @@ __device__ __forceinline__ void empty_row_wave(const SolveArgs& A, int bh) {
 // wavefront (rows of up to kWaveGroups groups: up to 65 536 candidates) nothing in here waits at a barrier.
 template <int R, bool ONE_WAVE, typename Max, typename SH>
 __device__ __forceinline__ void bound_groups(Max&& group_max, int n_chunks, float beta, int ibeta, SH& sh) {
+#pragma clang fp contract(off)
   const int lane = threadIdx.x & 63, w = ONE_WAVE ? 0 : uniform(threadIdx.x >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const int g0 = w * 64 * R + lane, last = max(n_chunks - 1, 0);
@@ -1029,6 +1042,7 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
 // result does not depend on the number of wavefronts.
 template <typename T, bool DENSE, typename SH>
 __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRef& R, float lo_u, float zmax, float seed_u, SH& sh) {
+#pragma clang fp contract(off)
   constexpr int KR = SH::kSegCap / 64, SPW = kSegs / SH::kWaves;
   const int tid = threadIdx.x, lane = tid & 63, s0 = uniform(tid >> 6) * SPW;
   const uint64_t lt = (1ull << lane) - 1ull;
@@ -1055,10 +1069,8 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
         for (int k = 0; k < KR; ++k) {
           if (64 * k < n[i]) {                                        // wave-uniform
             const float x = fmaxf(u[i][k] - t, 0.f);
-            const bool in = x > 0.f;
-            f += IB == 0 && !in ? 0.f : pow_beta(x, A.beta, IB);
-            d += in ? pow_beta_m1(x, A.beta, IB) : 0.f;
-            c += __popcll(__ballot(in));
+            add_mass<IB>(x, A.beta, f, d);
+            c += __popcll(__ballot(x > 0.f));
           }
         }
         f = wave_sum(f); d = wave_sum(d);
@@ -1183,6 +1195,7 @@ __device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_c
 template <typename T, bool DENSE, typename SH>
 __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowRef& R, const float* zr, float seed_z,
                                                   bool block_extras, SH& sh) {
+#pragma clang fp contract(off)
   constexpr int SPW = kSegs / SH::kWaves;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
   const float zmax = sh.zmax, bound = sh.bound;
@@ -1614,22 +1627,21 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
 // ------------------------------------------------------------------------------------------
 // both passes in one launch: short per-head page lists
 // ------------------------------------------------------------------------------------------
-// A list of at most kRowTokens tokens is decoded by ONE workgroup: it gathers the K pages, keeps the scores and their
-// maxima in LDS and goes on to the threshold and the values there.  Two launches over such lists are hardly more than two
-// launch latencies with a round trip of the scores through memory between them (4096-token float32 step: 7.6 + 12 us;
-// 64 sequences of 8192 tokens, 2048 lists of 11 pages: 26.5 + 14.2 us), and a workgroup that waits for its own rows
-// overlaps the others of its compute unit, which launches cannot.  A list of kRowTokens tokens is 512 KB of bf16 K: about
-// 8 us for one compute unit, the length at which splitting it over more of them begins to pay again.
-// Scores are those of pass 1 bit for bit (the same products in the same order), and so are the results.
-constexpr int kRowTokens = 2048;
-constexpr int kRowUnits = kRowTokens / 4;          // score units: 16-token chunks (matrix cores) or pages (FMA path)
+// A short list is decoded by ONE workgroup: it gathers the K pages, keeps the scores and their maxima in LDS and goes on
+// to the threshold and the values there.  Two launches over such lists are hardly more than two launch latencies with a
+// round trip of the scores through memory between them (4096-token float32 step: 7.6 + 12 us; 64 sequences of 8192
+// tokens, 2048 lists of 11 pages: 26.5 + 14.2 us), and a workgroup that waits for its own rows overlaps the others of its
+// compute unit, which launches cannot.  Against it stands the rate at which one compute unit reads K, about 75 GB/s:
+// see rows_in_one_launch.  Scores are those of pass 1 bit for bit (the same products in the same order), and so are the
+// results.
+constexpr int kRowTokens = 4096;                   // longest list of the sixteen-wavefront workgroup
+constexpr int kRowTokensMany = 2048;               // and of the four-wavefront one
 
 // GROUP: the least number of tokens in a group, 64 where the page size divides 64, else at least 36 (one page of 36).
 template <int NW, int TOKENS, int GROUP>
 struct RowShared {
   static constexpr int kWaves = NW, kGroups = (TOKENS + GROUP - 1) / GROUP;
   static constexpr int kSegCap = (kGroups + kSegs - 1) / kSegs * 64;   // a segment holds all tokens of its groups
-  static_assert(kGroups <= 64, "one maximum per lane");
   union {                                          // the scores are dead once the candidates are listed
     float z[TOKENS];
     float obuf[kSegs][kD];
@@ -1637,13 +1649,13 @@ struct RowShared {
   };
   union {                                          // and the maxima before that
     uint2 seg[kSegs * kSegCap];
-    float umax[kRowUnits];
+    float umax[TOKENS / 4];                        // per score unit: 16-token chunk (matrix cores) or page (FMA path)
   };
   float red[2][kSegs][3];
   int wcount[2][kSegs];
   int pre[kSegs + 1];
   float red1[NW];
-  uint16_t glist[64];
+  uint16_t glist[kGroups];
   float zmax, bound;
   int n_pass;
 };
@@ -1662,7 +1674,7 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
   const int gp = pmax_pages(P);
   constexpr int UPP = PT ? PT / 16 : 1;                   // score units per page
   const int n_units = n_slots * UPP;
-  // lane l: the page of this wavefront's unit l (units w, w + NW, ...); at most kRowUnits of them, 64 per batch
+  // lane l: the page of this wavefront's unit l (units w, w + NW, ...); 64 of them per batch
   for (int u0 = w; u0 < n_units; u0 += 64 * NW) {
     const int my_unit = min(u0 + NW * lane, n_units - 1);
     const int l_lp = clampi(S.page_idx[(size_t)bh * S.cap + my_unit / UPP], 0, S.Mmax - 1);
@@ -1771,7 +1783,7 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
       for (int i = 0; i < upg; ++i) mx = fmaxf(mx, sh.umax[min(g * upg + i, max(n_units - 1, 0))]);
       return mx;
     };
-    bound_groups<1, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+    bound_groups<(decltype(sh)::kGroups + 63) / 64, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
   }
   __syncthreads();
   const bool block_extras = A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr);
@@ -2024,17 +2036,28 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 #undef EKV_SCORES
 }
 
-// Short per-head lists, one workgroup each.  Up to two lists per compute unit get sixteen wavefronts (the length of one
-// list is what the call takes); more of them get four, and eight lists share a compute unit.
+// Short per-head lists, one workgroup each: sixteen wavefronts as long as every list has a compute unit to itself (the
+// length of one list is what the call takes), else four, and eight lists share a compute unit.
+// Whole top-k steps, two launches against one, us: 32 lists of 656 tokens 29 / 25.5, of 2000 tokens 32.3 / 33.4, of 3686
+// tokens 32 / 35.6; 128 lists of 2048 tokens 55 / 51.8, of 3686 tokens 45.5 / 38.9; 256 lists of 3686 tokens 63.6 / 55.5;
+// 2048 lists of 176 tokens 70 / 58.3.  With few lists most compute units idle in the one launch: the line is drawn at
+// 512 KB of K per list there (the capacity is what the host knows; lists are rarely full), at 1 MB otherwise.
+static bool rows_in_one_launch(const Dims& dm) {
+  const int cus = device_compute_units(), rows = dm.B * dm.Hq;
+  const long long tokens = (long long)dm.cap * dm.P;
+  if (rows > cus) return tokens <= kRowTokensMany;
+  const long long bytes = tokens * kD * (dm.dtype == EKV_F32 ? 4 : 2);
+  return tokens <= kRowTokens && bytes <= (rows <= cus / 4 ? 512 << 10 : 1 << 20);
+}
 template <typename T, int PT>
 static void launch_rows_T(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {
   const int rows = dm.B * dm.Hq;
-  if (rows <= 2 * device_compute_units())
+  if (rows <= device_compute_units())
     hipLaunchKernelGGL((decode_row_kernel<T, PT, 16, kRowTokens>), dim3(rows), dim3(1024), 0, st, sa, so);
-  else if ((long long)dm.cap * dm.P <= kRowTokens / 2)
-    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokens / 2>), dim3(rows), dim3(256), 0, st, sa, so);
+  else if ((long long)dm.cap * dm.P <= kRowTokensMany / 2)
+    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokensMany / 2>), dim3(rows), dim3(256), 0, st, sa, so);
   else
-    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokens>), dim3(rows), dim3(256), 0, st, sa, so);
+    hipLaunchKernelGGL((decode_row_kernel<T, PT, 4, kRowTokensMany>), dim3(rows), dim3(256), 0, st, sa, so);
 }
 static void launch_rows(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {
   if (dm.dtype == EKV_F32) launch_rows_T<float, 0>(dm, sa, so, st);
@@ -2125,7 +2148,7 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
       }
     } else {                                    // G == 1: a group list is a per-head list
       sa.U = dm.B * dm.Hq;
-      if ((long long)dm.cap * dm.P <= kRowTokens && !ex.score_pass_only) { launch_rows(dm, sa, so, st); return; }
+      if (rows_in_one_launch(dm) && !ex.score_pass_only) { launch_rows(dm, sa, so, st); return; }
       launch_scores<1, kPerHead>(dm, sa, ws.unit_pre, st);
     }
     if (ex.score_pass_only) return;

@@ -89,3 +89,51 @@ def test_solve_side_outputs_of_short_and_flat_rows(lens):
                 over = np.clip(z - t, 0, None)
                 assert abs(float(mass[b, hq]) - (over ** 2).sum()) < 1e-4
                 assert abs(int(cnt[b, hq]) - int((over > 0).sum())) <= int((np.abs(z - t) < 2e-6).sum())
+
+
+# batch, query heads, KV heads, page, dtype, pages per list: lists at the edges of the one-launch decode (a workgroup of
+# sixteen wavefronts, of four, and the two-launch path just beyond), page sizes of both score paths
+LISTS = [(1, 4, 2, 16, "bf16", 128), (1, 4, 2, 16, "bf16", 129), (1, 4, 2, 4, "f32", 256), (1, 4, 2, 36, "f32", 28),
+         (3, 32, 8, 36, "bf16", 113), (3, 32, 8, 32, "bf16", 128), (3, 32, 8, 64, "bf16", 64), (9, 32, 8, 12, "bf16", 85),
+         (9, 32, 8, 64, "bf16", 32), (9, 32, 8, 16, "bf16", 64), (9, 32, 32, 4, "f32", 512), (9, 32, 8, 16, "f32", 1)]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,page,dtype,k", LISTS)
+@pytest.mark.parametrize("scale", [1.0, 0.05])
+def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
+    """Ragged lists (one empty, one full) against the oracle, and, bit for bit, against the same lists in buffers so much
+    longer that they go through the two-launch path; the flat scale leaves most of a list in the support."""
+    n_pages = 2 * k + 3
+    w = synth.Workload("lists", batch, hq, hkv, 128, n_pages * page, page, dtype, scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(w, 9 + k, device="cpu")
+    inp["seq_lens"] = inp["seq_lens"] - torch.arange(batch, dtype=torch.int32) * 3
+    rng = np.random.default_rng(k)
+    lens = rng.integers(1, k + 1, size=(batch, hq))
+    lens[0, 0], lens[0, 1], lens[-1, -1] = k, 0, max(1, k - 1)
+    pages = [[np.sort(rng.choice(n_pages - 1, lens[b, h], replace=False)) for h in range(hq)] for b in range(batch)]
+    got = []
+    wide = w.scaled(context=max(w.context, 20000))                          # room for a capacity beyond the short lists'
+    for ww, cap in ((w, k), (wide, wide.pages_per_seq)):
+        big = dict(inp, block_table=torch.nn.functional.pad(inp["block_table"], (0, ww.pages_per_seq - w.pages_per_seq)))
+        st = DeviceState(ww, big, cap=cap)
+        for b in range(batch):
+            for h in range(hq):
+                st.page_idx[b, h, :lens[b, h]] = torch.from_numpy(pages[b][h].astype(np.int32)).to(st.page_idx.device)
+        st.n_sel.copy_(torch.from_numpy(lens.astype(np.int32)))
+        toks = torch.full((batch, hq, 4096), -1, device="cuda", dtype=torch.int32)
+        tau_ref = torch.full_like(st.tau, 0.5)
+        mass, cnt = torch.zeros_like(st.tau), torch.zeros_like(st.supp)
+        for extras in (ekv.decode_extras(support_tokens=toks), ekv.decode_extras(tau_ref=tau_ref, kept_mass_ref=mass, kept_supp_ref=cnt)):
+            ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                                  st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=extras)
+        torch.cuda.synchronize()
+        got.append([x.cpu() for x in (st.out, st.tau, st.supp, toks, cnt)])
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    out, tau, supp, toks, _ = [x.numpy() for x in got[0]]
+    assert supp[0, 1] == 0 and np.isposinf(tau[0, 1]) and not out[0, 1].any()
+    for b, h in ((0, 0), (batch - 1, hq - 1), (batch // 2, hq // 2)):
+        q, K, V = unit_kv(inp, w, b, h)
+        tok = orc.pages_to_tokens(pages[b][h], page, K.shape[0])
+        ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale, tok)
+        check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), toks[b, h], ref, boundary_expected=True)
