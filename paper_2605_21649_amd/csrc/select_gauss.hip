@@ -474,7 +474,6 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4, 
   __shared__ SelectShared sh;
   __shared__ int s_off[kGaussMaxSplits * kGaussWaves + 1];
   __shared__ int wtot[kSelWaves];
-  __shared__ float red_f[kSelWaves];
   __shared__ float bc[4];
   const int bh = blockIdx.x, b = bh / Hq, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const uint64_t lt = (1ull << lane) - 1ull;
@@ -486,29 +485,29 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const float* mu_r = mu + (size_t)bh * Mmax;
   const float* sg_r = sigma + (size_t)bh * Mmax;
   GaussState st, st1;
+  // SINGLE: this thread's pages, w * 64 * items + i * 64 + lane, read once and kept for every pass over them
+  constexpr int KP = SINGLE ? ITEMS : 1;
+  float mv[KP], sv[KP];
+  const int items = SINGLE ? (M + kSelThreads - 1) / kSelThreads : 0;      // <= ITEMS, workgroup-uniform
+  const int page0 = w * 64 * items + lane;
   if (SINGLE) {
     __shared__ float w_part[kSelWaves][7];                  // per wavefront: max a*mu, count, sum, sum of squares, hottest page
-    const int per_w = (M + kSelWaves - 1) / kSelWaves;      // wavefront w owns the pages [w per_w, (w+1) per_w)
-    const int p_lo = w * per_w, p_hi = min(p_lo + per_w, M);
+#pragma unroll
+    for (int i = 0; i < KP; ++i) {
+      const int p = min(page0 + i * 64, M - 1);             // clamped: loads stay unconditional
+      mv[i] = mu_r[p]; sv[i] = sg_r[p];
+    }
     float mx = -INFINITY, s0 = 0.f, s1 = 0.f, s2 = 0.f;
     float hk = -INFINITY, hm = 0.f, hs = 1.f, hc = 0.f;
-    for (int p0 = p_lo + lane; p0 - lane < p_hi; p0 += 4 * 64) {
-      float mv[4], sv[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = min(p0 + j * 64, M - 1);
-        mv[j] = mu_r[p]; sv[j] = sg_r[p];
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = p0 + j * 64;
-        if (p < p_hi) {
-          const float m = a * mv[j], sd = a * sv[j];
-          const float c = p == M - 1 ? cnt_last : (float)P;
-          mx = fmaxf(mx, m); s0 += c; s1 = fmaf(c, m, s1); s2 = fmaf(c, fmaf(m, m, sd * sd), s2);
-          const float key = fmaf(2.f, sd, m);
-          if (key > hk) { hk = key; hm = m; hs = sd; hc = c; }
-        }
+    for (int i = 0; i < KP; ++i) {
+      const int p = page0 + i * 64;
+      if (i < items && p < M) {
+        const float m = a * mv[i], sd = a * sv[i];
+        const float c = p == M - 1 ? cnt_last : (float)P;
+        mx = fmaxf(mx, m); s0 += c; s1 = fmaf(c, m, s1); s2 = fmaf(c, fmaf(m, m, sd * sd), s2);
+        const float key = fmaf(2.f, sd, m);
+        if (key > hk) { hk = key; hm = m; hs = sd; hc = c; }
       }
     }
     {
@@ -551,28 +550,45 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4, 
     st = advance_state(st1, F, (float)NB * D, (float)NB * D2);
   }
   int count = -1;
+  __shared__ float red_e[2][kSelWaves][3];
   for (int it = 0; it < 64 && !st.done; ++it) {            // finish the root iteration alone
     float f = 0.f, d = 0.f, d2 = 0.f;
-    for (int p0 = tid; p0 < M; p0 += 4 * kSelThreads) {      // four pages per batch of loads
-      float mv[4], sv[4];
+    if (SINGLE) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = min(p0 + j * kSelThreads, M - 1);
-        mv[j] = mu_r[p]; sv[j] = sg_r[p];
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = p0 + j * kSelThreads;
-        if (p < M) {
+      for (int i = 0; i < KP; ++i) {
+        const int p = page0 + i * 64;
+        if (i < items && p < M) {
           float fp, dp, dp2;
-          page_mass<NB>(fmaf(a, mv[j], -st.tau), a * sv[j], p == M - 1 ? cnt_last : (float)P, fp, dp, dp2);
+          page_mass<NB>(fmaf(a, mv[i], -st.tau), a * sv[i], p == M - 1 ? cnt_last : (float)P, fp, dp, dp2);
           f += fp; d += dp; d2 += dp2;
         }
       }
+    } else {
+      for (int p0 = tid; p0 < M; p0 += 4 * kSelThreads) {    // four pages per batch of loads
+        float mb[4], sb[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int p = min(p0 + j * kSelThreads, M - 1);
+          mb[j] = mu_r[p]; sb[j] = sg_r[p];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int p = p0 + j * kSelThreads;
+          if (p < M) {
+            float fp, dp, dp2;
+            page_mass<NB>(fmaf(a, mb[j], -st.tau), a * sb[j], p == M - 1 ? cnt_last : (float)P, fp, dp, dp2);
+            f += fp; d += dp; d2 += dp2;
+          }
+        }
+      }
     }
-    const float Fs = block_sum(f, red_f);
-    const float Ds = block_sum(d, red_f);
-    const float D2s = block_sum(d2, red_f);
+    // the three sums in one exchange (alternating buffers: one barrier), each a row sum over the wavefronts
+    f = wave_sum(f); d = wave_sum(d); d2 = wave_sum(d2);
+    float (&r)[kSelWaves][3] = red_e[it & 1];
+    if (lane == 0) { r[w][0] = f; r[w][1] = d; r[w][2] = d2; }
+    __syncthreads();
+    static_assert(kSelWaves == 16, "one DPP row");
+    const float Fs = row16_sum(r[lane & 15][0]), Ds = row16_sum(r[lane & 15][1]), D2s = row16_sum(r[lane & 15][2]);
     st = advance_state(st, Fs, (float)NB * Ds, (float)NB * D2s);
   }
   if (!SINGLE && st.tau - margin >= spec_threshold(st1.tau, margin)) {   // the candidates are complete
@@ -638,6 +654,36 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
   if (tid == 0) tau_hat[bh] = st.tau;
   const float z_full = zq.z[P], z_last = zq.z[n - (M - 1) * P];
+  if constexpr (SINGLE) {
+    // the estimates from the registers; the pages above the threshold in order
+    const uint32_t kthr = float_to_key(st.tau - margin);
+    uint32_t keep = 0;
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < KP; ++i) {
+      const int p = page0 + i * 64;
+      const bool in = i < items && p < M && float_to_key(a * fmaf(sv[i], p == M - 1 ? z_last : z_full, mv[i])) > kthr;
+      keep |= (uint32_t)in << i;
+      mine += __popcll(__ballot(in));
+    }
+    if (lane == 0) wtot[w] = mine;
+    __syncthreads();
+    int off = 0;
+    count = 0;
+#pragma unroll
+    for (int i = 0; i < kSelWaves; ++i) { const int ci = wtot[i]; if (i < w) off += ci; count += ci; }
+    if (count >= 1 && count <= cap) {
+#pragma unroll
+      for (int i = 0; i < KP; ++i) {
+        const bool in = (keep >> i) & 1u;
+        const uint64_t mk = __ballot(in);
+        if (in) out[off + __popcll(mk & lt)] = page0 + i * 64;
+        off += __popcll(mk);
+      }
+      if (tid == 0) { n_sel[bh] = count; overflow[bh] = 0; }
+      return;
+    }
+  }
   auto keyfn = [=](int p) { return float_to_key(a * fmaf(sg_r[p], p == M - 1 ? z_last : z_full, mu_r[p])); };
   KeySet<ITEMS, decltype(keyfn)> ks(keyfn, M);
   if (count < 0) {                                         // the candidates were not usable: count here
@@ -700,11 +746,14 @@ static void launch_gauss_NB(const Dims& dm, const float* mu, const float* sigma,
   const int BH = dm.B * dm.Hq;
   dim3 hgrid(BH), hblock(kSelThreads);
   if (BH <= kGaussSingleRows && dm.Mmax <= kGaussSinglePages) {     // short heads: one launch does it all
-    if (dm.Mmax <= 4 * kSelThreads)
+    if (dm.Mmax <= 2 * kSelThreads)
+      hipLaunchKernelGGL((gauss_gather_kernel<NB, 2, true>), hgrid, hblock, 0, st, mu, sigma, seq_lens, ws, zq, margin,
+                         dm.a, tau_hat, page_idx, n_sel, overflow, dm.Hq, dm.P, dm.Mmax, dm.cap, BH);
+    else if (dm.Mmax <= 4 * kSelThreads)
       hipLaunchKernelGGL((gauss_gather_kernel<NB, 4, true>), hgrid, hblock, 0, st, mu, sigma, seq_lens, ws, zq, margin,
                          dm.a, tau_hat, page_idx, n_sel, overflow, dm.Hq, dm.P, dm.Mmax, dm.cap, BH);
     else
-      hipLaunchKernelGGL((gauss_gather_kernel<NB, 16, true>), hgrid, hblock, 0, st, mu, sigma, seq_lens, ws, zq, margin,
+      hipLaunchKernelGGL((gauss_gather_kernel<NB, 8, true>), hgrid, hblock, 0, st, mu, sigma, seq_lens, ws, zq, margin,
                          dm.a, tau_hat, page_idx, n_sel, overflow, dm.Hq, dm.P, dm.Mmax, dm.cap, BH);
     return;
   }
