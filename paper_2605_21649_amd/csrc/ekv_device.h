@@ -172,6 +172,47 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+__device__ __forceinline__ uint32_t row16_min_u(uint32_t v) {
+  v = min(v, (uint32_t)dpp_move_i<0xB1>((int)v));
+  v = min(v, (uint32_t)dpp_move_i<0x4E>((int)v));
+  v = min(v, (uint32_t)dpp_move_i<0x141>((int)v));
+  return min(v, (uint32_t)dpp_move_i<0x140>((int)v));
+}
+__device__ __forceinline__ uint32_t row16_max_u(uint32_t v) {
+  v = max(v, (uint32_t)dpp_move_i<0xB1>((int)v));
+  v = max(v, (uint32_t)dpp_move_i<0x4E>((int)v));
+  v = max(v, (uint32_t)dpp_move_i<0x141>((int)v));
+  return max(v, (uint32_t)dpp_move_i<0x140>((int)v));
+}
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
+  v = row16_min_u(v);
+  v = min(v, (uint32_t)dpp_rows_i<0x142, 0xa>((int)v, (int)v));
+  v = min(v, (uint32_t)dpp_rows_i<0x143, 0xc>((int)v, (int)v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
+  v = row16_max_u(v);
+  v = max(v, (uint32_t)dpp_rows_i<0x142, 0xa>((int)v, (int)v));
+  v = max(v, (uint32_t)dpp_rows_i<0x143, 0xc>((int)v, (int)v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ int row16_sum_i(int v) {
+  v += dpp_move_i<0xB1>(v);
+  v += dpp_move_i<0x4E>(v);
+  v += dpp_move_i<0x141>(v);
+  return v + dpp_move_i<0x140>(v);
+}
+// Inclusive prefix sum over the wavefront (row shifts, then the two cross-row broadcasts).
+__device__ __forceinline__ int wave_incl_scan_i(int v) {
+  v += dpp_rows_i<0x111, 0xf>(0, v);     // row_shr 1, 2, 4, 8: lanes shifted in from outside the row count as 0
+  v += dpp_rows_i<0x112, 0xf>(0, v);
+  v += dpp_rows_i<0x114, 0xf>(0, v);
+  v += dpp_rows_i<0x118, 0xf>(0, v);
+  v += dpp_rows_i<0x142, 0xa>(0, v);     // row_bcast15 into rows 1 and 3
+  v += dpp_rows_i<0x143, 0xc>(0, v);     // row_bcast31 into rows 2 and 3
+  return v;
+}
+
 // Block-wide reductions through a small LDS array (one slot per wavefront); all threads get the
 // result.  The combination order is fixed (wavefront 0,1,2,...), so results are reproducible.
 // `buf` must hold blockDim.x/64 floats and must not be in use by a pending reduction.

@@ -18,11 +18,16 @@ constexpr int kRankMax = 256;             // elements ranked directly once the r
 
 struct SelectShared {
   uint32_t hist[kBins];
+  uint32_t list[kRankMax];                // keys that are ranked against each other
   int scan_buf[kSelWaves + 1];
-  uint32_t red_u[kSelWaves];
+  int wave_total[2][kSelWaves];
+  uint32_t red_lo[kSelWaves], red_hi[kSelWaves];
   int wave_gt[kSelWaves], wave_eq[kSelWaves];
   uint32_t digit, above;
+  int n_list;
 };
+static_assert(kSelWaves == 16, "one value per wavefront is one DPP row");
+static_assert(4 * kRankMax <= kSelThreads, "four lanes per ranked key");
 
 // Exclusive prefix sum over the block in thread order; `total` receives the block sum.
 // Contains barriers: all threads must call it.
@@ -122,15 +127,14 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
       if (ks.valid(i)) { const uint32_t key = ks.key(i); lo = min(lo, key); hi = max(hi, key); }
     }
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
-  }
-  // both extremes in one exchange (the histogram array is free here: it is zeroed at the start of every pass)
+  // one barrier for both extremes; the histogram and the list's counter are cleared on the way
+  lo = wave_min_u(lo); hi = wave_max_u(hi);
+  __syncthreads();                                 // whatever used the shared arrays before is done
+  for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
+  if ((tid & 63) == 0) { sh.red_lo[tid >> 6] = lo; sh.red_hi[tid >> 6] = hi; }
+  if (tid == 0) sh.n_list = 0;
   __syncthreads();
-  if ((tid & 63) == 0) { sh.red_u[tid >> 6] = lo; sh.hist[tid >> 6] = hi; }
-  __syncthreads();
-  for (int i = 0; i < kSelWaves; ++i) { lo = min(lo, sh.red_u[i]); hi = max(hi, sh.hist[i]); }
+  lo = row16_min_u(sh.red_lo[tid & 15]); hi = row16_max_u(sh.red_hi[tid & 15]);
   const uint32_t range = hi - lo;
   ks.rebase(lo);
   int shift = range ? 32 - __clz(range) : 0;     // significant bits of the rebased keys
@@ -138,16 +142,18 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
   uint32_t prefix = 0;       // high bits of the answer fixed so far: (v >> shift) == prefix
   int k_rem = k;             // rank of the answer among the elements sharing that prefix
   const int n_pad = kSelThreads * (ITEMS ? ITEMS : ks.items) - ks.M;
-  while (shift > 0) {
+  for (int pass = 0; shift > 0; ++pass) {
     const int dbits = min(kDigitBits, shift);
     shift -= dbits;
     const uint32_t dmask = (1u << dbits) - 1u;
     const int up = shift + dbits;                  // bits above the current digit: (v >> up) must equal prefix
     const bool first = up >= 32;                   // first pass of a full 32-bit range: every key matches
     const bool pad_counted = first || prefix == 0u;
-    __syncthreads();
-    for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
-    __syncthreads();
+    if (pass > 0) {
+      __syncthreads();
+      for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
+      __syncthreads();
+    }
     // Slots past M hold the rebased key 0.  They are counted (as copies of the smallest key) but not sent
     // through the histogram one by one: thousands of atomics on one LDS address serialise.
     if constexpr (ITEMS == 0) {
@@ -171,8 +177,11 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
     // thread t owns digits (kBins-1-2t) and (kBins-2-2t): scan from the top digit downwards
     const int d_hi = kBins - 1 - 2 * tid, d_lo = d_hi - 1;
     const int c_hi = (int)sh.hist[d_hi], c_lo = (int)sh.hist[d_lo];
-    int total;
-    const int above = block_excl_scan(c_hi + c_lo, sh.scan_buf, total);
+    const int inc = wave_incl_scan_i(c_hi + c_lo);
+    int* totals = sh.wave_total[pass & 1];
+    if ((tid & 63) == 63) totals[tid >> 6] = inc;
+    __syncthreads();
+    const int above = row16_sum_i((tid & 15) < (tid >> 6) ? totals[tid & 15] : 0) + inc - c_hi - c_lo;
     if (above < k_rem && k_rem <= above + c_hi) { sh.digit = d_hi; sh.above = above; }
     else if (above + c_hi < k_rem && k_rem <= above + c_hi + c_lo) { sh.digit = d_lo; sh.above = above + c_hi; }
     __syncthreads();
@@ -185,9 +194,6 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
     // decide the answer for k <= M, so they stay out.
     const int members = (int)sh.hist[digit] - (digit == 0u && pad_counted && n_pad > 0 ? n_pad : 0);
     if (members <= kRankMax) {                     // workgroup-uniform
-      __syncthreads();                             // every thread has read the count
-      if (tid == 0) sh.scan_buf[kSelWaves] = 0;
-      __syncthreads();
       if constexpr (ITEMS == 0) {
         for (int i0 = 0; i0 < ks.items; i0 += 8) {
           uint32_t kb[8];
@@ -195,22 +201,24 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
 #pragma unroll
           for (int j = 0; j < 8; ++j)
             if (i0 + j < ks.items && ks.page(i0 + j) < ks.M && (kb[j] >> shift) == prefix)
-              sh.hist[atomicAdd(&sh.scan_buf[kSelWaves], 1)] = kb[j];
+              sh.list[atomicAdd(&sh.n_list, 1)] = kb[j];
         }
       } else {
 #pragma unroll
         for (int i = 0; i < (ITEMS ? ITEMS : ks.items); ++i) {
           const uint32_t v = ks.key(i);
-          if (ks.page(i) < ks.M && (v >> shift) == prefix) sh.hist[atomicAdd(&sh.scan_buf[kSelWaves], 1)] = v;
+          if (ks.page(i) < ks.M && (v >> shift) == prefix) sh.list[atomicAdd(&sh.n_list, 1)] = v;
         }
       }
       __syncthreads();
-      if (tid < members) {
-        const uint32_t v = sh.hist[tid];
-        int g = 0, e = 0;
-        for (int j = 0; j < members; ++j) { const uint32_t u = sh.hist[j]; g += u > v; e += u == v; }
-        if (g < k_rem && k_rem <= g + e) { sh.digit = v; sh.above = (uint32_t)g; }    // equal keys write the same
-      }
+      // four lanes per member
+      const int mem = tid >> 2;
+      const uint32_t v = sh.list[min(mem, members - 1)];
+      int g = 0, e = 0;
+      for (int j = tid & 3; j < members; j += 4) { const uint32_t u = sh.list[j]; g += u > v; e += u == v; }
+      g += dpp_move_i<0xB1>(g); g += dpp_move_i<0x4E>(g);
+      e += dpp_move_i<0xB1>(e); e += dpp_move_i<0x4E>(e);
+      if (mem < members && g < k_rem && k_rem <= g + e) { sh.digit = v; sh.above = (uint32_t)g; }    // equal keys write the same
       __syncthreads();
       vT_out = sh.digit; k_eq_out = k_rem - (int)sh.above;
       return;
@@ -245,11 +253,10 @@ __device__ __forceinline__ void compact_ordered(const KeySet<ITEMS, KeyFn>& ks, 
   }
   n_gt = wave_sum_i(n_gt);
   n_eq = wave_sum_i(n_eq);
+  if (lane == 0) { sh.wave_gt[w] = n_gt; sh.wave_eq[w] = n_eq; }     // written once per selection
   __syncthreads();
-  if (lane == 0) { sh.wave_gt[w] = n_gt; sh.wave_eq[w] = n_eq; }
-  __syncthreads();
-  int gt_before = 0, eq_before = 0;
-  for (int i = 0; i < w; ++i) { gt_before += sh.wave_gt[i]; eq_before += sh.wave_eq[i]; }
+  const int gt_before = row16_sum_i((lane & 15) < w ? sh.wave_gt[lane & 15] : 0);
+  const int eq_before = row16_sum_i((lane & 15) < w ? sh.wave_eq[lane & 15] : 0);
   int eq_run = eq_before;
   int o_run = gt_before + min(eq_before, k_eq);
   auto emit = [&](int i, uint32_t v) {
