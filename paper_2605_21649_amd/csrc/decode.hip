@@ -24,7 +24,6 @@ constexpr int kSegs = 16;               // candidate lists are cut into this man
 constexpr int kSpillCap = 65536;        // entries of a row's overflow list in the workspace (longer lists: the row is streamed)
 constexpr int kWaveGroups = 1024;       // up to this many group maxima are bounded by one wavefront, more by all of them
 constexpr int kRoundLoads = 16;         // loads per lane and compaction round
-constexpr int kRoundTokens = kSolveThreads * kRoundLoads;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
@@ -535,38 +534,51 @@ __global__ __launch_bounds__(kFilterThreads) void filter_compact_kernel(const Fi
 // ------------------------------------------------------------------------------------------
 // pass 2: threshold, probabilities, weighted value sum
 // ------------------------------------------------------------------------------------------
-struct SolveShared {
-  static constexpr int kWaves = kSolveWaves, kSegCap = 768;     // entries per segment, held in LDS and in registers
+// NW wavefronts, SEG candidates per segment, LIST entries of the general path's list, up to GROUPS groups per row.
+template <int NW, int SEG, int LIST, int GROUPS>
+struct SolveSharedT {
+  static constexpr int kWaves = NW, kSegCap = SEG, kListCap = LIST, kMaxGroups = GROUPS;
   union {
     // Candidates, z - zmax (float bits) and position in the candidate order; segment i is [i * kSegCap, (i + 1) * kSegCap).
-    uint2 seg[kSegs * kSegCap];
+    uint2 seg[kSegs * SEG];
     struct {                      // the general path's one list, and the support of a row that one wavefront finishes
-      float list_u[kListCap];
-      int32_t list_pos[kListCap];
+      float list_u[LIST];
+      int32_t list_pos[LIST];
     };
   };
   union {
-    uint32_t list_row[kListCap];  // their V row: (phys*Hkv + hkv)*P + tok
-    uint16_t glist[kPreGroups];   // the groups that can hold a candidate, ascending
+    uint32_t list_row[LIST];      // their V row: (phys*Hkv + hkv)*P + tok
+    uint16_t glist[GROUPS];       // the groups that can hold a candidate, ascending
   };
   float obuf[kSegs][kD];
   float red[2][kSegs][3];
   int wcount[2][kSegs];
   int pre[kSegs + 1];             // exclusive prefix of the segments' lengths
-  float red1[kSolveWaves];
+  float red1[NW];
   int hist[64];                   // candidates per 1/64 slice of [thr, zmax] (threshold tightening)
   int flags[64];
   float zmax, bound;              // row maximum, certified lower bound of tau relative to it
   int n_pass;
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
+// Rows up to one per compute unit; more rows than that, two to a compute unit; many rows of at most kWaveGroups groups,
+// whose usual solve is one wavefront's work anyway.
+using SolveShared = SolveSharedT<kSolveWaves, 768, kListCap, kPreGroups>;
+using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, kPreGroups>;
+using SolveSharedMany = SolveSharedT<4, 128, 2048, kWaveGroups>;
 
 // Sum of one value per segment (or wavefront) kept in LDS at a stride: one read per lane and a DPP row sum, the same in
 // every wavefront (a loop reads LDS sixteen times in a row).
 static_assert(kSegs == 16 && kSolveWaves == 16, "one DPP row");
-__device__ __forceinline__ float sum_waves(const float* v, int stride) { return row16_sum(v[(threadIdx.x & 15) * stride]); }
+template <int N = kSegs>
+__device__ __forceinline__ float sum_waves(const float* v, int stride) {
+  const int l = threadIdx.x & 15;
+  return row16_sum(l < N ? v[l * stride] : 0.f);
+}
+template <int N = kSegs>
 __device__ __forceinline__ int sum_waves_i(const int* v, int stride) {
-  int x = v[(threadIdx.x & 15) * stride];
+  const int l = threadIdx.x & 15;
+  int x = l < N ? v[l * stride] : 0;
   x += dpp_move_i<0xB1>(x); x += dpp_move_i<0x4E>(x); x += dpp_move_i<0x141>(x); x += dpp_move_i<0x140>(x);
   return __builtin_amdgcn_readfirstlane(x);
 }
@@ -585,17 +597,18 @@ struct RowSrc {
 
 // F = sum (u-tau)_+^beta, D = beta * sum (u-tau)_+^(beta-1), cnt = #{u > tau}; one barrier per call
 // (double-buffered by `parity`).
-template <typename Src>
-__device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta, int ibeta, SolveShared& sh,
+template <typename Src, typename SH>
+__device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta, int ibeta, SH& sh,
                                           int parity, float& F, float& D, int& cnt) {
+  constexpr int NT = 64 * SH::kWaves;
   float f = 0.f, d = 0.f; int c = 0;
-  for (int i0 = threadIdx.x; i0 < src.n; i0 += 8 * kSolveThreads) {     // eight loads in flight per thread
+  for (int i0 = threadIdx.x; i0 < src.n; i0 += 8 * NT) {     // eight loads in flight per thread
     float u[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) u[j] = src.get_u(min(i0 + j * kSolveThreads, src.n - 1));
+    for (int j = 0; j < 8; ++j) u[j] = src.get_u(min(i0 + j * NT, src.n - 1));
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const float x = i0 + j * kSolveThreads < src.n ? u[j] - tau : -1.f;
+      const float x = i0 + j * NT < src.n ? u[j] - tau : -1.f;
       if (x > 0.f) { f += pow_beta(x, beta, ibeta); d += pow_beta_m1(x, beta, ibeta); ++c; }
     }
   }
@@ -603,9 +616,9 @@ __device__ __forceinline__ void eval_mass(const Src& src, float tau, float beta,
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; sh.red[parity][w][2] = __int_as_float(c); }
   __syncthreads();
-  F = sum_waves(&sh.red[parity][0][0], 3);
-  D = beta * sum_waves(&sh.red[parity][0][1], 3);
-  cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
+  F = sum_waves<SH::kWaves>(&sh.red[parity][0][0], 3);
+  D = beta * sum_waves<SH::kWaves>(&sh.red[parity][0][1], 3);
+  cnt = sum_waves_i<SH::kWaves>(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
 }
 
 // f += x^beta, d += x^(beta - 1) (0 for x = 0), x >= 0.  The products are spelled out, and what follows of the solve is
@@ -678,9 +691,9 @@ __device__ __forceinline__ float solve_tau_core(Eval&& eval, float lo_init, floa
 }
 
 // The whole workgroup iterates (one barrier per evaluation).
-template <typename Src>
+template <typename Src, typename SH>
 __device__ __forceinline__ float solve_tau(const Src& src, float lo_init, float seed, float beta, int ibeta,
-                                           SolveShared& sh, int& supp, int& evals) {
+                                           SH& sh, int& supp, int& evals) {
   int parity = 0;
   return solve_tau_core([&](float tau, float& F, float& D, int& cnt) {
     eval_mass(src, tau, beta, ibeta, sh, parity, F, D, cnt);
@@ -711,8 +724,9 @@ __device__ __forceinline__ float solve_tau_regs(const float (&u)[KW], float lo_i
     }, lo_init, seed, IB, supp, evals);
   });
 }
+template <typename SH>
 __device__ __forceinline__ float solve_tau_wave(const float* list_u, int n, float lo_init, float seed, float beta,
-                                                int ibeta, SolveShared& sh, int& supp, int& evals) {
+                                                int ibeta, SH& sh, int& supp, int& evals) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     float u[kWaveList / 64];
@@ -775,13 +789,13 @@ __device__ __forceinline__ void store_partial(float (&acc)[8], SH& sh, int seg) 
   }
 }
 // The segments' partial outputs, added in their order.  Starts with a barrier.
-template <typename SH>
+template <int N = kSegs, typename SH>
 __device__ __forceinline__ void sum_partials(const SH& sh, float* __restrict__ out) {
   __syncthreads();
   if (threadIdx.x < kD) {
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < kSegs; ++i) s += sh.obuf[i][threadIdx.x];
+    for (int i = 0; i < N; ++i) s += sh.obuf[i][threadIdx.x];
     out[threadIdx.x] = s;
   }
 }
@@ -789,10 +803,10 @@ __device__ __forceinline__ void sum_partials(const SH& sh, float* __restrict__ o
 // Weighted sum of the V rows of the `tot` support entries in LDS (weight list_u[e], row list_row[e]): 64 row
 // slots x 16 lanes, eight independent 16-byte loads in flight per lane (clamped entries carry weight 0).  A row
 // slot adds its entries in ascending order.
-template <typename T>
-__device__ __forceinline__ void gather_support(const T* __restrict__ v_pool, const SolveShared& sh, int tot, float (&acc)[8]) {
+template <typename T, typename SH>
+__device__ __forceinline__ void gather_support(const T* __restrict__ v_pool, const SH& sh, int tot, float (&acc)[8]) {
   const int rs = threadIdx.x >> 4, c = threadIdx.x & 15;
-  constexpr int kSlots = kSolveThreads / 16;
+  constexpr int kSlots = 4 * SH::kWaves;
   for (int e0 = 0; e0 < tot; e0 += 8 * kSlots) {
     Raw8<T> vr[8]; float pw[8];
 #pragma unroll
@@ -985,7 +999,7 @@ __device__ __forceinline__ void bound_groups(Max&& group_max, int n_chunks, floa
       if (!ONE_WAVE) {
         if (lane == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; }
         __syncthreads();
-        f = sum_waves(&sh.red[parity][0][0], 3); d = sum_waves(&sh.red[parity][0][1], 3);
+        f = sum_waves<SH::kWaves>(&sh.red[parity][0][0], 3); d = sum_waves<SH::kWaves>(&sh.red[parity][0][1], 3);
         parity ^= 1;
       }
     });
@@ -1264,11 +1278,11 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
   return true;
 }
 
-// A row of at most kPreGroups groups, from the group maxima to the outputs.  False: its candidates outgrow the segments
-// (attention so flat that more than about 12 000 are left).
-template <typename T, bool DENSE>
+// A row of at most SH::kMaxGroups groups, from the group maxima to the outputs.  False: its candidates outgrow the
+// segments (attention so flat that more than 2000 to 12 000 are left).
+template <typename T, bool DENSE, typename SH>
 __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, const float* zr, const float* pm, float seed_z,
-                                          bool block_extras, SolveShared& sh) {
+                                          bool block_extras, SH& sh) {
   const int w = uniform(threadIdx.x >> 6);
   auto group_max = [pm](int g) { return pm[g]; };
   if (R.n_chunks <= kWaveGroups) {
@@ -1277,16 +1291,19 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
       else if (R.n_chunks <= kWaveGroups / 2) bound_groups<kWaveGroups / 128, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
       else bound_groups<kWaveGroups / 64, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
     }
-  } else {
-    bound_groups<kPreGroups / kSolveThreads, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+  } else if constexpr (SH::kMaxGroups > kWaveGroups) {
+    bound_groups<SH::kMaxGroups / (64 * SH::kWaves), false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
   }
   __syncthreads();
   return solve_bounded_row<T, DENSE>(A, R, zr, seed_z, block_extras, sh);
 }
 
-template <typename T, bool DENSE>
-__global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const SolveArgs A) {
-  __shared__ SolveShared sh;
+template <typename T, bool DENSE, typename SH>
+__global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const SolveArgs A) {
+  __shared__ SH sh;
+  constexpr int NT = 64 * SH::kWaves, NW = SH::kWaves, LIST = SH::kListCap;
+  constexpr int kRoundTokens = NT * kRoundLoads;
+  constexpr bool kLong = SH::kMaxGroups >= kPreGroups;   // false: the launch has only rows of at most kMaxGroups groups
   const int Hq = A.Hq, Hkv = A.Hkv, P = A.P;
   const int bh = blockIdx.x, b = bh / Hq, hq = bh % Hq, hkv = hq / (Hq / Hkv);
   const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
@@ -1309,14 +1326,14 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
                             (DENSE && A.ex.lse != nullptr);
   const RowRef R{b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks};
   float zmax, thr_f = 0.f;
-  const bool pre = n_chunks <= kPreGroups;
+  const bool pre = !kLong || n_chunks <= kPreGroups;
   if (__builtin_expect(pre, 1)) {
     if (__builtin_expect(solve_row<T, DENSE>(A, R, zr, pm, seed_z, block_extras, sh), 1)) return;
   }
   // Longer rows, and those whose candidates outgrow LDS.
   // The filter passes are launched when the list CAPACITY allows longer rows than kPreGroups; whether this row took
   // them is decided here, from its actual length (they leave shorter rows alone).
-  const bool filt = A.fcount != nullptr && !pre;
+  const bool filt = kLong && A.fcount != nullptr && !pre;
   if (filt) {
     zmax = n_cand > 0 ? A.frow[2 * bh] : -INFINITY;
     thr_f = n_cand > 0 ? A.frow[2 * bh + 1] : 0.f;
@@ -1324,7 +1341,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     zmax = sh.zmax; thr_f = sh.zmax + sh.bound;
   } else {
     float mx = -INFINITY;
-    for (int i = tid; i < n_chunks; i += kSolveThreads) mx = fmaxf(mx, pm[i]);
+    for (int i = tid; i < n_chunks; i += NT) mx = fmaxf(mx, pm[i]);
     zmax = block_max(mx, sh.red1);
   }
   if (!(zmax > -INFINITY)) {                // no valid candidate at all
@@ -1358,7 +1375,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
   bool prefilled = false;
   float* const su = A.spill_u != nullptr ? A.spill_u + (size_t)bh * A.spill_cap : nullptr;
   int32_t* const sp = A.spill_pos != nullptr ? A.spill_pos + (size_t)bh * A.spill_cap : nullptr;
-  if (filt) {
+  if constexpr (kLong) if (filt) {
     // survivors of the filter passes: gather the per-slice lists, in slice order, if they fit
     const int n_slices = (n_chunks + kFilterSliceChunks - 1) / kFilterSliceChunks;
     const int cs = tid < n_slices ? A.fcount[(size_t)bh * A.n_slices_max + tid] : 0;
@@ -1368,12 +1385,12 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     if (lane == 63) sh.wcount[0][w] = inc;
     const int bad = __syncthreads_or(cs > kFilterSliceCap);
     int base = 0, tot = 0;
-    for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[0][i]; if (i < w) base += ci; tot += ci; }
-    if (!bad && tot <= kListCap) {
+    for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[0][i]; if (i < w) base += ci; tot += ci; }
+    if (!bad && tot <= LIST) {
       int* start = reinterpret_cast<int*>(sh.list_row);      // free until the solve is done
       if (tid < n_slices) { start[2 * tid] = base + inc - cs; start[2 * tid + 1] = cs; }
       __syncthreads();
-      for (int sl = w; sl < n_slices; sl += kSolveWaves) {
+      for (int sl = w; sl < n_slices; sl += NW) {
         const int o0 = start[2 * sl], cnt = start[2 * sl + 1];
         const float* lu = A.flist_u + ((size_t)bh * A.n_slices_max + sl) * kFilterSliceCap;
         const int32_t* lp = A.flist_pos + ((size_t)bh * A.n_slices_max + sl) * kFilterSliceCap;
@@ -1387,7 +1404,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
       int* start = reinterpret_cast<int*>(sh.list_row);
       if (tid < n_slices) { start[2 * tid] = base + inc - cs; start[2 * tid + 1] = cs; }
       __syncthreads();
-      for (int sl = w; sl < n_slices; sl += kSolveWaves) {
+      for (int sl = w; sl < n_slices; sl += NW) {
         const int o0 = start[2 * sl], cnt = start[2 * sl + 1];
         const float* lu = A.flist_u + ((size_t)bh * A.n_slices_max + sl) * kFilterSliceCap;
         const int32_t* lp = A.flist_pos + ((size_t)bh * A.n_slices_max + sl) * kFilterSliceCap;
@@ -1405,11 +1422,11 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     const uint16_t* glist = sh.glist;
     const int n_pass = uniform(sh.n_pass);
     // wavefront w of a round owns `per` consecutive list entries: (round, w, load, lane) is candidate order
-    constexpr int kRoundGroups = kSolveWaves * kRoundLoads;
+    constexpr int kRoundGroups = NW * kRoundLoads;
     // second half of a round: mask, count, exchange the counts (one barrier), ordered compaction into the list
     auto compact_round = [&](int j0, float (&v)[kRoundLoads], const int (&vpos)[kRoundLoads]) {
       const int rem = min(n_pass - j0, kRoundGroups);
-      const int per = (rem + kSolveWaves - 1) / kSolveWaves;
+      const int per = (rem + NW - 1) / NW;
       const int jw = j0 + w * per, jend = j0 + rem;
       int c = 0;
 #pragma unroll
@@ -1421,16 +1438,16 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
       if (lane == 0) sh.wcount[parity][w] = c;
       __syncthreads();
       int off = n_list, tot = 0;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
+      for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
       n_list += tot;
       parity ^= 1;
-      if (__builtin_expect(in_lds && n_list > kListCap, 0)) {
+      if (__builtin_expect(in_lds && n_list > LIST, 0)) {
         // The list outgrows LDS: it continues in the row's overflow list, to which the entries of the earlier rounds
         // move first (the barrier above ordered their LDS writes).
         in_lds = false;
         if (su != nullptr) {
           in_spill = true;
-          for (int e = tid; e < n_list - tot; e += kSolveThreads) { su[e] = sh.list_u[e]; sp[e] = sh.list_pos[e]; }
+          for (int e = tid; e < n_list - tot; e += NT) { su[e] = sh.list_u[e]; sp[e] = sh.list_pos[e]; }
         }
       }
       if (in_spill && n_list > A.spill_cap) in_spill = false;
@@ -1452,7 +1469,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     };
     for (int j0 = 0; j0 < n_pass; j0 += kRoundGroups) {     // one round in the usual case
       const int rem = min(n_pass - j0, kRoundGroups);
-      const int per = (rem + kSolveWaves - 1) / kSolveWaves;
+      const int per = (rem + NW - 1) / NW;
       const int jw = j0 + w * per;
       float v[kRoundLoads]; int vpos[kRoundLoads];
 #pragma unroll
@@ -1468,7 +1485,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     }
     if (in_lds || in_spill) lo_u = fminf(thr - zmax, -1e-7f);
   }
-  for (int pass = 0; pass < 3 && !prefilled && !pre; ++pass) {
+  if constexpr (kLong) for (int pass = 0; pass < 3 && !prefilled && !pre; ++pass) {
     const float width = zmax - thr, slice = width * (1.0f / 64.0f), inv_slice = 64.0f / width;
     if (tid < 64) sh.hist[tid] = 0;
     n_list = 0; in_lds = true;
@@ -1501,10 +1518,10 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
       if (lane == 0) sh.wcount[parity][w] = c;
       __syncthreads();
       int off = n_list, tot = 0;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
+      for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
       n_list += tot;
       parity ^= 1;
-      if (n_list > kListCap) in_lds = false;
+      if (n_list > LIST) in_lds = false;
       if (in_lds) {
 #pragma unroll
         for (int i = 0; i < kRoundLoads; ++i) {
@@ -1533,24 +1550,24 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
   float tau_u; int supp;
   if (in_lds) {
     // V row of every candidate, fetched now (two dependent loads) and consumed after the solve
-    uint32_t rowreg[kListCap / kSolveThreads];
+    uint32_t rowreg[LIST / NT];
 #pragma unroll
-    for (int k = 0; k < kListCap / kSolveThreads; ++k) {
-      const int e = min(tid + k * kSolveThreads, n_list - 1);      // clamped: loads stay unconditional
+    for (int k = 0; k < LIST / NT; ++k) {
+      const int e = min(tid + k * NT, n_list - 1);      // clamped: loads stay unconditional
       rowreg[k] = v_row_of<DENSE>(A, b, lrow, hkv, sh.list_pos[e]);
     }
     const ListSrc ls{sh.list_u, sh.list_pos, n_list};
     if (n_list <= kWaveList) tau_u = solve_tau_wave(sh.list_u, n_list, lo_u, seed_u, beta, ibeta, sh, supp, evals);
     else tau_u = solve_tau(ls, lo_u, seed_u, beta, ibeta, sh, supp, evals);
 #pragma unroll
-    for (int k = 0; k < kListCap / kSolveThreads; ++k) {
-      const int e = tid + k * kSolveThreads;
+    for (int k = 0; k < LIST / NT; ++k) {
+      const int e = tid + k * NT;
       if (e < n_list) sh.list_row[e] = rowreg[k];
     }
     __syncthreads();
     // in-place ordered compaction of the support: entry e keeps (p_e, pos_e, row_e)
     int n_sup = 0;
-    for (int e0 = 0; e0 < n_list; e0 += kSolveThreads) {
+    for (int e0 = 0; e0 < n_list; e0 += NT) {
       const int e = e0 + tid;
       const float x = e < n_list ? sh.list_u[e] - tau_u : -1.f;
       const int pe = e < n_list ? sh.list_pos[e] : 0;
@@ -1560,7 +1577,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
       if (lane == 0) sh.wcount[parity][w] = __popcll(mk);
       __syncthreads();                                     // all reads of this block are done
       int off = n_sup, tot = 0;
-      for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
+      for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
       parity ^= 1;
       if (in) {
         const int o = off + __popcll(mk & lt);
@@ -1577,10 +1594,10 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     gather_support<T>(v_pool, sh, n_sup, acc);
     __syncthreads();
     store_partial(acc, sh, w);
-    sum_partials(sh, out);
+    sum_partials<NW>(sh, out);
     if (A.ex.support_tokens != nullptr) {
       int32_t* dst = A.ex.support_tokens + (size_t)bh * A.ex.support_cap;
-      for (int e = tid; e < n_sup && e < A.ex.support_cap; e += kSolveThreads)
+      for (int e = tid; e < n_sup && e < A.ex.support_cap; e += NT)
         dst[e] = token_of<DENSE>(A, lrow, sh.list_pos[e]);
     }
   } else {
@@ -1595,7 +1612,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     int n_out = 0;
     auto finish = [&](const auto& src) {
       tau_u = solve_tau(src, lo_u, seed_u, beta, ibeta, sh, supp, evals);
-      for (int base = 0; base < src.n; base += 4 * kSolveThreads) {
+      for (int base = 0; base < src.n; base += 4 * NT) {
         float xs[4]; int ps[4]; uint32_t rw[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1613,7 +1630,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
         if (lane == 0) sh.wcount[parity][w] = cw;
         __syncthreads();                                   // also: the previous round's gather is done
         int off = 0, tot = 0;
-        for (int i = 0; i < kSolveWaves; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
+        for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
         parity ^= 1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1631,7 +1648,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
         gather_support<T>(v_pool, sh, tot, acc);
         if (A.ex.support_tokens != nullptr) {
           int32_t* dst = A.ex.support_tokens + (size_t)bh * A.ex.support_cap;
-          for (int e = tid; e < tot && n_out + e < A.ex.support_cap; e += kSolveThreads)
+          for (int e = tid; e < tot && n_out + e < A.ex.support_cap; e += NT)
             dst[n_out + e] = token_of<DENSE>(A, lrow, sh.list_pos[e]);
         }
         n_out += tot;
@@ -1645,7 +1662,7 @@ __global__ __launch_bounds__(kSolveThreads) void decode_solve_kernel(const Solve
     }
     __syncthreads();
     store_partial(acc, sh, w);
-    sum_partials(sh, out);
+    sum_partials<NW>(sh, out);
   }
   const float tau = tau_u + zmax;
   if (tid == 0) {
@@ -2070,6 +2087,18 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 #undef EKV_SCORES
 }
 
+// Pass 2: one workgroup per row, as many wavefronts and as much LDS as the number of rows leaves it.  LDS decides how flat a
+// row may be before its candidates go through the workspace, and how many rows share a compute unit.
+template <typename T, bool DENSE>
+static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStream_t st) {
+  if (rows <= device_compute_units())
+    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveShared>), dim3(rows), dim3(64 * SolveShared::kWaves), 0, st, so);
+  else if (n_chunks_max <= SolveSharedMany::kMaxGroups)
+    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveSharedMany>), dim3(rows), dim3(64 * SolveSharedMany::kWaves), 0, st, so);
+  else
+    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveSharedTwo>), dim3(rows), dim3(64 * SolveSharedTwo::kWaves), 0, st, so);
+}
+
 // Short per-head lists, one workgroup each: sixteen wavefronts as long as every list has a compute unit to itself (the
 // length of one list is what the call takes), else four, and eight lists share a compute unit.
 // Whole top-k steps, two launches against one, us: 32 lists of 656 tokens 29 / 25.5, of 2000 tokens 32.3 / 33.4, of 3686
@@ -2156,7 +2185,7 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
                 dm.Hq, dm.Hkv, grouped ? 1 : 0, dm.P, ws.n_slices_max, dense ? dm.Mmax : dm.cap, ws.n_chunks_max,
                 ws.zstride, dm.beta, dm.ibeta};
   dim3 fgrid(ws.n_slices_max, dm.B * dm.Hq), fblock(kFilterThreads);
-  dim3 sgrid(dm.B * dm.Hq), sblock(kSolveThreads);
+  const int rows = dm.B * dm.Hq;
   if (dense) {
     sa.U = dm.B * dm.Hkv;
     switch (dm.G) {
@@ -2170,8 +2199,8 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
       hipLaunchKernelGGL((filter_level_kernel<true>), dim3(dm.B * dm.Hq), fblock, 0, st, fa);
       hipLaunchKernelGGL((filter_compact_kernel<true>), fgrid, fblock, 0, st, fa);
     }
-    if (dm.dtype == EKV_F32) hipLaunchKernelGGL((decode_solve_kernel<float, true>), sgrid, sblock, 0, st, so);
-    else hipLaunchKernelGGL((decode_solve_kernel<bf16_t, true>), sgrid, sblock, 0, st, so);
+    if (dm.dtype == EKV_F32) launch_solve<float, true>(rows, ws.n_chunks_max, so, st);
+    else launch_solve<bf16_t, true>(rows, ws.n_chunks_max, so, st);
   } else {
     if (grouped && dm.G > 1) {
       sa.U = dm.B * dm.Hkv;
@@ -2190,7 +2219,6 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
       hipLaunchKernelGGL((filter_level_kernel<false>), dim3(dm.B * dm.Hq), fblock, 0, st, fa);
       hipLaunchKernelGGL((filter_compact_kernel<false>), fgrid, fblock, 0, st, fa);
     }
-    const int rows = dm.B * dm.Hq;
     const long long max_cand = (long long)dm.cap * dm.P;
     if (ws.fcount == nullptr && max_cand <= 2048 && rows > kWaveRowsMin) {
       // many short rows: one wavefront per row
@@ -2204,8 +2232,8 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
       }
       return;
     }
-    if (dm.dtype == EKV_F32) hipLaunchKernelGGL((decode_solve_kernel<float, false>), sgrid, sblock, 0, st, so);
-    else hipLaunchKernelGGL((decode_solve_kernel<bf16_t, false>), sgrid, sblock, 0, st, so);
+    if (dm.dtype == EKV_F32) launch_solve<float, false>(rows, ws.n_chunks_max, so, st);
+    else launch_solve<bf16_t, false>(rows, ws.n_chunks_max, so, st);
   }
 }
 

@@ -137,3 +137,37 @@ def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
         tok = orc.pages_to_tokens(pages[b][h], page, K.shape[0])
         ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale, tok)
         check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), toks[b, h], ref, boundary_expected=True)
+
+
+@pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (1024 * 64, 64, 1.0), (20000, 32, 0.03),
+                                               (1024 * 64 + 80, 16, 1.0), (1024 * 64 + 80, 16, 0.1), (70000, 12, 0.04)])
+def test_more_rows_than_compute_units(tokens, page, scale):
+    """288 rows (36 sequences over one shared set of pages, every length different): up to 1024 groups a row is solved by
+    four wavefronts, beyond by sixteen with two rows to a compute unit, and rows too flat for their LDS lists continue in
+    the workspace.  Sampled rows against the oracle; dense and the same pages as lists agree bit for bit."""
+    B, Hq = 36, 8
+    one = synth.Workload("rows", 1, Hq, 1, 128, tokens, page, "bf16", scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(one, 3 + tokens, device="cpu")
+    w = one.scaled(batch=B)
+    g = torch.Generator().manual_seed(tokens)
+    inp["q"] = torch.randn(B, Hq, 128, generator=g).to(torch.bfloat16)
+    inp["block_table"] = inp["block_table"].expand(B, -1).contiguous()
+    inp["seq_lens"] = torch.tensor([tokens - 7 * b for b in range(B)], dtype=torch.int32)
+    st = DeviceState(w, inp)
+    toks = torch.full((B, Hq, 32768), -1, device="cuda", dtype=torch.int32)
+    ex = ekv.decode_extras(support_tokens=toks)
+    ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL), extras=ex)
+    dense = [x.clone() for x in (st.out, st.tau, st.supp, toks)]
+    st.page_idx.copy_(torch.arange(st.cap, device="cuda", dtype=torch.int32).expand(B, Hq, st.cap))
+    st.n_sel.copy_(((st.inp["seq_lens"] + page - 1) // page)[:, None].expand(B, Hq))
+    toks.fill_(-1)
+    ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                          st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=ex)
+    torch.cuda.synchronize()
+    for a, b in zip(dense, (st.out, st.tau, st.supp, toks)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    for b, h in ((0, 0), (17, 5), (35, 7)):
+        q, K, V = unit_kv(inp, w, b, h)
+        ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
+        check_decode_unit(w, st.out[b, h].cpu().numpy(), float(st.tau[b, h]), int(st.supp[b, h]), toks[b, h].cpu().numpy(),
+                          ref, boundary_expected=True)
