@@ -194,10 +194,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_hist_kernel(const float* __re
       lo = min(lo, kk); hi = max(hi, kk);
     }
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
-  }
+  lo = wave_min_u(lo); hi = wave_max_u(hi);
   if (lane == 0) { red[0][w] = lo; red[1][w] = hi; }
   for (int i = tid; i < kBins; i += kTkThreads) hist[i] = 0;
   __syncthreads();
@@ -222,10 +219,9 @@ __global__ __launch_bounds__(kTkThreads) void topk_hist_kernel(const float* __re
   int tot = 0;
 #pragma unroll
   for (int i = 0; i < BPT; ++i) { c[i] = hist[tid * BPT + i]; tot += (int)c[i]; }
-  int inc = tot;                                   // inclusive sum over this and all HIGHER lanes
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) { const int t = __shfl_down(inc, d); if (lane + d < 64) inc += t; }
-  if (lane == 0) wsum[w] = inc;
+  const int low = wave_incl_scan_i(tot), wave_tot = __builtin_amdgcn_readlane(low, 63);
+  const int inc = wave_tot - low + tot;            // inclusive sum over this and all HIGHER lanes
+  if (lane == 0) wsum[w] = wave_tot;
   __syncthreads();
   int higher = 0;                                  // pages in bins owned by higher wavefronts
   for (int i = w + 1; i < kTkWaves; ++i) higher += wsum[i];
@@ -329,11 +325,9 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
     if (tid == 0) s_scan_mask = mask;
     // exclusive prefix of the copied counts (one lane per slice: a serial loop over LDS costs a latency per slice)
     const int cs = tid < S ? s_cnt_s[tid] : 0;
-    int inc = cs;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const int t = __shfl_up(inc, d); if (tid >= d) inc += t; }
+    const int inc = wave_incl_scan_i(cs);
     if (tid < S) s_start[tid] = inc - cs;
-    const int run = __shfl(inc, 63);
+    const int run = __builtin_amdgcn_readlane(inc, 63);
     if (tid == 0) { s_start[S] = run; s_m = run; }       // the scanned slices append behind the copied ones
   }
   __syncthreads();
@@ -517,19 +511,12 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
   if (tid < 64) {                                      // one lane per slice, wave scans instead of serial loops
     const int ab_s = tid < S ? (int)ws.above[((size_t)bh * S + tid) * kBins + b1] : 0;
     const int gt_s = tid < S ? s_gt[tid] : 0, eq_s = tid < S ? s_eq[tid] : 0;
-    int gt_inc = gt_s, eq_inc = eq_s;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int tg = __shfl_up(gt_inc, d), te = __shfl_up(eq_inc, d);
-      if (tid >= d) { gt_inc += tg; eq_inc += te; }
-    }
-    const int k_eq = k_bin - __shfl(gt_inc, 63);       // pages equal to key_t that are taken
+    const int gt_inc = wave_incl_scan_i(gt_s), eq_inc = wave_incl_scan_i(eq_s);
+    const int k_eq = k_bin - __builtin_amdgcn_readlane(gt_inc, 63);       // pages equal to key_t that are taken
     const int eq_before = eq_inc - eq_s;
     const int take_eq = max(0, min(eq_s, k_eq - eq_before));
-    int off_inc = ab_s + gt_s + take_eq;
-    const int mine = off_inc;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const int t = __shfl_up(off_inc, d); if (tid >= d) off_inc += t; }
+    const int mine = ab_s + gt_s + take_eq;
+    const int off_inc = wave_incl_scan_i(mine);
     if (tid < S) {
       ws.slice_off[(size_t)bh * S + tid] = off_inc - mine;
       ws.slice_eq[(size_t)bh * S + tid] = eq_before;
