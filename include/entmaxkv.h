@@ -224,10 +224,8 @@ ekv_status ekv_select_box_threshold(const ekv_config* cfg, const float* box, con
  *   tau_seed f32 [B][Hq] (input): a guess of tau for a warm start -- the Gaussian-aware estimate
  *       tau-hat of the same query (Sec. 4.3 uses it as the solver's starting point), or the threshold
  *       of an earlier solve.  It only chooses where the exact solve starts: the first evaluation is taken
- *       at the seed when it lies inside the certified bracket, and, on rows of at most 262 144 candidates,
- *       a seed that the group maxima certify as a lower bound of tau also serves as the candidate
- *       threshold.  Any value (wrong, infinite, NaN) is safe; tau, supp and out do not depend on it
- *       beyond float32 rounding of the last iterate.
+ *       at the seed when it lies inside the certified bracket.  Any value (wrong, infinite, NaN) is safe;
+ *       tau, supp and out do not depend on it beyond float32 rounding of the last iterate.
  *   solve_evals int32 [B][Hq]: number of evaluations of the mass sum_j (z_j - tau)_+^beta the solve
  *       took (a measure of what a seed saves).
  *   score_pass_only: measurement aid.  Non-zero: only the first pass runs (gather of the K pages, scores and group

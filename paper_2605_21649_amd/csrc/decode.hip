@@ -561,10 +561,12 @@ struct SolveSharedT {
   int n_pass;
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
-// Rows up to one per compute unit; more rows than that, two to a compute unit; many rows of at most kWaveGroups groups,
-// whose usual solve is one wavefront's work anyway.
+// Rows up to one per compute unit, or of any length; more rows than that, two to a compute unit; many rows of at most
+// kWaveGroups groups, whose usual solve is one wavefront's work anyway.  Sixteen maxima per thread take a row of a million
+// tokens from its group maxima in one launch; until there were four, such rows went through the filter passes first
+// (filter 8 + 9, solve 12 us, and two more launches).
 using SolveShared = SolveSharedT<kSolveWaves, 768, kListCap, kPreGroups>;
-using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, kPreGroups>;
+using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, 4 * kWaveGroups>;
 using SolveSharedMany = SolveSharedT<4, 128, 2048, kWaveGroups>;
 
 // Sum of one value per segment (or wavefront) kept in LDS at a stride: one read per lane and a DPP row sum, the same in
@@ -1292,7 +1294,11 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
       else bound_groups<kWaveGroups / 64, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
     }
   } else if constexpr (SH::kMaxGroups > kWaveGroups) {
-    bound_groups<SH::kMaxGroups / (64 * SH::kWaves), false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+    constexpr int kThreads = 64 * SH::kWaves;
+    if (SH::kMaxGroups == 4 * kThreads || R.n_chunks <= 4 * kThreads)
+      bound_groups<4, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+    else
+      bound_groups<SH::kMaxGroups / kThreads, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
   }
   __syncthreads();
   return solve_bounded_row<T, DENSE>(A, R, zr, seed_z, block_extras, sh);
@@ -2091,7 +2097,7 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 // row may be before its candidates go through the workspace, and how many rows share a compute unit.
 template <typename T, bool DENSE>
 static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStream_t st) {
-  if (rows <= device_compute_units())
+  if (rows <= device_compute_units() || n_chunks_max > SolveSharedTwo::kMaxGroups)
     hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveShared>), dim3(rows), dim3(64 * SolveShared::kWaves), 0, st, so);
   else if (n_chunks_max <= SolveSharedMany::kMaxGroups)
     hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveSharedMany>), dim3(rows), dim3(64 * SolveSharedMany::kWaves), 0, st, so);

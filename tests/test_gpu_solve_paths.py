@@ -171,3 +171,28 @@ def test_more_rows_than_compute_units(tokens, page, scale):
         ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
         check_decode_unit(w, st.out[b, h].cpu().numpy(), float(st.tau[b, h]), int(st.supp[b, h]), toks[b, h].cpu().numpy(),
                           ref, boundary_expected=True)
+
+
+@pytest.mark.parametrize("tokens,scale", [(4096 * 64 + 1, 1.0), (16384 * 64 - 30, 1.0), (16384 * 64 + 1, 1.0), (16384 * 64 + 1, 0.05)])
+def test_long_rows_at_the_ends_of_the_group_bound(tokens, scale):
+    """Rows of more than four maxima per thread, of sixteen, and one more group (which takes the filter passes, dense and as
+    a list); the flat one hands thousands of candidates over through them."""
+    w = synth.Workload("long", 1, 2, 1, 128, tokens, 16, "bf16", scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(w, tokens, device="cpu")
+    st = DeviceState(w, inp)
+    toks = torch.full((1, 2, 65536), -1, device="cuda", dtype=torch.int32)
+    ex = ekv.decode_extras(support_tokens=toks)
+    ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL), extras=ex)
+    dense = [x.clone() for x in (st.out, st.tau, st.supp, toks)]
+    st.page_idx.copy_(torch.arange(st.cap, device="cuda", dtype=torch.int32).expand(1, 2, st.cap))
+    st.n_sel.fill_(st.cap)
+    toks.fill_(-1)
+    ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                          st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=ex)
+    torch.cuda.synchronize()
+    for a, b in zip(dense, (st.out, st.tau, st.supp, toks)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    q, K, V = unit_kv(inp, w, 0, 1)
+    ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
+    check_decode_unit(w, st.out[0, 1].cpu().numpy(), float(st.tau[0, 1]), int(st.supp[0, 1]), toks[0, 1].cpu().numpy(), ref,
+                      boundary_expected=True)
