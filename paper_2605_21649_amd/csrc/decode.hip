@@ -6,10 +6,11 @@
 //           an MFMA tile's 16 rows are 4 tokens x 4 channel quarters, so each lane's A operand is the
 //           16 bytes of a fully coalesced load, its 16 columns are (query head, channel quarter); the
 //           blocks with matching quarters are summed with two DPP quad steps.
-//   pass 2 (one workgroup per (b,h)): zmax from the chunk maxima; only z > zmax-1 can be in the
-//           support (at tau = zmax-1 the largest entry alone has mass 1), and chunks whose maximum is
-//           below that are not read; the survivors are compacted IN ORDER into LDS; tau is solved
-//           there; p_j = (z_j - tau)^beta; V rows are gathered only where p_j > 0.
+//   pass 2 (one workgroup per (b,h)): the group maxima alone give the row maximum and a certified lower
+//           bound of tau; only groups whose maximum exceeds it are read, their survivors compacted IN
+//           ORDER into LDS; tau is solved there; p_j = (z_j - tau)^beta; V rows are gathered only where
+//           p_j > 0.
+// Short per-head lists take both passes in one launch with the scores in LDS (decode_row_kernel).
 // All reductions have a fixed order, so results are bit-reproducible.
 #include "ekv_device.h"
 #include "ekv_internal.h"
@@ -538,6 +539,7 @@ __global__ __launch_bounds__(kFilterThreads) void filter_compact_kernel(const Fi
 template <int NW, int SEG, int LIST, int GROUPS>
 struct SolveSharedT {
   static constexpr int kWaves = NW, kSegCap = SEG, kListCap = LIST, kMaxGroups = GROUPS;
+  static constexpr bool kOverflows = true;   // a segment may have more candidates than it holds
   union {
     // Candidates, z - zmax (float bits) and position in the candidate order; segment i is [i * kSegCap, (i + 1) * kSegCap).
     uint2 seg[kSegs * SEG];
@@ -559,15 +561,17 @@ struct SolveSharedT {
   int flags[64];
   float zmax, bound;              // row maximum, certified lower bound of tau relative to it
   int n_pass;
+  int kept[kSegs];                // entries of a segment that overflowed
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
 // Rows up to one per compute unit, or of any length; more rows than that, two to a compute unit; many rows of at most
-// kWaveGroups groups, whose usual solve is one wavefront's work anyway.  Sixteen maxima per thread take a row of a million
+// 256 groups, whose usual solve is one wavefront's work and whose flattest has few candidates (with 1024 groups allowed,
+// 384 flat rows of 64K tokens outgrew the small segments: 485 -> 519 us).  Sixteen maxima per thread take a row of a million
 // tokens from its group maxima in one launch; until there were four, such rows went through the filter passes first
 // (filter 8 + 9, solve 12 us, and two more launches).
 using SolveShared = SolveSharedT<kSolveWaves, 768, kListCap, kPreGroups>;
 using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, 4 * kWaveGroups>;
-using SolveSharedMany = SolveSharedT<4, 128, 2048, kWaveGroups>;
+using SolveSharedMany = SolveSharedT<4, 128, 2048, kWaveGroups / 4>;
 
 // Sum of one value per segment (or wavefront) kept in LDS at a stride: one read per lane and a DPP row sum, the same in
 // every wavefront (a loop reads LDS sixteen times in a row).
@@ -1057,7 +1061,10 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, o));
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2, o));
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3, o));
+    const int before = cnt;
     cnt += __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
+    if constexpr (SH::kOverflows)
+      if (cnt > SH::kSegCap && before <= SH::kSegCap && lane == 0) sh.kept[s] = before;
     if (cnt <= SH::kSegCap) {                                             // wave-uniform
       if (i0) seg[o] = make_uint2(__float_as_uint(v.x - zmax), (uint32_t)p);
       o += i0;
@@ -1246,20 +1253,54 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
 #pragma clang fp contract(off)
   constexpr int SPW = kSegs / SH::kWaves;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  const float zmax = sh.zmax, bound = sh.bound;
+  const float zmax = sh.zmax;
+  float bound = sh.bound;
   if (!(zmax > -INFINITY)) {                                          // no valid candidate at all
     if (w == 0) empty_row_wave<DENSE>(A, R.bh);
     return true;
   }
   const int n_pass = uniform(sh.n_pass);
+  int cw;
+  for (int attempt = 0;; ++attempt) {
 #pragma unroll
-  for (int i = 0; i < SPW; ++i) {
-    const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
-    if (lane == 0) sh.wcount[1][w * SPW + i] = n;
+    for (int i = 0; i < SPW; ++i) {
+      const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
+      if (lane == 0) sh.wcount[1][w * SPW + i] = n;
+    }
+    __syncthreads();
+    cw = lane < kSegs ? sh.wcount[1][lane] : 0;
+    if constexpr (!SH::kOverflows) break;
+    if (__builtin_expect(__ballot(cw > SH::kSegCap) == 0, 1)) break;
+    // a row that a tighter bound leaves far too many candidates will not fit after the next one either
+    if (attempt == 3 || (attempt > 0 && __ballot(cw > SH::kSegCap + SH::kSegCap / 2) != 0)) return false;
+    // A segment is too small.  What the segments do hold is a subset of the candidates, so its mass bounds tau from below
+    // like the maxima's, and far tighter on a row this flat: the groups are read again against that bound, which a
+    // support that fits the segments reaches after one or two rounds.
+    if constexpr (SH::kOverflows) {
+      constexpr int KR = SH::kSegCap / 64;
+      float u[SPW * KR];
+#pragma unroll
+      for (int i = 0; i < SPW; ++i) {
+        const int n = uniform(sh.wcount[1][w * SPW + i]);
+        // a batch that found no room was counted but not written: only whole batches before it are entries
+        const int kept = n > SH::kSegCap ? sh.kept[w * SPW + i] : n;
+#pragma unroll
+        for (int k = 0; k < KR; ++k)
+          u[i * KR + k] = lane + 64 * k < kept ? __uint_as_float(sh.seg[(w * SPW + i) * SH::kSegCap + lane + 64 * k].x) : -INFINITY;
+      }
+      int parity = 0;
+      const float t = group_bound(u, bound, A.beta, A.ibeta, [&](float& f, float& d) {
+        f = wave_sum(f); d = wave_sum(d);
+        if (lane == 0) { sh.red[parity][w][0] = f; sh.red[parity][w][1] = d; }
+        __syncthreads();
+        f = sum_waves<SH::kWaves>(&sh.red[parity][0][0], 3); d = sum_waves<SH::kWaves>(&sh.red[parity][0][1], 3);
+        parity ^= 1;
+      });
+      bound = fmaxf(bound, t - 4e-6f * fmaxf(1.f, fabsf(zmax)));
+      if (threadIdx.x == 0) sh.bound = bound;
+      __syncthreads();                                                // the segments are read
+    }
   }
-  __syncthreads();
-  const int cw = lane < kSegs ? sh.wcount[1][lane] : 0;
-  if (__ballot(cw > SH::kSegCap) != 0) return false;
   const int total = sum_waves_i(sh.wcount[1], 1);
   const float lo_u = fminf(bound, -1e-7f), seed_u = seed_z - zmax;
   if (__builtin_expect(block_extras, 0)) side_outputs<DENSE>(A, R.bh, R.n_cand, zr, zmax, sh);
@@ -1361,13 +1402,12 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
     }
     return;
   }
-  // Only z > zmax - 1 can be in the support.  That set is compacted IN ORDER into LDS in rounds of
-  // kRoundTokens candidates: wavefront w of a round owns 64*kRoundLoads consecutive positions, so
-  // (round, w, load, lane) order is candidate order.  A 64-position load whose chunk maximum is <= thr is
-  // not issued.  The same pass histograms the candidates over 64 slices of [thr, zmax]; counts alone give
-  // a lower bound of the mass at every slice boundary (an entry of slice j lies at least j-i slices above
-  // boundary i), hence a tighter valid threshold: it becomes the starting point of the solve, and, if the
-  // candidates did not fit in LDS, the threshold of one more compaction pass.
+  // The candidates above the bound (only z > zmax - 1 can be in the support; `pre` and filtered rows have a tighter
+  // one) are compacted IN ORDER in rounds: wavefront w of a round owns consecutive positions, so (round, w, load, lane)
+  // order is candidate order.  Rows that have neither list of groups nor filter results sweep their scores, skipping
+  // chunks whose maximum is <= thr, and histogram the candidates over 64 slices of [thr, zmax]: counts alone give a lower
+  // bound of the mass at every slice boundary (an entry of slice j lies at least j-i slices above boundary i), hence a
+  // tighter threshold for the solve or, if the candidates did not fit in LDS, for one more compaction pass.
   float thr = filt || pre ? thr_f : zmax - 1.0f - 4e-6f * fmaxf(1.f, fabsf(zmax));
   const float seed_u = seed_z - zmax;
   int evals = 0;
@@ -1696,6 +1736,7 @@ constexpr int kRowTokensMany = 2048;               // and of the four-wavefront 
 template <int NW, int TOKENS, int GROUP>
 struct RowShared {
   static constexpr int kWaves = NW, kGroups = (TOKENS + GROUP - 1) / GROUP;
+  static constexpr bool kOverflows = false;
   static constexpr int kSegCap = (kGroups + kSegs - 1) / kSegs * 64;   // a segment holds all tokens of its groups
   union {                                          // the scores are dead once the candidates are listed
     float z[TOKENS];
@@ -1848,12 +1889,12 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
 // ------------------------------------------------------------------------------------------
 // pass 2 for short candidate rows: one wavefront per (b, h)
 // ------------------------------------------------------------------------------------------
-// Rows of at most 64*KZ candidate tokens (page lists of a few dozen pages): all scores of a row sit in the
+// Lists shared per KV head, in more than kWaveRowsMin rows of at most 64*KZ candidate tokens (per-head lists of that
+// length are decoded in one launch, above): all scores of a row sit in the
 // registers of ONE wavefront (lane l holds candidates i*64 + l), the threshold is solved there, and the support
 // is gathered through a small LDS list in candidate order, flushed whenever it could overflow -- any support
 // size, no barrier.  Four rows per 256-thread workgroup: with hundreds or thousands of rows (many sequences
-// of a few thousand tokens) the 1024-thread workgroup per row of the kernel above fills the GPU several times
-// over.  Sparse and group-shared lists only.
+// of a few thousand tokens) the workgroup per row of the kernel above fills the GPU several times over.
 constexpr int kWaveRowList = 256;        // LDS list entries per wavefront
 constexpr int kWaveRowsMin = 512;        // up to 512 rows the workgroup kernel takes one round and is as fast
 

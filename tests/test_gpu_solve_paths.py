@@ -139,10 +139,11 @@ def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
         check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), toks[b, h], ref, boundary_expected=True)
 
 
-@pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (1024 * 64, 64, 1.0), (20000, 32, 0.03),
+@pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (16384, 16, 1.0), (16384, 32, 0.05),
+                                               (16385, 16, 1.0), (1024 * 64, 64, 1.0), (20000, 32, 0.03),
                                                (1024 * 64 + 80, 16, 1.0), (1024 * 64 + 80, 16, 0.1), (70000, 12, 0.04)])
 def test_more_rows_than_compute_units(tokens, page, scale):
-    """288 rows (36 sequences over one shared set of pages, every length different): up to 1024 groups a row is solved by
+    """288 rows (36 sequences over one shared set of pages, every length different): up to 256 groups a row is solved by
     four wavefronts, beyond by sixteen with two rows to a compute unit, and rows too flat for their LDS lists continue in
     the workspace.  Sampled rows against the oracle; dense and the same pages as lists agree bit for bit."""
     B, Hq = 36, 8
