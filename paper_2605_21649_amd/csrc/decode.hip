@@ -85,7 +85,6 @@ __global__ __launch_bounds__(1024) void unit_prefix_kernel(const ScoreArgs A, in
 // hardly overlap (2 % of a million tokens) 113.4 -> 112.6.
 constexpr int kXcds = 8;
 struct Part { int index, count; };             // this workgroup's part, parts per unit (1: units are not split)
-template <int MODE>
 __device__ __forceinline__ Part unit_part(const ScoreArgs& A) {
   return {A.parts == kXcds ? (int)(blockIdx.x % kXcds) : 0, A.parts};
 }
@@ -132,7 +131,7 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_valu_kernel(const
   const int gp = pmax_pages(P);
   const int r = lane >> 4, c = lane & 15;
   const int ratio = Hq / Hkv;
-  const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part<MODE>(A);
+  const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part(A);
   if (!PRE_GLOBAL)
     block_exclusive_prefix<kScoreThreads>(A.U, [&](int u) {
       return part_length(part, u / ratio, (unit_slots<MODE>(A, u) + gp - 1) / gp); }, pre_lds, wsum);
@@ -224,7 +223,7 @@ void decode_scores_mfma_kernel(const ScoreArgs A) {
   // row (token gl of the step, quarter kq), K group j -> bytes [gl*256 + (kq*4+j)*16, +16) of the step
   const int lane_off = gl * kD + (kq * 4 + j) * 8;
   const int ratio = Hq / Hkv;
-  const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part<MODE>(A);
+  const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part(A);
   if (!PRE_GLOBAL)
     block_exclusive_prefix<kScoreThreads>(A.U, [&](int u) {
       return part_length(part, u / ratio, (unit_slots<MODE>(A, u) + GP - 1) / GP); }, pre_lds, wsum);

@@ -29,29 +29,6 @@ struct SelectShared {
 static_assert(kSelWaves == 16, "one value per wavefront is one DPP row");
 static_assert(4 * kRankMax <= kSelThreads, "four lanes per ranked key");
 
-// Exclusive prefix sum over the block in thread order; `total` receives the block sum.
-// Contains barriers: all threads must call it.
-__device__ __forceinline__ int block_excl_scan(int v, int* buf, int& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(inc, d);
-    if (lane >= d) inc += t;
-  }
-  __syncthreads();
-  if (lane == 63) buf[w] = inc;
-  __syncthreads();
-  int base = 0, tot = 0;
-  for (int i = 0; i < kSelWaves; ++i) {
-    const int c = buf[i];
-    if (i < w) base += c;
-    tot += c;
-  }
-  total = tot;
-  return base + inc - v;
-}
-
 // Keys of one (b,h) row.  ITEMS > 0: held in registers (M <= 1024*ITEMS); ITEMS == 0: recomputed from
 // memory on every access (any M).  `fn(p)` gives the key of page p.  Slots past M hold the value 0.
 // After rebase(kmin) every key is stored relative to kmin (so only one register array is live).
