@@ -25,6 +25,7 @@ constexpr int kSegs = 16;               // candidate lists are cut into this man
 constexpr int kSpillCap = 65536;        // entries of a row's overflow list in the workspace (longer lists: the row is streamed)
 constexpr int kWaveGroups = 1024;       // up to this many group maxima are bounded by one wavefront, more by all of them
 constexpr int kRoundLoads = 16;         // loads per lane and compaction round
+constexpr int kWaveList = 256;          // candidates of a row that one wavefront finishes in registers
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
@@ -545,12 +546,10 @@ struct SolveSharedT {
     struct {                      // the general path's one list, and the support of a row that one wavefront finishes
       float list_u[LIST];
       int32_t list_pos[LIST];
+      uint32_t list_row[LIST];    // their V row: (phys*Hkv + hkv)*P + tok
     };
   };
-  union {
-    uint32_t list_row[LIST];      // their V row: (phys*Hkv + hkv)*P + tok
-    uint16_t glist[GROUPS];       // the groups that can hold a candidate, ascending
-  };
+  uint16_t glist[GROUPS];         // the groups that can hold a candidate, ascending
   float obuf[kSegs][kD];
   float red[2][kSegs][3];
   int wcount[2][kSegs];
@@ -570,7 +569,31 @@ static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
 // (filter 8 + 9, solve 12 us, and two more launches).
 using SolveShared = SolveSharedT<kSolveWaves, 768, kListCap, kPreGroups>;
 using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, 4 * kWaveGroups>;
-using SolveSharedMany = SolveSharedT<4, 128, 2048, kWaveGroups / 4>;
+// 192 entries per segment take all of a row of up to 2048 tokens whatever the page size (180 in groups of 60), so that such a
+// row's result is that of its one-launch decode to the last bit however flat it is.
+using SolveSharedMany = SolveSharedT<4, 192, 2048, kWaveGroups / 4>;
+constexpr int kOneGroups = kSegs;           // a row of at most this many groups has one in each segment
+
+// Many rows of at most kOneGroups groups (lists shared per KV head; per-head lists of that length are decoded in one launch,
+// below): one wavefront each.  A segment holds all tokens of its one group, so nothing overflows, and 9 KB of LDS let a
+// compute unit keep as many rows as its registers do.
+struct SolveSharedOne {
+  static constexpr int kWaves = 1, kSegCap = 64, kMaxGroups = kOneGroups;
+  static constexpr bool kOverflows = false;
+  union {
+    uint2 seg[kSegs * kSegCap];
+    float obuf[kSegs][kD];        // a segment's partial output replaces its candidates
+    struct { float list_u[kWaveList]; int32_t list_pos[kWaveList]; uint32_t list_row[kWaveList]; };
+  };
+  float red[2][kSegs][3];
+  int wcount[2][kSegs];
+  int pre[kSegs + 1];
+  float red1[1];
+  uint16_t glist[kOneGroups];
+  float zmax, bound;
+  int n_pass;
+};
+static_assert(sizeof(float[kD]) == sizeof(uint2[SolveSharedOne::kSegCap]), "partial output i covers segment i and no other");
 
 // Sum of one value per segment (or wavefront) kept in LDS at a stride: one read per lane and a DPP row sum, the same in
 // every wavefront (a loop reads LDS sixteen times in a row).
@@ -709,7 +732,6 @@ __device__ __forceinline__ float solve_tau(const Src& src, float lo_init, float 
 // Short candidate lists (at most kWaveList entries, the usual case once the certified bound has been
 // applied): one wavefront holds them in registers and iterates without any barrier; the result is handed
 // to the other wavefronts through LDS.  Called by the whole workgroup.
-constexpr int kWaveList = 256;
 // entries of one wavefront in registers (u[k] of lane l is list entry l + 64 k, -inf past the end)
 template <int KW>
 __device__ __forceinline__ float solve_tau_regs(const float (&u)[KW], float lo_init, float seed, float beta, int ibeta,
@@ -797,11 +819,11 @@ __device__ __forceinline__ void store_partial(float (&acc)[8], SH& sh, int seg) 
 template <int N = kSegs, typename SH>
 __device__ __forceinline__ void sum_partials(const SH& sh, float* __restrict__ out) {
   __syncthreads();
-  if (threadIdx.x < kD) {
+  for (int c = threadIdx.x; c < kD; c += 64 * SH::kWaves) {
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) s += sh.obuf[i][threadIdx.x];
-    out[threadIdx.x] = s;
+    for (int i = 0; i < N; ++i) s += sh.obuf[i][c];
+    out[c] = s;
   }
 }
 
@@ -1090,6 +1112,38 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
   return cnt;
 }
 
+// The same for a row with at most one group per segment, by one wavefront: four loads take all groups.
+template <typename SH>
+__device__ __forceinline__ void fetch_single_groups(const RowRef& R, const float* zr, int n_pass, float zmax, float thr, SH& sh) {
+  const int lane = threadIdx.x & 63, sub = lane >> 4, in_group = 4 * (lane & 15);
+  const uint64_t row = 0xffffull << (lane & 48), before = row & ((1ull << lane) - 1ull);
+  int p[kSegs / 4]; float4 v[kSegs / 4];
+#pragma unroll
+  for (int i = 0; i < kSegs / 4; ++i) {
+    const int g = sh.glist[min(4 * i + sub, max(n_pass - 1, 0))];
+    p[i] = min(g * R.chunk_tokens + min(in_group, R.chunk_tokens - 4), R.n_cand - 4);
+    v[i] = *reinterpret_cast<const float4*>(zr + p[i]);
+    if (4 * i + sub >= n_pass || in_group >= R.chunk_tokens || g * R.chunk_tokens + in_group >= R.n_cand) p[i] = -1;
+  }
+#pragma unroll
+  for (int i = 0; i < kSegs / 4; ++i) {
+    const float t = p[i] >= 0 ? thr : INFINITY;
+    const float z[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+    uint2* seg = sh.seg + (4 * i + sub) * SH::kSegCap;
+    int o = 0, n = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t m = __ballot(z[k] > t);
+      o += __popcll(m & before);
+      n += __popcll(m & row);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (z[k] > t) seg[o++] = make_uint2(__float_as_uint(z[k] - zmax), (uint32_t)(p[i] + k));
+    if ((lane & 15) == 0) sh.wcount[1][4 * i + sub] = n;
+  }
+}
+
 // Threshold, support and weighted value sum of a row whose candidates lie in the segments (sh.wcount[1]: their lengths).
 // A wavefront keeps the entries of its kSegs / kWaves segments in registers, an evaluation of the mass costs one barrier,
 // and each then gathers the value rows of its own part of the support.  Every sum is taken per segment first, so the
@@ -1111,30 +1165,53 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
     for (int k = 0; k < KR; ++k)
       u[i][k] = lane + 64 * k < n[i] ? __uint_as_float(seg0[i * SH::kSegCap + lane + 64 * k].x) : -INFINITY;
   }
+  const int n_groups = uniform(sh.n_pass);
   int supp = 0, evals = 0, parity = 0;
   const float tau_u = with_beta(A.ibeta, [&](auto ib) {
     constexpr int IB = decltype(ib)::value;
     return solve_tau_core([&](float t, float& F, float& D, int& cnt) {
-#pragma unroll
-      for (int i = 0; i < SPW; ++i) {
-        float f = 0.f, d = 0.f;
-        int c = 0;
+      auto segment_mass = [&](int i, float& f, float& d, int& c) {
+        f = d = 0.f;
+        c = 0;
 #pragma unroll
         for (int k = 0; k < KR; ++k) {
-          if (64 * k < n[i]) {                                        // wave-uniform
+          if (KR == 1 || 64 * k < n[i]) {                             // wave-uniform
             const float x = fmaxf(u[i][k] - t, 0.f);
             add_mass<IB>(x, A.beta, f, d);
             c += __popcll(__ballot(x > 0.f));
           }
         }
         f = wave_sum(f); d = wave_sum(d);
-        if (lane == 0) { sh.red[parity][s0 + i][0] = f; sh.red[parity][s0 + i][1] = d; sh.red[parity][s0 + i][2] = __int_as_float(c); }
+      };
+      float f, d;
+      int c;
+      if constexpr (SH::kWaves == 1) {
+        float fs = 0.f, ds = 0.f;                                     // lane i keeps segment i's sums
+        cnt = 0;
+#pragma unroll
+        for (int b = 0; b < SPW; b += 4) {                            // four segments at a time, as far as there are groups
+          if (b < n_groups) {
+#pragma unroll
+            for (int i = b; i < b + 4; ++i) {
+              segment_mass(i, f, d, c);
+              fs = (lane & 15) == i ? f : fs; ds = (lane & 15) == i ? d : ds;
+              cnt += c;
+            }
+          }
+        }
+        F = row16_sum(fs); D = A.beta * row16_sum(ds);
+      } else {
+#pragma unroll
+        for (int i = 0; i < SPW; ++i) {
+          segment_mass(i, f, d, c);
+          if (lane == 0) { sh.red[parity][s0 + i][0] = f; sh.red[parity][s0 + i][1] = d; sh.red[parity][s0 + i][2] = __int_as_float(c); }
+        }
+        __syncthreads();
+        F = sum_waves(&sh.red[parity][0][0], 3);
+        D = A.beta * sum_waves(&sh.red[parity][0][1], 3);
+        cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
+        parity ^= 1;
       }
-      __syncthreads();
-      F = sum_waves(&sh.red[parity][0][0], 3);
-      D = A.beta * sum_waves(&sh.red[parity][0][1], 3);
-      cnt = sum_waves_i(reinterpret_cast<const int*>(&sh.red[parity][0][2]), 3);
-      parity ^= 1;
     }, lo_u, seed_u, IB, supp, evals);
   });
   // the support in place: (weight, position), ascending
@@ -1156,44 +1233,6 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
       }
     }
   }
-  // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
-  // flight per lane; the next 64 are looked up before these are consumed
-  const int rs = lane >> 4, c = lane & 15;
-#pragma unroll 1
-  for (int i = 0; i < SPW; ++i) {
-    const uint2* seg = seg0 + i * SH::kSegCap;
-    int ns = n_sup[0];
-#pragma unroll
-    for (int j = 1; j < SPW; ++j) ns = i == j ? n_sup[j] : ns;
-    float acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    uint32_t row = ns > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(lane, ns - 1)].y) : 0u;
-    for (int e0 = 0; e0 < ns; e0 += 64) {
-      const uint32_t row_now = row;
-      row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, ns - 1)].y);
-      const float p_now = e0 + lane < ns ? __uint_as_float(seg[e0 + lane].x) : 0.f;
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        Raw8<T> vr[8]; float pw[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int src = 32 * half + 4 * j + rs;
-          pw[j] = __shfl(p_now, src);
-          load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float vv[8];
-          widen8(vr[j], vv);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
-        }
-        if (e0 + 32 >= ns) break;                                     // wave-uniform
-      }
-    }
-    store_partial(acc, sh, s0 + i);
-  }
   if (A.ex.support_tokens != nullptr) {
 #pragma unroll
     for (int i = 0; i < SPW; ++i)
@@ -1209,6 +1248,104 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
       off += n_sup[i];
     }
   }
+  const int rs = lane >> 4, c = lane & 15;
+  if constexpr (SH::kWaves == 1) {
+    // value rows of all segments are looked up together (page list -> block table) and take the positions' place; then 4
+    // row slots x 16 lanes, four rows of a segment per step and the steps of all segments in one sequence, sixteen loads in
+    // flight per lane (float32: eight).  A wait per segment was most of a flat row's time: 2048 rows of 512 tokens with a
+    // support of 80, whole call: 62 us, in sequence 54.
+    uint32_t row[SPW];
+    int ns_of = 0;                                                      // lane i: support entries of segment i
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      row[i] = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, n_sup[i] > 0 ? (int)seg0[i * SH::kSegCap + min(lane, n_sup[i] - 1)].y : 0);
+      ns_of = lane == i ? n_sup[i] : ns_of;
+    }
+    wave_order();
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      seg0[i * SH::kSegCap + lane].y = row[i];
+      if (lane >= n_sup[i]) seg0[i * SH::kSegCap + lane].x = 0u;        // past the end: its last row with weight 0
+    }
+    wave_order();
+    const uint32_t full = (uint32_t)__ballot(ns_of > 0);                // segments with an entry; the others' output is 0
+    for (uint32_t none = ~full & 0xffffu; none != 0; none &= none - 1) {
+      const int i = __builtin_ctz(none);
+      sh.obuf[i][lane] = 0.f; sh.obuf[i][lane + 64] = 0.f;
+    }
+    float acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+    uint32_t left = full;
+    int at = 0;
+    constexpr int U = sizeof(T) == 2 ? 16 : 8;
+    while (left != 0) {                                                 // wave-uniform, as everything about the steps
+      Raw8<T> vr[U]; float pw[U];
+      int ends[U];                                                      // the segment that ends with the step, or -1
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int i = left != 0 ? __builtin_ctz(left) : 0;
+        const bool real = left != 0;
+        const uint2 e = seg0[i * SH::kSegCap + min(at + rs, SH::kSegCap - 1)];
+        pw[j] = real ? __uint_as_float(e.x) : 0.f;
+        load_raw8(v_pool + (size_t)(real ? e.y : row[0]) * kD + 8 * c, vr[j]);
+        at += 4;
+        ends[j] = -1;
+        if (real && at >= __builtin_amdgcn_readlane(ns_of, i)) { ends[j] = i; left &= left - 1; at = 0; }
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        float vv[8];
+        widen8(vr[j], vv);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
+        if (ends[j] >= 0) {
+          wave_order();                                                 // the partial output takes the segment's place
+          store_partial(acc, sh, ends[j]);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+        }
+      }
+    }
+  } else {
+    // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
+    // flight per lane; the next 64 are looked up before these are consumed
+#pragma unroll 1
+    for (int i = 0; i < SPW; ++i) {
+      const uint2* seg = seg0 + i * SH::kSegCap;
+      int ns = n_sup[0];
+#pragma unroll
+      for (int j = 1; j < SPW; ++j) ns = i == j ? n_sup[j] : ns;
+      float acc[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+      uint32_t row = ns > 0 ? v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(lane, ns - 1)].y) : 0u;
+      for (int e0 = 0; e0 < ns; e0 += 64) {
+        const uint32_t row_now = row;
+        row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, ns - 1)].y);
+        const float p_now = e0 + lane < ns ? __uint_as_float(seg[e0 + lane].x) : 0.f;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          Raw8<T> vr[8]; float pw[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int src = 32 * half + 4 * j + rs;
+            pw[j] = __shfl(p_now, src);
+            load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            float vv[8];
+            widen8(vr[j], vv);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
+          }
+          if (e0 + 32 >= ns) break;                                     // wave-uniform
+        }
+      }
+      store_partial(acc, sh, s0 + i);
+    }
+  }
   sum_partials(sh, A.out + (size_t)R.bh * kD);
   if (tid == 0) {
     A.tau_out[R.bh] = tau_u + zmax; A.supp_out[R.bh] = supp;
@@ -1222,12 +1359,17 @@ __device__ __forceinline__ void side_outputs(const SolveArgs& A, int bh, int n_c
   const int tid = threadIdx.x;
   if (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) {
     const float tr = A.ex.tau_ref[bh];
+    constexpr int V = SH::kWaves == 1 ? 4 : 1;         // one wavefront adds up in the order of four
     float f = 0.f; int c = 0;
-    for (int i = tid; i < n_cand; i += 64 * SH::kWaves) {
-      const float x = zr[i] - tr;
-      if (x > 0.f) { f += pow_beta(x, A.beta, A.ibeta); ++c; }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      float part = 0.f;
+      for (int i = tid + 64 * v; i < n_cand; i += 64 * SH::kWaves * V) {
+        const float x = zr[i] - tr;
+        if (x > 0.f) { part += pow_beta(x, A.beta, A.ibeta); ++c; }
+      }
+      f += V == 1 ? block_sum(part, sh.red1) : wave_sum(part);
     }
-    f = block_sum(f, sh.red1);
     c = block_sum_i(c, sh.wcount[0]);
     if (tid == 0) {
       if (A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = f;
@@ -1261,10 +1403,14 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
   const int n_pass = uniform(sh.n_pass);
   int cw;
   for (int attempt = 0;; ++attempt) {
+    if constexpr (SH::kMaxGroups <= kSegs) {
+      fetch_single_groups(R, zr, n_pass, zmax, zmax + bound, sh);
+    } else {
 #pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-      const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
-      if (lane == 0) sh.wcount[1][w * SPW + i] = n;
+      for (int i = 0; i < SPW; ++i) {
+        const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
+        if (lane == 0) sh.wcount[1][w * SPW + i] = n;
+      }
     }
     __syncthreads();
     cw = lane < kSegs ? sh.wcount[1][lane] : 0;
@@ -1329,7 +1475,7 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
   auto group_max = [pm](int g) { return pm[g]; };
   if (R.n_chunks <= kWaveGroups) {
     if (w == 0) {
-      if (R.n_chunks <= 128) bound_groups<2, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
+      if (SH::kMaxGroups <= 128 || R.n_chunks <= 128) bound_groups<2, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
       else if (R.n_chunks <= kWaveGroups / 2) bound_groups<kWaveGroups / 128, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
       else bound_groups<kWaveGroups / 64, true>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
     }
@@ -1344,23 +1490,50 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
   return solve_bounded_row<T, DENSE>(A, R, zr, seed_z, block_extras, sh);
 }
 
+template <bool DENSE>
+__device__ __forceinline__ RowRef row_ref(const SolveArgs& A, int bh) {
+  const int b = bh / A.Hq, hq = bh % A.Hq, hkv = hq / (A.Hq / A.Hkv), gp = pmax_pages(A.P);
+  const int lrow = A.grouped ? b * A.Hkv + hkv : bh;        // row of the page list this head reads
+  const int n_slots = clampi(DENSE ? (A.seq_lens[b] + A.P - 1) / A.P : A.n_sel[lrow], 0, DENSE ? A.Mmax : A.cap);
+  return {b, bh, lrow, hkv, n_slots * A.P, gp * A.P, (n_slots + gp - 1) / gp};
+}
+// Side outputs that need a pass over all candidates.
+template <bool DENSE>
+__device__ __forceinline__ bool wants_side_outputs(const SolveArgs& A) {
+  return (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) ||
+         (DENSE && A.ex.lse != nullptr);
+}
+
+// Row of workgroup i: the heads of a group, whose supports are largely the same value rows, go to one XCD (workgroups go to
+// the XCDs in turn) as far as whole rounds of groups last.  A permutation of [0, rows).  2048 rows of 256 tokens, support 246,
+// groups of four: 37.5 -> 30.2 us; 4096 rows of 1024, support 720, groups of eight: 172 -> 136.
+__device__ __forceinline__ int group_on_one_xcd(int i, int rows, int heads) {
+  const int round = kXcds * heads, t = i / kXcds;
+  return i >= rows / round * round ? i : (t / heads * kXcds + i % kXcds) * heads + t % heads;
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void decode_solve_one_kernel(const SolveArgs A) {
+  __shared__ SolveSharedOne sh;
+  const int bh = group_on_one_xcd(blockIdx.x, gridDim.x, A.Hq / A.Hkv);
+  const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
+  const RowRef R = row_ref<false>(A, bh);
+  solve_row<T, false>(A, R, A.zbuf + (size_t)bh * A.zstride, A.pmax + (size_t)bh * A.n_chunks_max, seed_z,
+                      wants_side_outputs<false>(A), sh);
+}
+
 template <typename T, bool DENSE, typename SH>
 __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const SolveArgs A) {
   __shared__ SH sh;
   constexpr int NT = 64 * SH::kWaves, NW = SH::kWaves, LIST = SH::kListCap;
   constexpr int kRoundTokens = NT * kRoundLoads;
   constexpr bool kLong = SH::kMaxGroups >= kPreGroups;   // false: the launch has only rows of at most kMaxGroups groups
-  const int Hq = A.Hq, Hkv = A.Hkv, P = A.P;
-  const int bh = blockIdx.x, b = bh / Hq, hq = bh % Hq, hkv = hq / (Hq / Hkv);
+  const int bh = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
-  const int n = A.seq_lens[b];
-  const int lrow = A.grouped ? b * Hkv + hkv : bh;          // row of the page list this head reads
-  const int n_slots = clampi(DENSE ? (n + P - 1) / P : A.n_sel[lrow], 0, DENSE ? A.Mmax : A.cap);
-  const int n_cand = n_slots * P;
-  const int n_chunks = (n_slots + pmax_pages(P) - 1) / pmax_pages(P);
-  const int chunk_tokens = pmax_pages(P) * P;
+  const RowRef R = row_ref<DENSE>(A, bh);
+  const int b = R.b, lrow = R.lrow, hkv = R.hkv, n_cand = R.n_cand, n_chunks = R.n_chunks, chunk_tokens = R.chunk_tokens;
   const float* zr = A.zbuf + (size_t)bh * A.zstride;
   const float* pm = A.pmax + (size_t)bh * A.n_chunks_max;
   const float beta = A.beta; const int ibeta = A.ibeta;
@@ -1368,9 +1541,7 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
 
   // warm start (optional): requested with the first loads, used once zmax is known
   const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
-  const bool block_extras = (A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr)) ||
-                            (DENSE && A.ex.lse != nullptr);
-  const RowRef R{b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks};
+  const bool block_extras = wants_side_outputs<DENSE>(A);
   float zmax, thr_f = 0.f;
   const bool pre = !kLong || n_chunks <= kPreGroups;
   if (__builtin_expect(pre, 1)) {
@@ -1734,7 +1905,7 @@ constexpr int kRowTokensMany = 2048;               // and of the four-wavefront 
 // GROUP: the least number of tokens in a group, 64 where the page size divides 64, else at least 36 (one page of 36).
 template <int NW, int TOKENS, int GROUP>
 struct RowShared {
-  static constexpr int kWaves = NW, kGroups = (TOKENS + GROUP - 1) / GROUP;
+  static constexpr int kWaves = NW, kGroups = (TOKENS + GROUP - 1) / GROUP, kMaxGroups = kGroups;
   static constexpr bool kOverflows = false;
   static constexpr int kSegCap = (kGroups + kSegs - 1) / kSegs * 64;   // a segment holds all tokens of its groups
   union {                                          // the scores are dead once the candidates are listed
@@ -1886,194 +2057,6 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
 }
 
 // ------------------------------------------------------------------------------------------
-// pass 2 for short candidate rows: one wavefront per (b, h)
-// ------------------------------------------------------------------------------------------
-// Lists shared per KV head, in more than kWaveRowsMin rows of at most 64*KZ candidate tokens (per-head lists of that
-// length are decoded in one launch, above): all scores of a row sit in the
-// registers of ONE wavefront (lane l holds candidates i*64 + l), the threshold is solved there, and the support
-// is gathered through a small LDS list in candidate order, flushed whenever it could overflow -- any support
-// size, no barrier.  Four rows per 256-thread workgroup: with hundreds or thousands of rows (many sequences
-// of a few thousand tokens) the workgroup per row of the kernel above fills the GPU several times over.
-constexpr int kWaveRowList = 256;        // LDS list entries per wavefront
-constexpr int kWaveRowsMin = 512;        // up to 512 rows the workgroup kernel takes one round and is as fast
-
-template <typename T, int KZ>
-__global__ __launch_bounds__(256) void decode_solve_wave_kernel(const SolveArgs A, int BH) {
-  __shared__ float l_p[4][kWaveRowList];
-  __shared__ uint32_t l_row[4][kWaveRowList];
-  __shared__ int32_t l_pos[4][kWaveRowList];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int bh = blockIdx.x * 4 + wv;
-  if (bh >= BH) return;                                      // wave-uniform
-  const uint64_t lt = (1ull << lane) - 1ull;
-  const int Hq = A.Hq, Hkv = A.Hkv, P = A.P;
-  const int b = bh / Hq, hq = bh % Hq, hkv = hq / (Hq / Hkv);
-  const int lrow = A.grouped ? b * Hkv + hkv : bh;
-  const T* v_pool = (const T*)A.v_pool;
-  const float beta = A.beta; const int ibeta = A.ibeta;
-  float* out = A.out + (size_t)bh * kD;
-  const float* zr = A.zbuf + (size_t)bh * A.zstride;
-  const int n_cand = min(clampi(A.n_sel[lrow], 0, A.cap) * P, 64 * KZ);
-  const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
-  float u[KZ];
-#pragma unroll
-  for (int i = 0; i < KZ; ++i) u[i] = zr[min(i * 64 + lane, max(n_cand - 1, 0))];
-  float zmax = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < KZ; ++i) { u[i] = i * 64 + lane < n_cand ? u[i] : -INFINITY; zmax = fmaxf(zmax, u[i]); }
-  zmax = wave_max(zmax);
-  const bool want_kept = A.ex.tau_ref != nullptr && (A.ex.kept_mass_ref != nullptr || A.ex.kept_supp_ref != nullptr);
-  if (!(zmax > -INFINITY)) {                                 // no valid candidate at all
-    if (lane < 16) {
-      *reinterpret_cast<float4*>(out + 8 * lane) = make_float4(0.f, 0.f, 0.f, 0.f);
-      *reinterpret_cast<float4*>(out + 8 * lane + 4) = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (lane == 0) {
-      A.tau_out[bh] = INFINITY; A.supp_out[bh] = 0;
-      if (A.ex.solve_evals != nullptr) A.ex.solve_evals[bh] = 0;
-      if (want_kept && A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = 0.f;
-      if (want_kept && A.ex.kept_supp_ref != nullptr) A.ex.kept_supp_ref[bh] = 0;
-    }
-    return;
-  }
-  if (want_kept) {                                           // mass and count above a given threshold, all candidates
-    const float tr = A.ex.tau_ref[bh];
-    float f = 0.f; int c = 0;
-#pragma unroll
-    for (int i = 0; i < KZ; ++i) {
-      const float x = u[i] - tr;
-      if (x > 0.f) { f += pow_beta(x, beta, ibeta); ++c; }
-    }
-    f = wave_sum(f); c = wave_sum_i(c);
-    if (lane == 0) {
-      if (A.ex.kept_mass_ref != nullptr) A.ex.kept_mass_ref[bh] = f;
-      if (A.ex.kept_supp_ref != nullptr) A.ex.kept_supp_ref[bh] = c;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < KZ; ++i) u[i] -= zmax;
-  const float lo_u = -1.0f - 4e-6f * fmaxf(1.f, fabsf(zmax));
-  int supp = 0, evals = 0;
-  float tau_u;
-  // Only candidates above zmax - 1 can be in the support: usually a few dozen.  They are compacted (in order)
-  // into the LDS list and the threshold is solved over four registers per lane; if there are more than the list
-  // holds, it is solved over all KZ registers.
-  int n_c = 0;
-#pragma unroll
-  for (int i = 0; i < KZ; ++i) {
-    const bool in = u[i] > lo_u;
-    const uint64_t mk = __ballot(in);
-    const int r = n_c + __popcll(mk & lt);
-    if (in && r < kWaveRowList) { l_p[wv][r] = u[i]; l_pos[wv][r] = i * 64 + lane; }
-    n_c += __popcll(mk);
-  }
-  const bool short_list = n_c <= kWaveRowList;               // wave-uniform
-  float uu[kWaveRowList / 64]; int pp[kWaveRowList / 64];
-  if (short_list) {
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < kWaveRowList / 64; ++k) {
-      const int e = lane + 64 * k;
-      uu[k] = e < n_c ? l_p[wv][e] : -INFINITY;
-      pp[k] = e < n_c ? l_pos[wv][e] : 0;
-    }
-    __builtin_amdgcn_wave_barrier();
-    tau_u = solve_tau_regs(uu, lo_u, seed_z - zmax, beta, ibeta, supp, evals);
-  } else {
-    tau_u = solve_tau_core([&](float t, float& F, float& D, int& cnt) {
-      float f = 0.f, d = 0.f; int c = 0;
-#pragma unroll
-      for (int i = 0; i < KZ; ++i) {
-        const float x = u[i] - t;
-        if (x > 0.f) { f += pow_beta(x, beta, ibeta); d += pow_beta_m1(x, beta, ibeta); ++c; }
-      }
-      F = wave_sum(f); D = beta * wave_sum(d); cnt = wave_sum_i(c);
-    }, lo_u, seed_z - zmax, ibeta, supp, evals);
-  }
-
-  // weighted value sum: the support in candidate order through the LDS list; 4 row slots x 16 lanes gather it
-  const int rs = lane >> 4, c = lane & 15;
-  float acc[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  int32_t* tok_dst = A.ex.support_tokens != nullptr ? A.ex.support_tokens + (size_t)bh * A.ex.support_cap : nullptr;
-  // the support in candidate order, kWaveRowList tokens per pass (normally one pass): entry of rank r goes to
-  // slot r - w0 of the list (the unrolled loop over the registers has no gather inside, so the code stays small)
-  for (int w0 = 0; w0 < supp; w0 += kWaveRowList) {
-    int run = 0;
-    if (short_list) {                                        // one pass: the support is a subset of the list
-#pragma unroll
-      for (int k = 0; k < kWaveRowList / 64; ++k) {
-        const float x = uu[k] - tau_u;
-        const bool in = x > 0.f;
-        const uint64_t mk = __ballot(in);
-        const int r = run + __popcll(mk & lt);
-        if (in) { l_p[wv][r] = pow_beta(x, beta, ibeta); l_pos[wv][r] = pp[k]; }
-        run += __popcll(mk);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < KZ; ++i) {
-        const float x = u[i] - tau_u;
-        const bool in = x > 0.f;
-        const uint64_t mk = __ballot(in);
-        const int r = run + __popcll(mk & lt) - w0;
-        if (in && r >= 0 && r < kWaveRowList) { l_p[wv][r] = pow_beta(x, beta, ibeta); l_pos[wv][r] = i * 64 + lane; }
-        run += __popcll(mk);
-      }
-    }
-    const int n_list = min(supp - w0, kWaveRowList);
-    __builtin_amdgcn_wave_barrier();
-    {
-      // V rows of the listed tokens: page list -> block table, all lookups of the pass in flight together
-      uint32_t rw[kWaveRowList / 64];
-#pragma unroll
-      for (int j = 0; j < kWaveRowList / 64; ++j)
-        rw[j] = v_row_of<false>(A, b, lrow, hkv, l_pos[wv][min(lane + 64 * j, n_list - 1)]);
-#pragma unroll
-      for (int j = 0; j < kWaveRowList / 64; ++j)
-        if (lane + 64 * j < n_list) l_row[wv][lane + 64 * j] = rw[j];
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int e0 = 0; e0 < n_list; e0 += 32) {
-      Raw8<T> vr[8]; float pw[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = e0 + 4 * j + rs;
-        const int ec = min(e, n_list - 1);                   // clamped: loads stay unconditional
-        pw[j] = e < n_list ? l_p[wv][ec] : 0.f;
-        load_raw8(v_pool + (size_t)l_row[wv][ec] * kD + 8 * c, vr[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float vv[8];
-        widen8(vr[j], vv);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
-      }
-    }
-    if (tok_dst != nullptr) {
-      for (int e = lane; e < n_list && w0 + e < A.ex.support_cap; e += 64)
-        tok_dst[w0 + e] = token_of<false>(A, lrow, l_pos[wv][e]);
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    acc[i] += __shfl_xor(acc[i], 16);
-    acc[i] += __shfl_xor(acc[i], 32);
-  }
-  if (lane < 16) {
-    *reinterpret_cast<float4*>(out + 8 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    *reinterpret_cast<float4*>(out + 8 * c + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
-  }
-  if (lane == 0) {
-    A.tau_out[bh] = tau_u + zmax; A.supp_out[bh] = supp;
-    if (A.ex.solve_evals != nullptr) A.ex.solve_evals[bh] = evals;
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
 // Wavefronts of a pass-1 launch: enough to fill every compute unit several times over, never more than the
@@ -2135,8 +2118,18 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 
 // Pass 2: one workgroup per row, as many wavefronts and as much LDS as the number of rows leaves it.  LDS decides how flat a
 // row may be before its candidates go through the workspace, and how many rows share a compute unit.
+// One wavefront per row beyond two rows per compute unit, where a row has at most kOneGroups groups.  Whole grouped calls, us,
+// four wavefronts against one: 2048 rows of 512 of 1024 tokens 35.1 / 23.6, of 1024 tokens with a support of 700 107 / 97.5,
+// of 256 tokens, nearly all of them support, 49 / 30; 512 rows of 1024 tokens, support 700, 39.8 / 68, 288 rows 28 / 47.
+// Only nearly full supports of 512-token lists are slower than in the kernel that solved from zmax - 1 with all scores in
+// registers and agreed with the per-head decode to rounding only (2048 rows, support 440: 54.7 -> 58.3); peaked rows gain 20 %.
 template <typename T, bool DENSE>
 static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStream_t st) {
+  if constexpr (!DENSE)
+    if (rows > 2 * device_compute_units() && n_chunks_max <= kOneGroups) {
+      hipLaunchKernelGGL((decode_solve_one_kernel<T>), dim3(rows), dim3(64), 0, st, so);
+      return;
+    }
   if (rows <= device_compute_units() || n_chunks_max > SolveSharedTwo::kMaxGroups)
     hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveShared>), dim3(rows), dim3(64 * SolveShared::kWaves), 0, st, so);
   else if (n_chunks_max <= SolveSharedMany::kMaxGroups)
@@ -2264,19 +2257,6 @@ void launch_decode(const Dims& dm, bool dense, bool grouped, const void* q, cons
     if (ws.fcount != nullptr) {
       hipLaunchKernelGGL((filter_level_kernel<false>), dim3(dm.B * dm.Hq), fblock, 0, st, fa);
       hipLaunchKernelGGL((filter_compact_kernel<false>), fgrid, fblock, 0, st, fa);
-    }
-    const long long max_cand = (long long)dm.cap * dm.P;
-    if (ws.fcount == nullptr && max_cand <= 2048 && rows > kWaveRowsMin) {
-      // many short rows: one wavefront per row
-      dim3 wgrid((rows + 3) / 4), wblock(256);
-      if (dm.dtype == EKV_F32) {
-        if (max_cand <= 1024) hipLaunchKernelGGL((decode_solve_wave_kernel<float, 16>), wgrid, wblock, 0, st, so, rows);
-        else hipLaunchKernelGGL((decode_solve_wave_kernel<float, 32>), wgrid, wblock, 0, st, so, rows);
-      } else {
-        if (max_cand <= 1024) hipLaunchKernelGGL((decode_solve_wave_kernel<bf16_t, 16>), wgrid, wblock, 0, st, so, rows);
-        else hipLaunchKernelGGL((decode_solve_wave_kernel<bf16_t, 32>), wgrid, wblock, 0, st, so, rows);
-      }
-      return;
     }
     if (dm.dtype == EKV_F32) launch_solve<float, false>(rows, ws.n_chunks_max, so, st);
     else launch_solve<bf16_t, false>(rows, ws.n_chunks_max, so, st);

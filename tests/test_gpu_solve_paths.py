@@ -139,6 +139,61 @@ def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
         check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), toks[b, h], ref, boundary_expected=True)
 
 
+# batch, query heads, KV heads, page, dtype, pages per list: more rows than compute units, to twice as many and beyond,
+# lists of up to 1024 and 2048 tokens, groups of 64, 60, 48 and 36 tokens
+GROUPED = [(9, 64, 8, 16, "bf16", 64), (9, 64, 8, 16, "bf16", 128), (9, 32, 8, 12, "bf16", 170), (9, 64, 8, 24, "bf16", 85),
+           (9, 64, 16, 36, "f32", 56), (17, 32, 8, 64, "bf16", 32), (1, 32, 8, 16, "bf16", 128), (5, 32, 8, 16, "bf16", 256)]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,page,dtype,k", GROUPED)
+@pytest.mark.parametrize("scale", [1.0, 0.3, 0.05])
+def test_group_lists_and_the_same_lists_per_head_agree_bit_for_bit(batch, hq, hkv, page, dtype, k, scale):
+    """A list per KV head gives every head of the group what the same list gives it as its own, side outputs included,
+    however many rows the call has and however flat they are."""
+    n_pages = 2 * k + 3
+    w = synth.Workload("grouped", batch, hq, hkv, 128, n_pages * page, page, dtype, scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(w, 21 + k, device="cuda")
+    inp["seq_lens"] = inp["seq_lens"] - torch.arange(batch, dtype=torch.int32, device="cuda") * 3
+    rng = np.random.default_rng(k)
+    lens = rng.integers(1, k + 1, size=(batch, hkv))
+    lens[0, 0], lens[0, 1], lens[-1, -1] = k, 0, max(1, k - 1)
+    lists = np.zeros((batch, hkv, k), dtype=np.int32)
+    for b in range(batch):
+        for h in range(hkv):
+            lists[b, h, :lens[b, h]] = np.sort(rng.choice(n_pages - 1, lens[b, h], replace=False))
+    lists, counts = torch.from_numpy(lists).cuda(), torch.from_numpy(lens.astype(np.int32)).cuda()
+    st = DeviceState(w, inp, cap=k)
+    ws = st.workspace(ekv.EKV_OP_DECODE_SPARSE)
+    g = hq // hkv
+    got = []
+    for decode, idx, n in ((ekv.ekv_decode_sparse_group, lists, counts),
+                           (ekv.ekv_decode_sparse, lists.repeat_interleave(g, 1).contiguous(), counts.repeat_interleave(g, 1).contiguous())):
+        toks = torch.full((batch, hq, 2 * page * k), -1, device="cuda", dtype=torch.int32)
+        mass, cnt, evals = torch.zeros_like(st.tau), torch.zeros_like(st.supp), torch.zeros_like(st.supp)
+        decode(st.cfg, st.inp["q"], st.cache(), idx, n, st.out, st.tau, st.supp, ws,
+               extras=ekv.decode_extras(support_tokens=toks, solve_evals=evals))
+        plain = [x.clone() for x in (st.out, st.tau, st.supp, toks, evals)]
+        decode(st.cfg, st.inp["q"], st.cache(), idx, n, st.out, st.tau, st.supp, ws,
+               extras=ekv.decode_extras(tau_ref=plain[1] - 0.01, kept_mass_ref=mass, kept_supp_ref=cnt, tau_seed=plain[1] - 0.001))
+        got.append(plain + [x.clone() for x in (st.out, st.tau, st.supp, mass, cnt)])
+    torch.cuda.synchronize()
+    names = ("out", "tau", "support size", "support", "evaluations", "seeded out", "seeded tau", "seeded support size", "mass", "count")
+    assert not [n for n, a, b in zip(names, *got) if not torch.equal(a.view(torch.uint8), b.view(torch.uint8))]
+    out, tau, supp, toks, _, out2, tau2, supp2, mass, cnt = [x.cpu().numpy() for x in got[0]]
+    assert not out[0, g].any() and np.isposinf(tau[0, g]) and supp[0, g] == 0
+    inp = {key: x.cpu() for key, x in inp.items()}
+    for b, h in ((0, 0), (batch - 1, hq - 1)):
+        q, K, V = unit_kv(inp, w, b, h)
+        tok = orc.pages_to_tokens(lists[b, h // g, :lens[b, h // g]].cpu().numpy(), page, K.shape[0])
+        ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale, tok)
+        check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), toks[b, h], ref, boundary_expected=True)
+        check_decode_unit(w, out2[b, h], float(tau2[b, h]), int(supp2[b, h]), None, ref, boundary_expected=True)
+        z = (w.alpha - 1.0) * ref["s"]
+        over = np.clip(z - float(np.float32(tau[b, h]) - np.float32(0.01)), 0, None)
+        assert abs(float(mass[b, h]) - (over ** 2).sum()) < 1e-4
+        assert abs(int(cnt[b, h]) - int((over > 0).sum())) <= int((np.abs(z - tau[b, h] + 0.01) < 4e-6).sum())
+
+
 @pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (16384, 16, 1.0), (16384, 32, 0.05),
                                                (16385, 16, 1.0), (1024 * 64, 64, 1.0), (20000, 32, 0.03),
                                                (1024 * 64 + 80, 16, 1.0), (1024 * 64 + 80, 16, 0.1), (70000, 12, 0.04)])
