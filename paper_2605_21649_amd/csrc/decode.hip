@@ -2095,8 +2095,15 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
   if (wgs > wg_cap) wgs = wg_cap;
   if (wgs < 1) wgs = 1;
   const bool pre_global = sa.U > kUnitsLdsMax;
-  sa.parts = MODE == kPerHead && dm.G > 1 && !pre_global ? kXcds : 1;
-  if (sa.parts > 1) wgs = (wgs + kXcds - 1) / kXcds * kXcds;
+  // Lists are split over the XCDs as long as a wavefront's range is not longer than one and a half parts.  Where it spans
+  // more, it takes the same part of the heads of a group one after the other, hundreds of megabytes of other reads apart, and
+  // the pages they share are fetched again; unsplit, the heads meet in the cache all XCDs share.  Score pass, us, unsplit /
+  // split, for heads that select the same, half the same and hardly the same pages (a tenth of a sequence):
+  //   1024 units 246 / 125, 261 / 186, 253 / 231    1056 units 128 / 90, 129 / 121, 145 / 147    1536 units 390 / 360, 393 / 374, 422 / 433
+  //   2048 units 501 / 453, 486 / 525, 606 / 583    4096 units 647 / 1204, 875 / 1202, 932 / 1261
+  const bool split = MODE == kPerHead && dm.G > 1 && !pre_global && 3 * wgs * kScoreWaves >= 2ll * kXcds * sa.U;
+  sa.parts = split ? kXcds : 1;
+  if (split) wgs = (wgs + kXcds - 1) / kXcds * kXcds;
   dim3 grid((unsigned)wgs), block(kScoreThreads);
   const size_t lds = pre_global ? 0 : (size_t)(sa.U + 1) * sizeof(int);
   if (pre_global) {

@@ -142,7 +142,9 @@ def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
 # batch, query heads, KV heads, page, dtype, pages per list: more rows than compute units, to twice as many and beyond,
 # lists of up to 1024 and 2048 tokens, groups of 64, 60, 48 and 36 tokens
 GROUPED = [(9, 64, 8, 16, "bf16", 64), (9, 64, 8, 16, "bf16", 128), (9, 32, 8, 12, "bf16", 170), (9, 64, 8, 24, "bf16", 85),
-           (9, 64, 16, 36, "f32", 56), (17, 32, 8, 64, "bf16", 32), (1, 32, 8, 16, "bf16", 128), (5, 32, 8, 16, "bf16", 256)]
+           (9, 64, 16, 36, "f32", 56), (17, 32, 8, 64, "bf16", 32), (1, 32, 8, 16, "bf16", 128), (5, 32, 8, 16, "bf16", 256),
+           # lists beyond the one launch: the last number of units that is split over the XCDs, and the next
+           (12, 128, 16, 16, "bf16", 136), (25, 64, 8, 16, "bf16", 136), (25, 64, 8, 8, "f32", 260)]
 
 
 @pytest.mark.parametrize("batch,hq,hkv,page,dtype,k", GROUPED)
