@@ -559,7 +559,6 @@ struct SolveSharedT {
   int flags[64];
   float zmax, bound;              // row maximum, certified lower bound of tau relative to it
   int n_pass;
-  int kept[kSegs];                // entries of a segment that overflowed
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
 // Rows up to one per compute unit, or of any length; more rows than that, two to a compute unit; many rows of at most
@@ -1052,17 +1051,17 @@ __device__ __forceinline__ void bound_groups(Max&& group_max, int n_chunks, floa
   if (threadIdx.x == 0) { sh.zmax = zmax; sh.bound = t; sh.n_pass = n_pass; }
 }
 
-// Scores of the listed groups above thr -> segment s (z - zmax, position), in candidate order: it takes n_pass / kSegs
-// consecutive groups.  Sixteen lanes read the (at most 64) scores of a group with one 16-byte load
+// Scores of the listed groups above thr of segment s, in candidate order: put(i, z, position) for its i-th one.  Segment s
+// takes n_pass / kSegs consecutive groups.  Sixteen lanes read the (at most 64) scores of a group with one 16-byte load
 // each, so a load takes four groups and the usual row needs one; the lanes' order, and within a lane the four scores',
-// is candidate order.  Returns how many there are, also when they are more than the segment holds.
-template <typename SH>
-__device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int s, int n_pass, float zmax, float thr, SH& sh) {
+// is candidate order.  Returns how many there are.
+template <typename SH, typename Put>
+__device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr, int s, int n_pass, float thr, const SH& sh,
+                                                Put&& put) {
   const int lane = threadIdx.x & 63;
   const int per = (n_pass + kSegs - 1) / kSegs;
   const int j0 = s * per, j1 = min(j0 + per, n_pass);
   if (j0 >= j1) return 0;                                             // wave-uniform
-  uint2* seg = sh.seg + s * SH::kSegCap;
   const int sub = lane >> 4, in_group = 4 * (lane & 15);
   int cnt = 0;
   // tokens per group and per row are multiples of 4: a lane's four scores are valid together
@@ -1082,19 +1081,14 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, o));
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2, o));
     o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3, o));
-    const int before = cnt;
     cnt += __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
-    if constexpr (SH::kOverflows)
-      if (cnt > SH::kSegCap && before <= SH::kSegCap && lane == 0) sh.kept[s] = before;
-    if (cnt <= SH::kSegCap) {                                             // wave-uniform
-      if (i0) seg[o] = make_uint2(__float_as_uint(v.x - zmax), (uint32_t)p);
-      o += i0;
-      if (i1) seg[o] = make_uint2(__float_as_uint(v.y - zmax), (uint32_t)p + 1);
-      o += i1;
-      if (i2) seg[o] = make_uint2(__float_as_uint(v.z - zmax), (uint32_t)p + 2);
-      o += i2;
-      if (i3) seg[o] = make_uint2(__float_as_uint(v.w - zmax), (uint32_t)p + 3);
-    }
+    if (i0) put(o, v.x, p);
+    o += i0;
+    if (i1) put(o, v.y, p + 1);
+    o += i1;
+    if (i2) put(o, v.z, p + 2);
+    o += i2;
+    if (i3) put(o, v.w, p + 3);
   };
   if (j1 - j0 <= 4) {
     int p; float4 v;
@@ -1408,7 +1402,10 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
     } else {
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
-        const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax, zmax + bound, sh);
+        uint2* seg = sh.seg + (w * SPW + i) * SH::kSegCap;
+        const int n = fetch_candidates(R, zr, w * SPW + i, n_pass, zmax + bound, sh, [&](int o, float z, int p) {
+          if (!SH::kOverflows || o < SH::kSegCap) seg[o] = make_uint2(__float_as_uint(z - zmax), (uint32_t)p);
+        });
         if (lane == 0) sh.wcount[1][w * SPW + i] = n;
       }
     }
@@ -1426,9 +1423,7 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
       float u[SPW * KR];
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
-        const int n = uniform(sh.wcount[1][w * SPW + i]);
-        // a batch that found no room was counted but not written: only whole batches before it are entries
-        const int kept = n > SH::kSegCap ? sh.kept[w * SPW + i] : n;
+        const int kept = min(uniform(sh.wcount[1][w * SPW + i]), SH::kSegCap);
 #pragma unroll
         for (int k = 0; k < KR; ++k)
           u[i * KR + k] = lane + 64 * k < kept ? __uint_as_float(sh.seg[(w * SPW + i) * SH::kSegCap + lane + 64 * k].x) : -INFINITY;
@@ -1441,7 +1436,9 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
         f = sum_waves<SH::kWaves>(&sh.red[parity][0][0], 3); d = sum_waves<SH::kWaves>(&sh.red[parity][0][1], 3);
         parity ^= 1;
       });
-      bound = fmaxf(bound, t - 4e-6f * fmaxf(1.f, fabsf(zmax)));
+      const float tighter = t - 4e-6f * fmaxf(1.f, fabsf(zmax));
+      if (!(tighter > bound)) return false;                           // the same for all threads
+      bound = tighter;
       if (threadIdx.x == 0) sh.bound = bound;
       __syncthreads();                                                // the segments are read
     }
@@ -1634,71 +1631,27 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
     __syncthreads();
   }
   if (pre) {
-    // the groups above the bound are listed already (sh.glist)
-    const uint16_t* glist = sh.glist;
+    // The row outgrew its segments.  Their lengths are known (sh.wcount[1], from the last fetch against this bound), so every
+    // wavefront fetches its segments once more to their places in one list: in LDS if it fits, else in the row's overflow
+    // list.  (In rounds of 16 groups per wavefront with an exchange of the counts each, a million-token row with a support of
+    // 35 000 took 1220 us a call.)
+    constexpr int SPW = kSegs / NW;
     const int n_pass = uniform(sh.n_pass);
-    // wavefront w of a round owns `per` consecutive list entries: (round, w, load, lane) is candidate order
-    constexpr int kRoundGroups = NW * kRoundLoads;
-    // second half of a round: mask, count, exchange the counts (one barrier), ordered compaction into the list
-    auto compact_round = [&](int j0, float (&v)[kRoundLoads], const int (&vpos)[kRoundLoads]) {
-      const int rem = min(n_pass - j0, kRoundGroups);
-      const int per = (rem + NW - 1) / NW;
-      const int jw = j0 + w * per, jend = j0 + rem;
-      int c = 0;
+    int inc = lane < kSegs ? sh.wcount[1][lane] : 0;
 #pragma unroll
-      for (int i = 0; i < kRoundLoads; ++i) {
-        const bool ok = i < per && jw + i < jend && lane < chunk_tokens && vpos[i] < n_cand;
-        v[i] = ok ? v[i] : -INFINITY;
-        c += __popcll(__ballot(v[i] > thr));
+    for (int d = 1; d < kSegs; d <<= 1) { const int t = __shfl_up(inc, d); if (lane >= d) inc += t; }
+    n_list = __builtin_amdgcn_readlane(inc, kSegs - 1);
+    in_lds = n_list <= LIST;
+    in_spill = !in_lds && su != nullptr && n_list <= A.spill_cap;
+    auto fill = [&](float* du, int32_t* dp) {
+#pragma unroll 1
+      for (int i = 0; i < SPW; ++i) {
+        const int s = w * SPW + i, off = s > 0 ? __shfl(inc, s - 1) : 0;
+        fetch_candidates(R, zr, s, n_pass, thr, sh, [&](int o, float z, int p) { du[off + o] = z - zmax; dp[off + o] = p; });
       }
-      if (lane == 0) sh.wcount[parity][w] = c;
-      __syncthreads();
-      int off = n_list, tot = 0;
-      for (int i = 0; i < NW; ++i) { const int ci = sh.wcount[parity][i]; if (i < w) off += ci; tot += ci; }
-      n_list += tot;
-      parity ^= 1;
-      if (__builtin_expect(in_lds && n_list > LIST, 0)) {
-        // The list outgrows LDS: it continues in the row's overflow list, to which the entries of the earlier rounds
-        // move first (the barrier above ordered their LDS writes).
-        in_lds = false;
-        if (su != nullptr) {
-          in_spill = true;
-          for (int e = tid; e < n_list - tot; e += NT) { su[e] = sh.list_u[e]; sp[e] = sh.list_pos[e]; }
-        }
-      }
-      if (in_spill && n_list > A.spill_cap) in_spill = false;
-      auto emit = [&](auto* du, auto* dp) {
-#pragma unroll
-        for (int i = 0; i < kRoundLoads; ++i) {
-          const bool in = v[i] > thr;
-          const uint64_t mk = __ballot(in);
-          if (in) {
-            const int o = off + __popcll(mk & lt);
-            du[o] = v[i] - zmax;
-            dp[o] = vpos[i];
-          }
-          off += __popcll(mk);
-        }
-      };
-      if (__builtin_expect(in_lds, 1)) emit(sh.list_u, sh.list_pos);
-      else if (in_spill) emit(su, sp);
     };
-    for (int j0 = 0; j0 < n_pass; j0 += kRoundGroups) {     // one round in the usual case
-      const int rem = min(n_pass - j0, kRoundGroups);
-      const int per = (rem + NW - 1) / NW;
-      const int jw = j0 + w * per;
-      float v[kRoundLoads]; int vpos[kRoundLoads];
-#pragma unroll
-      for (int i = 0; i < kRoundLoads; ++i) {
-        v[i] = -INFINITY; vpos[i] = 0;
-        if (i < per) {                                   // wave-uniform
-          const int g = glist[min(jw + i, n_pass - 1)];
-          vpos[i] = g * chunk_tokens + lane;
-          v[i] = zr[min(vpos[i], n_cand - 1)];
-        }
-      }
-      compact_round(j0, v, vpos);
-    }
+    if (in_lds) fill(sh.list_u, sh.list_pos);
+    else if (in_spill) fill(su, sp);
     if (in_lds || in_spill) lo_u = fminf(thr - zmax, -1e-7f);
   }
   if constexpr (kLong) for (int pass = 0; pass < 3 && !prefilled && !pre; ++pass) {
