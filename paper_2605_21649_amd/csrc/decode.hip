@@ -561,15 +561,12 @@ struct SolveSharedT {
   int n_pass;
 };
 static_assert(kPreGroups <= 65536, "group numbers are 16 bits wide");
-// Rows up to one per compute unit, or of any length; more rows than that, two to a compute unit; many rows of at most
-// 256 groups, whose usual solve is one wavefront's work and whose flattest has few candidates (with 1024 groups allowed,
-// 384 flat rows of 64K tokens outgrew the small segments: 485 -> 519 us).  Sixteen maxima per thread take a row of a million
-// tokens from its group maxima in one launch; until there were four, such rows went through the filter passes first
-// (filter 8 + 9, solve 12 us, and two more launches).
+// One row per compute unit: sixteen wavefronts and most of the LDS, rows of any length.  Sixteen maxima per thread take a row
+// of a million tokens from its group maxima in one launch.
 using SolveShared = SolveSharedT<kSolveWaves, 768, kListCap, kPreGroups>;
-using SolveSharedTwo = SolveSharedT<kSolveWaves, 320, kListCap, 4 * kWaveGroups>;
-// 192 entries per segment take all of a row of up to 2048 tokens whatever the page size (180 in groups of 60), so that such a
-// row's result is that of its one-launch decode to the last bit however flat it is.
+// Four rows per compute unit (registers allow 16 wavefronts, LDS four times 34 KB): many short rows, whose usual solve is
+// one wavefront's work.  192 entries per segment take all of a row of up to 2048 tokens whatever the page size (180 in
+// groups of 60), so that such a row's result is that of its one-launch decode to the last bit however flat it is.
 using SolveSharedMany = SolveSharedT<4, 192, 2048, kWaveGroups / 4>;
 constexpr int kOneGroups = kSegs;           // a row of at most this many groups has one in each segment
 
@@ -1478,7 +1475,7 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
     }
   } else if constexpr (SH::kMaxGroups > kWaveGroups) {
     constexpr int kThreads = 64 * SH::kWaves;
-    if (SH::kMaxGroups == 4 * kThreads || R.n_chunks <= 4 * kThreads)
+    if (R.n_chunks <= 4 * kThreads)
       bound_groups<4, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
     else
       bound_groups<SH::kMaxGroups / kThreads, false>(group_max, R.n_chunks, A.beta, A.ibeta, sh);
@@ -2076,8 +2073,11 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
 #undef EKV_SCORES
 }
 
-// Pass 2: one workgroup per row, as many wavefronts and as much LDS as the number of rows leaves it.  LDS decides how flat a
-// row may be before its candidates go through the workspace, and how many rows share a compute unit.
+// Pass 2: one workgroup per row; four wavefronts, and four rows to a compute unit, for many short rows.  A flat row outgrows
+// their smaller LDS lists sooner and has a quarter of the wavefronts for its values, which shows while the compute units
+// hold all rows at once.  Dense calls, us, support 40 / 2100 / 11 000 of 16K tokens (256 groups): 512 rows by sixteen
+// wavefronts 130 / 189 / 378, by four 125 / 219 / 429, by the solve before the segments 135 / 247 / 411; 2048 rows 512 / 911 /
+// 1557 before, by four 467 / 717 / 1474.  12 000 tokens (188 groups), 288 rows: 70 / 154 / 254 before, by four 59 / 151 / 252.
 // One wavefront per row beyond two rows per compute unit, where a row has at most kOneGroups groups.  Whole grouped calls, us,
 // four wavefronts against one: 2048 rows of 512 of 1024 tokens 35.1 / 23.6, of 1024 tokens with a support of 700 107 / 97.5,
 // of 256 tokens, nearly all of them support, 49 / 30; 512 rows of 1024 tokens, support 700, 39.8 / 68, 288 rows 28 / 47.
@@ -2090,12 +2090,11 @@ static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStr
       hipLaunchKernelGGL((decode_solve_one_kernel<T>), dim3(rows), dim3(64), 0, st, so);
       return;
     }
-  if (rows <= device_compute_units() || n_chunks_max > SolveSharedTwo::kMaxGroups)
-    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveShared>), dim3(rows), dim3(64 * SolveShared::kWaves), 0, st, so);
-  else if (n_chunks_max <= SolveSharedMany::kMaxGroups)
+  const int cus = device_compute_units();
+  if (rows > cus && n_chunks_max <= (rows > 2 * cus ? SolveSharedMany::kMaxGroups : SolveSharedMany::kMaxGroups / 4 * 3))
     hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveSharedMany>), dim3(rows), dim3(64 * SolveSharedMany::kWaves), 0, st, so);
   else
-    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveSharedTwo>), dim3(rows), dim3(64 * SolveSharedTwo::kWaves), 0, st, so);
+    hipLaunchKernelGGL((decode_solve_kernel<T, DENSE, SolveShared>), dim3(rows), dim3(64 * SolveShared::kWaves), 0, st, so);
 }
 
 // Short per-head lists, one workgroup each: sixteen wavefronts as long as every list has a compute unit to itself (the

@@ -196,13 +196,15 @@ def test_group_lists_and_the_same_lists_per_head_agree_bit_for_bit(batch, hq, hk
         assert abs(int(cnt[b, h]) - int((over > 0).sum())) <= int((np.abs(z - tau[b, h] + 0.01) < 4e-6).sum())
 
 
-@pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (16384, 16, 1.0), (16384, 32, 0.05),
+@pytest.mark.parametrize("tokens,page,scale", [(4000, 16, 1.0), (4000, 16, 0.05), (192 * 64, 16, 0.05), (192 * 64 + 1, 16, 0.05),
+                                               (16384, 16, 1.0), (16384, 32, 0.05),
                                                (16385, 16, 1.0), (1024 * 64, 64, 1.0), (20000, 32, 0.03),
                                                (1024 * 64 + 80, 16, 1.0), (1024 * 64 + 80, 16, 0.1), (70000, 12, 0.04)])
 def test_more_rows_than_compute_units(tokens, page, scale):
-    """288 rows (36 sequences over one shared set of pages, every length different): up to 256 groups a row is solved by
-    four wavefronts, beyond by sixteen with two rows to a compute unit, and rows too flat for their LDS lists continue in
-    the workspace.  Sampled rows against the oracle; dense and the same pages as lists agree bit for bit."""
+    """288 rows (36 sequences over one shared set of pages, every length different): up to 192 groups a row is solved by
+    four wavefronts, beyond by sixteen, and rows too flat for their LDS lists continue in the workspace.  Sampled rows against the oracle;
+    dense and the same pages as lists agree bit for bit, and rows whose candidates fit all variants' segments with the same
+    sequence decoded alone."""
     B, Hq = 36, 8
     one = synth.Workload("rows", 1, Hq, 1, 128, tokens, page, "bf16", scale=scale / math.sqrt(128.0))
     inp = synth.make_inputs(one, 3 + tokens, device="cpu")
@@ -229,6 +231,13 @@ def test_more_rows_than_compute_units(tokens, page, scale):
         ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
         check_decode_unit(w, st.out[b, h].cpu().numpy(), float(st.tau[b, h]), int(st.supp[b, h]), toks[b, h].cpu().numpy(),
                           ref, boundary_expected=True)
+    if scale == 1.0:
+        alone = DeviceState(one, dict(inp, q=inp["q"][17:18], block_table=inp["block_table"][17:18], seq_lens=inp["seq_lens"][17:18]))
+        ekv.ekv_decode_full(alone.cfg, alone.inp["q"], alone.cache(), alone.out, alone.tau, alone.supp,
+                            alone.workspace(ekv.EKV_OP_DECODE_FULL))
+        torch.cuda.synchronize()
+        for a, b in zip((alone.out, alone.tau, alone.supp), (st.out, st.tau, st.supp)):
+            assert torch.equal(a[0].view(torch.uint8), b[17].view(torch.uint8))
 
 
 @pytest.mark.parametrize("tokens,scale", [(4096 * 64 + 1, 1.0), (16384 * 64 - 30, 1.0), (16384 * 64 + 1, 1.0), (16384 * 64 + 1, 0.05)])
