@@ -2098,17 +2098,21 @@ static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStr
 }
 
 // Short per-head lists, one workgroup each: sixteen wavefronts as long as every list has a compute unit to itself (the
-// length of one list is what the call takes), else four, and eight lists share a compute unit.
-// Whole top-k steps, two launches against one, us: 32 lists of 656 tokens 29 / 25.5, of 2000 tokens 32.3 / 33.4, of 3686
-// tokens 32 / 35.6; 128 lists of 2048 tokens 55 / 51.8, of 3686 tokens 45.5 / 38.9; 256 lists of 3686 tokens 63.6 / 55.5;
-// 2048 lists of 176 tokens 70 / 58.3.  With few lists most compute units idle in the one launch: the line is drawn at
-// 512 KB of K per list there (the capacity is what the host knows; lists are rarely full), at 1 MB otherwise.
+// length of one list is what the call takes), else four, and three to six lists share a compute unit.
+// One compute unit reads K at about 75 GB/s, so the line follows the bytes of a list; the host knows its capacity only, and
+// a full list near the line would be faster in two launches, a half full one is faster in one.  Decode calls on K that is in
+// no cache, us, two launches / one, half full and full:
+//   bf16   32 lists of 1024 tokens 13.8 / 10.2, 14.1 / 12.0, of 2048 14.0 / 12.0, 14.2 / 15.6    128 of 4096 19.5 / 17.2, 25.8 / 28.5
+//          192 of 4096 22.0 / 21.2, 32.4 / 35.5    256 of 3072 22.8 / 21.4, 32.5 / 35.8, of 4096 25.6 / 25.5, 38.1 / 45.0
+//          512 of 2048 28.5 / 26.8, 39.7 / 45.8    2048 of 2048 106 / 86, 184 / 156
+//   f32    64 lists of 1024 tokens 19.2 / 12.6, 20.3 / 16.4    256 of 2048 28.3 / 26.4, 43.3 / 44.7    2048 of 2048 183 / 155, 332 / 304
+// (256 full lists of 4096 tokens: 42.2 before there was the one launch; hence the shorter limit beyond 192 lists.)
 static bool rows_in_one_launch(const Dims& dm) {
   const int cus = device_compute_units(), rows = dm.B * dm.Hq;
   const long long tokens = (long long)dm.cap * dm.P;
   if (rows > cus) return tokens <= kRowTokensMany;
   const long long bytes = tokens * kD * (dm.dtype == EKV_F32 ? 4 : 2);
-  return tokens <= kRowTokens && bytes <= (rows <= cus / 4 ? 512 << 10 : 1 << 20);
+  return tokens <= (rows <= cus / 4 * 3 ? kRowTokens : kRowTokens / 4 * 3) && bytes <= (rows <= cus / 4 ? 512 << 10 : 1 << 20);
 }
 template <typename T, int PT>
 static void launch_rows_T(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {

@@ -95,7 +95,8 @@ def test_solve_side_outputs_of_short_and_flat_rows(lens):
 # sixteen wavefronts, of four, and the two-launch path just beyond), page sizes of both score paths
 LISTS = [(1, 4, 2, 16, "bf16", 128), (1, 4, 2, 16, "bf16", 129), (1, 4, 2, 4, "f32", 256), (1, 4, 2, 36, "f32", 28),
          (3, 32, 8, 36, "bf16", 113), (3, 32, 8, 32, "bf16", 128), (3, 32, 8, 64, "bf16", 64), (9, 32, 8, 12, "bf16", 85),
-         (9, 32, 8, 64, "bf16", 32), (9, 32, 8, 16, "bf16", 64), (9, 32, 32, 4, "f32", 512), (9, 32, 8, 16, "f32", 1)]
+         (9, 32, 8, 64, "bf16", 32), (9, 32, 8, 16, "bf16", 64), (9, 32, 32, 4, "f32", 512), (9, 32, 8, 16, "f32", 1),
+         (8, 32, 8, 64, "bf16", 48), (8, 32, 8, 64, "bf16", 49)]
 
 
 @pytest.mark.parametrize("batch,hq,hkv,page,dtype,k", LISTS)
