@@ -675,12 +675,13 @@ __device__ __forceinline__ float solve_tau_core(Eval&& eval, float lo_init, floa
   float tau = (seed > lo && seed < hi) ? seed : lo;
   int pending_cnt = -1;
   int cnt = 0;
-  bool reeval = false;
+  bool last = false;                                         // tau is settled; evaluated once more for its support
   evals = 0;
-  for (int it = 0; it < 64; ++it) {
+  for (int it = 0;; ++it) {                                  // one call of `eval`: it is most of the code of every solve
     float F, D;
     eval(tau, F, D, cnt);
     ++evals;
+    if (last) break;
     if (pending_cnt >= 0 && cnt == pending_cnt) break;       // exact step kept the support: done
     if (fabsf(F - 1.0f) <= 4e-7f) break;                     // float32 resolution of F: tau is the root
     pending_cnt = -1;
@@ -702,13 +703,9 @@ __device__ __forceinline__ float solve_tau_core(Eval&& eval, float lo_init, floa
     float next = tau + step;
     if (next == tau) break;                                  // no representable progress
     if (!(next > lo && next < hi)) { next = 0.5f * (lo + hi); pending_cnt = -1; }
-    if (hi - lo <= 1.2e-7f || (pending_cnt < 0 && fabsf(next - tau) <= 6e-8f)) { tau = next; reeval = true; break; }
+    last = hi - lo <= 1.2e-7f || (pending_cnt < 0 && fabsf(next - tau) <= 6e-8f);
     tau = next;
-  }
-  if (reeval) {                                              // tau moved after the last evaluation
-    float F, D;
-    eval(tau, F, D, cnt);
-    ++evals;
+    if (it == 63 && !last) break;
   }
   supp = cnt;
   return tau;
