@@ -1481,13 +1481,6 @@ __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, c
   return solve_bounded_row<T, DENSE>(A, R, zr, seed_z, block_extras, sh);
 }
 
-template <bool DENSE>
-__device__ __forceinline__ RowRef row_ref(const SolveArgs& A, int bh) {
-  const int b = bh / A.Hq, hq = bh % A.Hq, hkv = hq / (A.Hq / A.Hkv), gp = pmax_pages(A.P);
-  const int lrow = A.grouped ? b * A.Hkv + hkv : bh;        // row of the page list this head reads
-  const int n_slots = clampi(DENSE ? (A.seq_lens[b] + A.P - 1) / A.P : A.n_sel[lrow], 0, DENSE ? A.Mmax : A.cap);
-  return {b, bh, lrow, hkv, n_slots * A.P, gp * A.P, (n_slots + gp - 1) / gp};
-}
 // Side outputs that need a pass over all candidates.
 template <bool DENSE>
 __device__ __forceinline__ bool wants_side_outputs(const SolveArgs& A) {
@@ -1506,9 +1499,12 @@ __device__ __forceinline__ int group_on_one_xcd(int i, int rows, int heads) {
 template <typename T>
 __global__ __launch_bounds__(64) void decode_solve_one_kernel(const SolveArgs A) {
   __shared__ SolveSharedOne sh;
-  const int bh = group_on_one_xcd(blockIdx.x, gridDim.x, A.Hq / A.Hkv);
+  const int heads = A.Hq / A.Hkv, gp = pmax_pages(A.P);
+  const int bh = group_on_one_xcd(blockIdx.x, gridDim.x, heads), b = bh / A.Hq, hkv = (bh - b * A.Hq) / heads;
+  const int lrow = A.grouped ? b * A.Hkv + hkv : bh;
+  const int n_slots = clampi(A.n_sel[lrow], 0, A.cap);
   const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
-  const RowRef R = row_ref<false>(A, bh);
+  const RowRef R{b, bh, lrow, hkv, n_slots * A.P, gp * A.P, (n_slots + gp - 1) / gp};
   solve_row<T, false>(A, R, A.zbuf + (size_t)bh * A.zstride, A.pmax + (size_t)bh * A.n_chunks_max, seed_z,
                       wants_side_outputs<false>(A), sh);
 }
@@ -1519,12 +1515,17 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
   constexpr int NT = 64 * SH::kWaves, NW = SH::kWaves, LIST = SH::kListCap;
   constexpr int kRoundTokens = NT * kRoundLoads;
   constexpr bool kLong = SH::kMaxGroups >= kPreGroups;   // false: the launch has only rows of at most kMaxGroups groups
-  const int bh = blockIdx.x;
+  const int Hq = A.Hq, Hkv = A.Hkv, P = A.P;
+  const int bh = blockIdx.x, b = bh / Hq, hq = bh % Hq, hkv = hq / (Hq / Hkv);
   const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
   const uint64_t lt = (1ull << lane) - 1ull;
   const T* v_pool = (const T*)A.v_pool;
-  const RowRef R = row_ref<DENSE>(A, bh);
-  const int b = R.b, lrow = R.lrow, hkv = R.hkv, n_cand = R.n_cand, n_chunks = R.n_chunks, chunk_tokens = R.chunk_tokens;
+  const int n = A.seq_lens[b];
+  const int lrow = A.grouped ? b * Hkv + hkv : bh;          // row of the page list this head reads
+  const int n_slots = clampi(DENSE ? (n + P - 1) / P : A.n_sel[lrow], 0, DENSE ? A.Mmax : A.cap);
+  const int n_cand = n_slots * P;
+  const int n_chunks = (n_slots + pmax_pages(P) - 1) / pmax_pages(P);
+  const int chunk_tokens = pmax_pages(P) * P;
   const float* zr = A.zbuf + (size_t)bh * A.zstride;
   const float* pm = A.pmax + (size_t)bh * A.n_chunks_max;
   const float beta = A.beta; const int ibeta = A.ibeta;
@@ -1533,6 +1534,7 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
   // warm start (optional): requested with the first loads, used once zmax is known
   const float seed_z = A.ex.tau_seed != nullptr ? A.ex.tau_seed[bh] : NAN;
   const bool block_extras = wants_side_outputs<DENSE>(A);
+  const RowRef R{b, bh, lrow, hkv, n_cand, chunk_tokens, n_chunks};
   float zmax, thr_f = 0.f;
   const bool pre = !kLong || n_chunks <= kPreGroups;
   if (__builtin_expect(pre, 1)) {
