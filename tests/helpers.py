@@ -3,6 +3,8 @@
 The oracle never sees anything produced by the HIP path; where a stage test needs "the same stored
 statistics / scores on both sides", the oracle's values are uploaded to the GPU, never the reverse."""
 import math
+import os
+import re
 import numpy as np
 import torch
 
@@ -10,6 +12,12 @@ from oracle import entmaxkv_oracle as orc
 from paper_2605_21649_amd import binding as ekv
 from paper_2605_21649_amd import synth
 from tests.device_state import DeviceState  # noqa: F401  (re-exported for the tests)
+
+
+def pre_groups():
+    """Groups up to which a row is solved without the filter passes, as the library was compiled."""
+    src = open(os.path.join(os.path.dirname(ekv.__file__), "csrc", "ekv_internal.h")).read()
+    return int(re.search(r"kPreGroups = (\d+)", src).group(1))
 
 
 def to_f64(t):

@@ -41,7 +41,7 @@ def test_workspace_sizes():
     full = ekv.ekv_workspace_bytes(cfg, ekv.EKV_OP_DECODE_FULL)
     # scores: 4 B per candidate token and query head, plus one maximum per 64 tokens; rows that can exceed the
     # solve's 4096-entry list add an overflow list of min(row, 65536) (value, position) entries per head; rows of more
-    # than 262144 tokens add the filter lists (32 KiB per 32768-token slice and head)
+    # than 16384 groups add the filter lists (32 KiB per slice of 512 groups and head): not these of 1048576 tokens
     scores, spill = 32 * 2622 * 16 * 4, 32 * 2622 * 16 * 8
     assert scores + spill <= sparse < 1.1 * scores + spill
     spill = 32 * 65536 * 8

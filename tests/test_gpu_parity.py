@@ -21,7 +21,7 @@ from oracle import entmaxkv_oracle as orc
 from paper_2605_21649_amd import binding as ekv
 from paper_2605_21649_amd import synth
 from tests.helpers import (DeviceState, unit_kv, oracle_stats, storage_ulp, sets_equal_up_to_cut, rel_err,
-                           to_f64, OUT_TOL, check_decode_unit, check_decode_of_gpu_list)
+                           to_f64, OUT_TOL, check_decode_unit, check_decode_of_gpu_list, pre_groups)
 
 pytestmark = pytest.mark.gpu
 
@@ -648,24 +648,22 @@ LONG = [synth.C2.scaled(name="C2-long-bf16", context=100000, ragged=7, n_q_heads
         # filtered lists and falls back to streaming the row from that bound
         synth.C1.scaled(name="C1-long-flat", context=66000, n_planted=0, scale=0.02 / math.sqrt(128.0),
                         n_q_heads=2, n_kv_heads=2),
-        # rows of more than 4096 groups of 64 tokens: these take the multi-workgroup filter passes (the rows above
-        # are solved from the group maxima by one workgroup, two maxima per thread)
-        synth.C2.scaled(name="C2-filter-bf16", context=300000, ragged=11, n_q_heads=4, n_kv_heads=2),
-        synth.C1.scaled(name="C1-filter-f32", context=270000, ragged=3, n_q_heads=2, n_kv_heads=2,
+        # rows of more than 16384 groups: these take the multi-workgroup filter passes (the rows above are solved from
+        # the group maxima by one workgroup); one page of 36, 40 or 48 tokens is a group
+        synth.C2.scaled(name="C2-filter-bf16", context=790000, ragged=11, n_q_heads=2, n_kv_heads=1, page_size=48),
+        synth.C1.scaled(name="C1-filter-f32", context=592000, ragged=3, n_q_heads=2, n_kv_heads=1, page_size=36,
                         scale=1.0 / math.sqrt(128.0)),
-        synth.C1.scaled(name="C1-filter-flat", context=264000, n_planted=0, scale=0.02 / math.sqrt(128.0),
-                        n_q_heads=2, n_kv_heads=2),
-        # moderately flat rows, supports of hundreds to thousands of tokens.  Nearly every 64-token group holds a
-        # candidate, so the solve fetches the groups in many rounds (the next round requested while the current one is
-        # compacted); with a support of ~900 the candidates still fit the LDS list, with ~5000 they continue in the
-        # row's overflow list in the workspace, and the row of 300 000 tokens reaches that list through the filter
+        synth.C1.scaled(name="C1-filter-flat", context=592000, n_planted=0, scale=0.02 / math.sqrt(128.0),
+                        n_q_heads=2, n_kv_heads=1, page_size=36),
+        # moderately flat rows, supports of hundreds to thousands of tokens: the candidates stay in the segments of the
+        # solve or continue in the row's one list, and the row of 660 000 tokens reaches that list through the filter
         # passes' per-slice lists.
         synth.C1.scaled(name="C1-wide-900", context=100000, ragged=5, n_planted=0, scale=0.15 / math.sqrt(128.0),
                         n_q_heads=2, n_kv_heads=2),
         synth.C1.scaled(name="C1-wide-5000", context=100000, ragged=5, n_planted=0, scale=0.05 / math.sqrt(128.0),
                         n_q_heads=2, n_kv_heads=2),
-        synth.C1.scaled(name="C1-filter-wide-6000", context=300000, ragged=9, n_planted=0, scale=0.05 / math.sqrt(128.0),
-                        n_q_heads=2, n_kv_heads=2),
+        synth.C1.scaled(name="C1-filter-wide-6000", context=660000, ragged=9, n_planted=0, scale=0.05 / math.sqrt(128.0),
+                        n_q_heads=2, n_kv_heads=1, page_size=40),
         # the same through the matrix-core score pass: bf16 cache, pages of 32, two query heads per KV head, beta = 4
         synth.C5.scaled(name="C5-wide-a125-6000", batch=1, context=100000, ragged=5, n_planted=0,
                         scale=0.5 / math.sqrt(128.0), n_q_heads=2, n_kv_heads=1, alpha=1.25)]
@@ -673,14 +671,16 @@ LONG = [synth.C2.scaled(name="C2-long-bf16", context=100000, ragged=7, n_q_heads
 
 @pytest.mark.parametrize("w", LONG, ids=[w.name for w in LONG])
 def test_decode_long_rows_take_the_filter_passes(w):
-    """Long rows: up to 4096 groups (262 144 tokens) one workgroup solves them from the group maxima, several per
-    thread; longer ones are pre-filtered by the multi-workgroup passes (dense, and sparse with a large selection).
-    Results must meet the same bars as the short-row path."""
+    """Long rows: up to 16384 groups one workgroup solves them from the group maxima, several per thread; longer ones
+    are pre-filtered by the multi-workgroup passes (dense, and sparse with a large selection).  Results must meet the
+    same bars as the short-row path."""
     inp = get_inputs(w)
     M = w.pages_per_seq
     n = w.context - w.ragged
     n_pages = -(-n // w.page_size)
-    cap = min(M, -(-(263000 if "filter" in w.name else 66000) // w.page_size))   # a selection of that many tokens
+    filtered = "filter" in w.name
+    cap = pre_groups() + 1 if filtered else min(M, -(-66000 // w.page_size))     # pages of a selection
+    assert not filtered or (w.page_size > 32 and cap < M)                        # a page is a group of its own
     st = DeviceState(w, inp, cap=cap)
     dev = st.box.device
     supp_tok = torch.full((w.batch, w.n_q_heads, 8192), -1, device=dev, dtype=torch.int32)
@@ -1156,8 +1156,8 @@ def test_batch_slot_with_zero_tokens(kv_dtype, context, lens):
     """A sequence of length 0 (an idle slot of a serving batch) next to live ones: every entry point runs,
     the idle slot gets the documented empty results (no page, zero output, tau = +inf, empty support,
     log-sum-exp = -inf, tau-hat = 0), and the live sequences match the oracle as if the slot were not there.
-    Then a first token is appended to the idle slot and the step serves it.  The long case takes the dense
-    decode through its multi-workgroup filter passes."""
+    Then a first token is appended to the idle slot and the step serves it.  (Beside rows that take the filter passes:
+    test_filter_passes_beside_short_and_empty_rows.)"""
     w = synth.C2.scaled(name="C2-idle-slot", batch=len(lens), context=context, n_q_heads=4, n_kv_heads=2,
                         kv_dtype=kv_dtype)
     inp = {key: v.clone() for key, v in synth.make_inputs(w, 2000 + 31, device="cpu").items()}
@@ -1279,9 +1279,10 @@ def test_select_topk_many_short_rows(Mmax, k):
                          ids=["bf16-8-pages", "bf16-100-pages", "f32-20-pages", "bf16-flat-scores", "alpha-1.25",
                               "alpha-2"])
 def test_many_short_rows_step(kv_dtype, ctx, k, scale, alpha):
-    """More than 512 (sequence, head) rows with short page lists take the one-wavefront-per-row selection and
-    solve kernels: whole top-k step and the group-shared decode against the oracle on sampled rows, ragged
-    lengths; the flat-score case has more candidates near the maximum than the kernel's list holds."""
+    """More than 512 (sequence, head) rows with short page lists take the one-wavefront-per-row selection, the one-launch
+    decode and, as lists shared per KV head, the solve by one wavefront per row (by four, for the 100 pages): whole top-k
+    step and the group-shared decode against the oracle on sampled rows, ragged lengths; the flat-score case has more
+    candidates than one wavefront finishes in registers."""
     w = synth.C2.scaled(name="C2-many-rows", batch=24, context=ctx, n_q_heads=32, n_kv_heads=8, kv_dtype=kv_dtype,
                         n_planted=8, scale=scale / math.sqrt(128.0), alpha=alpha)
     inp = {key: v.clone() for key, v in synth.make_inputs(w, 2000 + 77, device="cpu").items()}
@@ -1328,7 +1329,7 @@ def test_many_short_rows_step(kv_dtype, ctx, k, scale, alpha):
     # (a threshold that moves within its tolerance moves the weights of a flat row by far more, relatively)
     assert float(((out2 - st.out).norm(dim=-1) / st.out.norm(dim=-1).clamp_min(1e-30)).max()) <= 2e-3
     assert int(evals.min()) >= 0 and int(evals.max()) <= 8
-    # one list per KV head through the same kernel
+    # one list per KV head
     gcfg = group_cfg(st, w, k)
     gbox = torch.zeros(w.batch, w.n_kv_heads, st.Mmax, device=dev)
     g_idx = torch.zeros(w.batch, w.n_kv_heads, k, dtype=torch.int32, device=dev)

@@ -13,7 +13,7 @@ import torch
 from oracle import entmaxkv_oracle as orc
 from paper_2605_21649_amd import binding as ekv
 from paper_2605_21649_amd import synth
-from tests.helpers import DeviceState, unit_kv, check_decode_unit
+from tests.helpers import DeviceState, unit_kv, check_decode_unit, pre_groups
 
 pytestmark = pytest.mark.gpu
 
@@ -264,3 +264,50 @@ def test_long_rows_at_the_ends_of_the_group_bound(tokens, scale):
     ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
     check_decode_unit(w, st.out[0, 1].cpu().numpy(), float(st.tau[0, 1]), int(st.supp[0, 1]), toks[0, 1].cpu().numpy(), ref,
                       boundary_expected=True)
+
+
+# page, dtype, alpha, score scale (times 1/sqrt(128)): every group is one page, so the rows are as short as rows of more than
+# kPreGroups groups can be; the flattest leaves a slice of the filter more candidates than its list holds
+BEYOND = [(36, "f32", 2.0, 1.0), (36, "f32", 1.25, 0.5), (48, "bf16", 1.7, 0.1), (40, "f32", 4.0 / 3.0, 0.3), (36, "f32", 1.5, 0.01)]
+
+
+@pytest.mark.parametrize("page,dtype,alpha,scale", BEYOND)
+def test_filter_passes_beside_short_and_empty_rows(page, dtype, alpha, scale):
+    """A row one group beyond the solve's own, an empty one and a short one over the same pages: dense, as lists of every
+    page (bit for bit the dense result), and a short list in the long capacity."""
+    pages = pre_groups() + 1
+    one = synth.Workload("beyond", 1, 2, 1, 128, pages * page, page, dtype, alpha=alpha, scale=scale / math.sqrt(128.0))
+    inp = synth.make_inputs(one, page, device="cuda")
+    w = one.scaled(batch=3)
+    g = torch.Generator(device="cuda").manual_seed(page)
+    inp["q"] = torch.randn(3, 2, 128, generator=g, device="cuda").to(inp["k_pool"].dtype)
+    inp["block_table"] = inp["block_table"].expand(3, -1).contiguous()
+    lens = (pages * page - 5, 0, 7003)
+    inp["seq_lens"] = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    st = DeviceState(w, inp)
+    toks = torch.full((3, 2, pages * page), -1, device="cuda", dtype=torch.int32)
+    ex = ekv.decode_extras(support_tokens=toks)
+    ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL), extras=ex)
+    dense = [x.clone() for x in (st.out, st.tau, st.supp, toks)]
+    st.page_idx.copy_(torch.arange(st.cap, device="cuda", dtype=torch.int32).expand(3, 2, st.cap))
+    st.n_sel.copy_(((st.inp["seq_lens"] + page - 1) // page)[:, None].expand(3, 2))
+    toks.fill_(-1)
+    ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                          st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=ex)
+    torch.cuda.synchronize()
+    for a, b in zip(dense, (st.out, st.tau, st.supp, toks)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert torch.isposinf(st.tau[1]).all() and not st.out[1].any() and not st.supp[1].any()
+    st.n_sel[0, 1] = 300                                       # sequence 0, head 1: a short list beside a long one
+    ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), st.page_idx, st.n_sel, st.out, st.tau, st.supp,
+                          st.workspace(ekv.EKV_OP_DECODE_SPARSE), extras=ex)
+    torch.cuda.synchronize()
+    assert torch.equal(st.out[0, 0], dense[0][0, 0]) and torch.equal(st.tau[0, 0], dense[1][0, 0])
+    inp = {key: x.cpu() for key, x in inp.items()}
+    q, K, V = unit_kv(inp, w, 0, 0)
+    q1 = unit_kv({**inp, "seq_lens": inp["seq_lens"] * 0}, w, 0, 1)[0]
+    cases = [(0, 0, q, K, V), (0, 1, q1, K[:300 * page], V[:300 * page]), (2, 1, *unit_kv(inp, w, 2, 1))]
+    for b, h, qq, kk, vv in cases:
+        ref = orc.entmax_attention(qq, kk, vv, w.alpha, w.score_scale)
+        check_decode_unit(w, st.out[b, h].cpu().numpy(), float(st.tau[b, h]), int(st.supp[b, h]), toks[b, h].cpu().numpy(), ref,
+                          boundary_expected=True)
