@@ -494,21 +494,24 @@ def main():
     # scores and group maxima written), timed alone through the score_pass_only measurement flag; `call` is the
     # whole entry point (score pass + solve, which also reads the V rows of the support).
     a7_bytes = bytes_k + bytes_z / 2 + B * Hq * sel_tokens / 64 * 4        # K pages read, z and group maxima written
-    a7_ach = a7_bytes / (t_dec_scores * 1e-6) / 1e9
+    # The heads of a group read the pages they share through one L2, so fewer bytes reach HBM than the lists name: the HBM
+    # rate is taken from the counted traffic where there is a count, and the rate of the named bytes stands beside it.
+    a7_traffic = PMC_TRAFFIC_DECODE_SCORES_C4 if (args.workload == "C4" and abs(args.budget - 0.02) < 1e-9) else None
+    a7_req = a7_bytes / (t_dec_scores * 1e-6) / 1e9
+    a7_ach = (a7_traffic or a7_bytes) / (t_dec_scores * 1e-6) / 1e9
     call_ach = kernel_alg_bytes["decode_sparse"] / (t_dec * 1e-6) / 1e9
     roofline_a7 = {
         "bound": "hbm", "kernel": "decode_scores_mfma_kernel<1, 0, %d> (score pass of ekv_decode_sparse)" % P,
         "achieved": round(a7_ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(a7_ach / HBM_PEAK_GBS, 4),
-        "traffic": PMC_TRAFFIC_DECODE_SCORES_C4 if (args.workload == "C4" and abs(args.budget - 0.02) < 1e-9) else None,
+        "traffic": a7_traffic, "requested_GBps": round(a7_req, 1),
         "algorithmic_bytes_per_launch": int(a7_bytes), "avg_launch_us": round(t_dec_scores, 2),
         "call": {"entry_point": "ekv_decode_sparse (score pass + solve)", "avg_us": round(t_dec, 2),
-                 "algorithmic_bytes": int(kernel_alg_bytes["decode_sparse"]), "GBps": round(call_ach, 1),
-                 "frac": round(call_ach / HBM_PEAK_GBS, 4)},
+                 "algorithmic_bytes": int(kernel_alg_bytes["decode_sparse"]), "requested_GBps": round(call_ach, 1)},
         "timing": "HIP events around 60 back-to-back launches on the launch stream, %d rotating copies" % args.copies,
     }
     roofline_a7["traffic_source"] = PMC_TRAFFIC_SOURCE if roofline_a7["traffic"] is not None else None
     kernels["decode_sparse(score pass only)"] = {"launch_us": round(t_dec_scores, 2), "algorithmic_bytes": int(a7_bytes),
-                                                 "GBps": round(a7_ach, 1), "kernels": 1}
+                                                 "GBps": round(a7_req, 1), "kernels": 1}
     dom_name = stage_names[int(np.argmax(stage_mean))]
 
     result = {
