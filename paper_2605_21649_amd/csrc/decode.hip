@@ -1858,7 +1858,7 @@ struct RowShared {
   static constexpr bool kOverflows = false;
   static constexpr int kSegCap = (kGroups + kSegs - 1) / kSegs * 64;   // a segment holds all tokens of its groups
   union {                                          // the scores are dead once the candidates are listed
-    float z[TOKENS];
+    alignas(16) float z[TOKENS];                   // read four at a time
     float obuf[kSegs][kD];
     struct { float list_u[kWaveList]; int32_t list_pos[kWaveList]; uint32_t list_row[kWaveList]; };
   };
