@@ -686,7 +686,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
   auto keyfn = [=](int p) { return float_to_key(a * fmaf(sg_r[p], p == M - 1 ? z_last : z_full, mu_r[p])); };
   KeySet<ITEMS, decltype(keyfn)> ks(keyfn, M);
-  if (count < 0) {                                         // the candidates were not usable: count here
+  if (!SINGLE && count < 0) {                              // the candidates were not usable: count here
     const uint32_t kthr = float_to_key(st.tau - margin);
     int c = 0;
     if constexpr (ITEMS == 0) {

@@ -112,8 +112,8 @@ def test_full_size_topk_step_as_timed(fs):
 
 
 def test_full_size_dense_decode(fs):
-    """Full-cache entmax over 1 048 576 tokens (16 384 groups, the longest row the solve takes from its group maxima) against the sorted exact
-    solution of the oracle for the sampled heads."""
+    """Full-cache entmax over 1 048 576 tokens (16 384 groups, the longest row the solve takes from its group maxima)
+    against the sorted exact solution of the oracle for the sampled heads."""
     st, inp = fs["st"], fs["inp"]
     seq_prev = (inp["seq_lens"] - 1).contiguous()
     cache_prev = ekv.cache_view(inp["k_pool"], inp["v_pool"], inp["block_table"], seq_prev)
