@@ -1488,7 +1488,7 @@ __device__ __forceinline__ bool wants_side_outputs(const SolveArgs& A) {
          (DENSE && A.ex.lse != nullptr);
 }
 
-// Row of workgroup i: the heads of a group, whose supports are largely the same value rows, go to one XCD (workgroups go to
+// Row of workgroup i: the heads of a group, which read many of the same pages and value rows, go to one XCD (workgroups go to
 // the XCDs in turn) as far as whole rounds of groups last.  A permutation of [0, rows).  2048 rows of 256 tokens, support 246,
 // groups of four: 37.5 -> 30.2 us; 4096 rows of 1024, support 720, groups of eight: 172 -> 136.
 __device__ __forceinline__ int group_on_one_xcd(int i, int rows, int heads) {
@@ -1881,7 +1881,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4
 void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
   __shared__ RowShared<NW, TOKENS, PT ? 64 : 36> sh;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  const int bh = blockIdx.x, b = bh / S.Hq, hkv = (bh - b * S.Hq) / (S.Hq / S.Hkv);
+  const int heads = S.Hq / S.Hkv;
+  const int bh = group_on_one_xcd(blockIdx.x, gridDim.x, heads), b = bh / S.Hq, hkv = (bh - b * S.Hq) / heads;
   const int P = PT ? PT : S.P;
   const int n = uniform_load(S.seq_lens + b);
   const int n_slots = clampi(uniform_load(S.n_sel + bh), 0, S.cap);
@@ -2099,19 +2100,20 @@ static void launch_solve(int rows, int n_chunks_max, const SolveArgs& so, hipStr
 // Short per-head lists, one workgroup each: sixteen wavefronts as long as every list has a compute unit to itself (the
 // length of one list is what the call takes), else four, and three to six lists share a compute unit.
 // One compute unit reads K at about 75 GB/s, so the line follows the bytes of a list; the host knows its capacity only, and
-// a full list near the line would be faster in two launches, a half full one is faster in one.  Decode calls on K that is in
-// no cache, us, two launches / one, half full and full:
-//   bf16   32 lists of 1024 tokens 13.8 / 10.2, 14.1 / 12.0, of 2048 14.0 / 12.0, 14.2 / 15.6    128 of 4096 19.5 / 17.2, 25.8 / 28.5
-//          192 of 4096 22.0 / 21.2, 32.4 / 35.5    256 of 3072 22.8 / 21.4, 32.5 / 35.8, of 4096 25.6 / 25.5, 38.1 / 45.0
-//          512 of 2048 28.5 / 26.8, 39.7 / 45.8    2048 of 2048 106 / 86, 184 / 156
-//   f32    64 lists of 1024 tokens 19.2 / 12.6, 20.3 / 16.4    256 of 2048 28.3 / 26.4, 43.3 / 44.7    2048 of 2048 183 / 155, 332 / 304
-// (256 full lists of 4096 tokens: 42.2 before there was the one launch; hence the shorter limit beyond 192 lists.)
+// a full list near the line of a few rows is a little faster in two launches, a half full one in one.  Decode calls on K that
+// is in no cache, us, two launches / one, lists of the heads of a group the same, half the same, hardly the same:
+//   32 half full lists of 2048 bf16 tokens 14.0 / 11.7, 14.4 / 12.2, 14.3 / 12.2, full 14.4 / 15.8, 14.8 / 15.8, 14.8 / 15.9
+//   128 full lists of 4096 21.4 / 23.4, 26.2 / 24.1, 29.6 / 26.8    256 of them 30.7 / 23.4, 39.4 / 36.3, 46.7 / 43.9
+//   512 full lists of 2048 31.4 / 22.9, 45.2 / 30.5, 50.7 / 40.7    2048 of them 182 / 81, 181 / 108, 209 / 151
+// and 64 float32 lists of 1024 tokens, half full 19.2 / 12.6, full 20.3 / 16.4.  The heads of a group run on one XCD: dealt
+// out in turn they fetched the pages they share into as many L2s (256 full lists of 4096: 45.6, 43.4, 44.2; before there was
+// the one launch 35.5, 45.8, 52.1).
 static bool rows_in_one_launch(const Dims& dm) {
   const int cus = device_compute_units(), rows = dm.B * dm.Hq;
   const long long tokens = (long long)dm.cap * dm.P;
   if (rows > cus) return tokens <= kRowTokensMany;
   const long long bytes = tokens * kD * (dm.dtype == EKV_F32 ? 4 : 2);
-  return tokens <= (rows <= cus / 4 * 3 ? kRowTokens : kRowTokens / 4 * 3) && bytes <= (rows <= cus / 4 ? 512 << 10 : 1 << 20);
+  return tokens <= kRowTokens && bytes <= (rows <= cus / 4 ? 512 << 10 : 1 << 20);
 }
 template <typename T, int PT>
 static void launch_rows_T(const Dims& dm, const ScoreArgs& sa, const SolveArgs& so, hipStream_t st) {

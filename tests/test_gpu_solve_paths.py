@@ -96,7 +96,8 @@ def test_solve_side_outputs_of_short_and_flat_rows(lens):
 LISTS = [(1, 4, 2, 16, "bf16", 128), (1, 4, 2, 16, "bf16", 129), (1, 4, 2, 4, "f32", 256), (1, 4, 2, 36, "f32", 28),
          (3, 32, 8, 36, "bf16", 113), (3, 32, 8, 32, "bf16", 128), (3, 32, 8, 64, "bf16", 64), (9, 32, 8, 12, "bf16", 85),
          (9, 32, 8, 64, "bf16", 32), (9, 32, 8, 16, "bf16", 64), (9, 32, 32, 4, "f32", 512), (9, 32, 8, 16, "f32", 1),
-         (8, 32, 8, 64, "bf16", 48), (8, 32, 8, 64, "bf16", 49)]
+         (8, 32, 8, 64, "bf16", 64), (8, 32, 8, 64, "bf16", 65),
+         (5, 8, 2, 16, "bf16", 64)]                                                  # rows left over from whole rounds of the XCDs
 
 
 @pytest.mark.parametrize("batch,hq,hkv,page,dtype,k", LISTS)
@@ -143,7 +144,7 @@ def test_short_lists_in_one_launch(batch, hq, hkv, page, dtype, k, scale):
 # batch, query heads, KV heads, page, dtype, pages per list: more rows than compute units, to twice as many and beyond,
 # lists of up to 1024 and 2048 tokens, groups of 64, 60, 48 and 36 tokens
 GROUPED = [(9, 64, 8, 16, "bf16", 64), (9, 64, 8, 16, "bf16", 128), (9, 32, 8, 12, "bf16", 170), (9, 64, 8, 24, "bf16", 85),
-           (9, 64, 16, 36, "f32", 56), (17, 32, 8, 64, "bf16", 32), (1, 32, 8, 16, "bf16", 128), (5, 32, 8, 16, "bf16", 256),
+           (9, 64, 16, 36, "f32", 56), (17, 32, 8, 64, "bf16", 32), (67, 8, 2, 16, "bf16", 32), (1, 32, 8, 16, "bf16", 128), (5, 32, 8, 16, "bf16", 256),
            # lists beyond the one launch: the last number of units that is split over the XCDs, and the next
            (12, 128, 16, 16, "bf16", 136), (25, 64, 8, 16, "bf16", 136), (25, 64, 8, 8, "f32", 260)]
 
