@@ -1458,7 +1458,7 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
 }
 
 // A row of at most SH::kMaxGroups groups, from the group maxima to the outputs.  False: its candidates outgrow the
-// segments (attention so flat that more than 2000 to 12 000 are left).
+// segments (attention so flat that one of the sixteen gets more than 192 or 768).
 template <typename T, bool DENSE, typename SH>
 __device__ __forceinline__ bool solve_row(const SolveArgs& A, const RowRef& R, const float* zr, const float* pm, float seed_z,
                                           bool block_extras, SH& sh) {
@@ -1580,8 +1580,8 @@ __global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const Sol
     return;
   }
   // The candidates above the bound (only z > zmax - 1 can be in the support; `pre` and filtered rows have a tighter
-  // one) are compacted IN ORDER in rounds: wavefront w of a round owns consecutive positions, so (round, w, load, lane)
-  // order is candidate order.  Rows that have neither list of groups nor filter results sweep their scores, skipping
+  // one) are compacted IN ORDER.  Rows that have neither list of groups nor filter results sweep their scores in rounds
+  // (wavefront w of a round owns consecutive positions, so (round, w, load, lane) order is candidate order), skipping
   // chunks whose maximum is <= thr, and histogram the candidates over 64 slices of [thr, zmax]: counts alone give a lower
   // bound of the mass at every slice boundary (an entry of slice j lies at least j-i slices above boundary i), hence a
   // tighter threshold for the solve or, if the candidates did not fit in LDS, for one more compaction pass.
