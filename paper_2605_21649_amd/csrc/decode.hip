@@ -1497,6 +1497,7 @@ __device__ __forceinline__ bool wants_side_outputs(const SolveArgs& A) {
 // the XCDs in turn) as far as whole rounds of groups last.  A permutation of [0, rows).  2048 rows of 256 tokens, support 246,
 // groups of four: 37.5 -> 30.2 us; 4096 rows of 1024, support 720, groups of eight: 172 -> 136.
 __device__ __forceinline__ int group_on_one_xcd(int i, int rows, int heads) {
+  if (heads == 1) return i;
   const int round = kXcds * heads, t = i / kXcds;
   return i >= rows / round * round ? i : (t / heads * kXcds + i % kXcds) * heads + t % heads;
 }
