@@ -57,6 +57,12 @@ constexpr int kUnitsLdsMax = 8192;      // units whose item prefix a workgroup k
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return min(max(x, lo), hi); }
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// LDS accesses of one wavefront on either side keep their order (the hardware executes them in order; the compiler is told).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Work distribution of pass 1.  An item is one group of pmax_pages(P) page slots of one unit (64 tokens when P
 // divides 64): the granularity of pmax.  The launch has a fixed number of wavefronts that does not depend on the
 // capacity of the page lists: the items of all units, in (unit, group) order, form one sequence of T items, and
@@ -119,18 +125,72 @@ __device__ __forceinline__ WaveItems wave_item_range(const P pre, int U, int w, 
   return r;
 }
 
-// Generic path (float32 caches, or page sizes that are not 16, 32 or 64): FMAs + DPP row sums.
+// Sums of G values over the 16 lanes of a DPP row, one head's sum in 16 / G lanes: two heads share a step by passing each
+// other's half on, so eight heads take 8 exchanges instead of 32, and what follows is done once instead of per head.
+// The pairs added are those of row16_sum, so the sums are its to the last bit.  The mirrors of the third and fourth step turn
+// a quad round, which is why odd quads hold their heads in reverse.
+template <int G> struct RowHeads {
+  bool s1, s2, s3;                                 // which of two heads this lane keeps in steps 1, 2 and 3
+  int head, keep;                                  // its head, and its number among the lanes with that head
+  __device__ __forceinline__ explicit RowHeads(int c) {
+    const int quad = c >> 2;
+    s1 = ((c ^ quad) & 1) != 0; s2 = (((c >> 1) ^ quad) & 1) != 0; s3 = quad == 1 || quad == 2;
+    head = G == 1 ? 0 : G == 2 ? s1 : G == 4 ? s1 + 2 * s2 : s1 + 2 * s2 + 4 * s3;
+    keep = G == 1 ? c : G == 2 ? s2 + 2 * quad : G == 4 ? quad : quad >> 1;
+  }
+  template <int CTRL> static __device__ __forceinline__ float merge(bool second, float a, float b) {
+    return (second ? b : a) + dpp_move<CTRL>(second ? a : b);
+  }
+  __device__ __forceinline__ float sum(const float (&v)[G]) const {
+    float x[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) x[g] = v[g];
+    if constexpr (G == 1) x[0] += dpp_move<0xB1>(x[0]);
+    else {
+#pragma unroll
+      for (int g = 0; g < G / 2; ++g) x[g] = merge<0xB1>(s1, x[2 * g], x[2 * g + 1]);
+    }
+    if constexpr (G <= 2) x[0] += dpp_move<0x4E>(x[0]);
+    else {
+#pragma unroll
+      for (int g = 0; g < G / 4; ++g) x[g] = merge<0x4E>(s2, x[2 * g], x[2 * g + 1]);
+    }
+    if constexpr (G <= 4) x[0] += dpp_move<0x141>(x[0]);
+    else x[0] = merge<0x141>(s3, x[0], x[1]);
+    return x[0] + dpp_move<0x140>(x[0]);
+  }
+};
+
+// Any page size and either type, by steps of four tokens (the pages of an item hold 9 to 16 of them).  float32 caches, whose
+// products stay float32, take FMAs and DPP row sums; bf16 pages other than 16, 32 and 64 the matrix cores, as below.
+// The rows of 64 steps (four items) are resolved at once, one step per lane (page list -> block table), and handed out with
+// v_readlane; K is read in chunks of 4 KiB with two register sets, the next chunk requested before the current one is
+// consumed.  Page by page, with the lookups in front of every page and FMAs for either type, a wavefront had one step in
+// flight.  Whole calls, us, before / now, four heads to a KV head: all pages of 2 x 262144 bf16 tokens in pages of 12
+// 270.6 / 246.7 (1.07 GB, 4.6 TB/s in the pass; eight heads 377.7 / 283.7), per-head lists of 5000 tokens, 128 rows, pages of 8
+// 37.8 / 29.0; float32, 2 x 131072 tokens in pages of 8 242.6 / 231.0, 128 lists of 5000 tokens in pages of 16 52.7 / 44.5.
+// Not faster: float32 pages of 48 with four heads, all pages 227.5 / 231.5 (twelve steps behind one lookup before).
 template <typename T, int G, int MODE, bool PRE_GLOBAL>
-__global__ __launch_bounds__(kScoreThreads) void decode_scores_valu_kernel(const ScoreArgs A) {
-  constexpr bool DENSE = MODE == kAllPages, GROUPED = MODE != kPerHead;
+__global__ __launch_bounds__(kScoreThreads)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? (G <= 4 ? 8 : 6) : G == 1 ? 8 : G == 2 ? 6 : G == 4 ? 5 : 4)))
+void decode_scores_steps_kernel(const ScoreArgs A) {
+  constexpr bool DENSE = MODE == kAllPages, GROUPED = MODE != kPerHead, MFMA = sizeof(T) == 2;
+  constexpr int CS = MFMA ? 4 : 2;                 // steps per chunk of 4 KiB
+  constexpr int KS = 16 / G;                       // FMAs: steps whose scores the lanes of a row hold between them
+  constexpr int NR = MFMA ? CS : 2 * CS;           // 16-byte loads per lane and chunk
+  constexpr int NSET = (G + 3) / 4;
+  constexpr int kStepLanes = 16, kBatchItems = 64 / kStepLanes;
   extern __shared__ int pre_lds[];
   __shared__ int wsum[kScoreWaves];
   const T* q = (const T*)A.q;
-  const T* k_pool = (const T*)A.k_pool;
   const int P = A.P, Hq = A.Hq, Hkv = A.Hkv;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-  const int gp = pmax_pages(P);
-  const int r = lane >> 4, c = lane & 15;
+  const int gp = pmax_pages(P), spp = P / 4, spi = gp * spp;      // steps per page and per item
+  const int item_steps = (spi + CS - 1) / CS * CS;                // in whole chunks; the last step again past the item's end
+  const int my_st = min(lane % kStepLanes, spi - 1), my_pg = my_st / spp, my_t0 = 4 * (my_st - my_pg * spp);
+  const int r = lane >> 4, c = lane & 15;          // FMAs: token of the step, channels 8c..8c+7
+  const int m = lane & 15, j = lane >> 4, kq = m & 3, gl = m >> 2;      // matrix cores: as in decode_scores_mfma_kernel
+  const T* k_pool = (const T*)A.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : r * kD + 8 * c);
   const int ratio = Hq / Hkv;
   const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part(A);
   if (!PRE_GLOBAL)
@@ -138,63 +198,169 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_valu_kernel(const
       return part_length(part, u / ratio, (unit_slots<MODE>(A, u) + gp - 1) / gp); }, pre_lds, wsum);
   const int* pre = PRE_GLOBAL ? A.pre_g : pre_lds;
   const WaveItems wi = wave_item_range(pre, A.U, w, part);
-  int unit = wi.unit;
-  for (int it = wi.begin; it < wi.end; ++it) {
-    while (it >= uniform(pre[unit + 1])) ++unit;
-    const int grp = it - uniform(pre[unit]) + part_first(part, unit / ratio, (unit_slots<MODE>(A, unit) + gp - 1) / gp);
-    const int b = GROUPED ? unit / Hkv : unit / Hq;
-    const int hkv = GROUPED ? unit % Hkv : (unit % Hq) / (Hq / Hkv);
-    const int hq0 = GROUPED ? hkv * G : unit % Hq;          // first (only) query head of this unit
-    const int n = A.seq_lens[b];
-    const int n_slots = unit_slots<MODE>(A, unit);
-    float coef[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) load8<T>(q + ((size_t)b * Hq + hq0 + g) * kD + 8 * c, coef[g]);
-    float wmax[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) wmax[g] = -INFINITY;
-    for (int pg = 0; pg < gp; ++pg) {
-      const int slot = grp * gp + pg;
-      if (slot >= n_slots) break;
-      const int lp = clampi(DENSE ? slot : A.page_idx[(size_t)unit * A.cap + slot], 0, A.Mmax - 1);
+  const int last = (DENSE ? A.Mmax : A.cap) - 1;
+
+  for (int it0 = wi.begin; it0 < wi.end; it0 += kBatchItems) {
+    // lane l: step l % 16 of item it0 + l / 16 (clamped to the last item and step): its row of K and how many of its
+    // tokens are valid (-1: the step is not stored)
+    int l_unit, l_grp, l_row, l_left;
+    {
+      const int my_it = min(it0 + lane / kStepLanes, wi.end - 1);
+      int lo = 0, hi = A.U;
+      while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (pre[mid] <= my_it) lo = mid; else hi = mid; }
+      l_unit = lo;
+      const int b = GROUPED ? lo / Hkv : lo / Hq, hkv = GROUPED ? lo - b * Hkv : (lo - b * Hq) / ratio;
+      const int n = A.seq_lens[b], n_slots = DENSE ? clampi((n + P - 1) / P, 0, A.Mmax) : unit_slots<MODE>(A, lo);
+      l_grp = my_it - pre[lo];
+      if (!GROUPED && part.count != 1) l_grp += part_first(part, lo / ratio, (n_slots + gp - 1) / gp);
+      const int slot = l_grp * gp + my_pg, slot_c = min(slot, last);
+      const int lp = clampi(DENSE ? slot_c : A.page_idx[(size_t)lo * A.cap + slot_c], 0, A.Mmax - 1);
       const int phys = clampi(A.block_table[(size_t)b * A.Mmax + lp], 0, A.n_phys - 1);
-      const T* kpage = k_pool + ((size_t)phys * A.HkvPool + hkv) * P * kD + 8 * c;
-      for (int s0 = 0; s0 < P / 4; s0 += 16) {          // 16 steps (64 tokens) per sweep of the c lanes
-        float zkeep[G];
+      l_row = (phys * A.HkvPool + hkv) * P + my_t0;
+      l_left = lane % kStepLanes < spi && slot < n_slots ? clampi(n - (lp * P + my_t0), 0, 4) : -1;
+    }
+    const uint64_t stored = __ballot(l_left >= 0);
+    const int total = (min(it0 + kBatchItems, wi.end) - it0) * (item_steps / CS);
+
+    // cursors: the chunk requested next and the one consumed next, as (first lane of the item, first step in it)
+    int rq = 0, rq_s = 0, at = 0, at_s = 0;
+    auto request = [&](uint4 (&a)[NR]) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) zkeep[g] = -INFINITY;
-        const int s1 = min(P / 4, s0 + 16);
-        for (int s = s0; s < s1; ++s) {
-          float x[8];
-          load8<T>(kpage + (size_t)(4 * s + r) * kD, x);
-          const bool valid = lp * P + 4 * s + r < n;
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float acc = 0.f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc = fmaf(coef[g][i], x[i], acc);
-            acc = row16_sum(acc);
-            const float z = valid ? A.zscale * acc : -INFINITY;
-            if (c == s - s0) zkeep[g] = z;
-            wmax[g] = fmaxf(wmax[g], z);
-          }
-        }
-        if (c < s1 - s0) {
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            const size_t row = GROUPED ? (size_t)b * Hq + hq0 + g : (size_t)unit;
-            A.zbuf[row * A.zstride + (size_t)slot * P + 4 * (s0 + c) + r] = zkeep[g];
-          }
+      for (int s = 0; s < CS; ++s) {
+        const int row = __builtin_amdgcn_readlane(l_row, rq + rq_s + s);
+        const T* p = k_pool + (size_t)(uint32_t)row * kD;
+        if constexpr (MFMA) a[s] = *reinterpret_cast<const uint4*>(p);
+        else {
+          a[2 * s] = *reinterpret_cast<const uint4*>(p);
+          a[2 * s + 1] = *reinterpret_cast<const uint4*>(p + 4);
         }
       }
-    }
+      rq_s += CS;
+      if (rq_s == item_steps) { rq_s = 0; rq += kStepLanes; }
+    };
+    // state of the item being consumed, refreshed at its first chunk
+    size_t row0 = 0;                               // first row of z / pmax written
+    int grp = 0, lim = 0;                          // its stored steps
+    uint4 bq[MFMA ? NSET : 1];
+    float coef[MFMA ? 1 : G][8], zkeep[MFMA ? NSET : 1], wmax[MFMA ? NSET : 1];
+    const RowHeads<G> rh(c);
+    auto open_item = [&]() {
+      const int unit = __builtin_amdgcn_readlane(l_unit, at);
+      const int b = GROUPED ? unit / Hkv : unit / Hq, hq0 = GROUPED ? (unit - b * Hkv) * G : unit - b * Hq;
+      grp = __builtin_amdgcn_readlane(l_grp, at);
+      lim = __popc((uint32_t)(stored >> at) & 0xffffu);
+      row0 = GROUPED ? (size_t)b * Hq + hq0 : (size_t)unit;
+      const T* qr = q + ((size_t)b * Hq + hq0) * kD;
+      if constexpr (MFMA) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float m = wmax[g];                                   // equal over the 16 lanes of a row
-      m = fmaxf(m, __shfl_xor(m, 16));
-      m = fmaxf(m, __shfl_xor(m, 32));
-      const size_t row = GROUPED ? (size_t)b * Hq + hq0 + g : (size_t)unit;
-      if (lane == 0) A.pmax[row * A.n_chunks_max + grp] = m;
+        for (int s = 0; s < NSET; ++s) {
+          bq[s] = *reinterpret_cast<const uint4*>(qr + min(4 * s + gl, G - 1) * kD + kq * 32 + j * 8);
+          wmax[s] = -INFINITY;
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < G; ++g) load8<T>(qr + g * kD + 8 * c, coef[g]);
+        wmax[0] = -INFINITY;
+      }
+    };
+    auto consume = [&](const uint4 (&a)[NR]) {
+      const int z0 = grp * spi * 4;                // first token of the item in its row of z
+      int left[CS];
+#pragma unroll
+      for (int s = 0; s < CS; ++s) left[s] = __builtin_amdgcn_readlane(l_left, at + at_s + s);
+      if constexpr (MFMA) {
+#pragma unroll
+        for (int s = 0; s < CS; ++s) {
+          const bool valid = j < left[s];
+#pragma unroll
+          for (int cs = 0; cs < NSET; ++cs) {
+            const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+            const f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[s]),
+                                                                      __builtin_bit_cast(bf16x8_t, bq[cs]), zero, 0, 0, 0);
+            const float v01 = (kq & 1) ? d[1] : d[0], v23 = (kq & 1) ? d[3] : d[2];
+            float v = (kq & 2) ? v23 : v01;
+            v += dpp_move<0xB1>(v);
+            v += dpp_move<0x4E>(v);
+            const float z = valid ? A.zscale * v : -INFINITY;
+            if (s == kq) zkeep[cs] = z;
+            wmax[cs] = fmaxf(wmax[cs], z);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int s = 0; s < CS; ++s) {
+          const Raw8<float> raw = {__builtin_bit_cast(float4, a[2 * s]), __builtin_bit_cast(float4, a[2 * s + 1])};
+          float x[8], acc[G];
+          widen8(raw, x);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            acc[g] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[g] = fmaf(coef[g][i], x[i], acc[g]);
+          }
+          const float v = rh.sum(acc), z = r < left[s] ? A.zscale * v : -INFINITY;
+          if ((at_s + s) % KS == rh.keep) zkeep[0] = z;          // lane (r, c) keeps token r of that step
+          wmax[0] = fmaxf(wmax[0], z);
+        }
+      }
+      if constexpr (MFMA) {
+        if (at_s + kq < lim) {                     // lane (j, head, kq) holds token j of the chunk's step kq
+#pragma unroll
+          for (int cs = 0; cs < NSET; ++cs) {
+            const int g = 4 * cs + gl;
+            if (g < G) A.zbuf[(row0 + g) * A.zstride + z0 + 4 * (at_s + kq) + j] = zkeep[cs];
+          }
+        }
+      } else if ((at_s + CS) % KS == 0 || at_s + CS == item_steps) {
+        const int st = at_s / KS * KS + rh.keep;
+        if (st < lim) A.zbuf[(row0 + rh.head) * A.zstride + z0 + 4 * st + r] = zkeep[0];
+      }
+      at_s += CS;
+      if (at_s == item_steps) {                     // last chunk of the item: its maximum (and its scores)
+        at_s = 0; at += kStepLanes;
+        if constexpr (MFMA) {
+#pragma unroll
+          for (int cs = 0; cs < NSET; ++cs) {
+            float mx = wmax[cs];                   // equal over the four kq lanes of a head
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const int g = 4 * cs + gl;
+            if (j == 0 && kq == 0 && g < G) A.pmax[(row0 + g) * A.n_chunks_max + grp] = mx;
+          }
+        } else {
+          float mx = wmax[0];
+          mx = fmaxf(mx, __shfl_xor(mx, 16));
+          mx = fmaxf(mx, __shfl_xor(mx, 32));
+          if (r == 0 && rh.keep == 0) A.pmax[(row0 + rh.head) * A.n_chunks_max + grp] = mx;
+        }
+      }
+    };
+
+    // two chunks in flight; the query of a new item is requested before the next chunk (see decode_scores_mfma_kernel)
+    uint4 a0[NR], a1[NR];
+    request(a0);
+    int ck = 0;
+    for (; ck + 2 < total; ck += 2) {
+      if (at_s == 0) open_item();
+      __builtin_amdgcn_sched_barrier(0);
+      request(a1);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(a0);
+      if (at_s == 0) open_item();
+      __builtin_amdgcn_sched_barrier(0);
+      request(a0);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(a1);
+    }
+    if (at_s == 0) open_item();
+    __builtin_amdgcn_sched_barrier(0);
+    if (ck + 1 < total) {
+      request(a1);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(a0);
+      consume(a1);                                 // of the same item: an item has at least two chunks
+    } else {
+      consume(a0);
     }
   }
 }
@@ -844,12 +1010,6 @@ __device__ __forceinline__ void gather_support(const T* __restrict__ v_pool, con
       for (int i = 0; i < 8; ++i) acc[i] = fmaf(pw[j], vv[i], acc[i]);
     }
   }
-}
-
-// LDS accesses of one wavefront on either side keep their order (the hardware executes them in order; the compiler is told).
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_wave_barrier();
-  asm volatile("" ::: "memory");
 }
 
 // Ranges of a row's candidates, as a wavefront that finishes the row needs them.
@@ -1879,7 +2039,7 @@ struct RowShared {
   };
   union {                                          // and the maxima before that
     uint2 seg[kSegs * kSegCap];
-    float umax[TOKENS / 4];                        // per score unit: 16-token chunk (matrix cores) or page (FMA path)
+    float umax[TOKENS / 4];                        // per score unit: 16-token chunk, or page where PT is 0
   };
   float red[2][kSegs][3];
   int wcount[2][kSegs];
@@ -1890,7 +2050,7 @@ struct RowShared {
   int n_pass;
 };
 
-// PT: page size of the matrix-core path (16, 32, 64), 0: FMA path (float32, or any other page size).
+// PT: page size of a bf16 cache (16, 32, 64), 0: float32 (FMAs), or bf16 pages of any other size.
 template <typename T, int PT, int NW, int TOKENS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 && PT ? (TOKENS > 1024 ? 5 : 6) : 4)))
 void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
@@ -1955,37 +2115,53 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
         consume(i + 1, a1);
       }
     } else {
-      const int r = lane >> 4, c = lane & 15;                               // as in decode_scores_valu_kernel, G = 1
-      const T* k_pool = (const T*)S.k_pool + 8 * c;
+      // as in decode_scores_steps_kernel, G = 1
+      constexpr bool MFMA = sizeof(T) == 2;
+      const int r = lane >> 4, c = lane & 15, kq = lane & 3, gl = (lane >> 2) & 3, j = r;
+      const T* k_pool = (const T*)S.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : r * kD + 8 * c);
+      const T* qr = (const T*)S.q + (size_t)bh * kD;
       float coef[8];
-      load8<T>((const T*)S.q + (size_t)bh * kD + 8 * c, coef);
+      Raw8<T> bq;
+      if constexpr (MFMA) load_raw8(qr + kq * 32 + j * 8, bq);
+      else load8<T>(qr + 8 * c, coef);
       const int steps = P / 4, batches = (steps + 3) / 4, total = mine * batches;   // four steps = 16 tokens per batch
       auto request = [&](int i, Raw8<T> (&x)[4]) {
         const int ic = min(i, total - 1), pg = ic / batches, s0 = 4 * (ic - pg * batches);
         const T* kpage = k_pool + ((size_t)__builtin_amdgcn_readlane(l_phys, pg) * S.HkvPool + hkv) * P * kD;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) load_raw8(kpage + (size_t)(4 * min(s0 + s, steps - 1) + r) * kD, x[s]);
+        for (int s = 0; s < 4; ++s) load_raw8(kpage + (size_t)(4 * min(s0 + s, steps - 1)) * kD, x[s]);
       };
       float wmax = -INFINITY;
       auto consume = [&](int i, const Raw8<T> (&x)[4]) {
         if (i >= total) return;                                             // wave-uniform
         const int pg = i / batches, bt = i - pg * batches, unit = u0 + NW * pg;
         const int tok0 = __builtin_amdgcn_readlane(l_lp, pg) * P;
+        const int keep = MFMA ? kq : c;                                     // the step whose score this lane stores
         float zkeep = -INFINITY;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const int st = 4 * bt + s;
-          float xv[8];
-          widen8(x[s], xv);
-          float acc = 0.f;
+          float v = 0.f;
+          if constexpr (MFMA) {
+            const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+            const f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[s].a),
+                                                                      __builtin_bit_cast(bf16x8_t, bq.a), zero, 0, 0, 0);
+            const float v01 = (kq & 1) ? d[1] : d[0], v23 = (kq & 1) ? d[3] : d[2];
+            v = (kq & 2) ? v23 : v01;
+            v += dpp_move<0xB1>(v);
+            v += dpp_move<0x4E>(v);
+          } else {
+            float xv[8];
+            widen8(x[s], xv);
 #pragma unroll
-          for (int q = 0; q < 8; ++q) acc = fmaf(coef[q], xv[q], acc);
-          acc = row16_sum(acc);
-          const float z = st < steps && tok0 + 4 * st + r < n ? S.zscale * acc : -INFINITY;
-          if (c == s) zkeep = z;
+            for (int q = 0; q < 8; ++q) v = fmaf(coef[q], xv[q], v);
+            v = row16_sum(v);
+          }
+          const float z = st < steps && tok0 + 4 * st + r < n ? S.zscale * v : -INFINITY;
+          if (keep == s) zkeep = z;
           wmax = fmaxf(wmax, z);
         }
-        if (c < 4 && 4 * bt + c < steps) sh.z[unit * P + 4 * (4 * bt + c) + r] = zkeep;
+        if ((MFMA ? gl == 0 : c < 4) && 4 * bt + keep < steps) sh.z[unit * P + 4 * (4 * bt + keep) + r] = zkeep;
         if (bt == batches - 1) {
           wmax = fmaxf(wmax, __shfl_xor(wmax, 16));
           wmax = fmaxf(wmax, __shfl_xor(wmax, 32));
@@ -2083,8 +2259,8 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
   if (dm.dtype == EKV_BF16 && dm.P == 16) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 16);
   else if (dm.dtype == EKV_BF16 && dm.P == 32) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 32);
   else if (dm.dtype == EKV_BF16 && dm.P == 64) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 64);
-  else if (dm.dtype == EKV_BF16) EKV_SCORES(decode_scores_valu_kernel, bf16_t, G, MODE);
-  else EKV_SCORES(decode_scores_valu_kernel, float, G, MODE);
+  else if (dm.dtype == EKV_BF16) EKV_SCORES(decode_scores_steps_kernel, bf16_t, G, MODE);
+  else EKV_SCORES(decode_scores_steps_kernel, float, G, MODE);
 #undef EKV_SCORES
 }
 
