@@ -29,6 +29,19 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 typedef const int32_t __attribute__((address_space(4)))* const_i32_ptr;
 __device__ __forceinline__ int32_t uniform_load(const int32_t* p) { return *(const_i32_ptr)(uintptr_t)p; }
 
+// 16 bytes; STREAM: of a stream that this launch reads once.  A non-temporal load takes the line that leaves the caches
+// first, so that a stream does not push out what the call itself writes and reads again (scores, page lists) and its
+// half-written lines stay until they are whole.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+template <bool STREAM = false> __device__ __forceinline__ uint4 load16(const void* p) {
+  if constexpr (STREAM) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
+  else return *reinterpret_cast<const uint4*>(p);
+}
+template <bool STREAM = false> __device__ __forceinline__ void store16(void* p, const uint4& v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(p));
+  else *reinterpret_cast<uint4*>(p) = v;
+}
+
 // Load 8 consecutive channels (one lane's share of a 128-channel row) as float.
 template <typename T> __device__ __forceinline__ void load8(const T* p, float (&x)[8]);
 

@@ -26,6 +26,10 @@ constexpr int kPreGroups = 16384;         // rows of at most this many groups ar
 constexpr int kFilterMaxSlices = 1024;    // ... unless they would need more slices than this
 constexpr int kFilterSliceCap = 4096;     // candidates kept per slice (the solve holds this many in LDS)
 
+// Streams of at least this many bytes -- the eight L2s together hold as many -- are read past the caches (load16<true>).
+// What is smaller may still be there from the call before, and is fetched no faster.  Sides measured at the launchers.
+constexpr long long kStreamBytes = 32ll << 20;
+
 struct DecodeWorkspace {
   float* z;        // [B*Hq][zstride] candidate scores z_j (or -inf where masked)
   float* pmax;     // [B*Hq][n_chunks_max] maxima of z per pmax_pages(P) page slots

@@ -12,6 +12,7 @@
 // has 16 bits).  float32 statistics use plain FMAs and DPP row reductions.
 // With EKV_SCORE_GROUP_MAX the box scores of the G heads are reduced to their maximum before they are
 // written (one list of pages per KV head, shared by its query heads).
+#include <type_traits>
 #include "ekv_device.h"
 #include "ekv_internal.h"
 #include "ekv_stats.h"
@@ -152,7 +153,7 @@ __host__ __device__ constexpr int score_tile(int kind) { return kind == kKindBox
 // At least six wavefronts per SIMD: the scoring loop needs about 45 registers, the fused append path about 90, and
 // the stream is faster with the append squeezed (a few spilled values in its one wavefront) than with every
 // workgroup of the launch at an occupancy of four.
-template <int G, int KIND, bool APPEND>
+template <int G, int KIND, bool APPEND, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void score_pages_mfma_kernel(const bf16_t* __restrict__ q,
                                                                const void* __restrict__ stats_any,
@@ -212,7 +213,7 @@ void score_pages_mfma_kernel(const bf16_t* __restrict__ q,
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int p = min(pw0 + 4 * t + pg, M - 1);   // clamped: pages past the end are masked on output
-      raw[t] = *reinterpret_cast<const uint4*>(base8 + (size_t)p * 256);
+      raw[t] = load16<STREAM>(base8 + (size_t)p * 256);
     }
   } else {
     const bf16_t* base = (const bf16_t*)stats_any + (((size_t)b * Hkv + h) * Mmax) * 2 * kD + (kq * 4 + j) * 8;
@@ -220,7 +221,7 @@ void score_pages_mfma_kernel(const bf16_t* __restrict__ q,
     for (int t = 0; t < NT; ++t) {
       const int p = min(pw0 + 4 * t + pg, M - 1);   // clamped: pages past the end are masked on output
 #pragma unroll
-      for (int s = 0; s < 2; ++s) a[t][s] = *reinterpret_cast<const uint4*>(base + ((size_t)p * 2 + s) * kD);
+      for (int s = 0; s < 2; ++s) a[t][s] = load16<STREAM>(base + ((size_t)p * 2 + s) * kD);
     }
   }
 #pragma unroll
@@ -376,18 +377,28 @@ static void launch_score_GA(const Dims& dm, const void* q, const ekv_stats_view&
   const dim3 grid = score_grid(dm, kScoreTile, APPEND && ap_box.mode == 1, &ap_box);       // 512-byte records
   const dim3 grid_g = score_grid(dm, kScoreTile, APPEND && ap_gauss.mode == 1, &ap_gauss);
   if (dm.dtype == EKV_BF16) {
+    // Statistics are read once a step.  Past the caches they leave room there for the pages and scores the rest of the step
+    // shares, and stream faster.  Whole steps on changing inputs, us, kept / past the caches: top-k on 268 MB (1 x 1M tokens)
+    // 111.5 / 107.1 and on 134 MB (16 x 32K) 60.7 / 55.8, 8-bit groups on 134 MB 61.6 / 53.0, Gaussian on 67 MB (1 x 256K)
+    // 64.3 / 58.7, top-k on 134 MB (64 x 8K) 58.4 / 54.9 and on 34 MB 33.7 / 33.3; but on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
+    const long long records = (long long)dm.B * dm.Hkv * dm.Mmax;
+    const auto launch = [&](auto kind, const dim3& g, const void* stats, float* out0, float* out1, int group_max, const ScoreAppend& ap) {
+      constexpr int KIND = decltype(kind)::value;
+      const long long bytes = records * (KIND == kKindBox8 ? 2 * kD : 4 * kD);
+      if (bytes >= kStreamBytes)
+        hipLaunchKernelGGL((score_pages_mfma_kernel<G, KIND, APPEND, true>), g, block, 0, st, (const bf16_t*)q, stats, seq_lens,
+                           out0, out1, dm.Hkv, dm.P, dm.Mmax, dm.scale, group_max, ap);
+      else
+        hipLaunchKernelGGL((score_pages_mfma_kernel<G, KIND, APPEND, false>), g, block, 0, st, (const bf16_t*)q, stats, seq_lens,
+                           out0, out1, dm.Hkv, dm.P, dm.Mmax, dm.scale, group_max, ap);
+    };
     if (mode & EKV_SCORE_BOX8) {
       ScoreAppend ap8 = ap_box;
       const dim3 grid8 = score_grid(dm, score_tile(kKindBox8), APPEND && ap8.mode == 1, &ap8);
-      hipLaunchKernelGGL((score_pages_mfma_kernel<G, kKindBox8, APPEND>), grid8, block, 0, st, (const bf16_t*)q,
-                         (const void*)s.box8, seq_lens, box, (float*)nullptr, dm.Hkv, dm.P, dm.Mmax, dm.scale, gmax, ap8);
+      launch(std::integral_constant<int, kKindBox8>{}, grid8, s.box8, box, nullptr, gmax, ap8);
     }
-    if (mode & EKV_SCORE_BOX)
-      hipLaunchKernelGGL((score_pages_mfma_kernel<G, kKindBox, APPEND>), grid, block, 0, st, (const bf16_t*)q,
-                         (const void*)s.box, seq_lens, box, (float*)nullptr, dm.Hkv, dm.P, dm.Mmax, dm.scale, gmax, ap_box);
-    if (mode & EKV_SCORE_GAUSS)
-      hipLaunchKernelGGL((score_pages_mfma_kernel<G, kKindGauss, APPEND>), grid_g, block, 0, st, (const bf16_t*)q,
-                         (const void*)s.gauss, seq_lens, mu, sigma, dm.Hkv, dm.P, dm.Mmax, dm.scale, 0, ap_gauss);
+    if (mode & EKV_SCORE_BOX) launch(std::integral_constant<int, kKindBox>{}, grid, s.box, box, nullptr, gmax, ap_box);
+    if (mode & EKV_SCORE_GAUSS) launch(std::integral_constant<int, kKindGauss>{}, grid_g, s.gauss, mu, sigma, 0, ap_gauss);
   } else {
     if (mode & EKV_SCORE_BOX)
       hipLaunchKernelGGL((score_pages_f32_kernel<G, false, APPEND>), grid, block, 0, st, (const float*)q,

@@ -1,0 +1,54 @@
+"""Calls large enough to read their streams past the caches (32 MiB and more of statistics) against the same sequences one
+by one, which are small enough not to: bit for bit, since only the kind of the loads differs."""
+import pytest
+import torch
+
+from paper_2605_21649_amd import binding as ekv
+from paper_2605_21649_amd import synth
+from tests.helpers import DeviceState
+
+pytestmark = pytest.mark.gpu
+
+
+def same(a, b):
+    return torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
+
+
+def alone(w, inp, b, **kw):
+    """Sequence b of a batch as a problem of its own, on the same pools."""
+    one = {key: (x if key.endswith("pool") else x[b:b + 1].contiguous()) for key, x in inp.items()}
+    return DeviceState(w.scaled(batch=1), one, **kw)
+
+
+@pytest.mark.parametrize("heads", [(8, 8), (16, 8), (32, 8), (64, 8)])
+def test_scores_of_large_statistics(heads):
+    # 5 x 8 x 3876 pages: 39.7 MB of 8-bit bounds, 79 MB of bf16 ones; a fifth of it per sequence
+    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 62011, 16, "bf16")
+    inp = synth.make_inputs(w, 5, device="cuda")
+    inp["seq_lens"] = torch.tensor([62010, 61000, 1, 50000 + 15, 62010], device="cuda", dtype=torch.int32)
+    big = DeviceState(w, inp, cap=64)
+    big.enable_box8()
+    ekv.ekv_stats_build(big.cfg, big.cache(), big.stats())
+    new = [torch.randn(5, heads[1], 128, device="cuda").bfloat16() for _ in range(2)]
+
+    def scores(st, k_new, v_new):
+        lens, cfg, q = st.inp["seq_lens"], st.cfg, st.inp["q"]
+        box8, got = torch.zeros_like(st.box), []
+        ekv.ekv_score_pages(cfg, q, st.stats(), lens, ekv.EKV_SCORE_BOTH, st.box, st.mu, st.sigma)
+        ekv.ekv_score_pages(cfg, q, st.stats(), lens, ekv.EKV_SCORE_BOX8, box8)
+        got += [x.clone() for x in (st.box, st.mu, st.sigma, box8)]
+        for mode in (ekv.EKV_SCORE_BOTH, ekv.EKV_SCORE_BOX8):     # the same token twice at one length: idempotent
+            ekv.ekv_append_score_pages(cfg, st.cache(), st.stats(), k_new, v_new, q, mode,
+                                       box=st.box if mode == ekv.EKV_SCORE_BOTH else box8, mu=st.mu, sigma=st.sigma)
+        torch.cuda.synchronize()
+        return got + [x.clone() for x in (st.box, st.mu, st.sigma, box8)]
+
+    singles = []
+    for b in range(5):                                  # before the batch appends: the pools are shared
+        st = alone(w, inp, b, cap=64)
+        st.box_stats, st.gauss_stats = big.box_stats[b:b + 1].clone(), big.gauss_stats[b:b + 1].clone()
+        st.box8_stats = big.box8_stats[b:b + 1].clone()
+        singles.append(scores(st, new[0][b:b + 1].contiguous(), new[1][b:b + 1].contiguous()))
+    for whole, *parts in zip(scores(big, *new), *singles):
+        for b in range(5):
+            assert same(whole[b:b + 1], parts[b])
