@@ -170,7 +170,7 @@ template <int G> struct RowHeads {
 // 270.6 / 246.7 (1.07 GB, 4.6 TB/s in the pass; eight heads 377.7 / 283.7), per-head lists of 5000 tokens, 128 rows, pages of 8
 // 37.8 / 29.0; float32, 2 x 131072 tokens in pages of 8 242.6 / 231.0, 128 lists of 5000 tokens in pages of 16 52.7 / 44.5.
 // Not faster: float32 pages of 48 with four heads, all pages 227.5 / 231.5 (twelve steps behind one lookup before).
-template <typename T, int G, int MODE, bool PRE_GLOBAL>
+template <typename T, int G, int MODE, bool STREAM, bool PRE_GLOBAL>
 __global__ __launch_bounds__(kScoreThreads)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? (G <= 4 ? 8 : 6) : G == 1 ? 8 : G == 2 ? 6 : G == 4 ? 5 : 4)))
 void decode_scores_steps_kernel(const ScoreArgs A) {
@@ -229,7 +229,7 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
       for (int s = 0; s < CS; ++s) {
         const int row = __builtin_amdgcn_readlane(l_row, rq + rq_s + s);
         const T* p = k_pool + (size_t)(uint32_t)row * kD;
-        if constexpr (MFMA) a[s] = *reinterpret_cast<const uint4*>(p);
+        if constexpr (MFMA) a[s] = load16<STREAM>(p);
         else {
           a[2 * s] = *reinterpret_cast<const uint4*>(p);
           a[2 * s + 1] = *reinterpret_cast<const uint4*>(p + 4);
@@ -370,7 +370,7 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
 // of 16 tokens at a time (the next chunk is requested before the current one is consumed).  The page-list and block-table entries
 // of up to 64 page slots are resolved at once, one slot per lane (two dependent vector loads per batch of 64 / GP
 // items instead of two per page), and handed out with v_readlane.
-template <int G, int MODE, int PT, bool PRE_GLOBAL>
+template <int G, int MODE, int PT, bool STREAM, bool PRE_GLOBAL>
 __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 8 : 6)))
 void decode_scores_mfma_kernel(const ScoreArgs A) {
   constexpr bool DENSE = MODE == kAllPages, GROUPED = MODE != kPerHead;
@@ -444,7 +444,7 @@ void decode_scores_mfma_kernel(const ScoreArgs A) {
       const int phys = __builtin_amdgcn_readlane(l_phys, pg);
       const bf16_t* kc = k_pool + (((size_t)phys * A.HkvPool + hkv) * PT + 16 * t) * kD + lane_off;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) a[s] = *reinterpret_cast<const uint4*>(kc + s * 4 * kD);
+      for (int s = 0; s < 4; ++s) a[s] = load16<STREAM>(kc + s * 4 * kD);
     };
     auto consume = [&](int ck, const uint4 (&a)[4]) {
       const int pg = ck / KEEP, t = ck % KEEP;
@@ -2251,17 +2251,33 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
     sa.pre_g = pre_ws;
     hipLaunchKernelGGL((unit_prefix_kernel<MODE>), dim3(1), dim3(1024), 0, st, sa, pre_ws);
   }
-#define EKV_SCORES(KERNEL, ...)                                                                          \
-  do {                                                                                                   \
-    if (pre_global) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), grid, block, lds, st, sa);            \
-    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, false>), grid, block, lds, st, sa);                      \
+  // K of a large call over all pages, or over lists that the heads of a group share, passes once and goes past the caches
+  // (load16<true>): otherwise it pushes out the lines of scores, which the wavefronts fill 64 bytes at a time, before they are
+  // whole.  Calls, us, kept / past the caches: all pages of 1 x 1M tokens 473 / 427, 8 x 256K in pages of 32 954 / 925,
+  // 2 x 128K for 64 heads 140.7 / 124.4, 2 x 128K in pages of 12 135.1 / 125.7, 2 x 32K (134 MB) 41.8 / 37.4; 1 x 32K 23.4 /
+  // 22.5 with four inputs in turn, 22.4 / 22.9 with three, which the last cache holds, 1 x 4K 13.4 / 13.8.  Group steps, whose
+  // lists follow a stream of statistics, by the capacity, all that the host knows (it is filled to half here): 134 MB 61.6 /
+  // 56.3, 86 MB 87 / 86, 67 MB 34.7 / 34.1, 17 MB 26.4 / 27.2.  Lists per head meet in the caches (16 x 16K Gaussian step 253
+  // / 324), and two loads take a float32 row in halves of its lines (2 x 128K 229 / 249): both keep theirs.
+  const long long k_bytes = (long long)sa.U * (MODE == kAllPages ? dm.Mmax : dm.cap) * dm.P * kD * (long long)sizeof(bf16_t);
+  const bool past_caches = MODE != kPerHead && k_bytes >= (MODE == kAllPages ? kStreamKBytes : kStreamKBytes / 2);
+#define EKV_SCORES_S(KERNEL, STREAM, ...)                                                                 \
+  do {                                                                                                       \
+    if (pre_global) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, STREAM, true>), grid, block, lds, st, sa);     \
+    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, STREAM, false>), grid, block, lds, st, sa);               \
+  } while (0)
+#define EKV_SCORES(KERNEL, ...)                                                  \
+  do {                                                                           \
+    if (past_caches) EKV_SCORES_S(KERNEL, (MODE != kPerHead), __VA_ARGS__);       \
+    else EKV_SCORES_S(KERNEL, false, __VA_ARGS__);                                \
   } while (0)
   if (dm.dtype == EKV_BF16 && dm.P == 16) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 16);
   else if (dm.dtype == EKV_BF16 && dm.P == 32) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 32);
   else if (dm.dtype == EKV_BF16 && dm.P == 64) EKV_SCORES(decode_scores_mfma_kernel, G, MODE, 64);
   else if (dm.dtype == EKV_BF16) EKV_SCORES(decode_scores_steps_kernel, bf16_t, G, MODE);
-  else EKV_SCORES(decode_scores_steps_kernel, float, G, MODE);
+  else EKV_SCORES_S(decode_scores_steps_kernel, false, float, G, MODE);
 #undef EKV_SCORES
+#undef EKV_SCORES_S
 }
 
 // Pass 2: one workgroup per row; four wavefronts, and four rows to a compute unit, for many short rows.  A flat row outgrows

@@ -26,9 +26,10 @@ constexpr int kPreGroups = 16384;         // rows of at most this many groups ar
 constexpr int kFilterMaxSlices = 1024;    // ... unless they would need more slices than this
 constexpr int kFilterSliceCap = 4096;     // candidates kept per slice (the solve holds this many in LDS)
 
-// Streams of at least this many bytes -- the eight L2s together hold as many -- are read past the caches (load16<true>).
-// What is smaller may still be there from the call before, and is fetched no faster.  Sides measured at the launchers.
-constexpr long long kStreamBytes = 32ll << 20;
+// Streams of at least this many bytes are read past the caches (load16<true>).  Smaller ones may still be there from the call
+// before, and a fetch would be no faster: statistics, of which a step has several tables, from the size of all L2s together,
+// K from half the size of the last cache.  Both sides as measured stand at the launchers.
+constexpr long long kStreamStatsBytes = 32ll << 20, kStreamKBytes = 128ll << 20;
 
 struct DecodeWorkspace {
   float* z;        // [B*Hq][zstride] candidate scores z_j (or -inf where masked)

@@ -379,13 +379,13 @@ static void launch_score_GA(const Dims& dm, const void* q, const ekv_stats_view&
   if (dm.dtype == EKV_BF16) {
     // Statistics are read once a step.  Past the caches they leave room there for the pages and scores the rest of the step
     // shares, and stream faster.  Whole steps on changing inputs, us, kept / past the caches: top-k on 268 MB (1 x 1M tokens)
-    // 111.5 / 107.1 and on 134 MB (16 x 32K) 60.7 / 55.8, 8-bit groups on 134 MB 61.6 / 53.0, Gaussian on 67 MB (1 x 256K)
-    // 64.3 / 58.7, top-k on 134 MB (64 x 8K) 58.4 / 54.9 and on 34 MB 33.7 / 33.3; but on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
+    // 112.1 / 107.2, on 134 MB (64 x 8K) 58.4 / 54.9 and on 34 MB 33.7 / 33.3, 8-bit groups on 134 MB 62.0 / 54.3, Gaussian on
+    // 67 MB (1 x 256K) 64.3 / 58.7; but top-k on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
     const long long records = (long long)dm.B * dm.Hkv * dm.Mmax;
     const auto launch = [&](auto kind, const dim3& g, const void* stats, float* out0, float* out1, int group_max, const ScoreAppend& ap) {
       constexpr int KIND = decltype(kind)::value;
       const long long bytes = records * (KIND == kKindBox8 ? 2 * kD : 4 * kD);
-      if (bytes >= kStreamBytes)
+      if (bytes >= kStreamStatsBytes)
         hipLaunchKernelGGL((score_pages_mfma_kernel<G, KIND, APPEND, true>), g, block, 0, st, (const bf16_t*)q, stats, seq_lens,
                            out0, out1, dm.Hkv, dm.P, dm.Mmax, dm.scale, group_max, ap);
       else

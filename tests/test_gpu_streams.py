@@ -1,4 +1,4 @@
-"""Calls large enough to read their streams past the caches (32 MiB and more of statistics) against the same sequences one
+"""Calls large enough to read their streams past the caches (32 MiB of statistics, 128 MiB of K) against the same sequences one
 by one, which are small enough not to: bit for bit, since only the kind of the loads differs."""
 import pytest
 import torch
@@ -52,3 +52,30 @@ def test_scores_of_large_statistics(heads):
     for whole, *parts in zip(scores(big, *new), *singles):
         for b in range(5):
             assert same(whole[b:b + 1], parts[b])
+
+
+@pytest.mark.parametrize("page", [12, 16, 32, 64])
+@pytest.mark.parametrize("heads", [(8, 8), (16, 8), (32, 8), (64, 8)])
+def test_decode_of_large_calls(heads, page):
+    # K of five sequences 143 MB, of one 29 MB
+    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 14001, page, "bf16")
+    inp = synth.make_inputs(w, 6 + page, device="cuda")
+    inp["seq_lens"] = torch.tensor([14001, 13990, 1, 4097, 14001], device="cuda", dtype=torch.int32)
+    pages = w.pages_per_seq
+
+    def decode(st, lens):
+        st.out.zero_()
+        ekv.ekv_decode_full(st.cfg, st.inp["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL))
+        got = [x.clone() for x in (st.out, st.tau, st.supp)]
+        idx = torch.arange(pages, device="cuda", dtype=torch.int32).expand(st.w.batch, heads[1], pages).contiguous()
+        cnt = ((lens + page - 1) // page)[:, None].expand(st.w.batch, heads[1]).contiguous()
+        ekv.ekv_decode_sparse_group(st.cfg, st.inp["q"], st.cache(), idx, cnt, st.out, st.tau, st.supp,
+                                    st.workspace(ekv.EKV_OP_DECODE_SPARSE))
+        torch.cuda.synchronize()
+        return got + [x.clone() for x in (st.out, st.tau, st.supp)]
+
+    whole = decode(DeviceState(w, inp), inp["seq_lens"])
+    for b in range(5):
+        st = alone(w, inp, b)
+        for x, part in zip(whole, decode(st, st.inp["seq_lens"])):
+            assert same(x[b:b + 1], part)
