@@ -65,11 +65,14 @@ template <> __device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float
 template <typename T> struct Raw8;
 template <> struct Raw8<float> { float4 a, b; };
 template <> struct Raw8<bf16_t> { uint4 a; };
-__device__ __forceinline__ void load_raw8(const float* p, Raw8<float>& r) {
+// STREAM: as in load16, of bf16 only; two loads take a float32 row in halves of its lines, the second finds its half in a cache
+template <bool STREAM = false> __device__ __forceinline__ void load_raw8(const float* p, Raw8<float>& r) {
   r.a = *reinterpret_cast<const float4*>(p);
   r.b = *reinterpret_cast<const float4*>(p + 4);
 }
-__device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = *reinterpret_cast<const uint4*>(p); }
+template <bool STREAM = false> __device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) {
+  r.a = load16<STREAM>(p);
+}
 __device__ __forceinline__ void widen8(const Raw8<float>& r, float (&x)[8]) {
   x[0] = r.a.x; x[1] = r.a.y; x[2] = r.a.z; x[3] = r.a.w;
   x[4] = r.b.x; x[5] = r.b.y; x[6] = r.b.z; x[7] = r.b.w;
@@ -81,20 +84,18 @@ __device__ __forceinline__ void widen8(const Raw8<bf16_t>& r, float (&x)[8]) {
   x[6] = __uint_as_float(r.a.w << 16); x[7] = __uint_as_float(r.a.w & 0xffff0000u);
 }
 
-template <typename T> __device__ __forceinline__ void store8(T* p, const float (&x)[8]);
-
-template <> __device__ __forceinline__ void store8<float>(float* p, const float (&x)[8]) {
+// STREAM: as in load_raw8
+template <bool STREAM = false> __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
   *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
   *reinterpret_cast<float4*>(p + 4) = make_float4(x[4], x[5], x[6], x[7]);
 }
-
-template <> __device__ __forceinline__ void store8<bf16_t>(bf16_t* p, const float (&x)[8]) {
+template <bool STREAM = false> __device__ __forceinline__ void store8(bf16_t* p, const float (&x)[8]) {
   uint4 a;
   a.x = float_to_bf16_bits(x[0]) | ((uint32_t)float_to_bf16_bits(x[1]) << 16);
   a.y = float_to_bf16_bits(x[2]) | ((uint32_t)float_to_bf16_bits(x[3]) << 16);
   a.z = float_to_bf16_bits(x[4]) | ((uint32_t)float_to_bf16_bits(x[5]) << 16);
   a.w = float_to_bf16_bits(x[6]) | ((uint32_t)float_to_bf16_bits(x[7]) << 16);
-  *reinterpret_cast<uint4*>(p) = a;
+  store16<STREAM>(p, a);
 }
 
 // ---- 8-bit bounds: OCP E4M3 (bias 7, 3 mantissa bits, subnormals, max 448, 0x7f = NaN) -----------

@@ -71,10 +71,10 @@ __device__ __forceinline__ void page_stats_wave(const T* __restrict__ kpage, int
     sd[i] = var;
   }
   if (r == 0) {
-    store8<T>(box_out + 8 * c, mn);
-    store8<T>(box_out + kD + 8 * c, mx);
-    store8<T>(gauss_out + 8 * c, avg);
-    store8<T>(gauss_out + kD + 8 * c, sd);
+    store8(box_out + 8 * c, mn);
+    store8(box_out + kD + 8 * c, mx);
+    store8(gauss_out + 8 * c, avg);
+    store8(gauss_out + kD + 8 * c, sd);
     if (box8_out != nullptr) store_box8_unit(box8_out + 16 * c, mn, mx);
   }
 }
@@ -98,12 +98,12 @@ __device__ __forceinline__ void append_token_wave(T* __restrict__ k_pool, T* __r
   if (lane < 16) {
     float x[8];
     load8<T>(knew + 8 * lane, x);
-    store8<T>(k_pool + page_off + (size_t)slot * kD + 8 * lane, x);
+    store8(k_pool + page_off + (size_t)slot * kD + 8 * lane, x);
   } else if (lane < 32 && v_new != nullptr) {
     float x[8];
     const int c = lane - 16;
     load8<T>(v_new + ((size_t)b * Hkv + h) * kD + 8 * c, x);
-    store8<T>(v_pool + page_off + (size_t)slot * kD + 8 * c, x);
+    store8(v_pool + page_off + (size_t)slot * kD + 8 * c, x);
   }
   const size_t rec = (((size_t)b * Hkv + h) * Mmax + p) * 2 * kD;
   page_stats_wave<T, PT>(k_pool + page_off, slot + 1, P, knew, slot, box + rec, gauss + rec,

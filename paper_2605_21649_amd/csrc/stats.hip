@@ -20,7 +20,7 @@ constexpr int kStatRowBatch = 4;     // row loads in flight per lane in the bulk
 // Bulk layout: the 16 lanes of a DPP row own one page; lane c holds channels 8c..8c+7 and walks the
 // page's rows itself, so no statistic crosses lanes; a wavefront covers four pages, each row load being
 // four 256-byte segments.  `kpage` points at the page's [P][128] block; tokens [0,cnt) are valid.
-template <typename T, int PT>   // PT = compile-time page size, 0 = runtime
+template <typename T, int PT, bool STREAM>   // PT = compile-time page size, 0 = runtime
 __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int cnt, int P_rt, bool all_full,
                                                 T* __restrict__ box_out, T* __restrict__ gauss_out,
                                                 uint8_t* __restrict__ box8_out) {
@@ -42,7 +42,7 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
     for (int t0 = 0; t0 < P; t0 += RB) {
       Raw8<T> raw[RB];
 #pragma unroll
-      for (int j = 0; j < RB; ++j) load_raw8(kpage + (size_t)(t0 + j) * kD + 8 * c, raw[j]);   // P % 4 == 0
+      for (int j = 0; j < RB; ++j) load_raw8<STREAM>(kpage + (size_t)(t0 + j) * kD + 8 * c, raw[j]);   // P % 4 == 0
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         float x[8];
@@ -63,7 +63,7 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
       Raw8<T> raw[RB];
 #pragma unroll
       for (int j = 0; j < RB; ++j)                       // rows past cnt re-read row 0: loads stay unconditional
-        load_raw8(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + 8 * c, raw[j]);
+        load_raw8<STREAM>(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + 8 * c, raw[j]);
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         const bool ok = t0 + j < cnt;
@@ -90,14 +90,14 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
     var[i] = fmaxf(fmaf(-m1, m1, t2 * inv_n), 0.f);      // m2 - avg^2, clamped at 0
     avg[i] = k0[i] + m1;
   }
-  store8<T>(box_out + 8 * c, mn);
-  store8<T>(box_out + kD + 8 * c, mx);
-  store8<T>(gauss_out + 8 * c, avg);
-  store8<T>(gauss_out + kD + 8 * c, var);
+  store8<true>(box_out + 8 * c, mn);
+  store8<true>(box_out + kD + 8 * c, mx);
+  store8<true>(gauss_out + 8 * c, avg);
+  store8<true>(gauss_out + kD + 8 * c, var);
   if (box8_out != nullptr) store_box8_unit(box8_out + 16 * c, mn, mx);
 }
 
-template <typename T, int PT>
+template <typename T, int PT, bool STREAM>
 __global__ __launch_bounds__(256) void stats_build_kernel(const T* __restrict__ k_pool,
                                                           const int32_t* __restrict__ block_table,
                                                           const int32_t* __restrict__ seq_lens,
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void stats_build_kernel(const T* __restrict__ 
   const size_t rec = (((size_t)b * Hkv + h) * Mmax + pc) * 2 * kD;
   const bool all_full = __all(cnt == P);
   if (blockIdx.x * 16 + (int)(threadIdx.x >> 6) * 4 >= M) return;      // whole wavefront past the end
-  if (p < M) page_stats_rows<T, PT>(kpage, cnt, P, all_full, box + rec, gauss + rec,
+  if (p < M) page_stats_rows<T, PT, STREAM>(kpage, cnt, P, all_full, box + rec, gauss + rec,
                                     box8 != nullptr ? box8 + rec : nullptr);   // 256 bytes per page there
 }
 
@@ -134,11 +134,20 @@ __global__ __launch_bounds__(64) void stats_append_kernel(T* __restrict__ k_pool
                            blockIdx.y, blockIdx.x, Hkv, HkvPool, P, Mmax, n_phys);
 }
 
+// The statistics, and K of a large build, go past the caches (bf16): they stream faster so.  us, neither / K / statistics /
+// both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.3 GB, 6.1 TB/s), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
+// 64 121.5 / 112 / 115 / 104, 1 x 64K (134 MB of K) 45.6 / 38.7 / 43.3 / 38.4.  K of a smaller build may still lie in the last
+// cache, where the prefill wrote it: 1 x 32K 25.5 / 22.8 / 16.5 / 22.2, 1 x 16K 9.9 / 11.4 / 9.2 / 10.4, 1 x 4K 6.6 / 7.0 / 6.5 / 6.9.
 template <typename T, int PT>
 static void launch_build_T(const Dims& dm, const ekv_cache_view& c, const ekv_stats_view& s, hipStream_t st) {
   dim3 grid((dm.Mmax + 15) / 16, dm.Hkv, dm.B), block(256);
-  hipLaunchKernelGGL((stats_build_kernel<T, PT>), grid, block, 0, st, (const T*)c.k_pool, c.block_table, c.seq_lens,
-                     (T*)s.box, (T*)s.gauss, (uint8_t*)s.box8, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, c.n_phys_pages);
+  const auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, (const T*)c.k_pool, c.block_table, c.seq_lens, (T*)s.box, (T*)s.gauss,
+                       (uint8_t*)s.box8, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, c.n_phys_pages);
+  };
+  const long long k_bytes = (long long)dm.B * dm.Hkv * dm.Mmax * dm.P * kD * (long long)sizeof(T);
+  if (sizeof(T) == 2 && k_bytes >= kStreamKBytes) launch(stats_build_kernel<T, PT, sizeof(T) == 2>);
+  else launch(stats_build_kernel<T, PT, false>);
 }
 template <typename T, int PT>
 static void launch_append_T(const Dims& dm, const ekv_cache_view& c, const ekv_stats_view& s, const void* k_new,

@@ -79,3 +79,22 @@ def test_decode_of_large_calls(heads, page):
         st = alone(w, inp, b)
         for x, part in zip(whole, decode(st, st.inp["seq_lens"])):
             assert same(x[b:b + 1], part)
+
+
+@pytest.mark.parametrize("page", [12, 16, 32, 64])
+def test_build_of_large_caches(page):
+    # K of five sequences 143 MB, of one 29 MB
+    w = synth.Workload("streams", 5, 8, 8, 128, 14001, page, "bf16")
+    inp = synth.make_inputs(w, 7 + page, device="cuda")
+    inp["seq_lens"] = torch.tensor([14001, 13990, 1, 4097, 14001], device="cuda", dtype=torch.int32)
+
+    def build(st):
+        st.enable_box8()
+        ekv.ekv_stats_build(st.cfg, st.cache(), st.stats())
+        torch.cuda.synchronize()
+        return st.box_stats, st.gauss_stats, st.box8_stats
+
+    whole = build(DeviceState(w, inp))
+    for b in range(5):
+        for x, part in zip(whole, build(alone(w, inp, b))):
+            assert same(x[b:b + 1], part)
