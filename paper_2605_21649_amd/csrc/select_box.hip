@@ -8,6 +8,7 @@
 //   mark   (slices of 4096 pages x heads): membership bits of the given list in LDS, threshold test,
 //          ordered compaction of the slice into scratch + (total, added) counts;
 //   gather (one workgroup per head): prefix over the slices, copy into page_idx_out, flags.
+// Rows of up to 16384 pages are one slice, and the marking workgroup writes the output itself.
 #include "ekv_device.h"
 #include "ekv_internal.h"
 
@@ -16,6 +17,7 @@ namespace ekv {
 constexpr int kBxThreads = 256;
 constexpr int kBxItems = 16;
 constexpr int kBxSlice = kBxThreads * kBxItems;      // 4096 pages
+constexpr int kBxRowThreads = 1024;                  // of the one launch for a whole row, up to kBxItems pages each
 constexpr int kBxGatherThreads = 1024;
 constexpr int kBxMaxSlices = 1024;
 
@@ -35,42 +37,54 @@ struct BoxWs {
   int NS;
 };
 
-__global__ __launch_bounds__(kBxThreads) void box_mark_kernel(const float* __restrict__ box,
-                                                              const int32_t* __restrict__ seq_lens,
-                                                              const float* __restrict__ tau_lo,
-                                                              const int32_t* __restrict__ page_idx_in,
-                                                              const int32_t* __restrict__ n_sel_in, BoxWs ws,
-                                                              float a, int Hq, int P, int Mmax, int cap) {
-  __shared__ uint32_t bits[kBxSlice / 32];
-  __shared__ int wcnt[kBxThreads / 64][2];
+struct BoxOut { int32_t* page_idx; int32_t* n_sel; int32_t* n_added; int32_t* overflow; };
+
+// WHOLE: the slice is the row (the grid has one per head) and the result goes to `out`, whose page list may be the given
+// one: a workgroup has read its row of it before it writes.  Bounded by the latency of its loads and of the launch.
+template <int THREADS, int ITEMS, bool WHOLE>
+__global__ __launch_bounds__(THREADS) void box_mark_kernel(const float* __restrict__ box, const int32_t* __restrict__ seq_lens,
+                                                           const float* __restrict__ tau_lo, const int32_t* page_idx_in,
+                                                           const int32_t* n_sel_in, BoxWs ws, BoxOut out, float a, int Hq,
+                                                           int P, int Mmax, int cap) {
+  constexpr int SLICE = THREADS * ITEMS, WAVES = THREADS / 64;
+  __shared__ uint32_t bits[SLICE / 32];
+  __shared__ int wcnt[WAVES][2];
   const int bh = blockIdx.y, slice = blockIdx.x, b = bh / Hq, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n = seq_lens[b];
   const int M = min((n + P - 1) / P, Mmax);
-  int32_t* cnt_out = ws.cnt + ((size_t)bh * ws.NS + slice) * 2;
-  const int p_lo = slice * kBxSlice;
-  if (p_lo >= M) { if (tid == 0) { cnt_out[0] = 0; cnt_out[1] = 0; } return; }
+  const int p_lo = slice * SLICE;
+  const auto put_counts = [&](int tot, int tot_new) {
+    if (tid != 0) return;
+    if constexpr (WHOLE) {
+      out.n_sel[bh] = min(tot, cap); out.n_added[bh] = tot_new; out.overflow[bh] = tot > cap ? 1 : 0;
+    } else {
+      int32_t* cnt_out = ws.cnt + ((size_t)bh * ws.NS + slice) * 2;
+      cnt_out[0] = tot; cnt_out[1] = tot_new;
+    }
+  };
+  if (p_lo >= M) { put_counts(0, 0); return; }
   const float thr = tau_lo[bh];
   const float* box_r = box + (size_t)bh * Mmax;
-  // wavefront w owns 1024 consecutive pages: (load i, lane) order is page order
-  const int page0 = p_lo + w * (kBxSlice / (kBxThreads / 64)) + lane;
-  float sv[kBxItems];
+  // wavefront w owns 64 * ITEMS consecutive pages: (load i, lane) order is page order
+  const int page0 = p_lo + w * 64 * ITEMS + lane;
+  float sv[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kBxItems; ++i) sv[i] = box_r[min(page0 + i * 64, M - 1)];
-  if (tid < kBxSlice / 32) bits[tid] = 0u;
+  for (int i = 0; i < ITEMS; ++i) sv[i] = box_r[min(page0 + i * 64, M - 1)];
+  if (tid < SLICE / 32) bits[tid] = 0u;
   __syncthreads();
   if (page_idx_in != nullptr) {
     const int n_in = min(max(n_sel_in[bh], 0), cap);
     const int32_t* in = page_idx_in + (size_t)bh * cap;
-    for (int e = tid; e < n_in; e += kBxThreads) {
+    for (int e = tid; e < n_in; e += THREADS) {
       const int p = in[e] - p_lo;
-      if (p >= 0 && p < kBxSlice && p + p_lo < M) atomicOr(&bits[p >> 5], 1u << (p & 31));
+      if (p >= 0 && p < SLICE && p + p_lo < M) atomicOr(&bits[p >> 5], 1u << (p & 31));
     }
   }
   __syncthreads();
   uint32_t keep = 0;
   int c_all = 0, c_new = 0;
 #pragma unroll
-  for (int i = 0; i < kBxItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const int p = page0 + i * 64, pl = p - p_lo;
     const bool listed = (bits[pl >> 5] >> (pl & 31)) & 1u;
     const bool above = p < M && a * sv[i] > thr;
@@ -83,17 +97,19 @@ __global__ __launch_bounds__(kBxThreads) void box_mark_kernel(const float* __res
   if (lane == 0) { wcnt[w][0] = c_all; wcnt[w][1] = c_new; }
   __syncthreads();
   int o_run = 0, tot = 0, tot_new = 0;
-  for (int i = 0; i < kBxThreads / 64; ++i) { if (i < w) o_run += wcnt[i][0]; tot += wcnt[i][0]; tot_new += wcnt[i][1]; }
-  int32_t* list = ws.list + ((size_t)bh * ws.NS + slice) * kBxSlice;
+  for (int i = 0; i < WAVES; ++i) { if (i < w) o_run += wcnt[i][0]; tot += wcnt[i][0]; tot_new += wcnt[i][1]; }
+  int32_t* list = WHOLE ? out.page_idx + (size_t)bh * cap : ws.list + ((size_t)bh * ws.NS + slice) * SLICE;
+  const int room = WHOLE ? cap : SLICE;
   const uint64_t lt = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int i = 0; i < kBxItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const bool in = (keep >> i) & 1u;
     const uint64_t mk = __ballot(in);
-    if (in) list[o_run + __popcll(mk & lt)] = page0 + i * 64;
+    const int o = o_run + __popcll(mk & lt);
+    if (in && o < room) list[o] = page0 + i * 64;
     o_run += __popcll(mk);
   }
-  if (tid == 0) { cnt_out[0] = tot; cnt_out[1] = tot_new; }
+  put_counts(tot, tot_new);
 }
 
 __global__ __launch_bounds__(kBxGatherThreads) void box_gather_kernel(BoxWs ws, int32_t* __restrict__ page_idx_out,
@@ -138,8 +154,21 @@ void launch_select_box_threshold(const Dims& dm, const float* box, const int32_t
   ws.NS = box_slices(dm);
   ws.cnt = (int32_t*)workspace;
   ws.list = ws.cnt + (size_t)BH * ws.NS * 2;
-  hipLaunchKernelGGL(box_mark_kernel, dim3(ws.NS, BH), dim3(kBxThreads), 0, st, box, seq_lens, tau_lo, page_idx_in,
-                     n_sel_in, ws, dm.a, dm.Hq, dm.P, dm.Mmax, dm.cap);
+  const BoxOut out{page_idx_out, n_sel_out, n_added, overflow};
+  // Up to 16384 pages one workgroup holds a row, and one launch is enough.  Calls, us, two launches / one, lists of 4 % and of
+  // all pages: 48 rows of 2626 pages 8.0 / 5.6, 8.0 / 5.6; 128 of 8192 8.4 / 6.2, 11.5 / 6.6; 32 of 16384 8.3 / 6.1, 14.6 / 6.3;
+  // 512 of 16384 15.7 / 10.1, 29.3 / 15.4; 2048 of 512 16.3 / 14.3, 17.1 / 14.7; 1024 of 8192 16.0 / 16.4, 28.4 / 19.9.
+  if (dm.Mmax <= kBxRowThreads * kBxItems) {
+    const auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(1, BH), dim3(kBxRowThreads), 0, st, box, seq_lens, tau_lo, page_idx_in, n_sel_in, ws, out,
+                         dm.a, dm.Hq, dm.P, dm.Mmax, dm.cap);
+    };
+    if (dm.Mmax <= 4 * kBxRowThreads) launch(box_mark_kernel<kBxRowThreads, 4, true>);
+    else launch(box_mark_kernel<kBxRowThreads, kBxItems, true>);
+    return;
+  }
+  hipLaunchKernelGGL((box_mark_kernel<kBxThreads, kBxItems, false>), dim3(ws.NS, BH), dim3(kBxThreads), 0, st, box, seq_lens,
+                     tau_lo, page_idx_in, n_sel_in, ws, out, dm.a, dm.Hq, dm.P, dm.Mmax, dm.cap);
   hipLaunchKernelGGL(box_gather_kernel, dim3(BH), dim3(kBxGatherThreads), 0, st, ws, page_idx_out, n_sel_out, n_added,
                      overflow, dm.cap);
 }
