@@ -65,14 +65,20 @@ template <> __device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float
 template <typename T> struct Raw8;
 template <> struct Raw8<float> { float4 a, b; };
 template <> struct Raw8<bf16_t> { uint4 a; };
-// STREAM: as in load16, of bf16 only; two loads take a float32 row in halves of its lines, the second finds its half in a cache
-template <bool STREAM = false> __device__ __forceinline__ void load_raw8(const float* p, Raw8<float>& r) {
+__device__ __forceinline__ void load_raw8(const float* p, Raw8<float>& r) {
   r.a = *reinterpret_cast<const float4*>(p);
   r.b = *reinterpret_cast<const float4*>(p + 4);
 }
-template <bool STREAM = false> __device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) {
-  r.a = load16<STREAM>(p);
+__device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = load16(p); }
+// A row in the sixteen lanes of a DPP row, for streams (STREAM as in load16): bf16 channels 8c..8c+7 in lane c, float32
+// channels 4c..4c+3 and 64+4c..64+4c+3, so that either type takes whole lines with each load; eight channels in a row take a
+// float32 line in halves, and one that is not kept is fetched twice.  p: the row's first channel of the lane.
+template <typename T> __device__ __forceinline__ constexpr int lane_channel(int c) { return sizeof(T) == 4 ? 4 * c : 8 * c; }
+template <bool STREAM = false> __device__ __forceinline__ void load_row8(const float* p, Raw8<float>& r) {
+  r.a = __builtin_bit_cast(float4, load16<STREAM>(p));
+  r.b = __builtin_bit_cast(float4, load16<STREAM>(p + kD / 2));
 }
+template <bool STREAM = false> __device__ __forceinline__ void load_row8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = load16<STREAM>(p); }
 __device__ __forceinline__ void widen8(const Raw8<float>& r, float (&x)[8]) {
   x[0] = r.a.x; x[1] = r.a.y; x[2] = r.a.z; x[3] = r.a.w;
   x[4] = r.b.x; x[5] = r.b.y; x[6] = r.b.z; x[7] = r.b.w;
@@ -84,19 +90,25 @@ __device__ __forceinline__ void widen8(const Raw8<bf16_t>& r, float (&x)[8]) {
   x[6] = __uint_as_float(r.a.w << 16); x[7] = __uint_as_float(r.a.w & 0xffff0000u);
 }
 
-// STREAM: as in load_raw8
-template <bool STREAM = false> __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
-  *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
-  *reinterpret_cast<float4*>(p + 4) = make_float4(x[4], x[5], x[6], x[7]);
-}
-template <bool STREAM = false> __device__ __forceinline__ void store8(bf16_t* p, const float (&x)[8]) {
+__device__ __forceinline__ uint4 pack8(const float (&x)[8]) {
   uint4 a;
   a.x = float_to_bf16_bits(x[0]) | ((uint32_t)float_to_bf16_bits(x[1]) << 16);
   a.y = float_to_bf16_bits(x[2]) | ((uint32_t)float_to_bf16_bits(x[3]) << 16);
   a.z = float_to_bf16_bits(x[4]) | ((uint32_t)float_to_bf16_bits(x[5]) << 16);
   a.w = float_to_bf16_bits(x[6]) | ((uint32_t)float_to_bf16_bits(x[7]) << 16);
-  store16<STREAM>(p, a);
+  return a;
 }
+__device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
+  *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+  *reinterpret_cast<float4*>(p + 4) = make_float4(x[4], x[5], x[6], x[7]);
+}
+__device__ __forceinline__ void store8(bf16_t* p, const float (&x)[8]) { store16(p, pack8(x)); }
+// the lane's channels of load_row8, past the caches
+__device__ __forceinline__ void stream_row8(float* p, const float (&x)[8]) {
+  store16<true>(p, __builtin_bit_cast(uint4, make_float4(x[0], x[1], x[2], x[3])));
+  store16<true>(p + kD / 2, __builtin_bit_cast(uint4, make_float4(x[4], x[5], x[6], x[7])));
+}
+__device__ __forceinline__ void stream_row8(bf16_t* p, const float (&x)[8]) { store16<true>(p, pack8(x)); }
 
 // ---- 8-bit bounds: OCP E4M3 (bias 7, 3 mantissa bits, subnormals, max 448, 0x7f = NaN) -----------
 // Directed rounding of a float: UP gives the code of the smallest format value >= x, otherwise of the

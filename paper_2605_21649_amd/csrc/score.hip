@@ -275,7 +275,7 @@ void score_pages_mfma_kernel(const bf16_t* __restrict__ q,
 }
 
 // float32 statistics: one wavefront step = two page records, 32 lanes x 8 channels each.
-template <int G, bool GAUSS, bool APPEND>
+template <int G, bool GAUSS, bool APPEND, bool STREAM>
 __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __restrict__ q,
                                                               const float* __restrict__ stats,
                                                               const int32_t* __restrict__ seq_lens,
@@ -305,8 +305,10 @@ __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __res
   float coef[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
+    Raw8<float> raw;
+    load_row8(q + ((size_t)b * Hq + h * G + g) * kD + lane_channel<float>(c), raw);
     float qv[8];
-    load8<float>(q + ((size_t)b * Hq + h * G + g) * kD + 8 * c, qv);
+    widen8(raw, qv);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (GAUSS) coef[g][i] = which ? qv[i] * qv[i] : qv[i];
@@ -315,11 +317,17 @@ __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __res
   }
   const int pw0 = tile0 + w * (kScoreTile / 4);
   const float* base = stats + (((size_t)b * Hkv + h) * Mmax) * 2 * kD;
+  Raw8<float> rec[kSteps];
+#pragma unroll
   for (int it = 0; it < kSteps; ++it) {
     const int p = min(pw0 + 2 * it + half, M - 1);  // clamped: pages past the end are masked on output
+    load_row8<STREAM>(base + ((size_t)p * 2 + which) * kD + lane_channel<float>(c), rec[it]);
+  }
+#pragma unroll
+  for (int it = 0; it < kSteps; ++it) {
     const int pt = w * (kScoreTile / 4) + 2 * it + half;
     float x[8];
-    load8<float>(base + ((size_t)p * 2 + which) * kD + 8 * c, x);
+    widen8(rec[it], x);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       float acc = 0.f;
@@ -376,12 +384,12 @@ static void launch_score_GA(const Dims& dm, const void* q, const ekv_stats_view&
   if (ap0.mode == 1 && (mode & EKV_SCORE_BOX)) ap_gauss.mode = 2;
   const dim3 grid = score_grid(dm, kScoreTile, APPEND && ap_box.mode == 1, &ap_box);       // 512-byte records
   const dim3 grid_g = score_grid(dm, kScoreTile, APPEND && ap_gauss.mode == 1, &ap_gauss);
+  const long long records = (long long)dm.B * dm.Hkv * dm.Mmax;
   if (dm.dtype == EKV_BF16) {
     // Statistics are read once a step.  Past the caches they leave room there for the pages and scores the rest of the step
     // shares, and stream faster.  Whole steps on changing inputs, us, kept / past the caches: top-k on 268 MB (1 x 1M tokens)
     // 112.1 / 107.2, on 134 MB (64 x 8K) 58.4 / 54.9 and on 34 MB 33.7 / 33.3, 8-bit groups on 134 MB 62.0 / 54.3, Gaussian on
     // 67 MB (1 x 256K) 64.3 / 58.7; but top-k on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
-    const long long records = (long long)dm.B * dm.Hkv * dm.Mmax;
     const auto launch = [&](auto kind, const dim3& g, const void* stats, float* out0, float* out1, int group_max, const ScoreAppend& ap) {
       constexpr int KIND = decltype(kind)::value;
       const long long bytes = records * (KIND == kKindBox8 ? 2 * kD : 4 * kD);
@@ -400,12 +408,19 @@ static void launch_score_GA(const Dims& dm, const void* q, const ekv_stats_view&
     if (mode & EKV_SCORE_BOX) launch(std::integral_constant<int, kKindBox>{}, grid, s.box, box, nullptr, gmax, ap_box);
     if (mode & EKV_SCORE_GAUSS) launch(std::integral_constant<int, kKindGauss>{}, grid_g, s.gauss, mu, sigma, 0, ap_gauss);
   } else {
-    if (mode & EKV_SCORE_BOX)
-      hipLaunchKernelGGL((score_pages_f32_kernel<G, false, APPEND>), grid, block, 0, st, (const float*)q,
-                         (const float*)s.box, seq_lens, box, (float*)nullptr, dm.Hkv, dm.P, dm.Mmax, dm.scale, gmax, ap_box);
-    if (mode & EKV_SCORE_GAUSS)
-      hipLaunchKernelGGL((score_pages_f32_kernel<G, true, APPEND>), grid_g, block, 0, st, (const float*)q,
-                         (const float*)s.gauss, seq_lens, mu, sigma, dm.Hkv, dm.P, dm.Mmax, dm.scale, 0, ap_gauss);
+    // The same line; with all records of a wavefront requested at once, in whole lines, top-k steps on 134 MB (2 x 128K) and
+    // 67 MB (16 x 8K) 56.7 -> 48.4 and 42.7 -> 37.4.
+    const auto launch = [&](auto gauss, const dim3& g, const void* stats, float* out0, float* out1, int group_max, const ScoreAppend& ap) {
+      constexpr bool GAUSS = decltype(gauss)::value;
+      if (records * 8 * kD >= kStreamStatsBytes)
+        hipLaunchKernelGGL((score_pages_f32_kernel<G, GAUSS, APPEND, true>), g, block, 0, st, (const float*)q, (const float*)stats,
+                           seq_lens, out0, out1, dm.Hkv, dm.P, dm.Mmax, dm.scale, group_max, ap);
+      else
+        hipLaunchKernelGGL((score_pages_f32_kernel<G, GAUSS, APPEND, false>), g, block, 0, st, (const float*)q, (const float*)stats,
+                           seq_lens, out0, out1, dm.Hkv, dm.P, dm.Mmax, dm.scale, group_max, ap);
+    };
+    if (mode & EKV_SCORE_BOX) launch(std::false_type{}, grid, s.box, box, nullptr, gmax, ap_box);
+    if (mode & EKV_SCORE_GAUSS) launch(std::true_type{}, grid_g, s.gauss, mu, sigma, 0, ap_gauss);
   }
 }
 

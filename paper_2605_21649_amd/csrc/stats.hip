@@ -17,7 +17,7 @@ constexpr int kStatRowBatch = 4;     // row loads in flight per lane in the bulk
 // to the first token's value (so that m2 - avg^2 does not cancel for channels with a large common
 // offset), combined as (p0 + p1) + (p2 + p3).  Rows past cnt add exact zeros.
 
-// Bulk layout: the 16 lanes of a DPP row own one page; lane c holds channels 8c..8c+7 and walks the
+// Bulk layout: the 16 lanes of a DPP row own one page; lane c holds eight channels (load_row8) and walks the
 // page's rows itself, so no statistic crosses lanes; a wavefront covers four pages, each row load being
 // four 256-byte segments.  `kpage` points at the page's [P][128] block; tokens [0,cnt) are valid.
 template <typename T, int PT, bool STREAM>   // PT = compile-time page size, 0 = runtime
@@ -27,9 +27,11 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
   constexpr int RB = kStatRowBatch;
   static_assert(RB == 4, "one batch = one row of each partial sum");
   const int P = PT ? PT : P_rt;
-  const int c = threadIdx.x & 15;
+  const int c = threadIdx.x & 15, ch = lane_channel<T>(c);
+  Raw8<T> first;
+  load_row8(kpage + ch, first);
   float k0[8];
-  load8<T>(kpage + 8 * c, k0);
+  widen8(first, k0);
   float mn[8], mx[8], s1[4][8], s2[4][8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -42,7 +44,7 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
     for (int t0 = 0; t0 < P; t0 += RB) {
       Raw8<T> raw[RB];
 #pragma unroll
-      for (int j = 0; j < RB; ++j) load_raw8<STREAM>(kpage + (size_t)(t0 + j) * kD + 8 * c, raw[j]);   // P % 4 == 0
+      for (int j = 0; j < RB; ++j) load_row8<STREAM>(kpage + (size_t)(t0 + j) * kD + ch, raw[j]);   // P % 4 == 0
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         float x[8];
@@ -63,7 +65,7 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
       Raw8<T> raw[RB];
 #pragma unroll
       for (int j = 0; j < RB; ++j)                       // rows past cnt re-read row 0: loads stay unconditional
-        load_raw8<STREAM>(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + 8 * c, raw[j]);
+        load_row8<STREAM>(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + ch, raw[j]);
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         const bool ok = t0 + j < cnt;
@@ -90,10 +92,10 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
     var[i] = fmaxf(fmaf(-m1, m1, t2 * inv_n), 0.f);      // m2 - avg^2, clamped at 0
     avg[i] = k0[i] + m1;
   }
-  store8<true>(box_out + 8 * c, mn);
-  store8<true>(box_out + kD + 8 * c, mx);
-  store8<true>(gauss_out + 8 * c, avg);
-  store8<true>(gauss_out + kD + 8 * c, var);
+  stream_row8(box_out + ch, mn);
+  stream_row8(box_out + kD + ch, mx);
+  stream_row8(gauss_out + ch, avg);
+  stream_row8(gauss_out + kD + ch, var);
   if (box8_out != nullptr) store_box8_unit(box8_out + 16 * c, mn, mx);
 }
 
@@ -134,10 +136,11 @@ __global__ __launch_bounds__(64) void stats_append_kernel(T* __restrict__ k_pool
                            blockIdx.y, blockIdx.x, Hkv, HkvPool, P, Mmax, n_phys);
 }
 
-// The statistics, and K of a large build, go past the caches (bf16): they stream faster so.  us, neither / K / statistics /
+// The statistics, and K of a large build, go past the caches: they stream faster so.  us, neither / K / statistics /
 // both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.3 GB, 6.1 TB/s), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
 // 64 121.5 / 112 / 115 / 104, 1 x 64K (134 MB of K) 45.6 / 38.7 / 43.3 / 38.4.  K of a smaller build may still lie in the last
 // cache, where the prefill wrote it: 1 x 32K 25.5 / 22.8 / 16.5 / 22.2, 1 x 16K 9.9 / 11.4 / 9.2 / 10.4, 1 x 4K 6.6 / 7.0 / 6.5 / 6.9.
+// float32, by loads and stores of whole lines as well: 2 x 64K 137.6 -> 114.5, 1 x 16K 20.3 -> 13.7.
 template <typename T, int PT>
 static void launch_build_T(const Dims& dm, const ekv_cache_view& c, const ekv_stats_view& s, hipStream_t st) {
   dim3 grid((dm.Mmax + 15) / 16, dm.Hkv, dm.B), block(256);
@@ -146,7 +149,7 @@ static void launch_build_T(const Dims& dm, const ekv_cache_view& c, const ekv_st
                        (uint8_t*)s.box8, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, c.n_phys_pages);
   };
   const long long k_bytes = (long long)dm.B * dm.Hkv * dm.Mmax * dm.P * kD * (long long)sizeof(T);
-  if (sizeof(T) == 2 && k_bytes >= kStreamKBytes) launch(stats_build_kernel<T, PT, sizeof(T) == 2>);
+  if (k_bytes >= kStreamKBytes) launch(stats_build_kernel<T, PT, true>);
   else launch(stats_build_kernel<T, PT, false>);
 }
 template <typename T, int PT>

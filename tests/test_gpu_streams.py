@@ -20,24 +20,28 @@ def alone(w, inp, b, **kw):
     return DeviceState(w.scaled(batch=1), one, **kw)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("heads", [(8, 8), (16, 8), (32, 8), (64, 8)])
-def test_scores_of_large_statistics(heads):
-    # 5 x 8 x 3876 pages: 39.7 MB of 8-bit bounds, 79 MB of bf16 ones; a fifth of it per sequence
-    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 62011, 16, "bf16")
+def test_scores_of_large_statistics(heads, dtype):
+    # 5 x 8 x 3876 pages: 39.7 MB of 8-bit bounds, 79 MB of bf16 ones, 159 of float32; a fifth of it per sequence
+    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 62011, 16, dtype)
+    bounds8 = dtype == "bf16"
     inp = synth.make_inputs(w, 5, device="cuda")
     inp["seq_lens"] = torch.tensor([62010, 61000, 1, 50000 + 15, 62010], device="cuda", dtype=torch.int32)
     big = DeviceState(w, inp, cap=64)
-    big.enable_box8()
+    if bounds8:
+        big.enable_box8()
     ekv.ekv_stats_build(big.cfg, big.cache(), big.stats())
-    new = [torch.randn(5, heads[1], 128, device="cuda").bfloat16() for _ in range(2)]
+    new = [torch.randn(5, heads[1], 128, device="cuda").to(synth.torch_dtype(dtype)) for _ in range(2)]
 
     def scores(st, k_new, v_new):
         lens, cfg, q = st.inp["seq_lens"], st.cfg, st.inp["q"]
         box8, got = torch.zeros_like(st.box), []
         ekv.ekv_score_pages(cfg, q, st.stats(), lens, ekv.EKV_SCORE_BOTH, st.box, st.mu, st.sigma)
-        ekv.ekv_score_pages(cfg, q, st.stats(), lens, ekv.EKV_SCORE_BOX8, box8)
+        if bounds8:
+            ekv.ekv_score_pages(cfg, q, st.stats(), lens, ekv.EKV_SCORE_BOX8, box8)
         got += [x.clone() for x in (st.box, st.mu, st.sigma, box8)]
-        for mode in (ekv.EKV_SCORE_BOTH, ekv.EKV_SCORE_BOX8):     # the same token twice at one length: idempotent
+        for mode in (ekv.EKV_SCORE_BOTH, ekv.EKV_SCORE_BOX8)[:1 + bounds8]:     # the same token twice at one length: idempotent
             ekv.ekv_append_score_pages(cfg, st.cache(), st.stats(), k_new, v_new, q, mode,
                                        box=st.box if mode == ekv.EKV_SCORE_BOTH else box8, mu=st.mu, sigma=st.sigma)
         torch.cuda.synchronize()
@@ -47,18 +51,20 @@ def test_scores_of_large_statistics(heads):
     for b in range(5):                                  # before the batch appends: the pools are shared
         st = alone(w, inp, b, cap=64)
         st.box_stats, st.gauss_stats = big.box_stats[b:b + 1].clone(), big.gauss_stats[b:b + 1].clone()
-        st.box8_stats = big.box8_stats[b:b + 1].clone()
+        if bounds8:
+            st.box8_stats = big.box8_stats[b:b + 1].clone()
         singles.append(scores(st, new[0][b:b + 1].contiguous(), new[1][b:b + 1].contiguous()))
     for whole, *parts in zip(scores(big, *new), *singles):
         for b in range(5):
             assert same(whole[b:b + 1], parts[b])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("page", [12, 16, 32, 64])
 @pytest.mark.parametrize("heads", [(8, 8), (16, 8), (32, 8), (64, 8)])
-def test_decode_of_large_calls(heads, page):
-    # K of five sequences 143 MB, of one 29 MB
-    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 14001, page, "bf16")
+def test_decode_of_large_calls(heads, page, dtype):
+    # K of five sequences 143 MB (float32: 287), of one 29 MB (57)
+    w = synth.Workload("streams", 5, heads[0], heads[1], 128, 14001, page, dtype)
     inp = synth.make_inputs(w, 6 + page, device="cuda")
     inp["seq_lens"] = torch.tensor([14001, 13990, 1, 4097, 14001], device="cuda", dtype=torch.int32)
     pages = w.pages_per_seq
@@ -81,18 +87,19 @@ def test_decode_of_large_calls(heads, page):
             assert same(x[b:b + 1], part)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("page", [12, 16, 32, 64])
-def test_build_of_large_caches(page):
-    # K of five sequences 143 MB, of one 29 MB
-    w = synth.Workload("streams", 5, 8, 8, 128, 14001, page, "bf16")
+def test_build_of_large_caches(page, dtype):
+    # K of five sequences 143 MB (float32: 287), of one 29 MB (57)
+    w = synth.Workload("streams", 5, 8, 8, 128, 14001, page, dtype)
     inp = synth.make_inputs(w, 7 + page, device="cuda")
     inp["seq_lens"] = torch.tensor([14001, 13990, 1, 4097, 14001], device="cuda", dtype=torch.int32)
 
     def build(st):
-        st.enable_box8()
+        got = [st.box_stats, st.gauss_stats] + ([st.enable_box8()] if dtype == "bf16" else [])
         ekv.ekv_stats_build(st.cfg, st.cache(), st.stats())
         torch.cuda.synchronize()
-        return st.box_stats, st.gauss_stats, st.box8_stats
+        return got
 
     whole = build(DeviceState(w, inp))
     for b in range(5):
