@@ -69,7 +69,7 @@ __device__ __forceinline__ void load_raw8(const float* p, Raw8<float>& r) {
   r.a = *reinterpret_cast<const float4*>(p);
   r.b = *reinterpret_cast<const float4*>(p + 4);
 }
-__device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = load16(p); }
+__device__ __forceinline__ void load_raw8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = *reinterpret_cast<const uint4*>(p); }
 // A row in the sixteen lanes of a DPP row, for streams (STREAM as in load16): bf16 channels 8c..8c+7 in lane c, float32
 // channels 4c..4c+3 and 64+4c..64+4c+3, so that either type takes whole lines with each load; eight channels in a row take a
 // float32 line in halves, and one that is not kept is fetched twice.  p: the row's first channel of the lane.
