@@ -12,9 +12,10 @@ constexpr int kSmWaves = kSmThreads / 64;
 constexpr int kSmRec = kD + 2;          // floats per partial record: o[128], m, l
 constexpr int kSmPagesPerBlock = 8;     // page slots per workgroup (one partial record)
 
-// One wavefront handles kSmPagesPerBlock / kSmWaves pages; the K and V rows of a page are fetched as one
-// batch of unconditional loads (lane = (token mod 4, channel group)), the running maximum is updated once
-// per page.  Page and block-table indices are clamped into range; tokens past the sequence end are masked.
+// One wavefront handles kSmPagesPerBlock / kSmWaves pages, their tokens in batches of four steps of four (lane = (token mod 4,
+// channels of load_row8)): the K and V rows of a batch are fetched by unconditional loads and the running maximum is updated
+// once per batch.  A batch may hold steps of two pages, so pages of 8 tokens waste none, pages of 12 a quarter of the second
+// batch.  Page and block-table indices are clamped into range; tokens past the sequence end are masked.
 // Work distribution: an item is one chunk of kSmPagesPerBlock page slots of one (b,h) row.  The launch has a fixed
 // number of workgroups that does not depend on the capacity of the page lists: every workgroup builds the exclusive
 // prefix of the chunks per row from the device-side list lengths (LDS) and takes a contiguous range of the
@@ -23,63 +24,67 @@ struct SmArgs {
   const void* q; const void* k_pool; const void* v_pool;
   const int32_t* block_table; const int32_t* seq_lens; const int32_t* page_idx; const int32_t* n_sel;
   float* part;
-  int rows, Hq, Hkv, HkvPool, P_rt, Mmax, cap, n_chunks_max, n_phys;
+  int rows, Hq, Hkv, HkvPool, P, Mmax, cap, n_chunks_max, n_phys;
   float scale;
 };
 constexpr int kSmRowsLdsMax = 8192;
 
-template <typename T, int PT>   // PT = compile-time page size (16 or 32), 0 = runtime
+template <typename T, int PT>   // PT = compile-time page size (16), 0 = runtime
 __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk, float (&s_o)[kSmWaves][kD],
                                               float (&s_m)[kSmWaves], float (&s_l)[kSmWaves]) {
-  const T* q = (const T*)A.q;
-  const T* k_pool = (const T*)A.k_pool;
-  const T* v_pool = (const T*)A.v_pool;
-  constexpr int kPagesPerWave = kSmPagesPerBlock / kSmWaves;
-  constexpr int SMAX = PT ? PT / 4 : 16;            // row steps per page (page size <= 64)
-  const int P = PT ? PT : A.P_rt;
+  constexpr int kPagesPerWave = kSmPagesPerBlock / kSmWaves, kBatch = 4;
+  static_assert(kPagesPerWave == 2, "a step is of the first page or of the second");
+  const int P = PT ? PT : A.P;
   const int Hq = A.Hq, Hkv = A.Hkv, cap = A.cap, Mmax = A.Mmax;
   const int b = bh / Hq, hkv = (bh % Hq) / (Hq / Hkv);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = lane >> 4, c = lane & 15;
-  const int slot0 = chunk * kSmPagesPerBlock;
-  const int wslot0 = slot0 + w * kPagesPerWave;
-  int lps[kPagesPerWave], physs[kPagesPerWave];
+  const int r = lane >> 4, c = lane & 15, ch = lane_channel<T>(c);
+  const T* k_pool = (const T*)A.k_pool + r * kD + ch;
+  const T* v_pool = (const T*)A.v_pool + r * kD + ch;
+  const int wslot0 = chunk * kSmPagesPerBlock + w * kPagesPerWave;
+  int lps[kPagesPerWave], row0[kPagesPerWave], left[kPagesPerWave];
 #pragma unroll
   for (int i = 0; i < kPagesPerWave; ++i)
     lps[i] = min(max(A.page_idx[(size_t)bh * cap + min(wslot0 + i, cap - 1)], 0), Mmax - 1);
   const int n = A.seq_lens[b];
   const int n_slots = min(max(A.n_sel[bh], 0), cap);
 #pragma unroll
-  for (int i = 0; i < kPagesPerWave; ++i)
-    physs[i] = min(max(A.block_table[(size_t)b * Mmax + lps[i]], 0), A.n_phys - 1);
+  for (int i = 0; i < kPagesPerWave; ++i) {
+    const int phys = min(max(A.block_table[(size_t)b * Mmax + lps[i]], 0), A.n_phys - 1);
+    row0[i] = __builtin_amdgcn_readfirstlane((phys * A.HkvPool + hkv) * P);          // first row of the page in the pools
+    left[i] = wslot0 + i < n_slots ? n - lps[i] * P : 0;                             // its valid tokens (or more)
+  }
+  Raw8<T> qr;
+  load_row8((const T*)A.q + (size_t)bh * kD + ch, qr);
   float qv[8];
-  load8<T>(q + (size_t)bh * kD + 8 * c, qv);
+  widen8(qr, qv);
   float m_run = -INFINITY, l_run = 0.f, acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+  const int steps = P / 4, total = kPagesPerWave * steps;
+  constexpr int kUnroll = PT ? kPagesPerWave : 1;
+#pragma unroll kUnroll
+  for (int g0 = 0; g0 < total; g0 += kBatch) {
+    Raw8<T> kr[kBatch], vr[kBatch];
 #pragma unroll
-  for (int pw = 0; pw < kPagesPerWave; ++pw) {
-    const bool slot_ok = wslot0 + pw < n_slots;      // wave-uniform
-    const size_t page_off = ((size_t)physs[pw] * A.HkvPool + hkv) * P * kD + 8 * c;
-    const int steps = P / 4;
-    Raw8<T> kr[SMAX], vr[SMAX];
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) {
-      const int tok = 4 * min(s, steps - 1) + r;
-      load_raw8(k_pool + page_off + (size_t)tok * kD, kr[s]);
-      load_raw8(v_pool + page_off + (size_t)tok * kD, vr[s]);
+    for (int s = 0; s < kBatch; ++s) {
+      const int g = min(g0 + s, total - 1);
+      const size_t row = (uint32_t)(g < steps ? row0[0] + 4 * g : row0[1] + 4 * (g - steps));
+      load_row8(k_pool + row * kD, kr[s]);
+      load_row8(v_pool + row * kD, vr[s]);
     }
-    float sc[SMAX];
+    float sc[kBatch];
     float mx = -INFINITY;
 #pragma unroll
-    for (int s = 0; s < SMAX; ++s) {
+    for (int s = 0; s < kBatch; ++s) {
       float x[8];
       widen8(kr[s], x);
       float d = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) d = fmaf(qv[i], x[i], d);
       d = row16_sum(d);
-      const bool valid = slot_ok && s < steps && lps[pw] * P + 4 * s + r < n;
+      const int g = g0 + s;
+      const bool valid = g < total && (g < steps ? 4 * g + r < left[0] : 4 * (g - steps) + r < left[1]);
       sc[s] = valid ? A.scale * d : -INFINITY;
       mx = fmaxf(mx, sc[s]);
     }
@@ -87,12 +92,12 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     const float m_new = fmaxf(m_run, mx);
     if (m_new > -INFINITY) {                          // wave-uniform; no loads inside
-      const float resc = __expf(m_run - m_new);      // exp(-inf) = 0 on the first valid page
+      const float resc = __expf(m_run - m_new);      // exp(-inf) = 0 on the first valid batch
       l_run *= resc;
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] *= resc;
 #pragma unroll
-      for (int s = 0; s < SMAX; ++s) {
+      for (int s = 0; s < kBatch; ++s) {
         const float p = __expf(sc[s] - m_new);       // 0 for masked tokens
         l_run += p;
         float v[8];
@@ -109,7 +114,7 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
   for (int i = 0; i < 8; ++i) { acc[i] += __shfl_xor(acc[i], 16); acc[i] += __shfl_xor(acc[i], 32); }
   if (lane < 16) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s_o[w][8 * c + i] = acc[i];
+    for (int i = 0; i < 8; ++i) s_o[w][(sizeof(T) == 4 && i >= 4 ? kD / 2 - 4 : 0) + ch + i] = acc[i];
   }
   if (lane == 0) { s_m[w] = m_run; s_l[w] = l_run; }
   __syncthreads();
@@ -213,15 +218,20 @@ static int sm_compute_units() {
 template <typename T>
 static void launch_softmax_T(const Dims& dm, const void* q, const ekv_cache_view& c, const int32_t* page_idx,
                              const int32_t* n_sel, float* ws, int n_chunks_max, hipStream_t st) {
+  // A wavefront had all steps of a page in flight, sixteen where the size is not known, repeated on smaller pages: whole steps
+  // on 2 x 128K tokens, 4 % of the pages, in pages of 4 / 8 / 12 / 32 / 48 / 64 tokens 241 / 134 / 102 / 60.3 / 66.0 / 57.2 us,
+  // by batches of four steps 112 / 75 / 67 / 60.3 / 63.0 / 57.2; float32, 2 x 64K, pages of 8 / 16 / 32 / 64 142 / 57.0 / 57.7 /
+  // 62.6, so 69.8 / 57.0 / 57.4 / 58.3.  bf16 pages of 16, two batches, are written out: 4 x 128K 67.7 -> 66.4 (by the loop
+  // 66.9), 64 x 8K 120.6 -> 119.2 (121.5); float32 ones are not: 57.0, written out 57.7.
+  constexpr int PT = sizeof(T) == 2 ? 16 : 0;
   const int rows = dm.B * dm.Hq;
   SmArgs sa{q, c.k_pool, c.v_pool, c.block_table, c.seq_lens, page_idx, n_sel, ws,
             rows, dm.Hq, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, dm.cap, n_chunks_max, c.n_phys_pages, dm.scale};
   dim3 block(kSmThreads);
   if (rows > kSmRowsLdsMax) {
     dim3 grid(n_chunks_max, rows);
-#define EKV_SM(PT) hipLaunchKernelGGL((softmax_partial_kernel<T, PT, true>), grid, block, 0, st, sa)
-    if (dm.P == 16) EKV_SM(16); else if (dm.P == 32) EKV_SM(32); else EKV_SM(0);
-#undef EKV_SM
+    if (PT != 0 && dm.P == PT) hipLaunchKernelGGL((softmax_partial_kernel<T, PT, true>), grid, block, 0, st, sa);
+    else hipLaunchKernelGGL((softmax_partial_kernel<T, 0, true>), grid, block, 0, st, sa);
     return;
   }
   // a fixed grid (16 workgroups per compute unit, never more than the lists can hold chunks)
@@ -231,9 +241,8 @@ static void launch_softmax_T(const Dims& dm, const void* q, const ekv_cache_view
   if (wgs < 1) wgs = 1;
   dim3 grid((unsigned)wgs);
   const size_t lds = (size_t)(rows + 1) * sizeof(int);
-#define EKV_SM(PT) hipLaunchKernelGGL((softmax_partial_kernel<T, PT, false>), grid, block, lds, st, sa)
-  if (dm.P == 16) EKV_SM(16); else if (dm.P == 32) EKV_SM(32); else EKV_SM(0);
-#undef EKV_SM
+  if (PT != 0 && dm.P == PT) hipLaunchKernelGGL((softmax_partial_kernel<T, PT, false>), grid, block, lds, st, sa);
+  else hipLaunchKernelGGL((softmax_partial_kernel<T, 0, false>), grid, block, lds, st, sa);
 }
 
 void launch_decode_sparse_softmax(const Dims& dm, const void* q, const ekv_cache_view& c,
