@@ -77,6 +77,11 @@ def test_decode_of_large_calls(heads, page, dtype):
         cnt = ((lens + page - 1) // page)[:, None].expand(st.w.batch, heads[1]).contiguous()
         ekv.ekv_decode_sparse_group(st.cfg, st.inp["q"], st.cache(), idx, cnt, st.out, st.tau, st.supp,
                                     st.workspace(ekv.EKV_OP_DECODE_SPARSE))
+        got += [x.clone() for x in (st.out, st.tau, st.supp)]
+        idx = torch.arange(pages, device="cuda", dtype=torch.int32).expand(st.w.batch, heads[0], pages).contiguous()
+        cnt = ((lens + page - 1) // page)[:, None].expand(st.w.batch, heads[0]).contiguous()
+        ekv.ekv_decode_sparse(st.cfg, st.inp["q"], st.cache(), idx, cnt, st.out, st.tau, st.supp,
+                              st.workspace(ekv.EKV_OP_DECODE_SPARSE))
         torch.cuda.synchronize()
         return got + [x.clone() for x in (st.out, st.tau, st.supp)]
 
