@@ -79,6 +79,20 @@ template <bool STREAM = false> __device__ __forceinline__ void load_row8(const f
   r.b = __builtin_bit_cast(float4, load16<STREAM>(p + kD / 2));
 }
 template <bool STREAM = false> __device__ __forceinline__ void load_row8(const bf16_t* p, Raw8<bf16_t>& r) { r.a = load16<STREAM>(p); }
+// The same for two groups of float32 rows, one per half of the wavefront, where a row's sum has to run over lane c's channels
+// 8c..8c+7: r.a is fetched from the lower half's group and r.b from the upper's, each whole, and the halves then hand each
+// other what is theirs.  p0, p1: the lane's row of the group at channel 8c + 4 * (its half).
+template <bool STREAM = false> __device__ __forceinline__ void load_halves(const float* p0, const float* p1, Raw8<float>& r) {
+  r.a = __builtin_bit_cast(float4, load16<STREAM>(p0));
+  r.b = __builtin_bit_cast(float4, load16<STREAM>(p1));
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b) {      // lanes 32..63 of a with lanes 0..31 of b
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_halves(Raw8<float>& r) {
+  swap_halves(r.a.x, r.b.x); swap_halves(r.a.y, r.b.y); swap_halves(r.a.z, r.b.z); swap_halves(r.a.w, r.b.w);
+}
 __device__ __forceinline__ void widen8(const Raw8<float>& r, float (&x)[8]) {
   x[0] = r.a.x; x[1] = r.a.y; x[2] = r.a.z; x[3] = r.a.w;
   x[4] = r.b.x; x[5] = r.b.y; x[6] = r.b.z; x[7] = r.b.w;

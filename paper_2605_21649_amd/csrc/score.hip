@@ -274,7 +274,11 @@ void score_pages_mfma_kernel(const bf16_t* __restrict__ q,
   }
 }
 
-// float32 statistics: one wavefront step = two page records, 32 lanes x 8 channels each.
+// float32 statistics: one wavefront step = two page records, 32 lanes x 8 channels each.  A score is one fixed order of
+// summation (channels 8c..8c+7 in turn in lane c, row16_sum, the two rows of the record): pages are selected by comparing
+// scores, and under a flat attention a last bit at the cut changes the output by more than any rounding.  A record is fetched
+// in whole lines all the same (load_halves); the exchange costs nothing measurable beside lanes that sum what they fetched:
+// top-k of 2 x 128K 48.0 / 48.1 us, of 16 x 8K 37.4 / 37.4, Gaussian step of 2 x 64K 107.8 / 107.3.
 template <int G, bool GAUSS, bool APPEND, bool STREAM>
 __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __restrict__ q,
                                                               const float* __restrict__ stats,
@@ -305,10 +309,8 @@ __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __res
   float coef[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    Raw8<float> raw;
-    load_row8(q + ((size_t)b * Hq + h * G + g) * kD + lane_channel<float>(c), raw);
     float qv[8];
-    widen8(raw, qv);
+    load8<float>(q + ((size_t)b * Hq + h * G + g) * kD + 8 * c, qv);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (GAUSS) coef[g][i] = which ? qv[i] * qv[i] : qv[i];
@@ -316,16 +318,18 @@ __global__ __launch_bounds__(256) void score_pages_f32_kernel(const float* __res
     }
   }
   const int pw0 = tile0 + w * (kScoreTile / 4);
-  const float* base = stats + (((size_t)b * Hkv + h) * Mmax) * 2 * kD;
+  const float* base = stats + (((size_t)b * Hkv + h) * Mmax) * 2 * kD + which * kD + 8 * c + 4 * half;
   Raw8<float> rec[kSteps];
 #pragma unroll
   for (int it = 0; it < kSteps; ++it) {
-    const int p = min(pw0 + 2 * it + half, M - 1);  // clamped: pages past the end are masked on output
-    load_row8<STREAM>(base + ((size_t)p * 2 + which) * kD + lane_channel<float>(c), rec[it]);
+    // clamped: pages past the end are masked on output
+    const int p0 = min(pw0 + 2 * it, M - 1), p1 = min(pw0 + 2 * it + 1, M - 1);
+    load_halves<STREAM>(base + (size_t)p0 * 2 * kD, base + (size_t)p1 * 2 * kD, rec[it]);
   }
 #pragma unroll
   for (int it = 0; it < kSteps; ++it) {
     const int pt = w * (kScoreTile / 4) + 2 * it + half;
+    swap_halves(rec[it]);
     float x[8];
     widen8(rec[it], x);
 #pragma unroll
