@@ -169,8 +169,10 @@ template <int G> struct RowHeads {
 // flight.  Whole calls, us, before / now, four heads to a KV head: all pages of 2 x 262144 bf16 tokens in pages of 12
 // 270.6 / 246.7 (1.07 GB, 4.6 TB/s in the pass; eight heads 377.7 / 283.7), per-head lists of 5000 tokens, 128 rows, pages of 8
 // 37.8 / 29.0; float32, 2 x 131072 tokens in pages of 8 242.6 / 231.0, 128 lists of 5000 tokens in pages of 16 52.7 / 44.5.
-// float32 rows by loads of whole lines and past the caches (load_row8): 2 x 131072 tokens in pages of 16 229.6 -> 208.5, 262144
-// in pages of 48 237.3 -> 217.5 (227.5 page by page), refined step of 3 x 21003 tokens in pages of 8 109.0 -> 104.9.
+// float32 rows by loads of whole lines and past the caches, as load_halves: 2 x 131072 tokens in pages of 16 229.6 -> 208.5,
+// 262144 in pages of 48 237.3 -> 217.5 (227.5 page by page), refined step of 3 x 21003 tokens in pages of 8 109.0 -> 104.9.
+// The sum runs over channels 8c..8c+7 in lane c and then over the lanes, as in decode_row_kernel and in the page scores:
+// a threshold on page bounds compares them with what is solved from these scores.
 template <typename T, int G, int MODE, bool STREAM, bool PRE_GLOBAL>
 __global__ __launch_bounds__(kScoreThreads)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? (G <= 4 ? 8 : 6) : G == 1 ? 8 : G == 2 ? 6 : G == 4 ? 5 : 4)))
@@ -191,7 +193,7 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
   const int my_st = min(lane % kStepLanes, spi - 1), my_pg = my_st / spp, my_t0 = 4 * (my_st - my_pg * spp);
   const int r = lane >> 4, c = lane & 15;          // FMAs: token of the step, the lane's channels
   const int m = lane & 15, j = lane >> 4, kq = m & 3, gl = m >> 2;      // matrix cores: as in decode_scores_mfma_kernel
-  const T* k_pool = (const T*)A.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : r * kD + lane_channel<T>(c));
+  const T* k_pool = (const T*)A.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : (r & 1) * kD + 8 * c + 4 * (r >> 1));
   const int ratio = Hq / Hkv;
   const Part part = PRE_GLOBAL || GROUPED ? Part{0, 1} : unit_part(A);
   if (!PRE_GLOBAL)
@@ -231,9 +233,9 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
         const int row = __builtin_amdgcn_readlane(l_row, rq + rq_s + s);
         const T* p = k_pool + (size_t)(uint32_t)row * kD;
         if constexpr (MFMA) a[s] = load16<STREAM>(p);
-        else {
+        else {                                     // as load_halves: tokens 0 and 1, tokens 2 and 3
           a[2 * s] = load16<STREAM>(p);
-          a[2 * s + 1] = load16<STREAM>(p + kD / 2);
+          a[2 * s + 1] = load16<STREAM>(p + 2 * kD);
         }
       }
       rq_s += CS;
@@ -260,11 +262,7 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
         }
       } else {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          Raw8<T> raw;
-          load_row8(qr + g * kD + lane_channel<T>(c), raw);
-          widen8(raw, coef[g]);
-        }
+        for (int g = 0; g < G; ++g) load8<T>(qr + g * kD + 8 * c, coef[g]);
         wmax[0] = -INFINITY;
       }
     };
@@ -294,7 +292,8 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
       } else {
 #pragma unroll
         for (int s = 0; s < CS; ++s) {
-          const Raw8<float> raw = {__builtin_bit_cast(float4, a[2 * s]), __builtin_bit_cast(float4, a[2 * s + 1])};
+          Raw8<float> raw = {__builtin_bit_cast(float4, a[2 * s]), __builtin_bit_cast(float4, a[2 * s + 1])};
+          swap_halves(raw);
           float x[8], acc[G];
           widen8(raw, x);
 #pragma unroll
@@ -2123,18 +2122,18 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
       // as in decode_scores_steps_kernel, G = 1
       constexpr bool MFMA = sizeof(T) == 2;
       const int r = lane >> 4, c = lane & 15, kq = lane & 3, gl = (lane >> 2) & 3, j = r;
-      const T* k_pool = (const T*)S.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : r * kD + lane_channel<T>(c));
+      const T* k_pool = (const T*)S.k_pool + (MFMA ? gl * kD + (kq * 4 + j) * 8 : r * kD + 8 * c);
       const T* qr = (const T*)S.q + (size_t)bh * kD;
       float coef[8];
       Raw8<T> bq;
-      load_row8(qr + (MFMA ? kq * 32 + j * 8 : lane_channel<T>(c)), bq);
+      load_raw8(qr + (MFMA ? kq * 32 + j * 8 : 8 * c), bq);
       if constexpr (!MFMA) widen8(bq, coef);
       const int steps = P / 4, batches = (steps + 3) / 4, total = mine * batches;   // four steps = 16 tokens per batch
       auto request = [&](int i, Raw8<T> (&x)[4]) {
         const int ic = min(i, total - 1), pg = ic / batches, s0 = 4 * (ic - pg * batches);
         const T* kpage = k_pool + ((size_t)__builtin_amdgcn_readlane(l_phys, pg) * S.HkvPool + hkv) * P * kD;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) load_row8(kpage + (size_t)(4 * min(s0 + s, steps - 1)) * kD, x[s]);
+        for (int s = 0; s < 4; ++s) load_raw8(kpage + (size_t)(4 * min(s0 + s, steps - 1)) * kD, x[s]);
       };
       float wmax = -INFINITY;
       auto consume = [&](int i, const Raw8<T> (&x)[4]) {
@@ -2263,7 +2262,7 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
   // MB) 41.8 / 37.4; 1 x 32K 23.4 / 22.5 with four inputs in turn, 22.4 / 22.9 with three, which the last cache holds, 1 x
   // 4K 13.4 / 13.8.  Group steps, whose lists follow a stream of statistics, by the capacity, all that the host knows (it
   // is filled to half here): 134 MB 61.6 / 56.3, 86 MB 87 / 86, 67 MB 34.7 / 34.1, 17 MB 26.4 / 27.2.  float32 with both
-  // loads of a row on whole lines (load_row8): 2 x 128K 229 / 208, on half lines 249.  Lists of heads without a group:
+  // loads of a row on whole lines (load_halves): 2 x 128K 229 / 208, on half lines 249.  Lists of heads without a group:
   // Gaussian steps of 4 x 128K 71.0 / 67.4, 8 x 32K 89.6 / 79.8, refined 4 x 32K 99.9 / 90.1, top-k by capacity 268 MB 69.8
   // / 63.8, 134 MB 44.3 / 43.2, 67 MB 33.9 / 33.7.  Lists per head of a group meet in the caches (16 x 16K Gaussian step
   // 253 / 324) and keep theirs.

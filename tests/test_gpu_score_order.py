@@ -46,3 +46,42 @@ def test_float32_scores_keep_their_order(heads, tokens):
         assert np.array_equal(st.box[0, h].cpu().numpy()[pages], want)
         assert np.array_equal(st.mu[0, h].cpu().numpy()[pages], scale * row_sums(q, gauss[:, 0]))
         assert np.array_equal(st.sigma[0, h].cpu().numpy()[pages], scale * np.sqrt(row_sums(q * q, gauss[:, 1])))
+
+
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (16, 2)])
+@pytest.mark.parametrize("reserved", [32, 4096])                # capacity in tokens: 2 MB of K, and 268 (a stream)
+def test_float32_decode_scores_keep_their_order(heads, reserved):
+    """Over one token tau is its score less one, an exact difference for scores in [0.5, 2].  A threshold on page bounds
+    compares them with tau, so its last bit decides as well."""
+    w = synth.Workload("order", 64, heads[0], heads[1], 128, 16, 16, "f32")
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    dev = dict(device="cuda", dtype=torch.float32)
+    q = torch.rand(64, heads[0], 128, generator=gen, **dev)
+    k, v = torch.rand(64, heads[1], 16, 128, generator=gen, **dev), torch.randn(64, heads[1], 16, 128, generator=gen, **dev)
+    lens = torch.ones(64, device="cuda", dtype=torch.int32)
+    pages = reserved // 16
+    table = torch.arange(64, device="cuda", dtype=torch.int32)[:, None].expand(64, pages).contiguous()
+    cfg = ekv.make_config(64, heads[0], heads[1], 128, 16, "f32", 1.5, 1.0 / 16.0, pages, pages)
+    cache = ekv.cache_view(k, v, table, lens)
+    # 1 / 32 a channel, an exact factor: scores around 1
+    kq = k[:, :, 0].cpu().numpy().repeat(heads[0] // heads[1], 1)
+    want = np.float32(1.0 / 32.0) * row_sums(q.cpu().numpy(), kq)
+    sure = (want >= 0.5) & (want <= 2.0)
+    assert sure.mean() > 0.9
+
+    def room(op):
+        return torch.empty(max(256, ekv.ekv_workspace_bytes(cfg, op)), device="cuda", dtype=torch.uint8)
+
+    for way in ("all", "group", "head"):
+        lists = heads[1] if way == "group" else heads[0]
+        idx, cnt = (torch.zeros(64, lists, pages, device="cuda", dtype=torch.int32), torch.ones(64, lists, device="cuda", dtype=torch.int32))
+        out, tau = torch.zeros(64, heads[0], 128, **dev), torch.zeros(64, heads[0], **dev)
+        supp = torch.zeros(64, heads[0], device="cuda", dtype=torch.int32)
+        if way == "all":
+            ekv.ekv_decode_full(cfg, q, cache, out, tau, supp, room(ekv.EKV_OP_DECODE_FULL))
+        elif way == "group":
+            ekv.ekv_decode_sparse_group(cfg, q, cache, idx, cnt, out, tau, supp, room(ekv.EKV_OP_DECODE_SPARSE))
+        else:
+            ekv.ekv_decode_sparse(cfg, q, cache, idx, cnt, out, tau, supp, room(ekv.EKV_OP_DECODE_SPARSE))
+        torch.cuda.synchronize()
+        assert np.array_equal(tau.cpu().numpy()[sure], (want - np.float32(1.0))[sure]), way
