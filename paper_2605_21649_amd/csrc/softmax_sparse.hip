@@ -13,7 +13,7 @@ constexpr int kSmRec = kD + 2;          // floats per partial record: o[128], m,
 constexpr int kSmPagesPerBlock = 8;     // page slots per workgroup (one partial record)
 
 // One wavefront handles kSmPagesPerBlock / kSmWaves pages, their tokens in batches of four steps of four (lane = (token mod 4,
-// channels of load_row8)): the K and V rows of a batch are fetched by unconditional loads and the running maximum is updated
+// channels 8c..8c+7 of K, whose order of summation is the decode's, and those of load_row8 of V)): the K and V rows of a batch are fetched by unconditional loads and the running maximum is updated
 // once per batch.  A batch may hold steps of two pages, so pages of 8 tokens waste none, pages of 12 a quarter of the second
 // batch.  Page and block-table indices are clamped into range; tokens past the sequence end are masked.
 // Work distribution: an item is one chunk of kSmPagesPerBlock page slots of one (b,h) row.  The launch has a fixed
@@ -39,7 +39,7 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
   const int b = bh / Hq, hkv = (bh % Hq) / (Hq / Hkv);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane >> 4, c = lane & 15, ch = lane_channel<T>(c);
-  const T* k_pool = (const T*)A.k_pool + r * kD + ch;
+  const T* k_pool = (const T*)A.k_pool + (sizeof(T) == 4 ? (r & 1) * kD + 8 * c + 4 * (r >> 1) : r * kD + ch);
   const T* v_pool = (const T*)A.v_pool + r * kD + ch;
   const int wslot0 = chunk * kSmPagesPerBlock + w * kPagesPerWave;
   int lps[kPagesPerWave], row0[kPagesPerWave], left[kPagesPerWave];
@@ -54,10 +54,8 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
     row0[i] = __builtin_amdgcn_readfirstlane((phys * A.HkvPool + hkv) * P);          // first row of the page in the pools
     left[i] = wslot0 + i < n_slots ? n - lps[i] * P : 0;                             // its valid tokens (or more)
   }
-  Raw8<T> qr;
-  load_row8((const T*)A.q + (size_t)bh * kD + ch, qr);
   float qv[8];
-  widen8(qr, qv);
+  load8<T>((const T*)A.q + (size_t)bh * kD + 8 * c, qv);
   float m_run = -INFINITY, l_run = 0.f, acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
@@ -70,13 +68,15 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
     for (int s = 0; s < kBatch; ++s) {
       const int g = min(g0 + s, total - 1);
       const size_t row = (uint32_t)(g < steps ? row0[0] + 4 * g : row0[1] + 4 * (g - steps));
-      load_row8(k_pool + row * kD, kr[s]);
+      if constexpr (sizeof(T) == 4) load_halves(k_pool + row * kD, k_pool + (row + 2) * kD, kr[s]);
+      else load_row8(k_pool + row * kD, kr[s]);
       load_row8(v_pool + row * kD, vr[s]);
     }
     float sc[kBatch];
     float mx = -INFINITY;
 #pragma unroll
     for (int s = 0; s < kBatch; ++s) {
+      if constexpr (sizeof(T) == 4) swap_halves(kr[s]);
       float x[8];
       widen8(kr[s], x);
       float d = 0.f;

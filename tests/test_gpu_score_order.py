@@ -51,8 +51,8 @@ def test_float32_scores_keep_their_order(heads, tokens):
 @pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (16, 2)])
 @pytest.mark.parametrize("reserved", [32, 4096])                # capacity in tokens: 2 MB of K, and 268 (a stream)
 def test_float32_decode_scores_keep_their_order(heads, reserved):
-    """Over one token tau is its score less one, an exact difference for scores in [0.5, 2].  A threshold on page bounds
-    compares them with tau, so its last bit decides as well."""
+    """Over one token tau is its score less one, an exact difference for scores in [0.5, 2], and the softmax's lse the score.
+    A threshold on page bounds compares them with tau, so its last bit decides as well."""
     w = synth.Workload("order", 64, heads[0], heads[1], 128, 16, 16, "f32")
     gen = torch.Generator(device="cuda").manual_seed(9)
     dev = dict(device="cuda", dtype=torch.float32)
@@ -63,9 +63,10 @@ def test_float32_decode_scores_keep_their_order(heads, reserved):
     table = torch.arange(64, device="cuda", dtype=torch.int32)[:, None].expand(64, pages).contiguous()
     cfg = ekv.make_config(64, heads[0], heads[1], 128, 16, "f32", 1.5, 1.0 / 16.0, pages, pages)
     cache = ekv.cache_view(k, v, table, lens)
-    # 1 / 32 a channel, an exact factor: scores around 1
+    # 1 / 32 a channel, an exact factor: (alpha - 1) * score around 1
     kq = k[:, :, 0].cpu().numpy().repeat(heads[0] // heads[1], 1)
-    want = np.float32(1.0 / 32.0) * row_sums(q.cpu().numpy(), kq)
+    score = np.float32(1.0 / 16.0) * row_sums(q.cpu().numpy(), kq)
+    want = np.float32(0.5) * score
     sure = (want >= 0.5) & (want <= 2.0)
     assert sure.mean() > 0.9
 
@@ -85,3 +86,7 @@ def test_float32_decode_scores_keep_their_order(heads, reserved):
             ekv.ekv_decode_sparse(cfg, q, cache, idx, cnt, out, tau, supp, room(ekv.EKV_OP_DECODE_SPARSE))
         torch.cuda.synchronize()
         assert np.array_equal(tau.cpu().numpy()[sure], (want - np.float32(1.0))[sure]), way
+
+    ekv.ekv_decode_sparse_softmax(cfg, q, cache, idx, cnt, out, tau, room(ekv.EKV_OP_DECODE_SPARSE_SOFTMAX))
+    torch.cuda.synchronize()
+    assert np.array_equal(tau.cpu().numpy(), score)
