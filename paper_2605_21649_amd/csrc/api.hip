@@ -48,7 +48,9 @@ static ekv_status check_cache(const ekv_cache_view* c, bool need_v) {
   return EKV_OK;
 }
 
-// V rows are addressed by a 32-bit row index (phys*HkvPool + hkv)*P + tok inside the decode kernels.
+// Rows of K (float32, or pages other than 16, 32 and 64) and of V are addressed by a 32-bit row index (phys*HkvPool + hkv)*P +
+// tok inside the entmax decode kernels.  (The softmax takes any declared number of pages; its index wraps at 2^32 rows, more
+// than the memory holds.)
 static ekv_status check_pool_rows(const ekv_cache_view* c, const Dims& dm) {
   if ((int64_t)c->n_phys_pages * dm.HkvPool * dm.P > (int64_t)0x7fffffff) return EKV_ERR_UNSUPPORTED;
   return EKV_OK;

@@ -42,7 +42,8 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
   const T* k_pool = (const T*)A.k_pool + (sizeof(T) == 4 ? (r & 1) * kD + 8 * c + 4 * (r >> 1) : r * kD + ch);
   const T* v_pool = (const T*)A.v_pool + r * kD + ch;
   const int wslot0 = chunk * kSmPagesPerBlock + w * kPagesPerWave;
-  int lps[kPagesPerWave], row0[kPagesPerWave], left[kPagesPerWave];
+  int lps[kPagesPerWave], left[kPagesPerWave];
+  uint32_t row0[kPagesPerWave];
 #pragma unroll
   for (int i = 0; i < kPagesPerWave; ++i)
     lps[i] = min(max(A.page_idx[(size_t)bh * cap + min(wslot0 + i, cap - 1)], 0), Mmax - 1);
@@ -51,7 +52,9 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
 #pragma unroll
   for (int i = 0; i < kPagesPerWave; ++i) {
     const int phys = min(max(A.block_table[(size_t)b * Mmax + lps[i]], 0), A.n_phys - 1);
-    row0[i] = __builtin_amdgcn_readfirstlane((phys * A.HkvPool + hkv) * P);          // first row of the page in the pools
+    // first row of the page in the pools, modulo 2^32: rows take 256 bytes and more, so that many are over a terabyte (64 bits
+    // cost 2 % on 64 x 8K tokens, 119.3 -> 122.0 us), and a view may declare more pages than there are
+    row0[i] = __builtin_amdgcn_readfirstlane(((uint32_t)phys * (uint32_t)A.HkvPool + (uint32_t)hkv) * (uint32_t)P);
     left[i] = wslot0 + i < n_slots ? n - lps[i] * P : 0;                             // its valid tokens (or more)
   }
   float qv[8];
@@ -67,7 +70,7 @@ __device__ __forceinline__ void softmax_chunk(const SmArgs& A, int bh, int chunk
 #pragma unroll
     for (int s = 0; s < kBatch; ++s) {
       const int g = min(g0 + s, total - 1);
-      const size_t row = (uint32_t)(g < steps ? row0[0] + 4 * g : row0[1] + 4 * (g - steps));
+      const size_t row = g < steps ? row0[0] + 4u * g : row0[1] + 4u * (g - steps);
       if constexpr (sizeof(T) == 4) load_halves(k_pool + row * kD, k_pool + (row + 2) * kD, kr[s]);
       else load_row8(k_pool + row * kD, kr[s]);
       load_row8(v_pool + row * kD, vr[s]);
