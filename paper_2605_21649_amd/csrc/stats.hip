@@ -110,14 +110,15 @@ __global__ __launch_bounds__(256) void stats_build_kernel(const T* __restrict__ 
   const int p = blockIdx.x * 16 + (threadIdx.x >> 4);     // 16 pages per workgroup, 4 per wavefront
   const int n = seq_lens[b];
   const int M = min((n + P - 1) / P, Mmax);
+  // A wavefront past the end leaves on the length alone: with the table looked up first, 4K tokens in a capacity of a million
+  // took 18.3 us for 16.2, in float32 18.0 for 16.3.
+  if (blockIdx.x * 16 + (int)(threadIdx.x >> 6) * 4 >= M) return;
   const int pc = min(p, M - 1);                           // lanes past the end recompute the last page, unwritten
-  if (M <= 0) return;
   const int cnt = min(P, n - pc * P);
   const int phys = min(max(block_table[(size_t)b * Mmax + pc], 0), n_phys - 1);
   const T* kpage = k_pool + ((size_t)phys * HkvPool + h) * P * kD;
   const size_t rec = (((size_t)b * Hkv + h) * Mmax + pc) * 2 * kD;
   const bool all_full = __all(cnt == P);
-  if (blockIdx.x * 16 + (int)(threadIdx.x >> 6) * 4 >= M) return;      // whole wavefront past the end
   if (p < M) page_stats_rows<T, PT, STREAM>(kpage, cnt, P, all_full, box + rec, gauss + rec,
                                     box8 != nullptr ? box8 + rec : nullptr);   // 256 bytes per page there
 }
@@ -141,6 +142,8 @@ __global__ __launch_bounds__(64) void stats_append_kernel(T* __restrict__ k_pool
 // 64 121.5 / 112 / 115 / 104, 1 x 64K (134 MB of K) 45.6 / 38.7 / 43.3 / 38.4.  K of a smaller build may still lie in the last
 // cache, where the prefill wrote it: 1 x 32K 25.5 / 22.8 / 16.5 / 22.2, 1 x 16K 9.9 / 11.4 / 9.2 / 10.4, 1 x 4K 6.6 / 7.0 / 6.5 / 6.9.
 // float32, by loads and stores of whole lines as well: 2 x 64K 137.6 -> 114.5, 1 x 16K 20.3 -> 13.7.
+// The host knows the capacity alone.  A choice by length in the kernel cost more than it gave (the code of both loops slows
+// every workgroup's start: 4 x 128K 204.8 -> 246, 4K tokens in a capacity of a million 18.3 -> 20.6; K kept there, 17.7).
 template <typename T, int PT>
 static void launch_build_T(const Dims& dm, const ekv_cache_view& c, const ekv_stats_view& s, hipStream_t st) {
   dim3 grid((dm.Mmax + 15) / 16, dm.Hkv, dm.B), block(256);

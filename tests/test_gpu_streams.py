@@ -110,3 +110,30 @@ def test_build_of_large_caches(page, dtype):
     for b in range(5):
         for x, part in zip(whole, build(alone(w, inp, b))):
             assert same(x[b:b + 1], part)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_short_sequences_in_a_large_capacity(dtype):
+    """The kind of the loads follows the capacity (16 384 pages: 268 MB of statistics and more): short sequences in it give the
+    bits that they give in a capacity of their own, and what lies past them is not written."""
+    tight = synth.Workload("reserved", 2, 16, 8, 128, 1003, 16, dtype)
+    inp = synth.make_inputs(tight, 12, device="cuda")
+    inp["seq_lens"] = torch.tensor([1003, 17], device="cuda", dtype=torch.int32)
+    wide = tight.scaled(context=262144)
+    table = torch.zeros(2, wide.pages_per_seq, device="cuda", dtype=torch.int32)
+    table[:, :tight.pages_per_seq] = inp["block_table"]
+    got = []
+    for w, own in ((tight, inp), (wide, dict(inp, block_table=table))):
+        st = DeviceState(w, own)
+        st.box_stats.fill_(7.0)
+        st.gauss_stats.fill_(7.0)
+        ekv.ekv_stats_build(st.cfg, st.cache(), st.stats())
+        ekv.ekv_score_pages(st.cfg, own["q"], st.stats(), own["seq_lens"], ekv.EKV_SCORE_BOTH, st.box, st.mu, st.sigma)
+        ekv.ekv_decode_full(st.cfg, own["q"], st.cache(), st.out, st.tau, st.supp, st.workspace(ekv.EKV_OP_DECODE_FULL))
+        torch.cuda.synchronize()
+        for x in (st.box_stats, st.gauss_stats):
+            for b, pages in enumerate((63, 2)):
+                assert bool((x[b, :, pages:] == 7.0).all())
+        got.append([st.out, st.tau, st.supp] + [x[:, :, :63].clone() for x in (st.box_stats, st.gauss_stats, st.box, st.mu, st.sigma)])
+    for a, b in zip(*got):
+        assert same(a, b)
