@@ -4,6 +4,7 @@
 // statistic ever crosses lanes; a wavefront covers four pages, each row load being four 256-byte
 // segments.  The kernel is a stream over K (HBM-bound once the per-element work is this small: min,
 // max, subtract, add, fused multiply-add).
+#include <type_traits>
 #include "ekv_device.h"
 #include "ekv_internal.h"
 #include "ekv_stats.h"
@@ -21,7 +22,7 @@ constexpr int kStatRowBatch = 4;     // row loads in flight per lane in the bulk
 // page's rows itself, so no statistic crosses lanes; a wavefront covers four pages, each row load being
 // four 256-byte segments.  `kpage` points at the page's [P][128] block; tokens [0,cnt) are valid.
 template <typename T, int PT, bool STREAM>   // PT = compile-time page size, 0 = runtime
-__device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int cnt, int P_rt, bool all_full,
+__device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int cnt, int P_rt, bool all_full, bool past,
                                                 T* __restrict__ box_out, T* __restrict__ gauss_out,
                                                 uint8_t* __restrict__ box8_out) {
   constexpr int RB = kStatRowBatch;
@@ -43,8 +44,12 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
 #pragma unroll 1
     for (int t0 = 0; t0 < P; t0 += RB) {
       Raw8<T> raw[RB];
+      const auto fetch = [&](auto stream) {
 #pragma unroll
-      for (int j = 0; j < RB; ++j) load_row8<STREAM>(kpage + (size_t)(t0 + j) * kD + ch, raw[j]);   // P % 4 == 0
+        for (int j = 0; j < RB; ++j) load_row8<decltype(stream)::value>(kpage + (size_t)(t0 + j) * kD + ch, raw[j]);   // P % 4 == 0
+      };
+      if (STREAM && past) fetch(std::bool_constant<STREAM>{});
+      else fetch(std::false_type{});
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         float x[8];
@@ -65,7 +70,7 @@ __device__ __forceinline__ void page_stats_rows(const T* __restrict__ kpage, int
       Raw8<T> raw[RB];
 #pragma unroll
       for (int j = 0; j < RB; ++j)                       // rows past cnt re-read row 0: loads stay unconditional
-        load_row8<STREAM>(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + ch, raw[j]);
+        load_row8(kpage + (size_t)(t0 + j < cnt ? t0 + j : 0) * kD + ch, raw[j]);
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
         const bool ok = t0 + j < cnt;
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(256) void stats_build_kernel(const T* __restrict__ 
                                                           const int32_t* __restrict__ seq_lens,
                                                           T* __restrict__ box, T* __restrict__ gauss,
                                                           uint8_t* __restrict__ box8,
-                                                          int Hkv, int HkvPool, int P, int Mmax, int n_phys) {
+                                                          int Hkv, int HkvPool, int P, int Mmax, int n_phys, int stream_pages) {
   const int b = blockIdx.z, h = blockIdx.y;
   const int p = blockIdx.x * 16 + (threadIdx.x >> 4);     // 16 pages per workgroup, 4 per wavefront
   const int n = seq_lens[b];
@@ -119,7 +124,7 @@ __global__ __launch_bounds__(256) void stats_build_kernel(const T* __restrict__ 
   const T* kpage = k_pool + ((size_t)phys * HkvPool + h) * P * kD;
   const size_t rec = (((size_t)b * Hkv + h) * Mmax + pc) * 2 * kD;
   const bool all_full = __all(cnt == P);
-  if (p < M) page_stats_rows<T, PT, STREAM>(kpage, cnt, P, all_full, box + rec, gauss + rec,
+  if (p < M) page_stats_rows<T, PT, STREAM>(kpage, cnt, P, all_full, M >= stream_pages, box + rec, gauss + rec,
                                     box8 != nullptr ? box8 + rec : nullptr);   // 256 bytes per page there
 }
 
@@ -138,21 +143,25 @@ __global__ __launch_bounds__(64) void stats_append_kernel(T* __restrict__ k_pool
 }
 
 // The statistics, and K of a large build, go past the caches: they stream faster so.  us, neither / K / statistics /
-// both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.3 GB, 6.1 TB/s), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
+// both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.28 GB, 6.0 TB/s; 203 to 215 from box to box), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
 // 64 121.5 / 112 / 115 / 104, 1 x 64K (134 MB of K) 45.6 / 38.7 / 43.3 / 38.4.  K of a smaller build may still lie in the last
 // cache, where the prefill wrote it: 1 x 32K 25.5 / 22.8 / 16.5 / 22.2, 1 x 16K 9.9 / 11.4 / 9.2 / 10.4, 1 x 4K 6.6 / 7.0 / 6.5 / 6.9.
 // float32, by loads and stores of whole lines as well: 2 x 64K 137.6 -> 114.5, 1 x 16K 20.3 -> 13.7.
-// The host knows the capacity alone.  A choice by length in the kernel cost more than it gave (the code of both loops slows
-// every workgroup's start: 4 x 128K 204.8 -> 246, 4K tokens in a capacity of a million 18.3 -> 20.6; K kept there, 17.7).
+// The host knows the capacity alone: a launch that may hold so much K carries both loads, and a page takes the one that its
+// sequence's length asks for, as if all sequences were as long.  Sequences in a capacity of a million tokens, by capacity / by
+// length: 4K 16.1 / 15.3, 32K 24.7 / 21.3, float32 4K 16.1 / 14.3; 4 x 128K 211.8 / 211.6.  (With two whole loops instead of two
+// loads the kernel has room for two wavefronts per SIMD, not three: 246.)  K that lies in the last cache entirely is read
+// faster from there still at the line, 1 x 64K 29.2 / 36.4, from memory 46.0 / 38.7.
 template <typename T, int PT>
 static void launch_build_T(const Dims& dm, const ekv_cache_view& c, const ekv_stats_view& s, hipStream_t st) {
   dim3 grid((dm.Mmax + 15) / 16, dm.Hkv, dm.B), block(256);
+  const long long per_page = (long long)dm.B * dm.Hkv * dm.P * kD * (long long)sizeof(T);
+  const int stream_pages = (int)((kStreamKBytes + per_page - 1) / per_page);
   const auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, st, (const T*)c.k_pool, c.block_table, c.seq_lens, (T*)s.box, (T*)s.gauss,
-                       (uint8_t*)s.box8, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, c.n_phys_pages);
+                       (uint8_t*)s.box8, dm.Hkv, dm.HkvPool, dm.P, dm.Mmax, c.n_phys_pages, stream_pages);
   };
-  const long long k_bytes = (long long)dm.B * dm.Hkv * dm.Mmax * dm.P * kD * (long long)sizeof(T);
-  if (k_bytes >= kStreamKBytes) launch(stats_build_kernel<T, PT, true>);
+  if (dm.Mmax >= stream_pages) launch(stats_build_kernel<T, PT, true>);
   else launch(stats_build_kernel<T, PT, false>);
 }
 template <typename T, int PT>
