@@ -156,14 +156,19 @@ void launch_select_box_threshold(const Dims& dm, const float* box, const int32_t
   ws.list = ws.cnt + (size_t)BH * ws.NS * 2;
   const BoxOut out{page_idx_out, n_sel_out, n_added, overflow};
   // Up to 16384 pages one workgroup holds a row, and one launch is enough.  Calls, us, two launches / one, lists of 4 % and of
-  // all pages: 48 rows of 2626 pages 8.0 / 5.6, 8.0 / 5.6; 128 of 8192 8.4 / 6.2, 11.5 / 6.6; 32 of 16384 8.3 / 6.1, 14.6 / 6.3;
-  // 512 of 16384 15.7 / 10.1, 29.3 / 15.4; 2048 of 512 16.3 / 14.3, 17.1 / 14.7; 1024 of 8192 16.0 / 16.4, 28.4 / 19.9.
+  // all pages: 48 rows of 2626 pages 8.0 / 5.6, 8.0 / 5.6; 128 of 8192 8.1 / 5.6, 11.5 / 5.7; 32 of 16384 8.3 / 6.1, 14.6 / 6.3;
+  // 512 of 16384 15.7 / 10.1, 29.3 / 15.4; 2048 of 512 16.3 / 14.3, 17.1 / 14.7.  A lane's pages are four, eight, twelve or
+  // sixteen: with sixteen for all rows above 4096 pages many rows with short lists took longer than by two launches.  Two
+  // launches / sixteen / fewer: 2048 of 4100 25.0 / 29.5 / 18.8, 1024 of 8192 16.0 / 16.4 / 11.4, 4096 of 9000 54.5 / 58.7 / 48.3,
+  // 1024 of 12288 20.3 / 18.5 / 16.7; 4096 of 12300, by sixteen, 66.6 / 60.2.
   if (dm.Mmax <= kBxRowThreads * kBxItems) {
     const auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(1, BH), dim3(kBxRowThreads), 0, st, box, seq_lens, tau_lo, page_idx_in, n_sel_in, ws, out,
                          dm.a, dm.Hq, dm.P, dm.Mmax, dm.cap);
     };
     if (dm.Mmax <= 4 * kBxRowThreads) launch(box_mark_kernel<kBxRowThreads, 4, true>);
+    else if (dm.Mmax <= 8 * kBxRowThreads) launch(box_mark_kernel<kBxRowThreads, 8, true>);
+    else if (dm.Mmax <= 12 * kBxRowThreads) launch(box_mark_kernel<kBxRowThreads, 12, true>);
     else launch(box_mark_kernel<kBxRowThreads, kBxItems, true>);
     return;
   }

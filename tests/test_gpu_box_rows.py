@@ -1,4 +1,4 @@
-"""Box-threshold selection at the edges of its forms: one launch for rows of up to 4096 and 16384 pages, two beyond; lists cut
+"""Box-threshold selection at the edges of its forms: one launch for rows of up to 4096, 8192 and 16384 pages, two beyond; lists cut
 at their capacity; the given list as the output.  Scores times a = 1/2 are exact in float32, so the sets are the oracle's."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("M,cap", [(1, 1), (63, 20), (64, 64), (1024, 1000), (4095, 4095), (4096, 300), (4096, 4096), (4097, 4097),
+@pytest.mark.parametrize("M,cap", [(1, 1), (63, 20), (64, 64), (1024, 1000), (4095, 4095), (4096, 300), (4096, 4096), (4097, 4097), (8191, 500), (8192, 8192), (8193, 8193), (12288, 12288), (12289, 400),
                                    (16383, 16383), (16384, 700), (16385, 16385)])
 def test_rows_at_the_edges(M, cap, in_place):
     w = synth.Workload("box-rows", 2, 4, 4, 128, 4 * M, 4, "bf16")
