@@ -53,9 +53,39 @@ def test_every_page_size_and_number_of_heads(dtype, page, heads):
         check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), None, ref, boundary_expected=True)
 
 
+def items_per_wavefront(w, units, all_pages):
+    """Items (groups of pages of 33 to 64 tokens) that a wavefront of the score pass takes, by the launcher's rule."""
+    items = units * -(-w.pages_per_seq // max(1, 64 // w.page_size))
+    per_cu = (128 if units <= 1024 else 32) if all_pages else (16 if units <= 256 else 8)
+    workgroups = min(-(-items // 4), per_cu * torch.cuda.get_device_properties(0).multi_processor_count)
+    return items / (4 * workgroups)
+
+
+@pytest.mark.parametrize("dtype,page", [("f32", 8), ("f32", 20), ("f32", 36), ("bf16", 12), ("bf16", 28), ("bf16", 48)])
+@pytest.mark.parametrize("heads", [(8, 8), (16, 8), (32, 8), (64, 8)])
+def test_wavefronts_that_take_several_batches(heads, dtype, page):
+    """130 sequences on the same pages, 1040 units and more: in every mode a wavefront takes more items than the four that it
+    resolves at once, and crosses from unit to unit; the lists of 64 heads are so many that their prefix is kept in memory."""
+    w = synth.Workload("batches", 130, heads[0], heads[1], 128, 9603, page, dtype)
+    for units, all_pages in ((130 * heads[1], True), (130 * heads[1], False), (130 * heads[0], False)):
+        assert items_per_wavefront(w, units, all_pages) > 4.5
+    inp = synth.make_inputs(w.scaled(batch=1), 13 + page, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(page)
+    inp["q"] = torch.randn(130, heads[0], 128, generator=gen, device="cuda").to(inp["q"].dtype)
+    inp["block_table"] = inp["block_table"].expand(130, -1).contiguous()
+    inp["seq_lens"] = torch.tensor([9603 - 7 * (b % 5) for b in range(130)], device="cuda", dtype=torch.int32)
+    out, tau, supp = decode_three_ways(w, inp)
+    inp = {key: x.cpu() for key, x in inp.items()}
+    for b, h in ((0, 0), (64, heads[0] // 2), (129, heads[0] - 1)):
+        q, K, V = unit_kv(inp, w, b, h)
+        ref = orc.entmax_attention(q, K, V, w.alpha, w.score_scale)
+        check_decode_unit(w, out[b, h], float(tau[b, h]), int(supp[b, h]), None, ref, boundary_expected=True)
+
+
 @pytest.mark.parametrize("dtype,page", [("f32", 8), ("f32", 36), ("bf16", 12), ("bf16", 48)])
 def test_more_items_than_a_wavefront_resolves_at_once(dtype, page):
-    """128 lists of 40 000 tokens: five and more items to each of the score pass's wavefronts (four per batch of lookups)."""
+    """128 lists of 40 000 tokens: by lists per head five and more items to a wavefront of the score pass in pages of 36 and 48,
+    four and fewer in the others; one or two by the other ways (more of them: the test above)."""
     w = synth.Workload("steps", 4, 32, 8, 128, 40003, page, dtype)
     inp = synth.make_inputs(w, 11 + page, device="cuda")
     inp["seq_lens"] = torch.tensor([40003, 39000, 37, 40000], device="cuda", dtype=torch.int32)
