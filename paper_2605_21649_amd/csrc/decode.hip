@@ -1679,8 +1679,11 @@ __global__ __launch_bounds__(64) void decode_solve_one_kernel(const SolveArgs A)
                       wants_side_outputs<false>(A), sh);
 }
 
+// Its 160 KB of code are fetched anew by few compute units in every call, behind a stream that has emptied the caches, so that
+// where they lie shows: the same instructions at other addresses took 1 x 32K tokens from 22.4 to 22.7 us (across a boundary
+// of 2 MB) and its Gaussian step from 42.9 to 43.5.  From the start of a page on: 22.4 and 42.6.
 template <typename T, bool DENSE, typename SH>
-__global__ __launch_bounds__(64 * SH::kWaves) void decode_solve_kernel(const SolveArgs A) {
+__global__ __launch_bounds__(64 * SH::kWaves) __attribute__((aligned(4096))) void decode_solve_kernel(const SolveArgs A) {
   __shared__ SH sh;
   constexpr int NT = 64 * SH::kWaves, NW = SH::kWaves, LIST = SH::kListCap;
   constexpr int kRoundTokens = NT * kRoundLoads;
