@@ -31,11 +31,11 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch from the committed counter runs (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, each scaled by
 # the same counter's reading for a plain copy of known size): NOT measured in this run, copied from
 # profiles/bench_topk_step_C4.md, and valid for the C4 workload at the default budget only.
-#   page scoring with the append inside (the launch the step runs): 256.32 MiB read + 8.02 MiB written;
-#   without the append: 256.12 + 8.00;  score pass of the sparse decode: PMC_TRAFFIC_DECODE_SCORES_C4
+#   page scoring, statistics read past the caches, with the append inside (the launch the step runs): 256.33 MiB read +
+#   8.02 MiB written;  without the append: 256.12 + 8.00;  score pass of the sparse decode: PMC_TRAFFIC_DECODE_SCORES_C4
 PMC_TRAFFIC_SOURCE = "profiles/bench_topk_step_C4.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a plain copy)"
-PMC_TRAFFIC_SCORE_PAGES_C4 = {True: int((256.32 + 8.02) * 1024 * 1024), False: int((256.12 + 8.00) * 1024 * 1024)}
-PMC_TRAFFIC_DECODE_SCORES_C4 = int((150.30 + 2.81) * 1024 * 1024)
+PMC_TRAFFIC_SCORE_PAGES_C4 = {True: int((256.33 + 8.02) * 1024 * 1024), False: int((256.12 + 8.00) * 1024 * 1024)}
+PMC_TRAFFIC_DECODE_SCORES_C4 = int((150.39 + 2.80) * 1024 * 1024)
 
 # the append runs inside the scoring launch (ekv_append_score_pages) unless --two-launch-append is given
 STAGE_NAMES = {"topk": ["append_own_launch", "append+score_box", "select_topk", "decode_sparse"],
@@ -481,9 +481,11 @@ def main():
     pmc_traffic = {"C4": PMC_TRAFFIC_SCORE_PAGES_C4[bool(R.fused_append)]}
     roofline = {
         "bound": "hbm",
-        "kernel": "score_pages_mfma_kernel<%d, 0, %s> (%s)" % (w.group, "true" if R.fused_append else "false",
-                                                              "ekv_append_score_pages" if R.fused_append
-                                                              else "ekv_score_pages"),
+        # the last argument: statistics of 32 MiB and more are read past the caches
+        "kernel": "score_pages_%s_kernel<%d, %s, %s, %s> (%s)" % (
+            *(("mfma", w.group, "0") if w.kv_dtype == "bf16" else ("f32", w.group, "false")),
+            "true" if R.fused_append else "false", "true" if bytes_meta >= 32 << 20 else "false",
+            "ekv_append_score_pages" if R.fused_append else "ekv_score_pages"),
         "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
         "traffic": pmc_traffic.get(args.workload),
         "algorithmic_bytes_per_launch": int(roof_bytes), "avg_launch_us": round(roof_us, 2),
@@ -501,7 +503,7 @@ def main():
     a7_ach = (a7_traffic or a7_bytes) / (t_dec_scores * 1e-6) / 1e9
     call_ach = kernel_alg_bytes["decode_sparse"] / (t_dec * 1e-6) / 1e9
     roofline_a7 = {
-        "bound": "hbm", "kernel": "decode_scores_mfma_kernel<1, 0, %d> (score pass of ekv_decode_sparse)" % P,
+        "bound": "hbm", "kernel": "decode_scores_mfma_kernel<1, 0, %d, false, false> (score pass of ekv_decode_sparse)" % P,
         "achieved": round(a7_ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(a7_ach / HBM_PEAK_GBS, 4),
         "traffic": a7_traffic, "requested_GBps": round(a7_req, 1),
         "algorithmic_bytes_per_launch": int(a7_bytes), "avg_launch_us": round(t_dec_scores, 2),

@@ -2259,8 +2259,7 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
     hipLaunchKernelGGL((unit_prefix_kernel<MODE>), dim3(1), dim3(1024), 0, st, sa, pre_ws);
   }
   // K of a large call over all pages, or over lists that the heads of a group share or that are one head's own, passes once
-  // and goes past the caches (load16<true>): otherwise it pushes out the lines of scores, which the wavefronts fill 64
-  // bytes at a time, before they are whole.  Calls, us, kept / past the caches: all pages of 1 x 1M tokens 473 / 427, 8 x
+  // and goes past the caches (load16<true>).  Calls, us, kept / past the caches: all pages of 1 x 1M tokens 473 / 427, 8 x
   // 256K in pages of 32 954 / 925, 2 x 128K for 64 heads 140.7 / 124.4, 2 x 128K in pages of 12 135.1 / 125.7, 2 x 32K (134
   // MB) 41.8 / 37.4; 1 x 32K 23.4 / 22.5 with four inputs in turn, 22.4 / 22.9 with three, which the last cache holds, 1 x
   // 4K 13.4 / 13.8.  Group steps, whose lists follow a stream of statistics, by the capacity, all that the host knows (it
@@ -2268,9 +2267,11 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
   // loads of a row on whole lines (load_halves): 2 x 128K 229 / 208, on half lines 249.  Lists of heads without a group:
   // Gaussian steps of 4 x 128K 71.0 / 67.4, 8 x 32K 89.6 / 79.8, refined 4 x 32K 99.9 / 90.1, top-k by capacity 268 MB 69.8
   // / 63.8, 134 MB 44.3 / 43.2, 67 MB 33.9 / 33.7.  Lists per head of a group meet in the caches (16 x 16K Gaussian step
-  // 253 / 324) and keep theirs.
+  // 253 / 324) and keep theirs.  The line is the capacity's, not the lists': lists of 4K tokens in a capacity of a million,
+  // repeated, take 12.8 / 13.5 (on changing inputs 13.5 / 13.7); kernels with both loops, which choose by the lists, take 13.2
+  // there but 31.3 for 28.8 over all pages of 4K tokens in that capacity.
   const long long k_bytes = (long long)sa.U * (MODE == kAllPages ? dm.Mmax : dm.cap) * dm.P * kD * (dm.dtype == EKV_F32 ? 4 : 2);
-  const bool past_caches = (MODE != kPerHead || dm.G == 1) && k_bytes >= (MODE == kAllPages ? kStreamKBytes : kStreamKBytes / 2);
+  const bool past_caches = (MODE != kPerHead || dm.G == 1) && k_bytes >= (MODE == kAllPages ? kStreamKBytes : kStreamListBytes);
 #define EKV_SCORES_S(KERNEL, STREAM, ...)                                                                 \
   do {                                                                                                       \
     if (pre_global) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, STREAM, true>), grid, block, lds, st, sa);     \

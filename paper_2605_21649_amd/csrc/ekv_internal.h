@@ -26,10 +26,11 @@ constexpr int kPreGroups = 16384;         // rows of at most this many groups ar
 constexpr int kFilterMaxSlices = 1024;    // ... unless they would need more slices than this
 constexpr int kFilterSliceCap = 4096;     // candidates kept per slice (the solve holds this many in LDS)
 
-// Streams of at least this many bytes are read past the caches (load16<true>).  Smaller ones may still be there from the call
-// before, and a fetch would be no faster: statistics, of which a step has several tables, from the size of all L2s together,
-// K from half the size of the last cache.  Both sides as measured stand at the launchers.
-constexpr long long kStreamStatsBytes = 32ll << 20, kStreamKBytes = 128ll << 20;
+// Streams of at least this many bytes are read past the caches (load16<true>); of smaller ones enough may still be there that a
+// fetch is no faster.  The lines are drawn where whole steps on changing inputs gain: statistics, of which a step reads one
+// table of several, K of decodes over all pages and of builds, K of lists (by their capacity, which steps fill to half or
+// less).  Both sides as measured stand at the launchers.
+constexpr long long kStreamStatsBytes = 32ll << 20, kStreamKBytes = 128ll << 20, kStreamListBytes = 64ll << 20;
 
 struct DecodeWorkspace {
   float* z;        // [B*Hq][zstride] candidate scores z_j (or -inf where masked)

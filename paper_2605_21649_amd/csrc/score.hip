@@ -390,10 +390,16 @@ static void launch_score_GA(const Dims& dm, const void* q, const ekv_stats_view&
   const dim3 grid_g = score_grid(dm, kScoreTile, APPEND && ap_gauss.mode == 1, &ap_gauss);
   const long long records = (long long)dm.B * dm.Hkv * dm.Mmax;
   if (dm.dtype == EKV_BF16) {
-    // Statistics are read once a step.  Past the caches they leave room there for the pages and scores the rest of the step
-    // shares, and stream faster.  Whole steps on changing inputs, us, kept / past the caches: top-k on 268 MB (1 x 1M tokens)
-    // 112.1 / 107.2, on 134 MB (64 x 8K) 58.4 / 54.9 and on 34 MB 33.7 / 33.3, 8-bit groups on 134 MB 62.0 / 54.3, Gaussian on
-    // 67 MB (1 x 256K) 64.3 / 58.7; but top-k on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
+    // Statistics are read once a step, and past the caches they stream faster.  Whole steps on changing inputs, us, kept / past
+    // the caches: top-k on 268 MB (1 x 1M tokens) 112.2 / 108.8, on 134 MB (64 x 8K) 62.4 / 59.3, on 67 MB 47.7 / 43.8 and on 34 MB
+    // 33.9 / 33.8, 8-bit groups on 134 MB 56.5 / 54.3, on 67 MB 46.6 / 43.7, on 34 MB 39.4 / 37.8, Gaussian on 67 MB 64.7 / 59.1, on
+    // 34 MB 60.0 / 57.4; but top-k on 17 MB, which several steps' inputs find in the last cache, 28.7 / 29.3.
+    // On a table that a launch just before has written, and that the last cache may hold, the two are even: top-k on 34, 67, 134
+    // and 268 MB 35.8 / 36.6, 45.4 / 46.4, 72.0 / 68.1 and 128.5 / 108.8, 8-bit groups on 34, 67 and 134 MB 41.6 / 40.9, 47.2 / 46.2
+    // and 60.4 / 60.7, Gaussian on 67 MB 60.4 / 59.8 (the first step of all on new inputs, 8-bit groups on 134 MB, 74.3 / 79.1).  A
+    // model's steps find other layers' tables and weights there, so that the line follows the changing inputs.
+    // It is drawn by the capacity.  4K to 64K tokens in a capacity of a million, scored alone, 15.8 / 15.9, in float32 17.1 to
+    // 18.0 / 17.1 to 19.5; loads chosen by length in the kernel cost every step as much (64 x 8K 58.5 -> 59.1, 1 x 128K 33.4 -> 33.7).
     const auto launch = [&](auto kind, const dim3& g, const void* stats, float* out0, float* out1, int group_max, const ScoreAppend& ap) {
       constexpr int KIND = decltype(kind)::value;
       const long long bytes = records * (KIND == kKindBox8 ? 2 * kD : 4 * kD);

@@ -13,9 +13,10 @@ constexpr int kSmRec = kD + 2;          // floats per partial record: o[128], m,
 constexpr int kSmPagesPerBlock = 8;     // page slots per workgroup (one partial record)
 
 // One wavefront handles kSmPagesPerBlock / kSmWaves pages, their tokens in batches of four steps of four (lane = (token mod 4,
-// channels 8c..8c+7 of K, whose order of summation is the decode's, and those of load_row8 of V)): the K and V rows of a batch are fetched by unconditional loads and the running maximum is updated
-// once per batch.  A batch may hold steps of two pages, so pages of 8 tokens waste none, pages of 12 a quarter of the second
-// batch.  Page and block-table indices are clamped into range; tokens past the sequence end are masked.
+// channels 8c..8c+7 of K, whose order of summation is the decode's, and those of load_row8 of V)): the K and V rows of a batch
+// are fetched by unconditional loads and the running maximum is updated once per batch.  A batch may hold steps of two pages,
+// so pages of 8 tokens waste none, pages of 12 half of the second batch.  Page and block-table indices are clamped into range;
+// tokens past the sequence end are masked.
 // Work distribution: an item is one chunk of kSmPagesPerBlock page slots of one (b,h) row.  The launch has a fixed
 // number of workgroups that does not depend on the capacity of the page lists: every workgroup builds the exclusive
 // prefix of the chunks per row from the device-side list lengths (LDS) and takes a contiguous range of the

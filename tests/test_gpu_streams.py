@@ -1,5 +1,6 @@
-"""Calls large enough to read their streams past the caches (32 MiB of statistics, 128 MiB of K) against the same sequences one
-by one, which are small enough not to: bit for bit, since only the kind of the loads differs."""
+"""Calls large enough to read their streams past the caches (32 MiB of statistics, 128 MiB of K of decodes over all pages and of
+builds, 64 MiB of K of lists that a group shares or a head without one has) against the same sequences one by one, which are
+small enough not to: bit for bit, since only the kind of the loads differs."""
 import pytest
 import torch
 
