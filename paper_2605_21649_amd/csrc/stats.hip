@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64) void stats_append_kernel(T* __restrict__ k_pool
 }
 
 // The statistics, and K of a large build, go past the caches: they stream faster so.  us, neither / K / statistics /
-// both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.28 GB, 6.0 TB/s; 203 to 215 from box to box), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
+// both: 4 x 128K tokens 249.6 / 251 / 225.7 / 211 (1.28 GB, 6.0 TB/s; 203 to 215 from machine to machine), 64 x 4K 138 / 136 / 128 / 115, 1 x 256K in pages of
 // 64 121.5 / 112 / 115 / 104, 1 x 64K (134 MB of K) 45.6 / 38.7 / 43.3 / 38.4.  K of a smaller build may still lie in the last
 // cache, where the prefill wrote it: 1 x 32K 25.5 / 22.8 / 16.5 / 22.2, 1 x 16K 9.9 / 11.4 / 9.2 / 10.4, 1 x 4K 6.6 / 7.0 / 6.5 / 6.9.
 // float32, by loads and stores of whole lines as well: 2 x 64K 137.6 -> 114.5, 1 x 16K 20.3 -> 13.7.
