@@ -39,6 +39,8 @@ template <bool STREAM = false> __device__ __forceinline__ uint4 load16(const voi
   if constexpr (STREAM) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
   else return *reinterpret_cast<const uint4*>(p);
 }
+// Buffer resources of plain bytes, and the cache bits of the buffer instructions: non-temporal; through the caches to memory.
+constexpr int kBufferFlags = 0x00020000, kBufferNt = 2, kBufferThrough = 17;
 template <bool STREAM = false> __device__ __forceinline__ void store16(void* p, const uint4& v) {
   if constexpr (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(p));
   else *reinterpret_cast<uint4*>(p) = v;
