@@ -123,15 +123,16 @@ void decode_scores_steps_kernel(const ScoreArgs A) {
   const WaveItems wi = wave_item_range(pre, A.U, w, part);
   const int last = (DENSE ? A.Mmax : A.cap) - 1;
 
+  int unit0 = wi.unit;                             // the batch's first unit, or one before
   for (int it0 = wi.begin; it0 < wi.end; it0 += kBatchItems) {
     // lane l: step l % 16 of item it0 + l / 16 (clamped to the last item and step): its row of K and how many of its
     // tokens are valid (-1: the step is not stored)
     int l_unit, l_grp, l_row, l_left;
     {
       const int my_it = min(it0 + lane / kStepLanes, wi.end - 1);
-      int lo = 0, hi = A.U;
-      while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (pre[mid] <= my_it) lo = mid; else hi = mid; }
+      const int lo = lane_last_at_most(pre, A.U, unit0, my_it, min(it0 + kBatchItems, wi.end) - 1);
       l_unit = lo;
+      unit0 = __builtin_amdgcn_readlane(lo, 63);
       const int b = GROUPED ? lo / Hkv : lo / Hq, hkv = GROUPED ? lo - b * Hkv : (lo - b * Hq) / ratio;
       const int n = A.seq_lens[b], n_slots = DENSE ? clampi((n + P - 1) / P, 0, A.Mmax) : unit_slots<MODE>(A, lo);
       l_grp = my_it - pre[lo];
@@ -322,14 +323,15 @@ void decode_scores_mfma_kernel(const ScoreArgs A) {
   const WaveItems wi = wave_item_range(pre, A.U, w, part);
   const int last = (DENSE ? A.Mmax : A.cap) - 1;
 
+  int unit0 = wi.unit;                             // the batch's first unit, or one before
   for (int it0 = wi.begin; it0 < wi.end; it0 += kBatchItems) {
     // lane l: page slot l % GP of item it0 + l / GP (clamped to the last item): its unit, logical and physical page
     int l_unit, l_lp, l_phys, l_grp;
     {
       const int my_it = min(it0 + lane / GP, wi.end - 1);
-      int lo = 0, hi = A.U;
-      while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (pre[mid] <= my_it) lo = mid; else hi = mid; }
+      const int lo = lane_last_at_most(pre, A.U, unit0, my_it, min(it0 + kBatchItems, wi.end) - 1);
       l_unit = lo;
+      unit0 = __builtin_amdgcn_readlane(lo, 63);
       l_grp = my_it - pre[lo];
       if (!GROUPED && part.count != 1) l_grp += part_first(part, lo / ratio, (unit_slots<MODE>(A, lo) + GP - 1) / GP);
       const int slot = min(l_grp * GP + lane % GP, last);

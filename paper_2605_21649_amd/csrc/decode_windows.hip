@@ -38,10 +38,11 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_windows_kernel(co
 
   // lane l: page slot l % GP of item it0 + l / GP (clamped to the last item): unit, group, physical page
   struct Slots { int unit, grp, phys; };
+  int unit0 = wi.unit;                             // the batch's first unit, or one before
   auto look_up = [&](int it0) {
     const int my_it = min(it0 + lane / GP, wi.end - 1);
-    int lo = wi.unit, hi = A.U;
-    while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (pre_lds[mid] <= my_it) lo = mid; else hi = mid; }
+    const int lo = lane_last_at_most((const int*)pre_lds, A.U, unit0, my_it, min(it0 + kBatchItems, wi.end) - 1);
+    unit0 = __builtin_amdgcn_readlane(lo, 63);
     Slots s{lo, my_it - pre_lds[lo], 0};
     const int slot = min(s.grp * GP + lane % GP, A.Mmax - 1);
     s.phys = clampi(A.block_table[(size_t)(lo / A.Hkv) * A.Mmax + slot], 0, A.n_phys - 1);

@@ -76,12 +76,7 @@ __device__ __forceinline__ WaveItems wave_item_range(const P pre, int U, int w, 
   WaveItems r;
   r.begin = gw * per + min(gw, rem);
   r.end = r.begin + per + (gw < rem ? 1 : 0);
-  int lo = 0, hi = U;                                   // pre[lo] <= begin < pre[hi] whenever begin < total
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (uniform(pre[mid]) <= r.begin) lo = mid; else hi = mid;
-  }
-  r.unit = lo;
+  r.unit = wave_last_at_most(pre, U, r.begin);          // pre[unit] <= begin < pre[unit + 1] whenever begin < total
   return r;
 }
 

@@ -155,9 +155,7 @@ __global__ __launch_bounds__(kSmThreads) void softmax_partial_kernel(const SmArg
   const int per = total / G, rem = total - per * G;
   const int begin = wg * per + min(wg, rem), end = begin + per + (wg < rem ? 1 : 0);
   if (begin >= end) return;
-  int lo = 0, hi = A.rows;                          // sm_pre[lo] <= begin < sm_pre[hi]
-  while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (sm_pre[mid] <= begin) lo = mid; else hi = mid; }
-  int bh = lo;
+  int bh = wave_last_at_most((const int*)sm_pre, A.rows, begin);
   for (int it = begin; it < end; ++it) {
     while (it >= sm_pre[bh + 1]) ++bh;
     softmax_chunk<T, PT>(A, bh, it - sm_pre[bh], s_o, s_m, s_l);
