@@ -973,9 +973,10 @@ __device__ __forceinline__ float group_bound(const float (&u)[R], float t0, floa
 }
 
 // The end of a row whose candidates are few: threshold, support and weighted value sum by ONE wavefront, KW entries per
-// lane, taken from the segments (sh.pre: the prefix of their lengths).  V rows are looked up while the threshold is solved.
+// lane, taken from the segments (ends: where segment `lane` ends among the candidates).  V rows are looked up while the
+// threshold is solved.
 template <typename T, bool DENSE, int KW, typename SH>
-__device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef& R, int n_list, float lo_u, float zmax,
+__device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef& R, int n_list, int ends, float lo_u, float zmax,
                                                 float seed_u, SH& sh) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
@@ -984,13 +985,26 @@ __device__ __forceinline__ void finish_row_wave(const SolveArgs& A, const RowRef
   float* lu = sh.list_u; int32_t* lp = sh.list_pos; uint32_t* lr = sh.list_row;
   float u[KW]; int pos[KW]; uint32_t row[KW];
   int at[KW];
+  if constexpr (KW == 1) {                                            // segment ends from lane to lane: no LDS latency
+    int seg = 0, start = 0;
 #pragma unroll
-  for (int k = 0; k < KW; ++k) {
-    const int e = lane + 64 * k;
-    int seg = 0;                                                      // last segment that starts at or before e
+    for (int d = 0; d < kSegs - 1; ++d) {
+      const int end = __builtin_amdgcn_readlane(ends, d);
+      if (end <= lane) { seg = d + 1; start = end; }
+    }
+    at[0] = seg * SH::kSegCap + min(lane - start, SH::kSegCap - 1);
+  } else {
+    if (lane < kSegs) sh.pre[lane + 1] = ends;
+    if (lane == 0) sh.pre[0] = 0;
+    wave_order();
 #pragma unroll
-    for (int d = kSegs / 2; d >= 1; d >>= 1) seg += sh.pre[seg + d] <= e ? d : 0;
-    at[k] = seg * SH::kSegCap + min(e - sh.pre[seg], SH::kSegCap - 1);
+    for (int k = 0; k < KW; ++k) {
+      const int e = lane + 64 * k;
+      int seg = 0;                                                    // last segment that starts at or before e
+#pragma unroll
+      for (int d = kSegs / 2; d >= 1; d >>= 1) seg += sh.pre[seg + d] <= e ? d : 0;
+      at[k] = seg * SH::kSegCap + min(e - sh.pre[seg], SH::kSegCap - 1);
+    }
   }
 #pragma unroll
   for (int k = 0; k < KW; ++k) {
@@ -1145,15 +1159,27 @@ __device__ __forceinline__ int fetch_candidates(const RowRef& R, const float* zr
   const int sub = lane >> 4, in_group = 4 * (lane & 15);
   int cnt = 0;
   // tokens per group and per row are multiples of 4: a lane's four scores are valid together
+  const int in_c = min(in_group, R.chunk_tokens - 4), p_end = in_group < R.chunk_tokens ? R.n_cand : 0;
   auto request = [&](int j, int& p, float4& v) {
     const int g = sh.glist[min(j + sub, j1 - 1)];
-    p = g * R.chunk_tokens + min(in_group, R.chunk_tokens - 4);
-    p = min(p, R.n_cand - 4);
-    v = *reinterpret_cast<const float4*>(zr + p);
-    if (j + sub >= j1 || in_group >= R.chunk_tokens || g * R.chunk_tokens + in_group >= R.n_cand) p = -1;
+    p = g * R.chunk_tokens + in_c;
+    v = *reinterpret_cast<const float4*>(zr + min(p, R.n_cand - 4));
+    if (j + sub >= j1 || p >= p_end) p = -1;
   };
   auto compact = [&](int p, const float4& v) {
     const float t = p >= 0 ? thr : INFINITY;
+    const float hi0 = fmaxf(v.x, v.y), hi1 = fmaxf(v.z, v.w), top = fmaxf(hi0, hi1);
+    const uint64_t m = __ballot(top > t);
+    if (m == 0) return;                                               // wave-uniform, as the next
+    const float second = fmaxf(fmaxf(fminf(v.x, v.y), fminf(v.z, v.w)), fminf(hi0, hi1));
+    if (__ballot(second > t) == 0) {                                  // no lane has two: most loads of a flat row, nearly all of any other
+      if (top > t) {
+        const int o = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, cnt));
+        put(o, top, p + (hi0 > t ? (v.x > t ? 0 : 1) : (v.z > t ? 2 : 3)));
+      }
+      cnt += __popcll(m);
+      return;
+    }
     const bool i0 = v.x > t, i1 = v.y > t, i2 = v.z > t, i3 = v.w > t;
     const uint64_t m0 = __ballot(i0), m1 = __ballot(i1), m2 = __ballot(i2), m3 = __ballot(i3);
     int o = cnt;
@@ -1382,8 +1408,8 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
       }
     }
   } else {
-    // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
-    // flight per lane; the next 64 are looked up before these are consumed
+    // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, sixteen 16-byte loads in
+    // flight per lane (float32, or 32 rows and less: eight); the next 64 are looked up before these are consumed
 #pragma unroll 1
     for (int i = 0; i < SPW; ++i) {
       const uint2* seg = seg0 + i * SH::kSegCap;
@@ -1398,23 +1424,28 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
         const uint32_t row_now = row;
         row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, ns - 1)].y);
         const float p_now = e0 + lane < ns ? __uint_as_float(seg[e0 + lane].x) : 0.f;
+        auto add_rows = [&](int first, auto count) {
+          constexpr int N = decltype(count)::value;
+          Raw8<T> vr[N]; float pw[N];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          Raw8<T> vr[8]; float pw[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int src = 32 * half + 4 * j + rs;
+          for (int j = 0; j < N; ++j) {
+            const int src = first + 4 * j + rs;
             pw[j] = __shfl(p_now, src);
             load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
           }
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
+          for (int j = 0; j < N; ++j) {
             float vv[8];
             widen8(vr[j], vv);
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
           }
-          if (e0 + 32 >= ns) break;                                     // wave-uniform
+        };
+        const bool more = ns - e0 > 32;                                 // wave-uniform
+        if (sizeof(T) == 2 && more) add_rows(0, IntC<16>{});
+        else {
+          add_rows(0, IntC<8>{});
+          if (more) add_rows(32, IntC<8>{});
         }
       }
       store_partial(acc, sh, s0 + i);
@@ -1528,14 +1559,9 @@ __device__ __forceinline__ bool solve_bounded_row(const SolveArgs& A, const RowR
   if (__builtin_expect(block_extras, 0)) side_outputs<DENSE>(A, R.bh, R.n_cand, zr, zmax, sh);
   if (__builtin_expect(total <= kWaveList, 1)) {
     if (w == 0) {
-      int inc = cw;                                                   // prefix of the segments' lengths
-#pragma unroll
-      for (int d = 1; d < kSegs; d <<= 1) { const int t = __shfl_up(inc, d); if (lane >= d) inc += t; }
-      if (lane < kSegs) sh.pre[lane + 1] = inc;
-      if (lane == 0) sh.pre[0] = 0;
-      wave_order();
-      if (total <= 64) finish_row_wave<T, DENSE, 1>(A, R, total, lo_u, zmax, seed_u, sh);
-      else finish_row_wave<T, DENSE, kWaveList / 64>(A, R, total, lo_u, zmax, seed_u, sh);
+      const int ends = wave_incl_scan_i(cw);                          // where the segments end
+      if (total <= 64) finish_row_wave<T, DENSE, 1>(A, R, total, ends, lo_u, zmax, seed_u, sh);
+      else finish_row_wave<T, DENSE, kWaveList / 64>(A, R, total, ends, lo_u, zmax, seed_u, sh);
     }
   } else {
     finish_row_block<T, DENSE>(A, R, lo_u, zmax, seed_u, sh);
