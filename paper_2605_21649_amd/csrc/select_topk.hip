@@ -6,16 +6,19 @@
 // writes the indices with a ballot-based ordered compaction.
 //
 // Long contexts: a single compute unit per head is the bottleneck (the paper's "explicit top-k
-// bottleneck"), so the work is split over slices of 4096 pages and three launches:
+// bottleneck"), so the counting is split over slices of 4096 pages, in two or three launches:
 //   hist     (slices x heads workgroups)  2048-bin histogram of each slice over a key range estimated from
-//                                         the first 1024 pages (keys outside are clamped into the edge bins,
-//                                         which keeps the binning monotone), stored as counts-above per bin;
+//                                         1024 sampled pages (keys outside are clamped into the edge bins,
+//                                         which keeps the binning monotone), stored as counts-above per bin, and
+//                                         the slice's 512 best pages grouped by bin;
 //   find     (one workgroup per head)     bin of the k-th largest from the summed counts, its members are
-//                                         gathered and ranked exactly -> the k-th key, the tie quota and the
-//                                         output offset of every slice;
-//   compact  (slices x heads workgroups)  ordered compaction of each slice against that key.
+//                                         gathered and ranked exactly -> the k-th key.  Budgets of a few thousand pages:
+//                                         the selection is marked in a bitmap of the pages, from the slices'
+//                                         lists, and written out of it in order, for 1 us instead of a launch of 5.6;
+//   compact  (slices x heads workgroups)  larger budgets: ordered compaction of each slice against that key, with the
+//                                         tie quota and the output offsets of the find kernel.
 // If the bin of the k-th key holds more members than the ranking list (massive ties), the find workgroup
-// does that head by the single-workgroup algorithm itself and the compaction launch skips it.
+// does that head by the single-workgroup algorithm itself.
 #include "ekv_select.h"
 #include "ekv_internal.h"
 
@@ -122,13 +125,15 @@ constexpr int kTkSample = 1024;                               // pages the key r
 constexpr int kTkMembers = 1024;                              // ranking list of the find kernel
 constexpr int kTkMaxSlices = 64;
 constexpr int kTkPrefix = 512;                                // best pages of a slice kept sorted by bin
+constexpr int kTkEmitPages = 5376, kTkEmitSlice = 352;        // budgets, whole and per slice, that the find kernel writes itself
 
 struct TopkHead {             // per (b,h) state passed between the launches
   uint32_t lo;                // bin(key) = key <= lo ? 0 : min(kBins-1, (key - lo) >> shift)
   int32_t shift;
+  // for the compact kernel
   uint32_t key_t;             // the k-th largest key
   int32_t k_eq;               // how many pages with key == key_t are taken (lowest indices first)
-  int32_t redo;               // 1: the single-workgroup algorithm must redo this head
+  int32_t done;               // 1: the head is finished, by the single-workgroup algorithm
   int32_t pad[3];
 };
 struct TopkWs {
@@ -205,7 +210,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_hist_kernel(const float* __re
   const uint32_t range = hi_w - lo_w;
   const int bits = range ? 32 - __clz(range) : 0;
   const int shift = max(bits - kDigitBits, 0);
-  if (slice == 0 && tid == 0) { ws.head[bh].lo = lo_w; ws.head[bh].shift = shift; ws.head[bh].redo = 0; }
+  if (slice == 0 && tid == 0) { ws.head[bh].lo = lo_w; ws.head[bh].shift = shift; ws.head[bh].done = 0; }
 
   uint32_t key[kTkItems], vmask;
   load_slice_keys(s, M, slice * kTkSlice + w * (kTkSlice / kTkWaves) + lane, key, vmask);
@@ -255,6 +260,8 @@ __global__ __launch_bounds__(kTkThreads) void topk_hist_kernel(const float* __re
   for (int t = tid; t < min(kTkPrefix, n_valid); t += kTkThreads) { pk[t] = pre_key[t]; pp[t] = pre_page[t]; }
 }
 
+// EMIT: the selection is written here; otherwise what the compact kernel needs for it.
+template <bool EMIT>
 __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __restrict__ box,
                                                                 const int32_t* __restrict__ seq_lens, int k_pages,
                                                                 TopkWs ws, int32_t* __restrict__ page_idx,
@@ -266,14 +273,21 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
   __shared__ int s_gt[kTkMaxSlices], s_eq[kTkMaxSlices];
   __shared__ int s_bin, s_cnt, s_m;
   __shared__ uint32_t s_keyt;
+  extern __shared__ uint32_t page_bits[];              // [2][S * kTkSlice / 32]: keys above the k-th, keys equal to it
   const int bh = blockIdx.x, b = bh / Hq, tid = threadIdx.x;
   const int n = seq_lens[b];
   const int M = (n + P - 1) / P;
   const int k = min(min(k_pages, M), cap);
   const int S = ws.S;
   const float* s = box + (size_t)bh * Mmax;
-  if (M <= 0) { if (tid == 0) n_sel[bh] = 0; return; }
+  if (k <= 0) { if (tid == 0) n_sel[bh] = 0; return; }
   const TopkHead hd = ws.head[bh];
+  const int n_words = S * (kTkSlice / 32);
+  uint32_t* const bits_gt = page_bits;
+  uint32_t* const bits_eq = page_bits + n_words;
+  if constexpr (EMIT)
+    for (int i = tid; i < 2 * n_words; i += kSelThreads) page_bits[i] = 0u;
+  if (!EMIT && tid < kTkMaxSlices) { s_gt[tid] = 0; s_eq[tid] = 0; }
 
   // counts above each bin, summed over the slices (thread t owns bins 2t and 2t+1)
   uint32_t a0 = 0, a1 = 0;
@@ -289,7 +303,6 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
   }
   tot_above[2 * tid] = a0; tot_above[2 * tid + 1] = a1;
   if (tid == 0) { s_m = 0; s_bin = 0; s_cnt = 0; s_keyt = 0u; }
-  if (tid < kTkMaxSlices) { s_gt[tid] = 0; s_eq[tid] = 0; }
   __syncthreads();
   // bin b1 of the k-th largest: above[b1] < k <= above[b1 - 1]   (above[-1] := M)
 #pragma unroll
@@ -308,7 +321,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
   // (above_s[-1] := pages of the slice): copied from there when the range ends inside the list.  A slice
   // whose range does not (more than kTkPrefix of its pages at or above the bin: the top pages crowd into a
   // few slices, or the budget is very large) has its 4096 scores scanned instead.
-  __shared__ int s_lo[kTkMaxSlices], s_cnt_s[kTkMaxSlices], s_start[kTkMaxSlices + 1], s_all[kTkMaxSlices];
+  __shared__ int s_lo[kTkMaxSlices], s_hi[kTkMaxSlices], s_cnt_s[kTkMaxSlices], s_start[kTkMaxSlices + 1];
   __shared__ unsigned long long s_scan_mask;             // slices to scan (kTkMaxSlices <= 64: the first wavefront's ballot)
   static_assert(kTkMaxSlices <= 64, "one ballot covers the slices");
   if (tid < 64) {
@@ -319,7 +332,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
       const int valid_s = max(0, min(kTkSlice, M - tid * kTkSlice));
       const int hi_s = b1 == 0 ? valid_s : (int)ab[b1 - 1];
       scan = hi_s > kTkPrefix && hi_s > lo_s;
-      s_lo[tid] = lo_s; s_cnt_s[tid] = scan ? 0 : hi_s - lo_s; s_all[tid] = max(hi_s - lo_s, 0);
+      s_lo[tid] = lo_s; s_hi[tid] = hi_s; s_cnt_s[tid] = scan ? 0 : hi_s - lo_s;
     }
     const unsigned long long mask = __ballot(scan);
     if (tid == 0) s_scan_mask = mask;
@@ -331,6 +344,17 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
     if (tid == 0) { s_start[S] = run; s_m = run; }       // the scanned slices append behind the copied ones
   }
   __syncthreads();
+  // The slice's best pages, down to bin b1, that this wavefront marks at the end: requested before the ranking.
+  const int lane = tid & 63, wave = tid >> 6;
+  uint32_t first_key[2]; int first_page[2];
+  if constexpr (EMIT) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int sl = min(wave, S - 1), e = min(lane + 64 * i, max(min(s_hi[sl], kTkPrefix) - 1, 0));
+      first_key[i] = ws.prefix_key[((size_t)bh * S + sl) * kTkPrefix + e];
+      first_page[i] = ws.prefix_page[((size_t)bh * S + sl) * kTkPrefix + e];
+    }
+  }
   // Every member of bin b1, wherever it is kept: fn(has, key, page, slice) is called by whole wavefronts (`has` says
   // whether this lane holds a member); a wavefront is inside one slice at a time.
   auto for_each_member = [&](auto&& fn) {
@@ -414,7 +438,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
     all_equal = s_kmin == s_kmax;
     if (all_equal) {
       if (tid == 0) s_keyt = s_kmin;
-      if (tid < S) { s_gt[tid] = 0; s_eq[tid] = s_all[tid]; }
+      if (!EMIT && tid < S) s_eq[tid] = max(s_hi[tid] - s_lo[tid], 0);
     } else {
       // sub-bin of the k_rem-th largest member: thread t owns sub-bins 2t and 2t+1; counts above by a suffix scan
       int sub = -1, above2 = 0, m2 = m;
@@ -445,7 +469,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
         for_each_member([&](bool has, uint32_t kk, int page, int sl) {
           const int sb = has ? sub_of(kk) : -1;
           const unsigned long long up = __ballot(has && sb > sub);
-          if ((tid & 63) == 0 && up) atomicAdd(&s_gt[sl], __popcll(up));     // a wavefront is inside one slice
+          if (!EMIT && (tid & 63) == 0 && up) atomicAdd(&s_gt[sl], __popcll(up));     // a wavefront is inside one slice
           const bool mine = has && sb == sub;
           if (collect) {
             if (mine) {
@@ -470,7 +494,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
         all_equal = true;                                  // one value fills the sub-bin: it is the k-th key
         if (tid == 0) s_keyt = s_kmin;
       } else {
-        if (tid == 0) ws.head[bh].redo = 1;
+        if (!EMIT && tid == 0) ws.head[bh].done = 1;
         __shared__ SelectShared sh;
         topk_single<0>(box, seq_lens, k_pages, page_idx, n_sel, Hq, P, Mmax, cap, sh);
         return;
@@ -500,29 +524,88 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
   }
   __syncthreads();
   const uint32_t key_t = s_keyt;
-  if (!all_equal && tid < m) {
-    const uint32_t kk = mem_key[tid];
-    const int sl = mem_page[tid] / kTkSlice;
-    if (kk > key_t) atomicAdd(&s_gt[sl], 1);
-    else if (kk == key_t) atomicAdd(&s_eq[sl], 1);
+  if constexpr (!EMIT) {
+    if (!all_equal && tid < m) {
+      const uint32_t kk = mem_key[tid];
+      const int sl = mem_page[tid] / kTkSlice;
+      if (kk > key_t) atomicAdd(&s_gt[sl], 1);
+      else if (kk == key_t) atomicAdd(&s_eq[sl], 1);
+    }
+    __syncthreads();
+    // per-slice output offsets: the global loads are done in parallel, the short serial prefix runs on LDS
+    if (tid < 64) {                                      // one lane per slice, wave scans instead of serial loops
+      const int ab_s = tid < S ? (int)ws.above[((size_t)bh * S + tid) * kBins + b1] : 0;
+      const int gt_s = tid < S ? s_gt[tid] : 0, eq_s = tid < S ? s_eq[tid] : 0;
+      const int gt_inc = wave_incl_scan_i(gt_s), eq_inc = wave_incl_scan_i(eq_s);
+      const int k_eq = k_bin - __builtin_amdgcn_readlane(gt_inc, 63);       // pages equal to key_t that are taken
+      const int eq_before = eq_inc - eq_s;
+      const int take_eq = max(0, min(eq_s, k_eq - eq_before));
+      const int mine = ab_s + gt_s + take_eq;
+      const int off_inc = wave_incl_scan_i(mine);
+      if (tid < S) {
+        ws.slice_off[(size_t)bh * S + tid] = off_inc - mine;
+        ws.slice_eq[(size_t)bh * S + tid] = eq_before;
+      }
+      if (tid == 0) { ws.head[bh].key_t = key_t; ws.head[bh].k_eq = k_eq; n_sel[bh] = k; }
+    }
+    return;
+  }
+  // The selection as bits, one per page: from a slice's list as long as that holds all its pages down to bin b1, else
+  // from its scores.
+  for (int sl = wave; sl < S; sl += kSelWaves) {
+    const int hi_s = s_hi[sl];
+    if (hi_s <= kTkPrefix) {                             // wave-uniform
+      const uint32_t* pk = ws.prefix_key + ((size_t)bh * S + sl) * kTkPrefix;
+      const int32_t* pp = ws.prefix_page + ((size_t)bh * S + sl) * kTkPrefix;
+      auto mark = [&](int e, uint32_t kk, int page) {
+        if (e < hi_s && kk >= key_t) atomicOr(&(kk > key_t ? bits_gt : bits_eq)[page >> 5], 1u << (page & 31));
+      };
+      int e0 = 0;
+      if (sl == wave) {
+        mark(lane, first_key[0], first_page[0]);
+        mark(lane + 64, first_key[1], first_page[1]);
+        e0 = 128;
+      }
+      for (; e0 < hi_s; e0 += 64) {
+        const int e = min(e0 + lane, hi_s - 1);
+        mark(e0 + lane, pk[e], pp[e]);
+      }
+    }
+  }
+  for (uint64_t todo = __ballot(s_hi[min(lane, S - 1)] > kTkPrefix && lane < S); todo != 0; todo &= todo - 1) {
+    const int sl = __builtin_ctzll(todo);                 // by all wavefronts: four runs of 64 pages each
+    float raw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) raw[i] = s[min(sl * kTkSlice + (wave * 4 + i) * 64 + lane, M - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = sl * kTkSlice + (wave * 4 + i) * 64;
+      const uint32_t kk = float_to_key(raw[i]);
+      const uint64_t gt = __ballot(p + lane < M && kk > key_t), eq = __ballot(p + lane < M && kk == key_t);
+      if (lane < 2) { bits_gt[p / 32 + lane] = (uint32_t)(gt >> (32 * lane)); bits_eq[p / 32 + lane] = (uint32_t)(eq >> (32 * lane)); }
+    }
   }
   __syncthreads();
-  // per-slice output offsets: the global loads are done in parallel, the short serial prefix runs on LDS
-  if (tid < 64) {                                      // one lane per slice, wave scans instead of serial loops
-    const int ab_s = tid < S ? (int)ws.above[((size_t)bh * S + tid) * kBins + b1] : 0;
-    const int gt_s = tid < S ? s_gt[tid] : 0, eq_s = tid < S ? s_eq[tid] : 0;
-    const int gt_inc = wave_incl_scan_i(gt_s), eq_inc = wave_incl_scan_i(eq_s);
-    const int k_eq = k_bin - __builtin_amdgcn_readlane(gt_inc, 63);       // pages equal to key_t that are taken
-    const int eq_before = eq_inc - eq_s;
-    const int take_eq = max(0, min(eq_s, k_eq - eq_before));
-    const int mine = ab_s + gt_s + take_eq;
-    const int off_inc = wave_incl_scan_i(mine);
-    if (tid < S) {
-      ws.slice_off[(size_t)bh * S + tid] = off_inc - mine;
-      ws.slice_eq[(size_t)bh * S + tid] = eq_before;
-    }
-    if (tid == 0) { ws.head[bh].key_t = key_t; ws.head[bh].k_eq = k_eq; n_sel[bh] = k; }
+  // thread t lists the pages of words [t * wpt, (t + 1) * wpt), behind those of the threads before it
+  __shared__ int w_gt[kSelWaves], w_eq[kSelWaves];
+  const int wpt = (n_words + kSelThreads - 1) / kSelThreads, w0 = min(tid * wpt, n_words), w1 = min(w0 + wpt, n_words);
+  int n_gt = 0, n_eq = 0;
+  for (int i = w0; i < w1; ++i) { n_gt += __popc(bits_gt[i]); n_eq += __popc(bits_eq[i]); }
+  const int inc_gt = wave_incl_scan_i(n_gt), inc_eq = wave_incl_scan_i(n_eq);
+  if (lane == 63) { w_gt[wave] = inc_gt; w_eq[wave] = inc_eq; }
+  __syncthreads();
+  static_assert(kSelWaves == 16, "one DPP row");
+  const int wg = w_gt[lane & 15], we = w_eq[lane & 15];
+  const int k_eq = k - row16_sum_i(wg);                  // pages equal to the k-th key that are taken: the lowest
+  int eq_run = row16_sum_i((lane & 15) < wave ? we : 0) + inc_eq - n_eq;
+  int o = row16_sum_i((lane & 15) < wave ? wg : 0) + inc_gt - n_gt + min(eq_run, k_eq);
+  int32_t* out = page_idx + (size_t)bh * cap;
+  for (int i = w0; i < w1; ++i) {
+    uint32_t take = bits_gt[i];
+    for (uint32_t eq = bits_eq[i]; eq != 0 && eq_run < k_eq; eq &= eq - 1, ++eq_run) take |= eq & (0u - eq);
+    for (; take != 0 && o < k; take &= take - 1) out[o++] = i * 32 + __builtin_ctz(take);
   }
+  if (tid == 0) n_sel[bh] = k;
 }
 
 __global__ __launch_bounds__(kTkThreads) void topk_compact_kernel(const float* __restrict__ box,
@@ -535,7 +618,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_compact_kernel(const float* _
   const int M = (n + P - 1) / P;
   if (slice * kTkSlice >= M) return;
   const TopkHead hd = ws.head[bh];
-  if (hd.redo) return;
+  if (hd.done) return;
   const float* s = box + (size_t)bh * Mmax;
   const int page0 = slice * kTkSlice + w * (kTkSlice / kTkWaves) + lane;
   uint32_t key[kTkItems], vmask;
@@ -623,7 +706,18 @@ void launch_select_topk(const Dims& dm, const float* box, const int32_t* seq_len
   ws.prefix_page = (int32_t*)(ws.prefix_key + BH * ws.S * kTkPrefix);
   dim3 sgrid(ws.S, dm.B * dm.Hq), sblock(kTkThreads);
   hipLaunchKernelGGL(topk_hist_kernel, sgrid, sblock, 0, st, box, seq_lens, ws, dm.Hq, dm.P, dm.Mmax);
-  hipLaunchKernelGGL(topk_find_kernel, grid, block, 0, st, box, seq_lens, k_pages, ws, page_idx, n_sel, dm.Hq, dm.P,
+  // The find kernel writes the selection itself as long as one compute unit writes it sooner than a third launch does, and
+  // nearly all slices' lists hold their part of it.  Calls, us, three launches / two: 32 heads of 65536 pages, 2 % 19.0 / 15.2,
+  // 6 % 20.7 / 19.3, 8 % (5243 pages, 328 a slice) 23.0 / 22.7, 12.5 % (512 a slice) 35.6 / 45.4; of 262144, 2 % (5243)
+  // 44.6 / 41.9, 4 % 57.4 / 59.8; of 20000, 8 % (320 a slice) 16.9 / 15.0, 12.5 % (500) 19.3 / 20.4; 512 heads of 20000, 2 %
+  // 38.7 / 27.0.
+  if (k_pages <= kTkEmitPages && k_pages <= kTkEmitSlice * ws.S) {
+    const size_t lds = 2 * (size_t)ws.S * (kTkSlice / 8);   // at most 64 KiB
+    hipLaunchKernelGGL(topk_find_kernel<true>, grid, block, lds, st, box, seq_lens, k_pages, ws, page_idx, n_sel, dm.Hq, dm.P,
+                       dm.Mmax, dm.cap);
+    return;
+  }
+  hipLaunchKernelGGL(topk_find_kernel<false>, grid, block, 0, st, box, seq_lens, k_pages, ws, page_idx, n_sel, dm.Hq, dm.P,
                      dm.Mmax, dm.cap);
   hipLaunchKernelGGL(topk_compact_kernel, sgrid, sblock, 0, st, box, seq_lens, ws, page_idx, dm.Hq, dm.P, dm.Mmax,
                      dm.cap);
