@@ -359,6 +359,9 @@ __device__ __forceinline__ uint32_t float_to_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+constexpr uint32_t kKeyOfZero = 0x80000000u;
+__device__ __forceinline__ float key_to_float(uint32_t k) { return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k); }
+
 // x^beta for x > 0 with the small integer exponents special-cased (exact products).
 __device__ __forceinline__ float pow_beta(float x, float beta, int ibeta) {
   switch (ibeta) {
