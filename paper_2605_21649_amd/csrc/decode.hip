@@ -1408,8 +1408,8 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
       }
     }
   } else {
-    // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, sixteen 16-byte loads in
-    // flight per lane (float32, or 32 rows and less: eight); the next 64 are looked up before these are consumed
+    // value rows: 64 looked up at a time (page list -> block table), then 4 row slots x 16 lanes, eight 16-byte loads in
+    // flight per lane; the next 64 are looked up before these are consumed
 #pragma unroll 1
     for (int i = 0; i < SPW; ++i) {
       const uint2* seg = seg0 + i * SH::kSegCap;
@@ -1424,28 +1424,23 @@ __device__ __forceinline__ void finish_row_block(const SolveArgs& A, const RowRe
         const uint32_t row_now = row;
         row = v_row_of<DENSE>(A, R.b, R.lrow, R.hkv, (int)seg[min(e0 + 64 + lane, ns - 1)].y);
         const float p_now = e0 + lane < ns ? __uint_as_float(seg[e0 + lane].x) : 0.f;
-        auto add_rows = [&](int first, auto count) {
-          constexpr int N = decltype(count)::value;
-          Raw8<T> vr[N]; float pw[N];
 #pragma unroll
-          for (int j = 0; j < N; ++j) {
-            const int src = first + 4 * j + rs;
+        for (int half = 0; half < 2; ++half) {
+          Raw8<T> vr[8]; float pw[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int src = 32 * half + 4 * j + rs;
             pw[j] = __shfl(p_now, src);
             load_raw8(v_pool + (size_t)(uint32_t)__shfl((int)row_now, src) * kD + 8 * c, vr[j]);
           }
 #pragma unroll
-          for (int j = 0; j < N; ++j) {
+          for (int j = 0; j < 8; ++j) {
             float vv[8];
             widen8(vr[j], vv);
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc[q] = fmaf(pw[j], vv[q], acc[q]);
           }
-        };
-        const bool more = ns - e0 > 32;                                 // wave-uniform
-        if (sizeof(T) == 2 && more) add_rows(0, IntC<16>{});
-        else {
-          add_rows(0, IntC<8>{});
-          if (more) add_rows(32, IntC<8>{});
+          if (e0 + 32 >= ns) break;                                     // wave-uniform
         }
       }
       store_partial(acc, sh, s0 + i);
