@@ -465,7 +465,7 @@ def main():
         nb = kernel_alg_bytes[nm]
         kernels[nm] = {"launch_us": round(us, 2), "algorithmic_bytes": None if nb is None else int(nb),
                        "GBps": None if nb is None else round(nb / (us * 1e-6) / 1e9, 1)}
-    kernels["select_topk"]["kernels"] = 3       # histogram, find, compaction (latency-bound, not a stream)
+    kernels["select_topk"]["kernels"] = 2       # histogram, find and listing (latency-bound, not a stream)
     kernels["decode_sparse"]["kernels"] = 2     # score pass (HBM-bound gather) + single-workgroup solve
 
     # The roofline entry is for the longest single kernel of the step: the page-scoring stream

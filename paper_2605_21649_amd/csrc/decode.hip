@@ -2191,7 +2191,8 @@ static void launch_scores(const Dims& dm, ScoreArgs sa, int32_t* pre_ws, hipStre
     hipLaunchKernelGGL((unit_prefix_kernel<MODE>), dim3(1), dim3(1024), 0, st, sa, pre_ws);
   }
   // K of a large call over all pages, or over lists that the heads of a group share or that are one head's own, passes once
-  // and goes past the caches (load16<true>).  Calls, us, kept / past the caches: all pages of 1 x 1M tokens 473 / 427, 8 x
+  // and goes past the caches (load16<true>).  Calls, us, kept / past the caches (before large bf16 calls over all pages moved to
+  // decode_windows.hip): all pages of 1 x 1M tokens 473 / 427, 8 x
   // 256K in pages of 32 954 / 925, 2 x 128K for 64 heads 140.7 / 124.4, 2 x 128K in pages of 12 135.1 / 125.7, 2 x 32K (134
   // MB) 41.8 / 37.4; 1 x 32K 23.4 / 22.5 with four inputs in turn, 22.4 / 22.9 with three, which the last cache holds, 1 x
   // 4K 13.4 / 13.8.  Group steps, whose lists follow a stream of statistics, by the capacity, all that the host knows (it

@@ -181,7 +181,8 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_windows_kernel(co
 // wavefront per SIMD.  Score pass, us, by chunks / in windows, K and scores in MB: 134 + 8 (four heads to a KV head) 26.4 / 26.9,
 // 201 + 13 39.9 / 39.7, 268 + 17 51.7 / 50.2, 537 + 34 101.8 / 94.0; 268 + 34 (eight heads) 55.7 / 54.5; 268 + 8 (two) 48.6 /
 // 48.1; 268 + 4 (one) 46.2 / 49.3, 537 + 8 90.6 / 89.9.  A window is what fills most of a wavefront's LDS at full rate: 60 us at
-// four heads to a KV head.
+// four heads to a KV head.  The grid does not follow the capacity: decode of 4096 tokens in a capacity of a million 30.5 -> 15.4
+// us, of 32768 37.1 -> 22.8.
 template <int G>
 bool launch_scores_windows(const Dims& dm, const ScoreArgs& sa, long long items, size_t k_bytes, hipStream_t st) {
   const unsigned long long z_bytes = (unsigned long long)sa.U * G * sa.zstride * 4;

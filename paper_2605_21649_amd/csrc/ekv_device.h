@@ -32,8 +32,8 @@ __device__ __forceinline__ int32_t uniform_load(const int32_t* p) { return *(con
 // 16 bytes; STREAM: of a stream that this launch reads once (a non-temporal load: its line leaves the caches first).  Such
 // streams run faster by themselves, with the same bytes from memory: page scoring of a million tokens 46.3 -> 41.9 us at 256.3
 // MiB read and 8.0 written either way.  Beside a stream of stores, lines leave the caches before they are whole less often:
-// the dense score pass over a million tokens, 64 bytes of scores at a time, wrote 155 MiB for its 130 and now writes 133
-// (read 2052 and 2049), which is little of the 453 -> 409 us.
+// the dense score pass over a million tokens, 64 bytes of scores at a time, wrote 155 MiB for its 130 and then 133
+// (read 2052 and 2049), which is little of the 453 -> 409 us (362 since its stores go into windows: decode_windows.hip).
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 template <bool STREAM = false> __device__ __forceinline__ uint4 load16(const void* p) {
   if constexpr (STREAM) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
