@@ -143,7 +143,7 @@ template <int N> __device__ __forceinline__ float gauss_moment(float t) {       
 template <int NB>
 __device__ __forceinline__ void trunc_h_all(float t, float& h_nb, float& h_nbm1, float& h_nbm2) {
   h_nb = 0.f; h_nbm1 = 0.f; h_nbm2 = 0.f;
-  if (!(t >= -kRatioXHi)) return;                                         // below float32 resolution of the sum
+  if (t < -kRatioXHi) return;                                             // below float32 resolution of the sum; a NaN goes on
   const float x = fabsf(t), v = __builtin_amdgcn_rcpf(x + kRatioK), s = fmaf(v, kRatioInvHalf, -kRatioMid * kRatioInvHalf);
   const float phi = __expf(-0.5f * t * t) * kInvSqrt2Pi;
   float pv = phi;                                                         // phi * v^NB
