@@ -30,7 +30,7 @@ static_assert(kSelWaves == 16, "one value per wavefront is one DPP row");
 static_assert(4 * kRankMax <= kSelThreads, "four lanes per ranked key");
 
 // Keys of one (b,h) row.  ITEMS > 0: held in registers (M <= 1024*ITEMS); ITEMS == 0: recomputed from
-// memory on every access (any M).  `fn(p)` gives the key of page p.  Slots past M hold the value 0.
+// memory on every access (any M).  `fn(p)` gives the key of page p.  Slots past M hold the value 0, in registers no other does.
 // After rebase(kmin) every key is stored relative to kmin (so only one register array is live).
 template <int ITEMS, typename KeyFn>
 struct KeySet {
@@ -47,7 +47,7 @@ struct KeySet {
 #pragma unroll
       for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = fn(min(page(i), M - 1));
 #pragma unroll
-      for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = page(i) < M ? reg[i] : 0u;
+      for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = page(i) < M ? max(reg[i], 1u) : 0u;      // 0: the lowest NaN's key
     }
   }
   __device__ __forceinline__ int page(int i) const { return page0 + i * 64; }
