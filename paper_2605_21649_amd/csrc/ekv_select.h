@@ -22,6 +22,7 @@ struct SelectShared {
   int scan_buf[kSelWaves + 1];
   int wave_total[2][kSelWaves];
   uint32_t red_lo[kSelWaves], red_hi[kSelWaves];
+  uint32_t few_lo[kSelWaves], few_hi[kSelWaves];
   int wave_gt[kSelWaves], wave_eq[kSelWaves];
   uint32_t digit, above;
   int n_list;
@@ -47,13 +48,11 @@ struct KeySet {
 #pragma unroll
       for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = fn(min(page(i), M - 1));
 #pragma unroll
-      for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = page(i) < M ? max(reg[i], 1u) : 0u;      // 0: the lowest NaN's key
+      for (int i = 0; i < (ITEMS ? ITEMS : 1); ++i) reg[i] = page(i) < M ? reg[i] : 0u;
     }
   }
   __device__ __forceinline__ int page(int i) const { return page0 + i * 64; }
-  // before rebase(): slots past M hold 0 and no real key is 0 (checking the register instead of the page
-  // index keeps the 128 page indices from being held in registers)
-  __device__ __forceinline__ bool valid(int i) const { return ITEMS ? reg[i] != 0u : page(i) < M; }
+  __device__ __forceinline__ bool valid(int i) const { return page(i) < M; }
   // key of slot i relative to `base`; slots past M (and keys below base) give 0
   __device__ __forceinline__ uint32_t key(int i) const {
     if (ITEMS) return reg[i];
@@ -110,95 +109,68 @@ __device__ __forceinline__ void rank_list(int members, int k_rem, SelectShared& 
 
 // Scores on both sides of zero (a last page of one or two tokens is enough): their keys span most of the 32 bits, so that a
 // digit of the first pass is a quarter of an octave and holds hundreds of scores.  One histogram over equal steps of the
-// scores themselves finds the k-th among a few.  False, with nothing found: the range is not finite, or a step holds more than
-// kRankMax.  The histogram and the list's counter are cleared.  48 rows of 2626 float32 scores, one of them negative: 7.4 us
-// a call by the radix passes alone, 5.4 with this; refined step of 3 x 21003 tokens 104.2 -> 100.1.
+// scores lo..hi themselves finds the k-th among a few.  True: key_t is the k-th largest key, k_rem how many equal to it are taken.
+// False: the step with the k-th holds more than kRankMax scores; lo, hi and k_rem are narrowed to that step, the histogram
+// and the list's counter are cleared, and the radix passes go on inside it (seven values, 32 rows of 16384: 17.8 us a call by the
+// radix passes alone, 23.3 if they begin anew, 13.4 so; two clusters 1e-4 wide 20.7, 29.6, 18.9).
 template <int ITEMS, typename KeyFn>
-__device__ __forceinline__ bool select_kth_linear(KeySet<ITEMS, KeyFn>& ks, int k, uint32_t lo, uint32_t hi, SelectShared& sh,
-                                                  uint32_t& vT_out, int& k_eq_out) {
-  const float x0 = key_to_float(lo), width = key_to_float(hi) - x0, scale = ((float)kBins - 0.125f) / width;
-  if (!(width < INFINITY && scale < INFINITY)) return false;
-  auto bin = [&](uint32_t key) { return min((int)((key_to_float(key) - x0) * scale), kBins - 1); };     // ascends with the key
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i)
-    if (ks.valid(i)) atomicAdd(&sh.hist[bin(ks.key(i))], 1u);
-  __syncthreads();
-  find_digit(k, 0, sh);
-  const int digit = (int)sh.digit, k_rem = k - (int)sh.above, members = (int)sh.hist[digit];
-  if (members > kRankMax) return false;                                    // workgroup-uniform
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i)
-    if (ks.valid(i) && bin(ks.key(i)) == digit) sh.list[atomicAdd(&sh.n_list, 1)] = ks.key(i);
-  __syncthreads();
-  rank_list(members, k_rem, sh);
-  vT_out = sh.digit - lo;
-  k_eq_out = k_rem - (int)sh.above;
-  ks.rebase(lo);
-  return true;
-}
-
-// Finds the k-th largest key (1 <= k <= M) by radix selection on (key - min key), 11 bits per pass over
-// only as many bits as the key range needs.  Rebases the key set to the smallest valid key and returns
-// vT = the k-th largest rebased key and k_eq = how many elements equal to it belong to the top k.
-// Slots past M count as copies of the smallest key with the highest page indices, which never changes
-// the answer for k <= M.
-template <int ITEMS, typename KeyFn>
-__device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k, SelectShared& sh,
-                                                 uint32_t& vT_out, int& k_eq_out) {
+__device__ __forceinline__ bool select_kth_linear(const KeySet<ITEMS, KeyFn>& ks, float width, int& k_rem, uint32_t& lo, uint32_t& hi,
+                                                  SelectShared& sh, uint32_t& key_t) {
   const int tid = threadIdx.x;
-  uint32_t lo = 0xffffffffu, hi = 0u;
-  if constexpr (ITEMS == 0) {
-    for (int i0 = 0; i0 < ks.items; i0 += 8) {
-      uint32_t kb[8];
-      ks.key_batch(i0, kb);
+  const float x0 = key_to_float(lo), scale = ((float)kBins - 0.125f) / width;
+  auto bin = [&](int i) { return min((int)((key_to_float(ks.key(i)) - x0) * scale), kBins - 1); };     // ascends with the key
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (i0 + j < ks.items && ks.page(i0 + j) < ks.M) { lo = min(lo, kb[j]); hi = max(hi, kb[j]); }
-    }
-  } else {
+  for (int i = 0; i < ITEMS; ++i)
+    if (ks.valid(i)) atomicAdd(&sh.hist[bin(i)], 1u);
+  __syncthreads();
+  find_digit(k_rem, 0, sh);
+  const int digit = (int)sh.digit, members = (int)sh.hist[digit];
+  k_rem -= (int)sh.above;
+  if (members <= kRankMax) {                                               // workgroup-uniform
 #pragma unroll
-    for (int i = 0; i < (ITEMS ? ITEMS : ks.items); ++i) {
-      if (ks.valid(i)) { const uint32_t key = ks.key(i); lo = min(lo, key); hi = max(hi, key); }
-    }
+    for (int i = 0; i < ITEMS; ++i)
+      if (ks.valid(i) && bin(i) == digit) sh.list[atomicAdd(&sh.n_list, 1)] = ks.key(i);
+    __syncthreads();
+    rank_list(members, k_rem, sh);
+    key_t = sh.digit;
+    k_rem -= (int)sh.above;
+    return true;
   }
-  // one barrier for both extremes; the histogram and the list's counter are cleared on the way
+  lo = 0xffffffffu; hi = 0u;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (ks.valid(i) && bin(i) == digit) { lo = min(lo, ks.key(i)); hi = max(hi, ks.key(i)); }
   lo = wave_min_u(lo); hi = wave_max_u(hi);
-  __syncthreads();                                 // whatever used the shared arrays before is done
+  __syncthreads();                                                         // the histogram has been read
   for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
   if ((tid & 63) == 0) { sh.red_lo[tid >> 6] = lo; sh.red_hi[tid >> 6] = hi; }
-  if (tid == 0) sh.n_list = 0;
   __syncthreads();
   lo = row16_min_u(sh.red_lo[tid & 15]); hi = row16_max_u(sh.red_hi[tid & 15]);
-  const uint32_t range = hi - lo;
-  if constexpr (ITEMS > 0) {
-    if (lo < kKeyOfZero && hi >= kKeyOfZero) {
-      if (select_kth_linear(ks, k, lo, hi, sh, vT_out, k_eq_out)) return;
-      __syncthreads();
-      for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
-      if (tid == 0) sh.n_list = 0;
-      __syncthreads();
-    }
-  }
-  ks.rebase(lo);
-  int shift = range ? 32 - __clz(range) : 0;     // significant bits of the rebased keys
+  return false;
+}
 
-  uint32_t prefix = 0;       // high bits of the answer fixed so far: (v >> shift) == prefix
-  int k_rem = k;             // rank of the answer among the elements sharing that prefix
-  const int n_pad = kSelThreads * (ITEMS ? ITEMS : ks.items) - ks.M;
+// The radix passes: the k_rem-th largest of the keys by their distance from lo, at most range; returns the distance, and in
+// k_rem how many keys equal to it are taken.  INSIDE: only part of the keys lie in this range, and they are not rebased (slots past M
+// hold 0, below lo); otherwise all do, and are rebased to lo.  The histogram and the list's counter are cleared.
+template <bool INSIDE, int ITEMS, typename KeyFn>
+__device__ __forceinline__ uint32_t radix_passes(const KeySet<ITEMS, KeyFn>& ks, uint32_t lo, uint32_t range, int& k_rem, SelectShared& sh) {
+  const int tid = threadIdx.x;
+  auto dist = [&](int i) { return INSIDE ? ks.key(i) - lo : ks.key(i); };
+  auto in = [&](int i, uint32_t v) { return INSIDE ? v <= range : ks.valid(i); };
+  int shift = range ? 32 - __clz(range) : 0;     // significant bits of the distances
+  uint32_t prefix = 0;                           // high bits of the answer fixed so far: (v >> shift) == prefix
   for (int pass = 0; shift > 0; ++pass) {
     const int dbits = min(kDigitBits, shift);
     shift -= dbits;
     const uint32_t dmask = (1u << dbits) - 1u;
     const int up = shift + dbits;                  // bits above the current digit: (v >> up) must equal prefix
     const bool first = up >= 32;                   // first pass of a full 32-bit range: every key matches
-    const bool pad_counted = first || prefix == 0u;
     if (pass > 0) {
       __syncthreads();
       for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
       __syncthreads();
     }
-    // Slots past M hold the rebased key 0.  They are counted (as copies of the smallest key) but not sent
-    // through the histogram one by one: thousands of atomics on one LDS address serialise.
+    // Slots past M stay out: thousands of atomics on one LDS address serialise.
     if constexpr (ITEMS == 0) {
       for (int i0 = 0; i0 < ks.items; i0 += 8) {
         uint32_t kb[8];
@@ -210,22 +182,20 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < (ITEMS ? ITEMS : ks.items); ++i) {
-        const uint32_t v = ks.key(i);
-        if (ks.page(i) < ks.M && (first || (v >> up) == prefix)) atomicAdd(&sh.hist[(v >> shift) & dmask], 1u);
+      for (int i = 0; i < ITEMS; ++i) {
+        const uint32_t v = dist(i);
+        if (in(i, v) && (first || (v >> up) == prefix)) atomicAdd(&sh.hist[(v >> shift) & dmask], 1u);
       }
     }
-    if (tid == 0 && pad_counted && n_pad > 0) atomicAdd(&sh.hist[0], (uint32_t)n_pad);
     __syncthreads();
     find_digit(k_rem, pass, sh);
     const uint32_t digit = sh.digit;
     prefix = (prefix << dbits) | digit;
     k_rem -= (int)sh.above;
     if (shift == 0) break;
-    // Few real elements share the prefix (the usual case after the first pass): rank them against each other
-    // directly instead of taking more passes.  Padding slots are the last of the smallest keys and never
-    // decide the answer for k <= M, so they stay out.
-    const int members = (int)sh.hist[digit] - (digit == 0u && pad_counted && n_pad > 0 ? n_pad : 0);
+    // Few elements share the prefix (the usual case after the first pass): rank them against each other
+    // directly instead of taking more passes.
+    const int members = (int)sh.hist[digit];
     if (members <= kRankMax) {                     // workgroup-uniform
       if constexpr (ITEMS == 0) {
         for (int i0 = 0; i0 < ks.items; i0 += 8) {
@@ -238,18 +208,80 @@ __device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < (ITEMS ? ITEMS : ks.items); ++i) {
-          const uint32_t v = ks.key(i);
-          if (ks.page(i) < ks.M && (v >> shift) == prefix) sh.list[atomicAdd(&sh.n_list, 1)] = v;
+        for (int i = 0; i < ITEMS; ++i) {
+          const uint32_t v = dist(i);
+          if (in(i, v) && (v >> shift) == prefix) sh.list[atomicAdd(&sh.n_list, 1)] = v;
         }
       }
       __syncthreads();
       rank_list(members, k_rem, sh);
-      vT_out = sh.digit; k_eq_out = k_rem - (int)sh.above;
-      return;
+      k_rem -= (int)sh.above;
+      return sh.digit;
     }
   }
-  vT_out = prefix; k_eq_out = k_rem;
+  return prefix;
+}
+
+// Finds the k-th largest key (1 <= k <= M) by radix selection on (key - min key), 11 bits per pass over
+// only as many bits as the key range needs.  Rebases the key set to the smallest valid key and returns
+// vT = the k-th largest rebased key and k_eq = how many elements equal to it belong to the top k.
+// Slots past M are not counted.
+template <int ITEMS, typename KeyFn>
+__device__ __forceinline__ void radix_select_kth(KeySet<ITEMS, KeyFn>& ks, int k, SelectShared& sh,
+                                                 uint32_t& vT_out, int& k_eq_out) {
+  const int tid = threadIdx.x;
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  constexpr int kFew = ITEMS < 4 ? ITEMS : 4;
+  uint32_t few_lo = 0xffffffffu, few_hi = 0u;      // of this thread's first kFew keys
+  if constexpr (ITEMS == 0) {
+    for (int i0 = 0; i0 < ks.items; i0 += 8) {
+      uint32_t kb[8];
+      ks.key_batch(i0, kb);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (i0 + j < ks.items && ks.page(i0 + j) < ks.M) { lo = min(lo, kb[j]); hi = max(hi, kb[j]); }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < (ITEMS ? ITEMS : ks.items); ++i) {
+      if (ks.valid(i)) { const uint32_t key = ks.key(i); lo = min(lo, key); hi = max(hi, key); }
+      if (i == kFew - 1) { few_lo = lo; few_hi = hi; }
+    }
+  }
+  // one barrier for both extremes; the histogram and the list's counter are cleared on the way
+  lo = wave_min_u(lo); hi = wave_max_u(hi);
+  __syncthreads();                                 // whatever used the shared arrays before is done
+  for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
+  if ((tid & 63) == 0) {
+    sh.red_lo[tid >> 6] = lo; sh.red_hi[tid >> 6] = hi;
+    if (ITEMS > 0) { sh.few_lo[tid >> 6] = few_lo; sh.few_hi[tid >> 6] = few_hi; }
+  }
+  if (tid == 0) sh.n_list = 0;
+  __syncthreads();
+  lo = row16_min_u(sh.red_lo[tid & 15]); hi = row16_max_u(sh.red_hi[tid & 15]);
+  k_eq_out = k;
+  if constexpr (ITEMS > 0) {
+    if (lo < kKeyOfZero && hi >= kKeyOfZero) {
+      // Equal steps are the better digits unless outliers make up the range: in at least half of the wavefronts that hold scores,
+      // the first two or four of the first thread span a 256th or a 64th of it.  Calls over 32 rows of 16384 pages (48 of 2626), us,
+      // radix passes alone / equal steps without this rule / as here: one negative score 17.0 / 10.4 / 10.2 (6.9 / 5.2 / 5.3), on both
+      // sides of zero 14.6 / 10.2 / 10.1 (6.2 / 5.2 / 5.2), a tenth of the range wide beside one negative 24.1 / 11.0 / 10.8; two scores
+      // 3e4 times the others' deviation 17.5 / 32.3 / 17.6 (7.0 / 10.1 / 7.1), log-normal with deviation 3 13.0 / 26.0 / 13.0, one in
+      // fifty 5000 times the others 14.5 / 28.8 / 14.4.
+      const uint32_t base = lo, few = sh.few_lo[tid & 15], most = sh.few_hi[tid & 15];
+      const float width = key_to_float(hi) - key_to_float(lo);
+      const bool has = few <= most, wide = has && key_to_float(most) - key_to_float(few) >= (kFew == 4 ? 1 / 64.f : 1 / 256.f) * width;
+      if (width < INFINITY && (float)kBins / width < INFINITY && 2 * __popcll(__ballot(wide)) >= __popcll(__ballot(has))) {
+        uint32_t key_t;
+        if (!select_kth_linear(ks, width, k_eq_out, lo, hi, sh, key_t)) key_t = lo + radix_passes<true>(ks, lo, hi - lo, k_eq_out, sh);
+        vT_out = key_t - base;
+        ks.rebase(base);
+        return;
+      }
+    }
+  }
+  ks.rebase(lo);
+  vT_out = radix_passes<false>(ks, lo, hi - lo, k_eq_out, sh);
 }
 
 // Writes, in ascending page order, every page whose (rebased) key exceeds vT, plus the first k_eq
