@@ -415,7 +415,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
     // are equal that key is the answer and the per-slice counts are already known; otherwise the sub-bin of the
     // k-th key usually holds few enough members to rank, collected by a second pass that also counts, per slice,
     // the members of the higher sub-bins.  Only a sub-bin that is still too large sends the head to the
-    // single-workgroup algorithm (which the compaction launch then skips).
+    // single-workgroup algorithm, which writes the selection (a compaction launch then skips it).
     __shared__ uint32_t s_kmin, s_kmax;
     __shared__ int s_sub, s_above2, wsum2[kSelWaves];
     const bool edge = b1 == 0 || b1 == kBins - 1;        // clamped bins: keys outside the sampled range, no sub-bins
@@ -426,11 +426,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
     if (tid == 0) { s_kmin = 0xffffffffu; s_kmax = 0u; s_sub = -1; s_above2 = 0; }
     __syncthreads();
     for_each_member([&](bool has, uint32_t kk, int, int) {
-      uint32_t lo_k = has ? kk : 0xffffffffu, hi_k = has ? kk : 0u;
-      for (int d = 32; d >= 1; d >>= 1) {
-        lo_k = min(lo_k, (uint32_t)__shfl_xor((int)lo_k, d));
-        hi_k = max(hi_k, (uint32_t)__shfl_xor((int)hi_k, d));
-      }
+      const uint32_t lo_k = wave_min_u(has ? kk : 0xffffffffu), hi_k = wave_max_u(has ? kk : 0u);
       if ((tid & 63) == 0 && lo_k <= hi_k) { atomicMin(&s_kmin, lo_k); atomicMax(&s_kmax, hi_k); }
       if (has && !edge) atomicAdd(&tot_above[sub_of(kk)], 1u);
     });
@@ -477,11 +473,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_find_kernel(const float* __r
               if (slot < kTkMembers) { mem_key[slot] = kk; mem_page[slot] = page; }
             }
           } else {
-            uint32_t lo_k = mine ? kk : 0xffffffffu, hi_k = mine ? kk : 0u;
-            for (int d = 32; d >= 1; d >>= 1) {
-              lo_k = min(lo_k, (uint32_t)__shfl_xor((int)lo_k, d));
-              hi_k = max(hi_k, (uint32_t)__shfl_xor((int)hi_k, d));
-            }
+            const uint32_t lo_k = wave_min_u(mine ? kk : 0xffffffffu), hi_k = wave_max_u(mine ? kk : 0u);
             const unsigned long long eqm = __ballot(mine);
             if ((tid & 63) == 0 && eqm) { atomicMin(&s_kmin, lo_k); atomicMax(&s_kmax, hi_k); atomicAdd(&s_eq[sl], __popcll(eqm)); }
           }
