@@ -703,7 +703,13 @@ void launch_select_topk(const Dims& dm, const float* box, const int32_t* seq_len
   // 6 % 20.7 / 19.3, 8 % (5243 pages, 328 a slice) 23.0 / 22.7, 12.5 % (512 a slice) 35.6 / 45.4; of 262144, 2 % (5243)
   // 44.6 / 41.9, 4 % 57.4 / 59.8; of 20000, 8 % (320 a slice) 16.9 / 15.0, 12.5 % (500) 19.3 / 20.4; 512 heads of 20000, 2 %
   // 38.7 / 27.0.
-  if (k_pages <= kTkEmitPages && k_pages <= kTkEmitSlice * ws.S) {
+  // A row of more slices takes one compute unit longer (its words, and the serial run of pages where one slice holds most of
+  // the selection), and few rows a third launch no longer: 8 heads of 262144, 5242 pages, half of them in one slice 40.6 / 50.8, 524
+  // 38.9 / 41.0, 8 of 81920, 5243 pages 19.4 / 21.5, of 131072, 2621 28.2 / 30.4 (1311 28.3 / 28.6); 32 heads of 131072, 2621 51.7 /
+  // 52.0, of 262144, 2621 81.6 / 83.0; 128 heads of 131072, 5243 149 / 138, of 262144, 5243 193 / 177.
+  const long long rows = (long long)dm.B * dm.Hq, by_slices = (long long)k_pages * ws.S * ws.S;
+  if (k_pages <= kTkEmitPages && k_pages <= kTkEmitSlice * ws.S &&
+      (rows * ws.S >= 4096 || by_slices <= 16 * kTkEmitPages * (rows > 16 ? rows : 16))) {
     const size_t lds = 2 * (size_t)ws.S * (kTkSlice / 8);   // at most 64 KiB
     hipLaunchKernelGGL(topk_find_kernel<true>, grid, block, lds, st, box, seq_lens, k_pages, ws, page_idx, n_sel, dm.Hq, dm.P,
                        dm.Mmax, dm.cap);
