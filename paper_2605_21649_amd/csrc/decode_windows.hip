@@ -4,7 +4,7 @@
 namespace ekv {
 
 constexpr int kHoldScores = 8192;       // scores a wavefront of decode_scores_windows_kernel holds back
-constexpr int kHoldUnitsMax = 4096;     // and the most units of such a launch (16 KB of LDS beside the 132)
+constexpr int kHoldUnitsMax = 4096;     // and the most units of such a launch (16 KB of LDS beside 132, with one head 138)
 
 // bf16 pages with P in {16, 32, 64}, every page a candidate, calls whose scores the L2s do not hold.  What bounds such a call is
 // not the bytes: a stream of reads at 6.9 TB/s falls to 5.5 as soon as a few stores are mixed in, hardly further with more of
@@ -27,6 +27,8 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_windows_kernel(co
   __shared__ float hold_max[kScoreWaves][NB * G];
   __shared__ int4 hold_at[kScoreWaves][NB];        // first row, group, scores stored per row
   __shared__ int wsum[kScoreWaves];
+  static_assert(sizeof(hold_z) + sizeof(hold_max) + sizeof(hold_at) + sizeof(wsum) + (kHoldUnitsMax + 1) * sizeof(int) <= 160 * 1024,
+                "the LDS of a compute unit");
   const bf16_t* q = (const bf16_t*)A.q;
   const bf16_t* k_pool = (const bf16_t*)A.k_pool;
   const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
@@ -191,6 +193,12 @@ __global__ __launch_bounds__(kScoreThreads) void decode_scores_windows_kernel(co
 // 48.1; 268 + 4 (one) 46.2 / 49.3, 537 + 8 90.6 / 89.9.  A window is what fills most of a wavefront's LDS at full rate: 60 us at
 // four heads to a KV head.  The grid does not follow the capacity: decode of 4096 tokens in a capacity of a million 30.5 -> 15.4
 // us, of 32768 37.1 -> 22.8.
+// A change of unit waits for the new query behind the K in flight, and a workgroup starts only where a compute unit's LDS is free, on
+// a fixed share of the call: neither shows against the launch by chunks, which pays more for its many workgroups.  Calls, us,
+// by chunks / here, heads four to a KV head: 512 sequences of 512 tokens (4096 units of 8 items) 316 / 267, of 64 tokens in a
+// capacity of 4096 225 / 146, 64 of 512 in 8192 54.7 / 40.5; one head, caches of 537 MB filled to half 58.2 / 56.8, of 1 GB 111 /
+// 103; two calls at once on two streams, 1 x 262144 212 / 193 the pair, 64 x 8192 456 / 403, beside four calls of 32768 tokens each
+// 313 / 288.
 template <int G>
 bool launch_scores_windows(const Dims& dm, const ScoreArgs& sa, long long items, size_t k_bytes, hipStream_t st) {
   const unsigned long long z_bytes = (unsigned long long)sa.U * G * sa.zstride * 4;
