@@ -2162,17 +2162,18 @@ void decode_row_kernel(const ScoreArgs S, const SolveArgs A) {
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
-// Wavefronts of a pass-1 launch: enough to fill every compute unit several times over, never more than the
-// lists can hold items; independent of how full the lists are.
-// Workgroups per compute unit in a pass-1 launch.  Eight are resident at a time; launching twice that (when there
+// Workgroups per compute unit in a pass-1 launch; never more than the lists can hold items for, and independent of how full
+// they are.  Eight are resident at a time; launching twice that (when there
 // is that much work) measured 3-5 % faster than a grid of resident workgroups only -- a wavefront that starts fresh
 // streams better than one that loops -- while workgroups that find no work cost about half a microsecond per
 // thousand, which bounds what a list capacity far above the lists' lengths can cost.  Every workgroup reads the U
 // lengths, so launches with many units get fewer.
 // When every page is a candidate the launch is large whatever the lists hold, and one item per wavefront, left to
-// the hardware's scheduling, measured 2-3 % faster than eight per wavefront (five alternating pairs at 1M tokens:
-// 417-459 against 431-467 us; 64 sequences of 8K tokens, 512 units: 222 against 237 us): such launches get up to
-// 128 workgroups per compute unit (32 when the units are so many that reading their lengths is a cost of its own).
+// the hardware's scheduling, is up to 4 % faster: such launches get up to 128 workgroups per compute unit (32 when the units
+// are so many that reading their lengths is a cost of its own).  Of these come here what decode_windows.hip does not take:
+// float32, other page sizes, shorter calls, more units.  Calls, us, 16 / 128: float32 2 x 131072 209.5 / 205.2, 64 x 4096 215.1 /
+// 210.4, pages of 48 tokens 1 x 1048576 462 / 449, of 12 64 x 8192 241 / 232, 2 x 131072 122.9 / 122.9, bf16 1 x 32768 and 3 x 32768
+// the same.
 static int score_wgs_per_cu(int U, bool all_pages) {
   if (all_pages) return U <= 1024 ? 128 : 32;
   return U <= 256 ? 16 : 8;

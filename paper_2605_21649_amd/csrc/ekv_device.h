@@ -329,8 +329,9 @@ __device__ __forceinline__ void block_exclusive_prefix(int U, F&& count_of, int*
 
 // The last of entries [0, n) of the ascending pre that is not above v (pre[0] <= v), the same for the whole wavefront: 64 entries
 // compared at a time, so one LDS latency up to 64 entries and two up to 4096, where halving the range takes six and twelve.
-// Every launch over lists begins with the prefix of their lengths and this search; with scans by LDS permutes and halving
-// they took 0.4 to 0.7 us more: group step of 8 x 256K tokens 55.0 -> 54.6 us, Gaussian step of 1 x 32K 42.1 -> 41.5.
+// Every launch over lists begins with the prefix of their lengths and this search.  By LDS permutes and halving, and with the
+// solve's segment ends so too, decode calls took 0.4 to 0.6 us more: over shared lists of 328 pages of 262144 tokens 12.9 -> 12.5 us,
+// of 16 pages for 64 sequences 17.8 -> 17.3, lists per head of 328 17.6 -> 17.0.
 template <typename P> __device__ __forceinline__ int wave_last_at_most(const P pre, int n, int v) {
   const int lane = threadIdx.x & 63;
   int lo = 0;

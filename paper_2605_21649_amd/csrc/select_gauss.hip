@@ -126,8 +126,13 @@ __device__ __forceinline__ void page_mass(float muY, float sY, float cnt, float&
 // The same where all pages of a head are evaluated: one formula for every t, since the pages of a wavefront lie on all sides of
 // the lines above and each side's instructions are issued for all of them.  h_n(-x), x = |t|, from fitted polynomials in
 // 1 / (x + K) (trunc_ratio_coeffs.inc) for n = NB and NB - 1, h_{NB-2} by the recurrence backwards (all terms positive),
-// and t > 0 by reflection, h_n(t) = E[(t + Z)^n] - (-1)^n h_n(-t).  Relative error 2e-7 to 3e-7 rms, 8e-7 at most (the forward
-// recurrence above reaches 2e-6 for n = 2 and 3e-5 for n = 4 near t = -2.5).  An evaluation of 8192 pages by one compute unit
+// and t > 0 by reflection, h_n(t) = E[(t + Z)^n] - (-1)^n h_n(-t).  Relative error of the ratio to phi 1e-7 to 3e-7 rms, 9e-7 at
+// most; of the moments, with the exponential rounded correctly, 1e-6 at most for t > -2.5 and 1.7e-6 down to -8 (half a unit of
+// t^2 / 2 in the exponent, as in every form); below -8 they are under 1e-14 and in the end denormal.  The forward recurrence above
+// reaches 2e-6 for n = 2 and 3e-5 for n = 4 near t = -2.5; its tail polynomials are two to three times closer than these below
+// there (2.4e-7 and 3.5e-7 of the ratio).  tau_hat against 64 bits, six kinds of pages, 300 to 65536 of them, rms for beta 1 to 4
+// 6.0, 7.8, 34, 86e-8 by those, 6.0, 6.2, 6.1, 5.6e-8 so; largest 1.0e-6, 1.1e-6, 5.6e-6, 1.5e-5 and 9.6e-7 (beta 1), 3.7e-7.
+// A NaN mean goes on into the sum, and tau_hat is then the left end of its bracket.  An evaluation of 8192 pages by one compute unit
 // 4.6 -> 2.6 us; selector calls over 32 heads of 8192 pages 19.5 -> 15.2 us (beta 4: 21.9 -> 16.4), of 2048 11.2 -> 9.5.
 template <int N>
 __device__ __forceinline__ float horner_ratio(float s) {
